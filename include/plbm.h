@@ -188,13 +188,14 @@ int plbm_init3(const plbm_desc *d, const double *rho, const double *ux,
 /*
  * plbm_step -- nsteps applications of the SRT update, Eq. srt:
  *   f_i(x + v_i, t + 1) = (1 - omega) f_i(x, t) + omega f_eq_i(x, t),
- * each one a single fused pull kernel: gather f_k(x) = src_k(x - v_k), take
- * rho, u, theta, the Maxwell moments mu_0..mu_(q1d-1) per axis, the rule
- * r = C mu per axis, f_eq = rho r^x r^y, relax, and write dst at x.
+ * each one a fused pull: gather f_k(x) = src_k(x - v_k), take rho, u, theta,
+ * the Maxwell moments mu_0..mu_(q1d-1) per axis, the rule r = C mu per axis,
+ * f_eq = rho r^x r^y, relax, and write dst at x.  Steps of one call may share
+ * a launch; the populations are bitwise those of one launch per step.
  *   f_a, f_b : device pointers, two distinct buffers of plbm_buffer_elems(d)
- *              elements.  Step s reads f_a and writes f_b when s is even,
- *              the reverse when odd: the result is in f_a when nsteps is
- *              even and in f_b when it is odd.  nsteps >= 0.
+ *              elements.  The result is in f_a when nsteps is even and in
+ *              f_b when it is odd; the other buffer is scratch (after one
+ *              step it still holds the state before).  nsteps >= 0.
  *   sums     : NULL, or a host pointer to 4 doubles (5 when dim = 3)
  *              receiving, after the last step, the FP64 sums over all nodes
  *              of the post-collision populations it wrote: sum f, sum f v_x,

@@ -130,6 +130,7 @@ struct StF64 {
     // per-node key of the stochastic rounding (unused by the other forms)
     static __device__ __forceinline__ uint32_t key(uint32_t node) { return node; }
     static constexpr bool row_prio_pair = false;   // see StF16
+    static constexpr bool keyed = false;           // stochastic rounding reads the key
     static __device__ __forceinline__ C dec(T h, int, const KParams &) { return h; }
     static __device__ __forceinline__ T enc(C f, int, const KParams &, uint32_t = 0) { return f; }
     static __device__ __forceinline__ const SymRule<C> &R(const KParams &p) { return p.r64; }
@@ -141,6 +142,7 @@ struct StF32 {
     // per-node key of the stochastic rounding (unused by the other forms)
     static __device__ __forceinline__ uint32_t key(uint32_t node) { return node; }
     static constexpr bool row_prio_pair = false;   // see StF16
+    static constexpr bool keyed = false;           // stochastic rounding reads the key
     static __device__ __forceinline__ C dec(T h, int, const KParams &) { return h; }
     static __device__ __forceinline__ T enc(C f, int, const KParams &, uint32_t = 0) { return f; }
     static __device__ __forceinline__ const SymRule<C> &R(const KParams &p) { return p.r32; }
@@ -157,6 +159,7 @@ struct StF16 {
     static __device__ __forceinline__ uint32_t key(uint32_t node) { return node; }
     // an s_setprio 1 / 0 pair at the head of each row (see step_rows)
     static constexpr bool row_prio_pair = true;
+    static constexpr bool keyed = false;
     static __device__ __forceinline__ C dec(T h, int k, const KParams &p) {
         const int c = pclass(k);
         return fmaf((float)__builtin_bit_cast(_Float16, h), p.dscale[c], p.dbase[c]);
@@ -174,6 +177,7 @@ struct StBF16 {
     // per-node key of the stochastic rounding (unused by the other forms)
     static __device__ __forceinline__ uint32_t key(uint32_t node) { return node; }
     static constexpr bool row_prio_pair = true;    // see StF16
+    static constexpr bool keyed = false;
     static __device__ __forceinline__ C dec(T h, int k, const KParams &p) {
         const int c = pclass(k);
         return fmaf(__uint_as_float((uint32_t)h << 16), p.dscale[c], p.dbase[c]);
@@ -251,6 +255,7 @@ typedef __bf16 plbm_bf16x2 __attribute__((ext_vector_type(2)));
 struct StF16SR : StF16 {
     static __device__ __forceinline__ uint32_t key(uint32_t node) { return sr_key_reg(sr_node_key(node)); }
     static constexpr bool row_prio_pair = false;
+    static constexpr bool keyed = true;
     static __device__ __forceinline__ T enc(C f, int k, const KParams &p, uint32_t key) {
         const int c = pclass(k);
         const float v = fmaf(f, p.dinv[c], p.dnbi[c]);
@@ -266,6 +271,7 @@ struct StF16SR : StF16 {
 struct StBF16SR : StBF16 {
     static __device__ __forceinline__ uint32_t key(uint32_t node) { return sr_key_reg(sr_node_key(node)); }
     static constexpr bool row_prio_pair = false;
+    static constexpr bool keyed = true;
     static __device__ __forceinline__ T enc(C f, int k, const KParams &p, uint32_t key) {
         const int c = pclass(k);
         const float v = fmaf(f, p.dinv[c], p.dnbi[c]);

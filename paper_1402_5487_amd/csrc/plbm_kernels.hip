@@ -23,6 +23,9 @@
 //    lane keeps five 32-bit offsets (one per x velocity), so each of the 50
 //    accesses is a scalar base plus a vector offset.  Only the waves whose
 //    windows cross the periodic seam in x take a per-node wrapped path.
+//  * Calls of four steps and more on larger lattices take them two at a time
+//    (plbm_sweep.h): the populations between the two steps stay in LDS and
+//    registers, so a pair reads and writes them once.
 //  * Arithmetic per node: column/row sums give rho, j and sum f|v|^2; the
 //    Maxwell moments follow mu_(n+1) = u mu_n + n theta mu_(n-1); the 1D rule
 //    r = C mu uses the reduced table of a symmetric velocity set; f_eq =
@@ -37,9 +40,11 @@
 #include <cstring>
 
 #include <mutex>
+#include <type_traits>
 
 #include "plbm_device.h"
 #include "plbm_internal.h"
+#include "plbm_sweep.h"
 
 // Scratch of plbm_step_noalloc: the per-workgroup FP64 partial sums of its
 // sums launch (at most NOALLOC_BLOCKS workgroups, four doubles each) and the
@@ -85,6 +90,49 @@ __global__ __launch_bounds__(TX, PLBM_MIN_WAVES) void k_step2d_fields(const type
 #pragma unroll 1
     for (int tile = slot; tile < p.ntiles; tile += gridDim.x)
         step_tile<S, NV, false, true>(src, dst, p, tile, acc, fo);
+}
+
+// Two steps in one launch (plbm_sweep.h) of the set {0, +-1, +-3} in the
+// paper's order.
+template <class S>
+struct Thermal25 {
+    using T = typename S::T;
+    using C = typename S::C;
+    using P = KParams;
+    static constexpr int Q1 = Q;
+    static constexpr int V[Q] = {0, 1, -1, 3, -3};
+    static constexpr bool KEYED = S::keyed;
+    static __device__ __forceinline__ C dec(T h, int k, const P &p) { return S::dec(h, k, p); }
+    static __device__ __forceinline__ T enc(C f, int k, const P &p, uint32_t key)
+    {
+        const T h = S::enc(f, k, p, key);
+        if constexpr (std::is_same_v<S, StF16>) {
+            // one value at a time: the compiler turns pairs into an FP32 FMA
+            // and a packed conversion, which rounds twice where the single
+            // step's v_fma_mixlo_f16 rounds once
+            _Float16 one = __builtin_bit_cast(_Float16, h);
+            asm("" : "+v"(one));
+            return __builtin_bit_cast(T, one);
+        } else {
+            return h;
+        }
+    }
+    static __device__ __forceinline__ uint32_t key(uint32_t node) { return S::key(node); }
+    static __device__ __forceinline__ void collide(C (&f)[NQ], const P &p) { collide2d<S>(f, p); }
+    static __device__ __forceinline__ void collide(C (&f)[NQ], const P &p, C (&mom)[4]) { collide2d<S>(f, p, mom); }
+};
+constexpr int PAIR = 2;
+
+template <class S, bool FIELDS>
+__global__ __launch_bounds__(SWEEP_T, (sweep_per_cu<Thermal25<S>, PAIR>())) void
+k_step2d_pair(const typename S::T *__restrict__ src, typename S::T *__restrict__ dst, KParams p, SweepGrid g,
+              FieldsOut fo)
+{
+    extern __shared__ __align__(16) unsigned char sweep_lds[];
+    const int b = xcd_tile(blockIdx.x, gridDim.x);
+    const int c = b / g.strips, ya = c * g.h;
+    sweep<Thermal25<S>, PAIR, FIELDS>(src, dst, p, (b - c * g.strips) * g.w, g.w, ya, min(ya + g.h, p.ny),
+                                      reinterpret_cast<typename S::T *>(sweep_lds), fo);
 }
 
 // ---------------------------------------------------------------------------
@@ -403,26 +451,73 @@ int launch_step(const KParams &p, const plbm_desc *d, const void *src, void *dst
     return launch_status();
 }
 
+// Two fused steps src -> dst.
+template <class S, bool FIELDS>
+int launch_pair(const KParams &p, const void *src, void *dst, hipStream_t st, FieldsOut fo = FieldsOut{})
+{
+    using T = typename S::T;
+    const SweepGrid g = sweep_grid<Thermal25<S>, PAIR>(p.nx, p.ny);
+    clear_launch_error();
+    hipLaunchKernelGGL((k_step2d_pair<S, FIELDS>), dim3(g.strips * g.chunks), dim3(SWEEP_T),
+                       (sweep_lds_bytes<Thermal25<S>, PAIR>()), st, (const T *)src, (T *)dst, p, g, fo);
+    return launch_status();
+}
+
+// Which lattices take fused pairs.  Measured per step against single steps
+// (us, single -> pair): FP64 256^2 6.3 -> 8.6, 384^2 15.5 -> 10.9, 4096^2
+// 1050 -> 607; FP32 256^2 4.9 -> 6.3, 384^2 7.6 -> 7.0, 4096^2 519 -> 312: from
+// 2^17 nodes on.  The 16-bit forms are bound by vector work, of which short
+// chunks add up to as much again: FP16 1024^2 21.4 -> 23.9, 1501 x 1100
+// 40.7 -> 30.2, 4096^2 276 -> 202: from 1.5 M nodes on.  Rows that leave half
+// the lanes of their strips idle (a quarter: 16-bit) stay with single steps.
+template <class S>
+bool use_pairs(const KParams &p, const plbm_desc *d)
+{
+    constexpr bool narrow = sizeof(typename S::T) == 2;
+    using M = Thermal25<S>;
+    if (d->dim != 2 || !sweep_fits<M>(p.nx)) return false;
+    for (int i = 0; i < Q; ++i)
+        if (p.sx[i] != M::V[i]) return false;
+    if ((long long)p.nx * p.ny < (narrow ? 1500000 : 1 << 17)) return false;
+    constexpr long long wmax = sweep_wmax<M, PAIR>();
+    const long long lanes = (p.nx + wmax - 1) / wmax * wmax;
+    return narrow ? 4ll * p.nx >= 3 * lanes : 2ll * p.nx >= lanes;
+}
+
+// Of n steps, as many in fused pairs as leave the state in the buffer where
+// single steps leave it: an even number of launches of two.
+inline int pairs_of(int n) { return n / 4 * 2; }
+
 // 2D steps of which the first also writes the fields of the state it reads.
 template <class S>
 int run_steps_fields(const KParams &p, const plbm_desc *d, void *fa, void *fb, int nsteps, FieldsOut fo,
                      hipStream_t st)
 {
     using T = typename S::T;
-    clear_launch_error();
-    const int nblocks = grid_for(p.ntiles);
-    const size_t lds = sizeof(T) == 2 ? (d->rounding == PLBM_ROUND_STOCHASTIC ? PLBM_LDS_CAP_16SR
-                                                                             : PLBM_LDS_CAP_16)
-                                      : PLBM_LDS_CAP_WIDE;
-    if (p.nv == 2)
-        hipLaunchKernelGGL((k_step2d_fields<S, 2>), dim3(nblocks), dim3(TX), lds, st, (const T *)fa, (T *)fb, p,
-                           fo);
-    else
-        hipLaunchKernelGGL((k_step2d_fields<S, 1>), dim3(nblocks), dim3(TX), lds, st, (const T *)fa, (T *)fb, p,
-                           fo);
+    int s0 = 1;
+    const int pairs = use_pairs<S>(p, d) ? pairs_of(nsteps) : 0;
+    if (pairs > 0) {
+        int rc = launch_pair<S, true>(p, fa, fb, st, fo);
+        for (int k = 1; k < pairs && rc == PLBM_OK; ++k)
+            rc = launch_pair<S, false>(p, (k & 1) ? fb : fa, (k & 1) ? fa : fb, st);
+        if (rc != PLBM_OK) return rc;
+        s0 = 2 * pairs;
+    } else {
+        clear_launch_error();
+        const int nblocks = grid_for(p.ntiles);
+        const size_t lds = sizeof(T) == 2 ? (d->rounding == PLBM_ROUND_STOCHASTIC ? PLBM_LDS_CAP_16SR
+                                                                                 : PLBM_LDS_CAP_16)
+                                          : PLBM_LDS_CAP_WIDE;
+        if (p.nv == 2)
+            hipLaunchKernelGGL((k_step2d_fields<S, 2>), dim3(nblocks), dim3(TX), lds, st, (const T *)fa, (T *)fb, p,
+                               fo);
+        else
+            hipLaunchKernelGGL((k_step2d_fields<S, 1>), dim3(nblocks), dim3(TX), lds, st, (const T *)fa, (T *)fb, p,
+                               fo);
+    }
     int rc = launch_status();
     int nb = 0;
-    for (int s = 1; s < nsteps && rc == PLBM_OK; ++s)
+    for (int s = s0; s < nsteps && rc == PLBM_OK; ++s)
         rc = launch_step<S, false>(p, d, (s & 1) ? fb : fa, (s & 1) ? fa : fb, nullptr, st, nb);
     return rc;
 }
@@ -435,7 +530,16 @@ int run_steps(const KParams &p, const plbm_desc *d, void *fa, void *fb, int nste
               hipStream_t st, double *scratch)
 {
     int nb = 0;
-    for (int s = 0; s < nsteps; ++s) {
+    int s0 = 0;
+    if (use_pairs<S>(p, d)) {
+        const int pairs = pairs_of(nsteps - (sums ? 1 : 0));    // a step that takes sums is a single one
+        for (int k = 0; k < pairs; ++k) {
+            const int rc = launch_pair<S, false>(p, (k & 1) ? fb : fa, (k & 1) ? fa : fb, st);
+            if (rc != PLBM_OK) return rc;
+        }
+        s0 = 2 * pairs;
+    }
+    for (int s = s0; s < nsteps; ++s) {
         const void *src = (s & 1) ? fb : fa;
         void *dst = (s & 1) ? fa : fb;
         const bool last = (s == nsteps - 1);

@@ -1,0 +1,344 @@
+// Several fused steps per launch on a periodic 2D lattice: a strip of columns
+// is swept in y and the populations between the steps never leave the CU.
+// Internal header (not part of the C ABI), on top of plbm_device.h.
+//
+// A model M gives the storage type T, the arithmetic type C, the velocities
+// V[Q1] of one axis (compile time), the parameters P (with nx and ny), and
+// dec / enc / key / collide of one node.  R = max |v|, q = Q1^2.
+//
+// A workgroup of SWEEP_T threads owns the output nodes [xs, xs + w) x
+// [ya, yb) of D steps; a thread holds one column.  In iteration `it` stage s
+// (the step s of the D) takes row ya - R (D - 1) + it - s R: R rows behind
+// stage s - 1, whose population (i, j) of row r it reads at row r + v_j, i.e.
+// v_j + R iterations after it was made.  So the line of velocity j holds
+// v_j + R + 1 rows, (R + 1) Q1 rows in all for a symmetric set.  The shifted x
+// velocities keep theirs in LDS (a neighbouring lane reads them), v_i = 0 in
+// registers (the same lane does).  Values between the steps are held in the
+// storage type, encoded and decoded as through memory, so the fused steps
+// give bitwise what D launches of the single step give.
+//
+// What bounds it: D single steps read and write every population D times at
+// the HBM rate; here once, plus the halo (R (D - 1) columns and rows on each
+// side are computed twice by neighbours).
+#pragma once
+#include "plbm_device.h"
+
+namespace {
+
+constexpr int SWEEP_T = 256;              // threads of a workgroup
+constexpr int SWEEP_CUS = 256;            // compute units of an MI355X
+constexpr size_t SWEEP_LDS = 160 * 1024;  // LDS of one of them
+
+// The delay lines of a velocity set.
+template <class M>
+struct Lines {
+    static constexpr int reach()
+    {
+        int r = 0;
+        for (int i = 0; i < M::Q1; ++i) r = M::V[i] > r ? M::V[i] : (-M::V[i] > r ? -M::V[i] : r);
+        return r;
+    }
+    static constexpr int R = reach();
+    static constexpr int len(int j) { return M::V[j] + R + 1; }
+    static constexpr int base(int j)           // first LDS row of line j
+    {
+        int b = 0;
+        for (int k = 0; k < j; ++k) b += len(k);
+        return b;
+    }
+    static constexpr int rbase(int j)          // first register of line j
+    {
+        int b = 0;
+        for (int k = 0; k < j; ++k) b += len(k) - 1;
+        return b;
+    }
+    static constexpr int still()               // the x velocity 0, or -1
+    {
+        for (int i = 0; i < M::Q1; ++i)
+            if (M::V[i] == 0) return i;
+        return -1;
+    }
+    static constexpr int I0 = still();
+    static constexpr int ROWS = base(M::Q1);
+    static constexpr int REGS = I0 < 0 ? 1 : rbase(M::Q1);
+    static constexpr int COLS = M::Q1 - (I0 >= 0 ? 1 : 0);    // x velocities kept in LDS
+    static constexpr int column(int i) { return I0 >= 0 && i > I0 ? i - 1 : i; }
+};
+
+template <class M, int D>
+constexpr size_t sweep_lds_bytes()
+{
+    return (size_t)(D - 1) * Lines<M>::ROWS * Lines<M>::COLS * SWEEP_T * sizeof(typename M::T);
+}
+// Workgroups a CU holds, four at most (one wave of each on every SIMD).
+template <class M, int D>
+constexpr int sweep_per_cu()
+{
+    return (int)(SWEEP_LDS / sweep_lds_bytes<M, D>()) < 4 ? (int)(SWEEP_LDS / sweep_lds_bytes<M, D>()) : 4;
+}
+
+// Strips of w columns, chunks of h rows; workgroup b takes strip b % strips
+// of chunk b / strips.
+struct SweepGrid {
+    int strips, chunks, w, h;
+};
+
+// The partition of an nx x ny lattice.  Strips begin on cache lines (128 B;
+// 64 B for the 16-bit forms, whose 128 B would cost a quarter of the lanes):
+// stores that end inside a line left the D2Q25 pair at 4096^2 at 489 us a step
+// in FP32 against 373.  Chunks: one round of resident workgroups while that
+// leaves them at most 24 rows, else 16 rows (32 for 16-bit storage, which
+// spends vector work and not bandwidth on the rows computed twice): long
+// chunks spread the accesses over so much memory that the FP32 pair took
+// 373 us a step with 157 rows, 318 with 64 and 313 with 16.
+template <class M>
+constexpr int sweep_align() { return sizeof(typename M::T) == 2 ? 32 : 128 / (int)sizeof(typename M::T); }
+template <class M, int D>
+constexpr int sweep_wmax()
+{
+    return (SWEEP_T - 2 * Lines<M>::R * (D - 1)) / sweep_align<M>() * sweep_align<M>();
+}
+template <class M, int D>
+inline SweepGrid sweep_grid(int nx, int ny)
+{
+    constexpr int es = (int)sizeof(typename M::T);
+    constexpr int align = sweep_align<M>(), wmax = sweep_wmax<M, D>();
+    constexpr int slots = SWEEP_CUS * sweep_per_cu<M, D>();
+    SweepGrid g;
+    g.strips = (nx + wmax - 1) / wmax;
+    g.w = ((nx + g.strips - 1) / g.strips + align - 1) / align * align;
+    g.strips = (nx + g.w - 1) / g.w;
+    const int round = std::max(1, slots / g.strips);
+    g.h = (ny + round - 1) / round;
+    if (g.h > 24) g.h = std::min(ny, es == 2 ? 32 : 16);
+    g.chunks = (ny + g.h - 1) / g.h;
+    return g;
+}
+
+// Barrier for LDS traffic only: global loads and stores stay in flight.
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+__device__ __forceinline__ int wrap_mod(int a, int n)
+{
+    a %= n;
+    return a < 0 ? a + n : a;
+}
+
+// Stores of one row block through a buffer descriptor: a lane whose byte
+// offset lies past the block writes nothing, so the stores need no branch and
+// the wait for the next row's loads can count them (a branch around them
+// makes the compiler wait for every store in flight).  A block holds less
+// than 2^31 bytes (see sweep_fits).
+constexpr unsigned SWEEP_DROP = 0x80000000u;
+struct RowStore {
+    __amdgpu_buffer_rsrc_t r;
+    __device__ __forceinline__ RowStore(void *base, unsigned bytes)
+        : r(__builtin_amdgcn_make_buffer_rsrc(base, 0, (int)bytes, 0x00020000)) {}
+    static constexpr int AUX = PLBM_NT_STORE ? 2 : 0;            // non-temporal
+    __device__ __forceinline__ void put(double v, unsigned vo, unsigned so) const
+    {
+        typedef unsigned U2 __attribute__((ext_vector_type(2)));
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U2, v), r, vo, so, AUX);
+    }
+    __device__ __forceinline__ void put(float v, unsigned vo, unsigned so) const
+    {
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, vo, so, AUX);
+    }
+    __device__ __forceinline__ void put(uint16_t v, unsigned vo, unsigned so) const
+    {
+        __builtin_amdgcn_raw_buffer_store_b16(v, r, vo, so, AUX);
+    }
+};
+
+template <class M>
+inline bool sweep_fits(int nx)
+{
+    return (long long)M::Q1 * M::Q1 * nx * (long long)sizeof(typename M::T) < (1ll << 31);
+}
+
+// D steps of the strip.  FIELDS (models with collide(f, p, mom)): the first
+// step also writes the fields of the owned nodes.
+template <class M, int D, bool FIELDS = false>
+__device__ __forceinline__ void sweep(const typename M::T *__restrict__ src, typename M::T *__restrict__ dst,
+                                      const typename M::P &p, int xs, int w, int ya, int yb,
+                                      typename M::T *__restrict__ lds, const FieldsOut &fo = FieldsOut{})
+{
+    using T = typename M::T;
+    using C = typename M::C;
+    using L = Lines<M>;
+    constexpr int Q1 = M::Q1, NP = Q1 * Q1, I0 = L::I0;
+    constexpr int halo = L::R * (D - 1);
+    const int nx = p.nx, ny = p.ny;
+    const int t = threadIdx.x;
+    const long long rowelems = (long long)NP * nx;
+    const unsigned colbytes = (unsigned)nx * (unsigned)sizeof(T);
+    // threads 0 .. w - 1 hold the strip's own columns, the next `halo` those
+    // on its right and as many more those on its left; threads past them
+    // repeat the last (no new bytes)
+    const int span = w + 2 * halo;
+    const int tc = min(t, span - 1);
+    const int x = wrap_mod(xs + (tc < w + halo ? tc : tc - span), nx);
+    const bool own = t < w && xs + t < nx;
+    const unsigned vo = own ? (unsigned)x * (unsigned)sizeof(T) : SWEEP_DROP;
+    // where column x - v_i stands in memory and among the strip's (the strip
+    // closes on itself: what wraps is read by columns that nothing needs)
+    unsigned lo[Q1];
+    int col[Q1];
+#pragma unroll
+    for (int i = 0; i < Q1; ++i) {
+        int c = x - M::V[i];
+        c += (c < 0) ? nx : 0;
+        c -= (c >= nx) ? nx : 0;
+        lo[i] = (unsigned)c * (unsigned)sizeof(T) + (unsigned)i * colbytes;
+        c = tc - M::V[i];
+        c += (c < 0) ? span : 0;
+        c -= (c >= span) ? span : 0;
+        col[i] = L::column(i) * SWEEP_T + c;
+        asm volatile("" : "+v"(lo[i]), "+v"(col[i]));
+    }
+    T raw[NP], h[NP], reg[D - 1][L::REGS];
+#pragma unroll
+    for (int s = 0; s < D - 1; ++s)
+#pragma unroll
+        for (int m = 0; m < L::REGS; ++m) reg[s][m] = T(0);
+    auto load_row = [&](int yr) {
+#pragma unroll
+        for (int j = 0; j < Q1; ++j) {
+            int ys = yr - M::V[j];
+            ys += (ys < 0) ? ny : 0;
+            ys -= (ys >= ny) ? ny : 0;
+            const T *base = src + (ys * rowelems + (long long)(Q1 * j) * nx);
+#pragma unroll
+            for (int i = 0; i < Q1; ++i) {
+                const T *q = &base[lo[i] / sizeof(T)];
+                // the still column reads the wave's own nodes only
+                raw[i + Q1 * j] = i == I0 ? __builtin_nontemporal_load(q) : *q;
+            }
+        }
+    };
+    const int iters = yb - ya + 2 * halo;
+    int slot[Q1];                       // of each line: the row being written, then the oldest
+#pragma unroll
+    for (int j = 0; j < Q1; ++j) slot[j] = 0;
+    auto row_of = [&](int it, int s) {  // the lattice row of stage s
+        return wrap_mod(ya - halo + it - s * L::R, ny);
+    };
+    auto key_of = [&](int it, int s) {
+        return M::KEYED ? M::key((uint32_t)row_of(it, s) * (uint32_t)nx + (uint32_t)x) : 0u;
+    };
+    auto put_lines = [&](int s) {
+        T *ring = lds + s * (L::ROWS * L::COLS * SWEEP_T) + t;
+#pragma unroll
+        for (int j = 0; j < Q1; ++j)
+#pragma unroll
+            for (int i = 0; i < Q1; ++i)
+                if (i != I0) ring[((L::base(j) + slot[j]) * L::COLS + L::column(i)) * SWEEP_T] = h[i + Q1 * j];
+    };
+    // stage s of iteration `it`: f <- the rows stage s - 1 left, relaxed
+    auto stage = [&](int s, C(&f)[NP]) {
+        const T *ring = lds + (s - 1) * (L::ROWS * L::COLS * SWEEP_T);
+#pragma unroll
+        for (int j = 0; j < Q1; ++j) {
+            int old = slot[j] + 1 == L::len(j) ? 0 : slot[j] + 1;
+            const T *row = ring + (L::base(j) + old) * (L::COLS * SWEEP_T);
+#pragma unroll
+            for (int i = 0; i < Q1; ++i) {
+                T v;
+                if (i != I0) v = row[col[i]];
+                else if (L::len(j) == 1) v = h[i + Q1 * j];
+                else v = reg[s - 1][L::rbase(j) + (L::len(j) > 1 ? L::len(j) - 2 : 0)];
+                f[i + Q1 * j] = M::dec(v, i + Q1 * j, p);
+            }
+        }
+        // the registers' lines move on by one row, newest first
+        if constexpr (I0 >= 0) {
+#pragma unroll
+            for (int j = 0; j < Q1; ++j)
+#pragma unroll
+                for (int m = L::len(j) - 2; m >= 0; --m)
+                    reg[s - 1][L::rbase(j) + m] = m == 0 ? h[I0 + Q1 * j] : reg[s - 1][L::rbase(j) + m - 1];
+        }
+        M::collide(f, p);
+    };
+    auto next_slot = [&]() {
+#pragma unroll
+        for (int j = 0; j < Q1; ++j) slot[j] = slot[j] + 1 == L::len(j) ? 0 : slot[j] + 1;
+    };
+    // stages 0 .. D - 2 of an iteration, and the next row's loads behind the
+    // first of them
+    auto front = [&](int it, int yr, int ynext) {
+        C f[NP];
+#pragma unroll
+        for (int k = 0; k < NP; ++k) f[k] = M::dec(raw[k], k, p);
+        if constexpr (FIELDS) {
+            C mom[4];
+            M::collide(f, p, mom);
+            if (own && it >= halo && it < iters - halo) {
+                const long long n = (long long)yr * nx + x;
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (fo.p[q]) fo.p[q][n] = (double)mom[q];
+            }
+        } else {
+            M::collide(f, p);
+        }
+        const uint32_t k0 = key_of(it, 0);
+#pragma unroll
+        for (int k = 0; k < NP; ++k) h[k] = M::enc(f[k], k, p, k0);
+        put_lines(0);
+        load_row(ynext);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 1; s < D - 1; ++s) {
+            lds_barrier();
+            stage(s, f);
+            const uint32_t ks = key_of(it, s);
+#pragma unroll
+            for (int k = 0; k < NP; ++k) h[k] = M::enc(f[k], k, p, ks);
+            put_lines(s);
+        }
+        lds_barrier();
+    };
+    int yr = row_of(0, 0);
+    load_row(yr);
+#pragma unroll 1
+    for (int it = 0; it < 2 * halo; ++it) {
+        const int yn = yr + 1 == ny ? 0 : yr + 1;
+        front(it, yr, yn);
+        C f[NP];
+        stage(D - 1, f);                // moves the last stage's registers on
+        if constexpr (D == 2) lds_barrier();
+        next_slot();
+        yr = yn;
+    }
+    // as many (dropped) stores behind the loads as the loop leaves there, so
+    // that its wait for the loads may let that many stores pass
+    {
+        const RowStore out(dst, colbytes * NP);
+#pragma unroll
+        for (int k = 0; k < NP; ++k) out.put(raw[k], SWEEP_DROP, (unsigned)k * colbytes);
+    }
+#pragma unroll 1
+    for (int it = 2 * halo; it < iters; ++it) {
+        // the last time: a row read before, not used
+        const int yn = it + 1 == iters ? yr : (yr + 1 == ny ? 0 : yr + 1);
+        front(it, yr, yn);
+        C f[NP];
+        stage(D - 1, f);
+        const int yo = ya + it - 2 * halo;
+        const uint32_t ko = M::KEYED ? M::key((uint32_t)yo * (uint32_t)nx + (uint32_t)x) : 0u;
+        const RowStore out(dst + yo * rowelems, colbytes * NP);
+#pragma unroll
+        for (int k = 0; k < NP; ++k) out.put(M::enc(f[k], k, p, ko), vo, (unsigned)k * colbytes);
+        if constexpr (D == 2) lds_barrier();
+        next_slot();
+        yr = yn;
+    }
+}
+
+} // namespace

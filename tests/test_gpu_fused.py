@@ -1,0 +1,80 @@
+"""Several steps fused into one launch against the same steps launched one by
+one.  Both round the same operations in the same order and hold the values
+between the steps in the storage type, so every population must be equal bit
+for bit; the tolerance is zero."""
+import pytest
+import torch
+
+from paper_1402_5487_amd import inputs
+from paper_1402_5487_amd.lattice import Lattice
+
+pytestmark = pytest.mark.gpu
+
+
+def _pair(make, fields, split, whole):
+    """Two lattices of one state: one stepped step by step, one in calls of `whole`."""
+    a, b = make().init(*fields), make().init(*fields)
+    for n in whole:
+        a.step(n)
+    for _ in range(split):
+        b.step(1)
+    return a, b
+
+
+# strips of 224 (FP32) and 240 (FP64) columns: just below, at and past their
+# multiples, ragged rows, rows that leave the last strip a single column,
+# more rows than a chunk and fewer than its halo
+@pytest.mark.parametrize("nx,ny", [(224, 601), (225, 590), (241, 600), (448, 293), (449, 300),
+                                   (1501, 97), (16385, 8), (4096, 37)])
+@pytest.mark.parametrize("storage", ["f64", "f32"])
+def test_fused_steps_equal_single_steps(nx, ny, storage):
+    fields = inputs.random_fields(nx, ny, seed=nx + ny)
+    a, b = _pair(lambda: Lattice(2, nx, ny, omega=1.7, storage=storage), fields, 11, (5, 4, 2))
+    assert torch.equal(a.f, b.f) and a.cur == b.cur
+
+
+@pytest.mark.parametrize("nx,ny", [(1501, 1100), (1345, 1121), (224, 6700)])
+@pytest.mark.parametrize("storage,rounding", [("f16dev", "nearest"), ("bf16dev", "nearest"),
+                                              ("f16dev", "stochastic"), ("bf16dev", "stochastic")])
+def test_fused_16_bit_steps_equal_single_steps(nx, ny, storage, rounding):
+    fields = inputs.random_fields(nx, ny, seed=nx)
+    a, b = _pair(lambda: Lattice(2, nx, ny, omega=1.7, storage=storage, rounding=rounding, theta0=0.35),
+                 fields, 8, (8,))
+    assert torch.equal(a.f, b.f)
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32"])
+def test_fused_steps_with_fields_and_sums(storage):
+    """The first of the fused steps writes the fields of the state it reads;
+    a step that takes sums comes after fused ones."""
+    nx, ny = 450, 400
+    fields = inputs.random_fields(nx, ny, seed=5)
+    a, b = (Lattice(2, nx, ny, omega=1.7, storage=storage).init(*fields) for _ in range(2))
+    got, want = a.step_fields(7), b.step_fields(1)
+    for _ in range(6):
+        b.step(1)
+    assert torch.equal(a.f, b.f)
+    assert all(torch.equal(g, w) for g, w in zip(got, want))
+    s, t = a.step(6, sums=True), None
+    for _ in range(6):
+        t = b.step(1, sums=True)
+    assert torch.equal(a.f, b.f) and s == t
+
+
+def test_fused_steps_in_a_graph():
+    """Captured once, replayed between eager work: every replay as eager."""
+    nx, ny = 700, 300
+    fields = inputs.random_fields(nx, ny, seed=2)
+    a, b = (Lattice(2, nx, ny, omega=1.7, storage="f32").init(*fields) for _ in range(2))
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(s):
+        with torch.cuda.graph(g, stream=s):
+            a.step(4)
+    torch.cuda.current_stream().wait_stream(s)
+    for _ in range(3):
+        g.replay()
+        b.step(4)
+        torch.cuda.synchronize()
+        assert torch.equal(a.f, b.f)
