@@ -13,7 +13,8 @@
 // (y q + k) nx + x with q = q1d^2 and k = i + q1d j.  Same streaming design
 // as the specialised steps: one 256-node row segment per workgroup,
 // XCD-contiguous tiles, a scalar row base per y velocity and a lane offset
-// per x velocity (x wrap folded in), non-temporal stores.  FP64 storage
+// per x velocity (x wrap folded in), non-temporal stores; larger D2Q16 {+-1,
+// +-3} and D2Q49 lattices take two steps a launch.  FP64 storage
 // computes in FP64, FP32 in FP32.
 #include <hip/hip_runtime.h>
 
@@ -24,6 +25,7 @@
 
 #include "plbm_device.h"
 #include "plbm_internal.h"
+#include "plbm_sweep.h"
 
 namespace {
 
@@ -222,6 +224,33 @@ __global__ __launch_bounds__(TX) void k_step_gen2d(const T *__restrict__ src, T 
         }
     }
     if constexpr (SUMS) block_sums_store<4>(acc, partials + (size_t)blockIdx.x * 4);
+}
+
+// Two steps per launch (plbm_sweep.h) of one velocity set.
+template <typename T_, int SPAN_, int... Vs>
+struct GenSet {
+    using T = T_;
+    using C = T_;
+    using P = GenParams;
+    static constexpr int Q1 = sizeof...(Vs);
+    static constexpr int V[Q1] = {Vs...};
+    static constexpr bool KEYED = false;
+    static constexpr int SPAN = SPAN_, WGS = 4, ROUNDS_H = 16;
+    static __device__ __forceinline__ C dec(T h, int, const P &) { return h; }
+    static __device__ __forceinline__ T enc(C f, int, const P &, uint32_t) { return f; }
+    static __device__ __forceinline__ uint32_t key(uint32_t node) { return node; }
+    static __device__ __forceinline__ void collide(C (&f)[Q1 * Q1], const P &p) { collide_gen2d<Q1, C>(f, p); }
+};
+
+template <class M>
+__global__ __launch_bounds__(sweep_threads<M>(), (sweep_per_cu<M, 2>())) void
+k_pair_gen(const typename M::T *__restrict__ src, typename M::T *__restrict__ dst, GenParams p, SweepGrid g)
+{
+    extern __shared__ __align__(16) unsigned char sweep_lds[];
+    const int b = xcd_tile(blockIdx.x, gridDim.x);
+    const int c = b / g.strips, ya = c * g.h;
+    sweep<M, 2>(src, dst, p, (b - c * g.strips) * g.w, g.w, ya, min(ya + g.h, p.ny),
+                reinterpret_cast<typename M::T *>(sweep_lds));
 }
 
 // Initial state: f_eq of node (x, y) in FP64, written to (x - v_i, y - v_j).
@@ -473,11 +502,55 @@ void gen_launch(const GenParams &p, const T *src, T *dst, double *part, hipStrea
         hipLaunchKernelGGL((k_step_gen1d<Q1, T, SUMS>), dim3(grid_g(p)), dim3(TX), 0, st, src, dst, p, part);
 }
 
+// Fused pairs fa -> fb -> fa .. of n steps; returns how many steps they took,
+// or a (negative) status.  Which lattices take them: from 2^18 nodes on, with
+// at least half the lanes of their strips in use.  Measured per step (us,
+// single -> pair): D2Q16 FP32 256^2 4.8 -> 5.2, 512^2 8.7 -> 7.5, 2048^2
+// 90 -> 58, FP64 2048^2 173 -> 108; D2Q49 FP32 256^2 6.0 -> 11.0, 512^2
+// 22.4 -> 21.2, 2048^2 270 -> 198, FP64 1501 x 1100 289 -> 215, 2048^2
+// 554 -> 490.  Three steps a launch leave D2Q16 one workgroup per CU: 70.
+template <class M>
+int gen_pairs(const GenParams &p, void *fa, void *fb, int n, hipStream_t st)
+{
+    using T = typename M::T;
+    constexpr int D = 2;
+    if (!sweep_fits<M>(p.nx) || (long long)p.nx * p.ny < 1 << 18) return 0;
+    for (int i = 0; i < M::Q1; ++i)
+        if (p.sx[i] != M::V[i]) return 0;
+    constexpr long long wmax = sweep_wmax<M, D>();
+    if (2ll * p.nx < (p.nx + wmax - 1) / wmax * wmax) return 0;
+    const SweepGrid g = sweep_grid<M, D>(p.nx, p.ny);
+    const int launches = fused_launches<D>(n);
+    for (int k = 0; k < launches; ++k) {
+        (void)hipGetLastError();
+        hipLaunchKernelGGL((k_pair_gen<M>), dim3(g.strips * g.chunks), dim3(sweep_threads<M>()),
+                           (sweep_lds_bytes<M, D>()), st, (const T *)((k & 1) ? fb : fa), (T *)((k & 1) ? fa : fb), p,
+                           g);
+        const int rc = gen_launch_status();
+        if (rc != PLBM_OK) return rc;
+    }
+    return launches * D;
+}
+
+// The sets that have fused pairs (in this order of their velocities).
+template <int Q1, typename T>
+int fused_steps(const GenParams &p, void *fa, void *fb, int n, hipStream_t st)
+{
+    if (p.dim != 2) return 0;
+    if constexpr (Q1 == 4) return gen_pairs<GenSet<T, 256, 1, -1, 3, -3>>(p, fa, fb, n, st);
+    // 28 rows of six columns: what the LDS of one workgroup holds
+    if constexpr (Q1 == 7)
+        return gen_pairs<GenSet<T, sizeof(T) == 8 ? 112 : 232, 0, 1, -1, 2, -2, 3, -3>>(p, fa, fb, n, st);
+    return 0;
+}
+
 template <int Q1, typename T>
 int gen_run(const GenParams &p, void *fa, void *fb, int nsteps, double *sums, hipStream_t st)
 {
     const int grid = grid_g(p);
-    for (int s = 0; s < nsteps; ++s) {
+    const int s0 = fused_steps<Q1, T>(p, fa, fb, nsteps - (sums ? 1 : 0), st);
+    if (s0 < 0) return s0;
+    for (int s = s0; s < nsteps; ++s) {
         const T *src = static_cast<const T *>((s & 1) ? fb : fa);
         T *dst = static_cast<T *>((s & 1) ? fa : fb);
         (void)hipGetLastError();

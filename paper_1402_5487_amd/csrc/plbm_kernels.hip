@@ -102,6 +102,9 @@ struct Thermal25 {
     static constexpr int Q1 = Q;
     static constexpr int V[Q] = {0, 1, -1, 3, -3};
     static constexpr bool KEYED = S::keyed;
+    static constexpr int SPAN = 256, WGS = 4;
+    // 16-bit storage spends vector work, not bandwidth, on rows computed twice
+    static constexpr int ROUNDS_H = sizeof(T) == 2 ? 32 : 16;
     static __device__ __forceinline__ C dec(T h, int k, const P &p) { return S::dec(h, k, p); }
     static __device__ __forceinline__ T enc(C f, int k, const P &p, uint32_t key)
     {
@@ -124,7 +127,7 @@ struct Thermal25 {
 constexpr int PAIR = 2;
 
 template <class S, bool FIELDS>
-__global__ __launch_bounds__(SWEEP_T, (sweep_per_cu<Thermal25<S>, PAIR>())) void
+__global__ __launch_bounds__(sweep_threads<Thermal25<S>>(), (sweep_per_cu<Thermal25<S>, PAIR>())) void
 k_step2d_pair(const typename S::T *__restrict__ src, typename S::T *__restrict__ dst, KParams p, SweepGrid g,
               FieldsOut fo)
 {
@@ -458,7 +461,7 @@ int launch_pair(const KParams &p, const void *src, void *dst, hipStream_t st, Fi
     using T = typename S::T;
     const SweepGrid g = sweep_grid<Thermal25<S>, PAIR>(p.nx, p.ny);
     clear_launch_error();
-    hipLaunchKernelGGL((k_step2d_pair<S, FIELDS>), dim3(g.strips * g.chunks), dim3(SWEEP_T),
+    hipLaunchKernelGGL((k_step2d_pair<S, FIELDS>), dim3(g.strips * g.chunks), dim3(sweep_threads<Thermal25<S>>()),
                        (sweep_lds_bytes<Thermal25<S>, PAIR>()), st, (const T *)src, (T *)dst, p, g, fo);
     return launch_status();
 }
@@ -484,10 +487,6 @@ bool use_pairs(const KParams &p, const plbm_desc *d)
     return narrow ? 4ll * p.nx >= 3 * lanes : 2ll * p.nx >= lanes;
 }
 
-// Of n steps, as many in fused pairs as leave the state in the buffer where
-// single steps leave it: an even number of launches of two.
-inline int pairs_of(int n) { return n / 4 * 2; }
-
 // 2D steps of which the first also writes the fields of the state it reads.
 template <class S>
 int run_steps_fields(const KParams &p, const plbm_desc *d, void *fa, void *fb, int nsteps, FieldsOut fo,
@@ -495,7 +494,7 @@ int run_steps_fields(const KParams &p, const plbm_desc *d, void *fa, void *fb, i
 {
     using T = typename S::T;
     int s0 = 1;
-    const int pairs = use_pairs<S>(p, d) ? pairs_of(nsteps) : 0;
+    const int pairs = use_pairs<S>(p, d) ? fused_launches<PAIR>(nsteps) : 0;
     if (pairs > 0) {
         int rc = launch_pair<S, true>(p, fa, fb, st, fo);
         for (int k = 1; k < pairs && rc == PLBM_OK; ++k)
@@ -532,7 +531,7 @@ int run_steps(const KParams &p, const plbm_desc *d, void *fa, void *fb, int nste
     int nb = 0;
     int s0 = 0;
     if (use_pairs<S>(p, d)) {
-        const int pairs = pairs_of(nsteps - (sums ? 1 : 0));    // a step that takes sums is a single one
+        const int pairs = fused_launches<PAIR>(nsteps - (sums ? 1 : 0));    // a step that takes sums is a single one
         for (int k = 0; k < pairs; ++k) {
             const int rc = launch_pair<S, false>(p, (k & 1) ? fb : fa, (k & 1) ? fa : fb, st);
             if (rc != PLBM_OK) return rc;

@@ -14,7 +14,8 @@
 // workgroup with XCD-contiguous tile numbering, a scalar row base per y
 // velocity plus a 32-bit lane offset per x velocity (the periodic wrap in x
 // folded into the offsets), non-temporal stores (and loads for 4- and
-// 8-byte populations).  FP64 storage computes in FP64, FP32 in FP32.
+// 8-byte populations).  The set {0, +-1} takes up to five steps a launch
+// (plbm_sweep.h).  FP64 storage computes in FP64, FP32 in FP32.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -24,6 +25,7 @@
 
 #include "plbm_device.h"
 #include "plbm_internal.h"
+#include "plbm_sweep.h"
 
 namespace {
 
@@ -133,6 +135,25 @@ __device__ __forceinline__ void gather9(const T *__restrict__ src, const Q9Param
     }
 }
 
+// In place: f <- (1 - omega) f + omega rho r^x_i r^y_j (Eq. srt, collision half).
+template <typename C>
+__device__ __forceinline__ void collide9(C (&f)[N9], const Rule3<C> &R)
+{
+    C rho, jx, jy, e;
+    sums9<C>(f, R, rho, jx, jy, e);
+    const C inv = C(1) / rho;
+    C rx[Q3], ry[Q3];
+    rule3<C>(jx * inv, R, rx);
+    rule3<C>(jy * inv, R, ry);
+    const C wr = R.omega * rho, keep = C(1) - R.omega;
+#pragma unroll
+    for (int i = 0; i < Q3; ++i) rx[i] *= wr;
+#pragma unroll
+    for (int j = 0; j < Q3; ++j)
+#pragma unroll
+        for (int i = 0; i < Q3; ++i) f[i + Q3 * j] = fma(keep, f[i + Q3 * j], rx[i] * ry[j]);
+}
+
 // One step (Eq. srt): gather, moments, isothermal equilibrium f_eq =
 // rho r^x_i r^y_j, relax, store at x.  Optional FP64 block sums of what is
 // stored (sum f, sum f v_x, sum f v_y, sum f |v|^2).
@@ -150,24 +171,13 @@ __global__ __launch_bounds__(TX) void k_step_q9(const T *__restrict__ src, T *__
         const int xb = (tile - y * p.tiles_x) * TX + threadIdx.x;
         C f[N9];
         gather9<T, C>(src, p, xb, y, f);
-        C rho, jx, jy, e;
-        sums9<C>(f, R, rho, jx, jy, e);
-        const C inv = C(1) / rho;
-        C rx[Q3], ry[Q3];
-        rule3<C>(jx * inv, R, rx);
-        rule3<C>(jy * inv, R, ry);
-        const C wr = R.omega * rho, keep = C(1) - R.omega;
-#pragma unroll
-        for (int i = 0; i < Q3; ++i) rx[i] *= wr;
-#pragma unroll
-        for (int j = 0; j < Q3; ++j)
-#pragma unroll
-            for (int i = 0; i < Q3; ++i) f[i + Q3 * j] = fma(keep, f[i + Q3 * j], rx[i] * ry[j]);
+        collide9<C>(f, R);
         if (xb < p.nx) {
             if constexpr (SUMS) {
                 C g[N9];
 #pragma unroll
                 for (int k = 0; k < N9; ++k) g[k] = (C)(T)f[k];
+                C rho, jx, jy, e;
                 sums9<C>(g, R, rho, jx, jy, e);
                 acc[0] += rho;
                 acc[1] += jx;
@@ -180,6 +190,33 @@ __global__ __launch_bounds__(TX) void k_step_q9(const T *__restrict__ src, T *__
         }
     }
     if constexpr (SUMS) block_sums_store<4>(acc, partials + (size_t)blockIdx.x * 4);
+}
+
+// Several steps per launch (plbm_sweep.h) of the set {0, +1, -1}.
+template <typename T_>
+struct Iso9 {
+    using T = T_;
+    using C = T_;
+    using P = Q9Params;
+    static constexpr int Q1 = Q3;
+    static constexpr int V[Q3] = {0, 1, -1};
+    static constexpr bool KEYED = false;
+    static constexpr int SPAN = 256, WGS = 4, ROUNDS_H = 24;
+    static __device__ __forceinline__ C dec(T h, int, const P &) { return h; }
+    static __device__ __forceinline__ T enc(C f, int, const P &, uint32_t) { return f; }
+    static __device__ __forceinline__ uint32_t key(uint32_t node) { return node; }
+    static __device__ __forceinline__ void collide(C (&f)[N9], const P &p) { collide9<C>(f, rule_of<C>(p)); }
+};
+
+template <class M, int D>
+__global__ __launch_bounds__(sweep_threads<M>(), (sweep_per_cu<M, D>())) void
+k_sweep_q9(const typename M::T *__restrict__ src, typename M::T *__restrict__ dst, Q9Params p, SweepGrid g)
+{
+    extern __shared__ __align__(16) unsigned char sweep_lds[];
+    const int b = xcd_tile(blockIdx.x, gridDim.x);
+    const int c = b / g.strips, ya = c * g.h;
+    sweep<M, D>(src, dst, p, (b - c * g.strips) * g.w, g.w, ya, min(ya + g.h, p.ny),
+                reinterpret_cast<typename M::T *>(sweep_lds));
 }
 
 // Initial state: node x evaluates f_eq(rho, u; theta0) in FP64 and writes
@@ -402,11 +439,52 @@ void q3_launch(const Q9Params &p, const T *src, T *dst, double *part, hipStream_
     }
 }
 
+template <class M, int D>
+int launch_sweep_q9(const Q9Params &p, const typename M::T *src, typename M::T *dst, hipStream_t st)
+{
+    const SweepGrid g = sweep_grid<M, D>(p.nx, p.ny);
+    (void)hipGetLastError();
+    hipLaunchKernelGGL((k_sweep_q9<M, D>), dim3(g.strips * g.chunks), dim3(sweep_threads<M>()),
+                       (sweep_lds_bytes<M, D>()), st, src, dst, p, g);
+    return q9_launch_status();
+}
+
+// Steps a launch takes.  Measured at 4096^2 (us a step; single 192 FP32, 374
+// FP64): FP32 three steps 77, four 58, five 54, seven 76 (the halo rows and
+// columns and the workgroups per CU go the other way); FP64 three 150, four
+// 112, five 124.
+template <typename T>
+constexpr int Q9_DEPTH = sizeof(T) == 8 ? 4 : 5;
+
+// Every lattice but the narrowest gains: FP32 64^2 4.6 -> 2.7 us a step, 512^2
+// 5.0 -> 4.4, 1024^2 16.3 -> 6.3, 100 x 4000 7.6 -> 5.7.
+template <typename T>
+bool use_sweeps(const Q9Params &p)
+{
+    return p.sx[1] == 1 && p.nx >= 16 && sweep_fits<Iso9<T>>(p.nx);
+}
+
 template <typename T, typename C>
 int q9_run(const Q9Params &p, void *fa, void *fb, int nsteps, double *sums, hipStream_t st)
 {
     const int nblocks = p.dim == 2 ? grid_for(p.ntiles) : p.tiles_x;
-    for (int s = 0; s < nsteps; ++s) {
+    int s0 = 0, launches = 0;
+    if (p.dim == 2 && use_sweeps<T>(p)) {
+        // D steps a launch, then three, and the rest (and a step that takes
+        // sums) one by one
+        using M = Iso9<T>;
+        const int n = nsteps - (sums ? 1 : 0);
+        const int deep = fused_launches<Q9_DEPTH<T>>(n), three = (n - deep * Q9_DEPTH<T>) / 3;
+        for (; launches < deep + three; ++launches) {
+            const T *src = static_cast<const T *>((launches & 1) ? fb : fa);
+            T *dst = static_cast<T *>((launches & 1) ? fa : fb);
+            const int rc = launches < deep ? launch_sweep_q9<M, Q9_DEPTH<T>>(p, src, dst, st)
+                                           : launch_sweep_q9<M, 3>(p, src, dst, st);
+            if (rc != PLBM_OK) return rc;
+        }
+        s0 = deep * Q9_DEPTH<T> + three * 3;
+    }
+    for (int s = s0; s < nsteps; ++s) {
         const T *src = static_cast<const T *>((s & 1) ? fb : fa);
         T *dst = static_cast<T *>((s & 1) ? fa : fb);
         (void)hipGetLastError();

@@ -6,8 +6,8 @@
 // V[Q1] of one axis (compile time), the parameters P (with nx and ny), and
 // dec / enc / key / collide of one node.  R = max |v|, q = Q1^2.
 //
-// A workgroup of SWEEP_T threads owns the output nodes [xs, xs + w) x
-// [ya, yb) of D steps; a thread holds one column.  In iteration `it` stage s
+// A workgroup owns the output nodes [xs, xs + w) x
+// [ya, yb) of D steps; a thread holds one of at most SPAN columns.  In iteration `it` stage s
 // (the step s of the D) takes row ya - R (D - 1) + it - s R: R rows behind
 // stage s - 1, whose population (i, j) of row r it reads at row r + v_j, i.e.
 // v_j + R iterations after it was made.  So the line of velocity j holds
@@ -25,7 +25,6 @@
 
 namespace {
 
-constexpr int SWEEP_T = 256;              // threads of a workgroup
 constexpr int SWEEP_CUS = 256;            // compute units of an MI355X
 constexpr size_t SWEEP_LDS = 160 * 1024;  // LDS of one of them
 
@@ -65,17 +64,25 @@ struct Lines {
     static constexpr int column(int i) { return I0 >= 0 && i > I0 ? i - 1 : i; }
 };
 
+// Threads of a workgroup: whole waves over M::SPAN columns.
+template <class M>
+constexpr int sweep_threads() { return (M::SPAN + 63) / 64 * 64; }
 template <class M, int D>
 constexpr size_t sweep_lds_bytes()
 {
-    return (size_t)(D - 1) * Lines<M>::ROWS * Lines<M>::COLS * SWEEP_T * sizeof(typename M::T);
+    return (size_t)(D - 1) * Lines<M>::ROWS * Lines<M>::COLS * M::SPAN * sizeof(typename M::T);
 }
-// Workgroups a CU holds, four at most (one wave of each on every SIMD).
+// Workgroups a CU holds, M::WGS at most (one wave of each on every SIMD).
 template <class M, int D>
 constexpr int sweep_per_cu()
 {
-    return (int)(SWEEP_LDS / sweep_lds_bytes<M, D>()) < 4 ? (int)(SWEEP_LDS / sweep_lds_bytes<M, D>()) : 4;
+    return (int)(SWEEP_LDS / sweep_lds_bytes<M, D>()) < M::WGS ? (int)(SWEEP_LDS / sweep_lds_bytes<M, D>()) : M::WGS;
 }
+
+// Of n steps, the launches of D that leave the state in the buffer where
+// single steps leave it: any number for odd D, an even one for even D.
+template <int D>
+inline int fused_launches(int n) { return D & 1 ? n / D : n / D & ~1; }
 
 // Strips of w columns, chunks of h rows; workgroup b takes strip b % strips
 // of chunk b / strips.
@@ -87,21 +94,19 @@ struct SweepGrid {
 // 64 B for the 16-bit forms, whose 128 B would cost a quarter of the lanes):
 // stores that end inside a line left the D2Q25 pair at 4096^2 at 489 us a step
 // in FP32 against 373.  Chunks: one round of resident workgroups while that
-// leaves them at most 24 rows, else 16 rows (32 for 16-bit storage, which
-// spends vector work and not bandwidth on the rows computed twice): long
-// chunks spread the accesses over so much memory that the FP32 pair took
-// 373 us a step with 157 rows, 318 with 64 and 313 with 16.
+// leaves them at most 24 rows, else M::ROUNDS_H rows: long chunks spread the
+// accesses over so much memory that the D2Q25 FP32 pair at 4096^2 took 373 us
+// a step with 157 rows, 318 with 64 and 313 with 16.
 template <class M>
 constexpr int sweep_align() { return sizeof(typename M::T) == 2 ? 32 : 128 / (int)sizeof(typename M::T); }
 template <class M, int D>
 constexpr int sweep_wmax()
 {
-    return (SWEEP_T - 2 * Lines<M>::R * (D - 1)) / sweep_align<M>() * sweep_align<M>();
+    return (M::SPAN - 2 * Lines<M>::R * (D - 1)) / sweep_align<M>() * sweep_align<M>();
 }
 template <class M, int D>
 inline SweepGrid sweep_grid(int nx, int ny)
 {
-    constexpr int es = (int)sizeof(typename M::T);
     constexpr int align = sweep_align<M>(), wmax = sweep_wmax<M, D>();
     constexpr int slots = SWEEP_CUS * sweep_per_cu<M, D>();
     SweepGrid g;
@@ -110,7 +115,7 @@ inline SweepGrid sweep_grid(int nx, int ny)
     g.strips = (nx + g.w - 1) / g.w;
     const int round = std::max(1, slots / g.strips);
     g.h = (ny + round - 1) / round;
-    if (g.h > 24) g.h = std::min(ny, es == 2 ? 32 : 16);
+    if (g.h > 24) g.h = std::min(ny, M::ROUNDS_H);
     g.chunks = (ny + g.h - 1) / g.h;
     return g;
 }
@@ -198,7 +203,7 @@ __device__ __forceinline__ void sweep(const typename M::T *__restrict__ src, typ
         c = tc - M::V[i];
         c += (c < 0) ? span : 0;
         c -= (c >= span) ? span : 0;
-        col[i] = L::column(i) * SWEEP_T + c;
+        col[i] = L::column(i) * M::SPAN + c;
         asm volatile("" : "+v"(lo[i]), "+v"(col[i]));
     }
     T raw[NP], h[NP], reg[D - 1][L::REGS];
@@ -232,20 +237,20 @@ __device__ __forceinline__ void sweep(const typename M::T *__restrict__ src, typ
         return M::KEYED ? M::key((uint32_t)row_of(it, s) * (uint32_t)nx + (uint32_t)x) : 0u;
     };
     auto put_lines = [&](int s) {
-        T *ring = lds + s * (L::ROWS * L::COLS * SWEEP_T) + t;
+        T *ring = lds + s * (L::ROWS * L::COLS * M::SPAN) + tc;
 #pragma unroll
         for (int j = 0; j < Q1; ++j)
 #pragma unroll
             for (int i = 0; i < Q1; ++i)
-                if (i != I0) ring[((L::base(j) + slot[j]) * L::COLS + L::column(i)) * SWEEP_T] = h[i + Q1 * j];
+                if (i != I0) ring[((L::base(j) + slot[j]) * L::COLS + L::column(i)) * M::SPAN] = h[i + Q1 * j];
     };
     // stage s of iteration `it`: f <- the rows stage s - 1 left, relaxed
     auto stage = [&](int s, C(&f)[NP]) {
-        const T *ring = lds + (s - 1) * (L::ROWS * L::COLS * SWEEP_T);
+        const T *ring = lds + (s - 1) * (L::ROWS * L::COLS * M::SPAN);
 #pragma unroll
         for (int j = 0; j < Q1; ++j) {
             int old = slot[j] + 1 == L::len(j) ? 0 : slot[j] + 1;
-            const T *row = ring + (L::base(j) + old) * (L::COLS * SWEEP_T);
+            const T *row = ring + (L::base(j) + old) * (L::COLS * M::SPAN);
 #pragma unroll
             for (int i = 0; i < Q1; ++i) {
                 T v;

@@ -78,3 +78,28 @@ def test_fused_steps_in_a_graph():
         b.step(4)
         torch.cuda.synchronize()
         assert torch.equal(a.f, b.f)
+
+
+# D2Q9: four (FP64) or five (FP32) steps a launch on strips of 240 and 224
+# columns, then three, then one; every remainder, fewer rows than the halo
+@pytest.mark.parametrize("nx,ny", [(16, 3), (17, 4), (31, 9), (224, 25), (225, 24), (241, 33), (700, 50)])
+@pytest.mark.parametrize("storage", ["f64", "f32"])
+def test_fused_d2q9_steps_equal_single_steps(nx, ny, storage):
+    fields = inputs.random_fields(nx, ny, seed=nx + ny, theta=(0.25, 0.25))
+    a, b = _pair(lambda: Lattice(2, nx, ny, omega=1.7, storage=storage, zeta=4.0), fields, 44,
+                 (11, 12, 8, 6, 7))
+    assert torch.equal(a.f, b.f) and a.cur == b.cur
+    s = a.step(9, sums=True)
+    for _ in range(8):
+        b.step(1)
+    assert s == b.step(1, sums=True) and torch.equal(a.f, b.f)
+
+
+@pytest.mark.parametrize("nx,ny", [(513, 512), (1121, 235), (8192, 33)])
+@pytest.mark.parametrize("storage", ["f64", "f32"])
+@pytest.mark.parametrize("v,theta", [((1, -1, 3, -3), 4.0 / 3.0), ((0, 1, -1, 2, -2, 3, -3), 1.0)])
+def test_fused_general_steps_equal_single_steps(nx, ny, storage, v, theta):
+    fields = inputs.random_fields(nx, ny, seed=nx + ny, theta=(theta, theta), u=0.03)
+    a, b = _pair(lambda: Lattice(2, nx, ny, omega=1.6, storage=storage, velocities=v, theta0=theta), fields, 11,
+                 (5, 4, 2))
+    assert torch.equal(a.f, b.f) and a.cur == b.cur
