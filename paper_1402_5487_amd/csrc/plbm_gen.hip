@@ -26,6 +26,7 @@
 #include "plbm_device.h"
 #include "plbm_internal.h"
 #include "plbm_sweep.h"
+#include "plbm_tube.h"
 
 namespace {
 
@@ -318,12 +319,43 @@ __global__ __launch_bounds__(TX) void k_moments_gen2d(const T *__restrict__ src,
 // 1D: pull f_k = src_k(x - v_k) from the padded rows, relax, write at x; the
 // three ghost nodes at each end take the edge node's post-collision values.
 // ---------------------------------------------------------------------------
-template <int Q1, typename T, bool SUMS>
-__global__ __launch_bounds__(TX) void k_step_gen1d(const T *__restrict__ src, T *__restrict__ dst, GenParams p,
+template <int Q1, typename C>
+__device__ __forceinline__ void collide_gen1d(C (&f)[Q1], const GenParams &p)
+{
+    const C *v = GenView<C>::v(p);
+    C rho = f[0], j = v[0] * f[0], e = v[0] * v[0] * f[0];
+#pragma unroll
+    for (int k = 1; k < Q1; ++k) {
+        rho += f[k];
+        j = fma(v[k], f[k], j);
+        e = fma(v[k] * v[k], f[k], e);
+    }
+    const C u = j / rho;
+    const C theta = p.iso ? GenView<C>::theta0(p) : e / rho - u * u;
+    C r[Q1];
+    rule_gen<Q1, C>(u, theta, p, r);
+    const C w = GenView<C>::omega(p);
+    const C wr = w * rho, keep = C(1) - w;
+#pragma unroll
+    for (int k = 0; k < Q1; ++k) f[k] = fma(keep, f[k], wr * r[k]);
+}
+
+// Many steps per launch (plbm_tube.h).
+template <int Q1_, typename T_>
+struct GenTube {
+    using T = T_;
+    using P = GenParams;
+    static constexpr int Q1 = Q1_, I0 = -1;
+    static __device__ __forceinline__ int shift(const P &p, int k) { return p.sx[k]; }
+    static __device__ __forceinline__ void collide(T (&f)[Q1], const P &p) { collide_gen1d<Q1, T>(f, p); }
+};
+
+// One step with the FP64 sums of what it stores.
+template <int Q1, typename T>
+__global__ __launch_bounds__(TX) void k_step_gen1d_sums(const T *__restrict__ src, T *__restrict__ dst, GenParams p,
                                                    double *__restrict__ partials)
 {
     using C = T;
-    const C *v = GenView<C>::v(p);
     const long long ps = (long long)p.nx + 2 * PLBM_GHOST;
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 1
@@ -333,36 +365,22 @@ __global__ __launch_bounds__(TX) void k_step_gen1d(const T *__restrict__ src, T 
         C f[Q1];
 #pragma unroll
         for (int k = 0; k < Q1; ++k) f[k] = (C)src[k * ps + x + PLBM_GHOST - p.sx[k]];
-        C rho = f[0], j = v[0] * f[0], e = v[0] * v[0] * f[0];
-#pragma unroll
-        for (int k = 1; k < Q1; ++k) {
-            rho += f[k];
-            j = fma(v[k], f[k], j);
-            e = fma(v[k] * v[k], f[k], e);
-        }
-        const C u = j / rho;
-        const C theta = p.iso ? GenView<C>::theta0(p) : e / rho - u * u;
-        C r[Q1];
-        rule_gen<Q1, C>(u, theta, p, r);
-        const C w = GenView<C>::omega(p);
-        const C wr = w * rho, keep = C(1) - w;
+        collide_gen1d<Q1, C>(f, p);
 #pragma unroll
         for (int k = 0; k < Q1; ++k) {
-            const T h = (T)fma(keep, f[k], wr * r[k]);
+            const T h = (T)f[k];
             dst[k * ps + x + PLBM_GHOST] = h;
             if (x == 0)
                 for (int g = 0; g < PLBM_GHOST; ++g) dst[k * ps + g] = h;
             if (x == p.nx - 1)
                 for (int g = 0; g < PLBM_GHOST; ++g) dst[k * ps + p.nx + PLBM_GHOST + g] = h;
-            if constexpr (SUMS) {
-                const double vk = p.v64[k];
-                acc[0] += (double)h;
-                acc[1] += (double)h * vk;
-                acc[3] += (double)h * vk * vk;
-            }
+            const double vk = p.v64[k];
+            acc[0] += (double)h;
+            acc[1] += (double)h * vk;
+            acc[3] += (double)h * vk * vk;
         }
     }
-    if constexpr (SUMS) block_sums_store<4>(acc, partials + (size_t)blockIdx.x * 4);
+    block_sums_store<4>(acc, partials + (size_t)blockIdx.x * 4);
 }
 
 // Padded index q holds node q - 3; its population k is f_eq_k of node
@@ -498,8 +516,8 @@ void gen_launch(const GenParams &p, const T *src, T *dst, double *part, hipStrea
     else if (p.dim == 2)
         hipLaunchKernelGGL((k_step_gen2d<Q1, T, SUMS, false>), dim3(grid_g(p)), dim3(TX), (gen_lds_cap<Q1, T>()), st,
                            src, dst, p, part);
-    else
-        hipLaunchKernelGGL((k_step_gen1d<Q1, T, SUMS>), dim3(grid_g(p)), dim3(TX), 0, st, src, dst, p, part);
+    else if constexpr (SUMS)
+        hipLaunchKernelGGL((k_step_gen1d_sums<Q1, T>), dim3(grid_g(p)), dim3(TX), 0, st, src, dst, p, part);
 }
 
 // Fused pairs fa -> fb -> fa .. of n steps; returns how many steps they took,
@@ -532,11 +550,20 @@ int gen_pairs(const GenParams &p, void *fa, void *fb, int n, hipStream_t st)
     return launches * D;
 }
 
-// The sets that have fused pairs (in this order of their velocities).
+// How many of n steps were taken several per launch, or a (negative) status:
+// all in 1D, fused pairs in 2D of the sets that have them (in this order of
+// their velocities).
 template <int Q1, typename T>
 int fused_steps(const GenParams &p, void *fa, void *fb, int n, hipStream_t st)
 {
-    if (p.dim != 2) return 0;
+    if (p.dim == 1) {
+        int reach = 0;
+        for (int i = 0; i < Q1; ++i) reach = std::max(reach, std::abs(p.sx[i]));
+        (void)hipGetLastError();
+        run_tube<GenTube<Q1, T>>(p, fa, fb, n, reach, st);
+        const int rc = gen_launch_status();
+        return rc == PLBM_OK ? n : rc;
+    }
     if constexpr (Q1 == 4) return gen_pairs<GenSet<T, 256, 1, -1, 3, -3>>(p, fa, fb, n, st);
     // 28 rows of six columns: what the LDS of one workgroup holds
     if constexpr (Q1 == 7)

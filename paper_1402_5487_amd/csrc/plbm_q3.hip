@@ -26,6 +26,7 @@
 #include "plbm_device.h"
 #include "plbm_internal.h"
 #include "plbm_sweep.h"
+#include "plbm_tube.h"
 
 namespace {
 
@@ -287,8 +288,31 @@ __global__ __launch_bounds__(TX) void k_moments_q9(const T *__restrict__ src, Q9
 // relax to rho r(u), write at x; the ghost nodes at each end take the edge
 // node's post-collision populations (zero-gradient ends, as for D1Q5).
 // ---------------------------------------------------------------------------
-template <typename T, typename C, bool SUMS>
-__global__ __launch_bounds__(TX) void k_step_q3_1d(const T *__restrict__ src, T *__restrict__ dst, Q9Params p,
+template <typename C>
+__device__ __forceinline__ void collide3(C (&f)[Q3], const Rule3<C> &R)
+{
+    const C rho = f[0] + (f[1] + f[2]);
+    const C u = R.a * (f[1] - f[2]) / rho;
+    C r[Q3];
+    rule3<C>(u, R, r);
+    const C wr = R.omega * rho, keep = C(1) - R.omega;
+#pragma unroll
+    for (int k = 0; k < Q3; ++k) f[k] = fma(keep, f[k], wr * r[k]);
+}
+
+// Many steps per launch (plbm_tube.h).
+template <typename T_>
+struct Iso3 {
+    using T = T_;
+    using P = Q9Params;
+    static constexpr int Q1 = Q3, I0 = 0;
+    static __device__ __forceinline__ int shift(const P &p, int k) { return p.sx[k]; }
+    static __device__ __forceinline__ void collide(T (&f)[Q3], const P &p) { collide3<T>(f, rule_of<T>(p)); }
+};
+
+// One step with the FP64 sums of what it stores.
+template <typename T, typename C>
+__global__ __launch_bounds__(TX) void k_step_q3_1d_sums(const T *__restrict__ src, T *__restrict__ dst, Q9Params p,
                                                    double *__restrict__ partials)
 {
     const Rule3<C> &R = rule_of<C>(p);
@@ -299,28 +323,22 @@ __global__ __launch_bounds__(TX) void k_step_q3_1d(const T *__restrict__ src, T 
         C f[Q3];
 #pragma unroll
         for (int k = 0; k < Q3; ++k) f[k] = (C)src[k * ps + x + PLBM_GHOST - p.sx[k]];
-        const C rho = f[0] + (f[1] + f[2]);
-        const C u = R.a * (f[1] - f[2]) / rho;
-        C r[Q3];
-        rule3<C>(u, R, r);
-        const C wr = R.omega * rho, keep = C(1) - R.omega;
+        collide3<C>(f, R);
 #pragma unroll
         for (int k = 0; k < Q3; ++k) {
-            const T h = (T)fma(keep, f[k], wr * r[k]);
+            const T h = (T)f[k];
             dst[k * ps + x + PLBM_GHOST] = h;
             if (x == 0)
                 for (int g = 0; g < PLBM_GHOST; ++g) dst[k * ps + g] = h;
             if (x == p.nx - 1)
                 for (int g = 0; g < PLBM_GHOST; ++g) dst[k * ps + p.nx + PLBM_GHOST + g] = h;
-            if constexpr (SUMS) {
-                const double vk = (double)p.sx[k];
-                acc[0] += (double)h;
-                acc[1] += (double)h * vk;
-                acc[3] += (double)h * vk * vk;
-            }
+            const double vk = (double)p.sx[k];
+            acc[0] += (double)h;
+            acc[1] += (double)h * vk;
+            acc[3] += (double)h * vk * vk;
         }
     }
-    if constexpr (SUMS) block_sums_store<4>(acc, partials + (size_t)blockIdx.x * 4);
+    block_sums_store<4>(acc, partials + (size_t)blockIdx.x * 4);
 }
 
 // Padded index q holds node y = q - 3; population k there is f_eq_k of node
@@ -434,8 +452,8 @@ void q3_launch(const Q9Params &p, const T *src, T *dst, double *part, hipStream_
         const size_t lds = sizeof(T) == 8 ? PLBM_Q9_LDS_F64 : PLBM_Q9_LDS_F32;
         hipLaunchKernelGGL((k_step_q9<T, C, SUMS>), dim3(grid_for(p.ntiles)), dim3(TX), lds, st, src, dst, p,
                            part);
-    } else {
-        hipLaunchKernelGGL((k_step_q3_1d<T, C, SUMS>), dim3(p.tiles_x), dim3(TX), 0, st, src, dst, p, part);
+    } else if constexpr (SUMS) {
+        hipLaunchKernelGGL((k_step_q3_1d_sums<T, C>), dim3(p.tiles_x), dim3(TX), 0, st, src, dst, p, part);
     }
 }
 
@@ -483,6 +501,13 @@ int q9_run(const Q9Params &p, void *fa, void *fb, int nsteps, double *sums, hipS
             if (rc != PLBM_OK) return rc;
         }
         s0 = deep * Q9_DEPTH<T> + three * 3;
+    }
+    if (p.dim == 1) {
+        s0 = nsteps - (sums ? 1 : 0);
+        (void)hipGetLastError();
+        run_tube<Iso3<T>>(p, fa, fb, s0, p.sx[1], st);
+        const int rc = q9_launch_status();
+        if (rc != PLBM_OK) return rc;
     }
     for (int s = s0; s < nsteps; ++s) {
         const T *src = static_cast<const T *>((s & 1) ? fb : fa);

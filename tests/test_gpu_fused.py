@@ -103,3 +103,24 @@ def test_fused_general_steps_equal_single_steps(nx, ny, storage, v, theta):
     a, b = _pair(lambda: Lattice(2, nx, ny, omega=1.6, storage=storage, velocities=v, theta0=theta), fields, 11,
                  (5, 4, 2))
     assert torch.equal(a.f, b.f) and a.cur == b.cur
+
+
+# 1D: one workgroup up to 1024 nodes (in place for an even number of steps);
+# tiles with halos beyond, the tile that leaves one node, fewer nodes than the
+# halo in the last tile; one step, few, many; the ghosts belong to the buffer
+@pytest.mark.parametrize("nx", [1, 2, 5, 63, 65, 1000, 1024, 1025, 1143, 5001, 70000])
+@pytest.mark.parametrize("model,storage", [("d1q5", "f64"), ("d1q5", "f32"), ("d1q3", "f64"), ("d1q3", "f32"),
+                                           ("d1q4", "f64"), ("d1q7", "f32"), ("d1q7", "f64")])
+def test_fused_tube_steps_equal_single_steps(nx, model, storage):
+    kw = {"d1q5": {}, "d1q3": dict(zeta=4.0), "d1q4": dict(velocities=(1, -1, 3, -3), theta0=4.0 / 3.0),
+          "d1q7": dict(velocities=(0, 1, -1, 2, -2, 3, -3), theta0=1.0)}[model]
+    g = torch.Generator().manual_seed(nx)
+    th = {"d1q5": 0.4, "d1q7": 1.0}.get(model, 0.25)
+    rho, ux, t = (c + a * torch.rand(nx, generator=g, dtype=torch.float64) for c, a in ((1.0, 0.05), (0.0, 0.02), (th, 0.01)))
+    a, b = _pair(lambda: Lattice(1, nx, omega=1.1, storage=storage, **kw), (rho, ux, None, t), 121,
+                 (1, 2, 3, 10, 105))
+    assert torch.equal(a.f, b.f) and a.cur == b.cur
+    s = a.step(5, sums=True)
+    for _ in range(4):
+        b.step(1)
+    assert s == b.step(1, sums=True) and torch.equal(a.f, b.f)
