@@ -74,7 +74,7 @@ __device__ __forceinline__ void batch_tile(const BTile &t, const KParams &proto,
     // select the buffers without indexing t.buf by a runtime value: such an
     // index makes the compiler place the tile in LDS (10 KB per workgroup)
     float *const b0 = t.buf[0], *const b1 = t.buf[1];
-    step_rows<StF32, 1, false>(parity ? b1 : b0, parity ? b0 : b1, q, xb, y_first, y_step, R, acc);
+    step_rows<StF32, 1, false, true>(parity ? b1 : b0, parity ? b0 : b1, q, xb, y_first, y_step, R, acc);
 }
 
 __global__ __launch_bounds__(TX) void k_step_batch(const BTile *__restrict__ tiles, int ntiles,

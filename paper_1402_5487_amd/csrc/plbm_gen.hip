@@ -191,7 +191,7 @@ __device__ __forceinline__ void collide_gen2d(C (&f)[Q1 * Q1], const GenParams &
         for (int i = 0; i < Q1; ++i) f[i + Q1 * j] = fma(keep, f[i + Q1 * j], rx[i] * ry[j]);
 }
 
-template <int Q1, typename T, bool SUMS, bool Z0>
+template <int Q1, typename T, bool SUMS, bool Z0, bool NTS>
 __global__ __launch_bounds__(TX) void k_step_gen2d(const T *__restrict__ src, T *__restrict__ dst, GenParams p,
                                                    double *__restrict__ partials)
 {
@@ -221,7 +221,7 @@ __global__ __launch_bounds__(TX) void k_step_gen2d(const T *__restrict__ src, T 
             }
             T *out = dst + (y * rowelems + xb);
 #pragma unroll
-            for (int k = 0; k < NG; ++k) store_stream((T)f[k], out + (long long)k * p.nx);
+            for (int k = 0; k < NG; ++k) store_stream<NTS>((T)f[k], out + (long long)k * p.nx);
         }
     }
     if constexpr (SUMS) block_sums_store<4>(acc, partials + (size_t)blockIdx.x * 4);
@@ -243,14 +243,14 @@ struct GenSet {
     static __device__ __forceinline__ void collide(C (&f)[Q1 * Q1], const P &p) { collide_gen2d<Q1, C>(f, p); }
 };
 
-template <class M>
+template <class M, bool NTS>
 __global__ __launch_bounds__(sweep_threads<M>(), (sweep_per_cu<M, 2>())) void
 k_pair_gen(const typename M::T *__restrict__ src, typename M::T *__restrict__ dst, GenParams p, SweepGrid g)
 {
     extern __shared__ __align__(16) unsigned char sweep_lds[];
     const int b = xcd_tile(blockIdx.x, gridDim.x);
     const int c = b / g.strips, ya = c * g.h;
-    sweep<M, 2>(src, dst, p, (b - c * g.strips) * g.w, g.w, ya, min(ya + g.h, p.ny),
+    sweep<M, 2, NTS>(src, dst, p, (b - c * g.strips) * g.w, g.w, ya, min(ya + g.h, p.ny),
                 reinterpret_cast<typename M::T *>(sweep_lds));
 }
 
@@ -510,13 +510,12 @@ int gen_finish_sums(double *dev, int nblocks, double *host, hipStream_t st)
 template <int Q1, typename T, bool SUMS>
 void gen_launch(const GenParams &p, const T *src, T *dst, double *part, hipStream_t st)
 {
-    if (p.dim == 2 && p.sx[0] == 0)
-        hipLaunchKernelGGL((k_step_gen2d<Q1, T, SUMS, true>), dim3(grid_g(p)), dim3(TX), (gen_lds_cap<Q1, T>()), st,
-                           src, dst, p, part);
-    else if (p.dim == 2)
-        hipLaunchKernelGGL((k_step_gen2d<Q1, T, SUMS, false>), dim3(grid_g(p)), dim3(TX), (gen_lds_cap<Q1, T>()), st,
-                           src, dst, p, part);
-    else if constexpr (SUMS)
+    if (p.dim == 2) {
+        const bool nts = rows_on_lines(p.nx, sizeof(T)), z0 = p.sx[0] == 0;
+        auto *kernel = z0 ? (nts ? k_step_gen2d<Q1, T, SUMS, true, true> : k_step_gen2d<Q1, T, SUMS, true, false>)
+                          : (nts ? k_step_gen2d<Q1, T, SUMS, false, true> : k_step_gen2d<Q1, T, SUMS, false, false>);
+        hipLaunchKernelGGL(kernel, dim3(grid_g(p)), dim3(TX), (gen_lds_cap<Q1, T>()), st, src, dst, p, part);
+    } else if constexpr (SUMS)
         hipLaunchKernelGGL((k_step_gen1d_sums<Q1, T>), dim3(grid_g(p)), dim3(TX), 0, st, src, dst, p, part);
 }
 
@@ -539,9 +538,13 @@ int gen_pairs(const GenParams &p, void *fa, void *fb, int n, hipStream_t st)
     if (2ll * p.nx < (p.nx + wmax - 1) / wmax * wmax) return 0;
     const SweepGrid g = sweep_grid<M, D>(p.nx, p.ny);
     const int launches = fused_launches<D>(n);
+    // D2Q49 in FP64, whose narrow strips write few whole lines either way:
+    // 215 us a step non-temporal at 1501 x 1100, 222 not
+    const bool nts = rows_on_lines(p.nx, sizeof(T)) || (M::Q1 == 7 && sizeof(T) == 8);
+    auto *kernel = nts ? k_pair_gen<M, true> : k_pair_gen<M, false>;
     for (int k = 0; k < launches; ++k) {
         (void)hipGetLastError();
-        hipLaunchKernelGGL((k_pair_gen<M>), dim3(g.strips * g.chunks), dim3(sweep_threads<M>()),
+        hipLaunchKernelGGL(kernel, dim3(g.strips * g.chunks), dim3(sweep_threads<M>()),
                            (sweep_lds_bytes<M, D>()), st, (const T *)((k & 1) ? fb : fa), (T *)((k & 1) ? fa : fb), p,
                            g);
         const int rc = gen_launch_status();

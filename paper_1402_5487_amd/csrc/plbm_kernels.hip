@@ -65,7 +65,7 @@ namespace {
 // runs of tiles, so the blocks sharing an L2 work on neighbouring tiles and
 // all blocks sweep memory together.  Every block ends when its next tile
 // index passes ntiles.
-template <class S, int NV, bool SUMS>
+template <class S, int NV, bool SUMS, bool NTS>
 __global__ __launch_bounds__(TX, PLBM_MIN_WAVES) void k_step2d(const typename S::T *__restrict__ src,
                                                                typename S::T *__restrict__ dst,
                                                                KParams p,
@@ -75,13 +75,13 @@ __global__ __launch_bounds__(TX, PLBM_MIN_WAVES) void k_step2d(const typename S:
     const int slot = xcd_tile(blockIdx.x, gridDim.x);
 #pragma unroll 1
     for (int tile = slot; tile < p.ntiles; tile += gridDim.x)
-        step_tile<S, NV, SUMS>(src, dst, p, tile, acc);
+        step_tile<S, NV, SUMS, NTS>(src, dst, p, tile, acc);
     if constexpr (SUMS) block_sums_store<4>(acc, partials + (size_t)blockIdx.x * 4);
 }
 
 // The same step, also writing the pre-collision fields of the state it reads
 // (the moments its collision uses, in its arithmetic).
-template <class S, int NV>
+template <class S, int NV, bool NTS>
 __global__ __launch_bounds__(TX, PLBM_MIN_WAVES) void k_step2d_fields(const typename S::T *__restrict__ src,
                                                                       typename S::T *__restrict__ dst,
                                                                       KParams p, FieldsOut fo)
@@ -90,7 +90,7 @@ __global__ __launch_bounds__(TX, PLBM_MIN_WAVES) void k_step2d_fields(const type
     const int slot = xcd_tile(blockIdx.x, gridDim.x);
 #pragma unroll 1
     for (int tile = slot; tile < p.ntiles; tile += gridDim.x)
-        step_tile<S, NV, false, true>(src, dst, p, tile, acc, fo);
+        step_tile<S, NV, false, NTS, true>(src, dst, p, tile, acc, fo);
 }
 
 // Two steps in one launch (plbm_sweep.h) of the set {0, +-1, +-3} in the
@@ -127,7 +127,7 @@ struct Thermal25 {
 };
 constexpr int PAIR = 2;
 
-template <class S, bool FIELDS>
+template <class S, bool NTS, bool FIELDS>
 __global__ __launch_bounds__(sweep_threads<Thermal25<S>>(), (sweep_per_cu<Thermal25<S>, PAIR>())) void
 k_step2d_pair(const typename S::T *__restrict__ src, typename S::T *__restrict__ dst, KParams p, SweepGrid g,
               FieldsOut fo)
@@ -135,7 +135,7 @@ k_step2d_pair(const typename S::T *__restrict__ src, typename S::T *__restrict__
     extern __shared__ __align__(16) unsigned char sweep_lds[];
     const int b = xcd_tile(blockIdx.x, gridDim.x);
     const int c = b / g.strips, ya = c * g.h;
-    sweep<Thermal25<S>, PAIR, FIELDS>(src, dst, p, (b - c * g.strips) * g.w, g.w, ya, min(ya + g.h, p.ny),
+    sweep<Thermal25<S>, PAIR, NTS, FIELDS>(src, dst, p, (b - c * g.strips) * g.w, g.w, ya, min(ya + g.h, p.ny),
                                       reinterpret_cast<typename S::T *>(sweep_lds), fo);
 }
 
@@ -450,12 +450,10 @@ int launch_step(const KParams &p, const plbm_desc *d, const void *src, void *dst
         const size_t lds = sizeof(T) == 2 ? (d->rounding == PLBM_ROUND_STOCHASTIC ? PLBM_LDS_CAP_16SR
                                                                                  : PLBM_LDS_CAP_16)
                                           : PLBM_LDS_CAP_WIDE;
-        if (p.nv == 2)
-            hipLaunchKernelGGL((k_step2d<S, 2, SUMS>), dim3(nblocks), dim3(TX), lds, st,
-                               (const T *)src, (T *)dst, p, partials);
-        else
-            hipLaunchKernelGGL((k_step2d<S, 1, SUMS>), dim3(nblocks), dim3(TX), lds, st,
-                               (const T *)src, (T *)dst, p, partials);
+        const bool nts = rows_on_lines(p.nx, sizeof(T));
+        auto *kernel = p.nv == 2 ? (nts ? k_step2d<S, 2, SUMS, true> : k_step2d<S, 2, SUMS, false>)
+                                 : (nts ? k_step2d<S, 1, SUMS, true> : k_step2d<S, 1, SUMS, false>);
+        hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(TX), lds, st, (const T *)src, (T *)dst, p, partials);
     } else if constexpr (SUMS && sizeof(T) >= 4) {
         nblocks = (p.nx + TX - 1) / TX;
         hipLaunchKernelGGL(k_step1d_sums<S>, dim3(nblocks), dim3(TX), 0, st, (const T *)src, (T *)dst, p, partials);
@@ -470,7 +468,8 @@ int launch_pair(const KParams &p, const void *src, void *dst, hipStream_t st, Fi
     using T = typename S::T;
     const SweepGrid g = sweep_grid<Thermal25<S>, PAIR>(p.nx, p.ny);
     clear_launch_error();
-    hipLaunchKernelGGL((k_step2d_pair<S, FIELDS>), dim3(g.strips * g.chunks), dim3(sweep_threads<Thermal25<S>>()),
+    auto *kernel = rows_on_lines(p.nx, sizeof(T)) ? k_step2d_pair<S, true, FIELDS> : k_step2d_pair<S, false, FIELDS>;
+    hipLaunchKernelGGL(kernel, dim3(g.strips * g.chunks), dim3(sweep_threads<Thermal25<S>>()),
                        (sweep_lds_bytes<Thermal25<S>, PAIR>()), st, (const T *)src, (T *)dst, p, g, fo);
     return launch_status();
 }
@@ -516,12 +515,10 @@ int run_steps_fields(const KParams &p, const plbm_desc *d, void *fa, void *fb, i
         const size_t lds = sizeof(T) == 2 ? (d->rounding == PLBM_ROUND_STOCHASTIC ? PLBM_LDS_CAP_16SR
                                                                                  : PLBM_LDS_CAP_16)
                                           : PLBM_LDS_CAP_WIDE;
-        if (p.nv == 2)
-            hipLaunchKernelGGL((k_step2d_fields<S, 2>), dim3(nblocks), dim3(TX), lds, st, (const T *)fa, (T *)fb, p,
-                               fo);
-        else
-            hipLaunchKernelGGL((k_step2d_fields<S, 1>), dim3(nblocks), dim3(TX), lds, st, (const T *)fa, (T *)fb, p,
-                               fo);
+        const bool nts = rows_on_lines(p.nx, sizeof(T));
+        auto *kernel = p.nv == 2 ? (nts ? k_step2d_fields<S, 2, true> : k_step2d_fields<S, 2, false>)
+                                 : (nts ? k_step2d_fields<S, 1, true> : k_step2d_fields<S, 1, false>);
+        hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(TX), lds, st, (const T *)fa, (T *)fb, p, fo);
     }
     int rc = launch_status();
     int nb = 0;

@@ -187,7 +187,7 @@ __device__ __forceinline__ void collide125(C (&f)[N125], const SymRule<C> &R)
 // One step over the row segments (z ny + y) segs_x + sx.  Optional
 // FP64 block sums of what is stored: (sum f, sum f v_x, sum f v_y,
 // sum f |v|^2, sum f v_z).
-template <typename T, bool SUMS>
+template <typename T, bool SUMS, bool NTS>
 __global__ __launch_bounds__(TX) void k_step3d(const T *__restrict__ src, T *__restrict__ dst, P3 p,
                                                double *__restrict__ partials)
 {
@@ -219,7 +219,7 @@ __global__ __launch_bounds__(TX) void k_step3d(const T *__restrict__ src, T *__r
             }
             T *base = dst + ((long long)row * rowelems + xb);
 #pragma unroll
-            for (int k = 0; k < N125; ++k) store_stream((T)f[k], base + (long long)k * p.nx);
+            for (int k = 0; k < N125; ++k) store_stream<NTS>((T)f[k], base + (long long)k * p.nx);
         }
     }
     if constexpr (SUMS) block_sums_store<5>(acc, partials + (size_t)blockIdx.x * 5);
@@ -356,6 +356,7 @@ template <typename T>
 int q125_run(const P3 &p, void *fa, void *fb, int nsteps, double *sums, hipStream_t st)
 {
     const int grid = grid_of(p);
+    const bool nts = rows_on_lines(p.nx, sizeof(T));
     for (int s = 0; s < nsteps; ++s) {
         const T *src = static_cast<const T *>((s & 1) ? fb : fa);
         T *dst = static_cast<T *>((s & 1) ? fa : fb);
@@ -364,13 +365,13 @@ int q125_run(const P3 &p, void *fa, void *fb, int nsteps, double *sums, hipStrea
             double *part = nullptr;
             int rc = q125_hip(hipMallocAsync((void **)&part, ((size_t)grid + 1) * 5 * sizeof(double), st));
             if (rc != PLBM_OK) return rc;
-            hipLaunchKernelGGL((k_step3d<T, true>), dim3(grid), dim3(TX), lds_cap<T>(), st, src, dst, p, part);
+            hipLaunchKernelGGL((nts ? k_step3d<T, true, true> : k_step3d<T, true, false>), dim3(grid), dim3(TX), lds_cap<T>(), st, src, dst, p, part);
             rc = q125_launch_status();
             if (rc == PLBM_OK) rc = q125_finish_sums(part, grid, sums, st);
             (void)hipFreeAsync(part, st);
             return rc;
         }
-        hipLaunchKernelGGL((k_step3d<T, false>), dim3(grid), dim3(TX), lds_cap<T>(), st, src, dst, p, nullptr);
+        hipLaunchKernelGGL((nts ? k_step3d<T, false, true> : k_step3d<T, false, false>), dim3(grid), dim3(TX), lds_cap<T>(), st, src, dst, p, nullptr);
         const int rc = q125_launch_status();
         if (rc != PLBM_OK) return rc;
     }

@@ -100,13 +100,6 @@ __device__ __forceinline__ void sums9(const C (&f)[N9], const Rule3<C> &R, C &rh
 #define PLBM_Q3_NT_MASK 1
 #endif
 
-template <typename T>
-__device__ __forceinline__ void store_pop(T v, T *p)
-{
-    if constexpr (PLBM_NT_STORE) __builtin_nontemporal_store(v, p);
-    else *p = v;
-}
-
 // Pull-gather of node (xb, y): f_k = src_k(x - v_i, y - v_j), k = i + 3 j.
 template <typename T, typename C>
 __device__ __forceinline__ void gather9(const T *__restrict__ src, const Q9Params &p, int xb, int y, C (&f)[N9])
@@ -158,7 +151,7 @@ __device__ __forceinline__ void collide9(C (&f)[N9], const Rule3<C> &R)
 // One step (Eq. srt): gather, moments, isothermal equilibrium f_eq =
 // rho r^x_i r^y_j, relax, store at x.  Optional FP64 block sums of what is
 // stored (sum f, sum f v_x, sum f v_y, sum f |v|^2).
-template <typename T, typename C, bool SUMS>
+template <typename T, typename C, bool SUMS, bool NTS>
 __global__ __launch_bounds__(TX) void k_step_q9(const T *__restrict__ src, T *__restrict__ dst, Q9Params p,
                                                 double *__restrict__ partials)
 {
@@ -187,7 +180,7 @@ __global__ __launch_bounds__(TX) void k_step_q9(const T *__restrict__ src, T *__
             }
             T *out = dst + (y * rowelems + xb);
 #pragma unroll
-            for (int k = 0; k < N9; ++k) store_pop((T)f[k], out + (long long)k * p.nx);
+            for (int k = 0; k < N9; ++k) store_stream<NTS>((T)f[k], out + (long long)k * p.nx);
         }
     }
     if constexpr (SUMS) block_sums_store<4>(acc, partials + (size_t)blockIdx.x * 4);
@@ -209,14 +202,14 @@ struct Iso9 {
     static __device__ __forceinline__ void collide(C (&f)[N9], const P &p) { collide9<C>(f, rule_of<C>(p)); }
 };
 
-template <class M, int D>
+template <class M, int D, bool NTS>
 __global__ __launch_bounds__(sweep_threads<M>(), (sweep_per_cu<M, D>())) void
 k_sweep_q9(const typename M::T *__restrict__ src, typename M::T *__restrict__ dst, Q9Params p, SweepGrid g)
 {
     extern __shared__ __align__(16) unsigned char sweep_lds[];
     const int b = xcd_tile(blockIdx.x, gridDim.x);
     const int c = b / g.strips, ya = c * g.h;
-    sweep<M, D>(src, dst, p, (b - c * g.strips) * g.w, g.w, ya, min(ya + g.h, p.ny),
+    sweep<M, D, NTS>(src, dst, p, (b - c * g.strips) * g.w, g.w, ya, min(ya + g.h, p.ny),
                 reinterpret_cast<typename M::T *>(sweep_lds));
 }
 
@@ -450,8 +443,8 @@ void q3_launch(const Q9Params &p, const T *src, T *dst, double *part, hipStream_
 {
     if (p.dim == 2) {
         const size_t lds = sizeof(T) == 8 ? PLBM_Q9_LDS_F64 : PLBM_Q9_LDS_F32;
-        hipLaunchKernelGGL((k_step_q9<T, C, SUMS>), dim3(grid_for(p.ntiles)), dim3(TX), lds, st, src, dst, p,
-                           part);
+        auto *kernel = rows_on_lines(p.nx, sizeof(T)) ? k_step_q9<T, C, SUMS, true> : k_step_q9<T, C, SUMS, false>;
+        hipLaunchKernelGGL(kernel, dim3(grid_for(p.ntiles)), dim3(TX), lds, st, src, dst, p, part);
     } else if constexpr (SUMS) {
         hipLaunchKernelGGL((k_step_q3_1d_sums<T, C>), dim3(p.tiles_x), dim3(TX), 0, st, src, dst, p, part);
     }
@@ -462,7 +455,8 @@ int launch_sweep_q9(const Q9Params &p, const typename M::T *src, typename M::T *
 {
     const SweepGrid g = sweep_grid<M, D>(p.nx, p.ny);
     (void)hipGetLastError();
-    hipLaunchKernelGGL((k_sweep_q9<M, D>), dim3(g.strips * g.chunks), dim3(sweep_threads<M>()),
+    auto *kernel = rows_on_lines(p.nx, sizeof(typename M::T)) ? k_sweep_q9<M, D, true> : k_sweep_q9<M, D, false>;
+    hipLaunchKernelGGL(kernel, dim3(g.strips * g.chunks), dim3(sweep_threads<M>()),
                        (sweep_lds_bytes<M, D>()), st, src, dst, p, g);
     return q9_launch_status();
 }

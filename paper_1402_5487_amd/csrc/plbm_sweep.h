@@ -140,11 +140,12 @@ __device__ __forceinline__ int wrap_mod(int a, int n)
 // makes the compiler wait for every store in flight).  A block holds less
 // than 2^31 bytes (see sweep_fits).
 constexpr unsigned SWEEP_DROP = 0x80000000u;
+template <bool NTS>
 struct RowStore {
     __amdgpu_buffer_rsrc_t r;
     __device__ __forceinline__ RowStore(void *base, unsigned bytes)
         : r(__builtin_amdgcn_make_buffer_rsrc(base, 0, (int)bytes, 0x00020000)) {}
-    static constexpr int AUX = PLBM_NT_STORE ? 2 : 0;            // non-temporal
+    static constexpr int AUX = NTS ? 2 : 0;                      // non-temporal
     __device__ __forceinline__ void put(double v, unsigned vo, unsigned so) const
     {
         typedef unsigned U2 __attribute__((ext_vector_type(2)));
@@ -166,9 +167,9 @@ inline bool sweep_fits(int nx)
     return (long long)M::Q1 * M::Q1 * nx * (long long)sizeof(typename M::T) < (1ll << 31);
 }
 
-// D steps of the strip.  FIELDS (models with collide(f, p, mom)): the first
+// D steps of the strip.  NTS: see store_stream.  FIELDS (models with collide(f, p, mom)): the first
 // step also writes the fields of the owned nodes.
-template <class M, int D, bool FIELDS = false>
+template <class M, int D, bool NTS, bool FIELDS = false>
 __device__ __forceinline__ void sweep(const typename M::T *__restrict__ src, typename M::T *__restrict__ dst,
                                       const typename M::P &p, int xs, int w, int ya, int yb,
                                       typename M::T *__restrict__ lds, const FieldsOut &fo = FieldsOut{})
@@ -324,7 +325,7 @@ __device__ __forceinline__ void sweep(const typename M::T *__restrict__ src, typ
     // as many (dropped) stores behind the loads as the loop leaves there, so
     // that its wait for the loads may let that many stores pass
     {
-        const RowStore out(dst, colbytes * NP);
+        const RowStore<NTS> out(dst, colbytes * NP);
 #pragma unroll
         for (int k = 0; k < NP; ++k) out.put(raw[k], SWEEP_DROP, (unsigned)k * colbytes);
     }
@@ -337,7 +338,7 @@ __device__ __forceinline__ void sweep(const typename M::T *__restrict__ src, typ
         stage(D - 1, f);
         const int yo = ya + it - 2 * halo;
         const uint32_t ko = M::KEYED ? M::key((uint32_t)yo * (uint32_t)nx + (uint32_t)x) : 0u;
-        const RowStore out(dst + yo * rowelems, colbytes * NP);
+        const RowStore<NTS> out(dst + yo * rowelems, colbytes * NP);
 #pragma unroll
         for (int k = 0; k < NP; ++k) out.put(M::enc(f[k], k, p, ko), vo, (unsigned)k * colbytes);
         if constexpr (D == 2) lds_barrier();
