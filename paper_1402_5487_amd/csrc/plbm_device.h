@@ -493,7 +493,7 @@ __device__ __forceinline__ void store_stream(T v, T *p)
     if constexpr (NTS) __builtin_nontemporal_store(v, p);
     else *p = v;
 }
-inline bool rows_on_lines(int nx, size_t elem) { return (size_t)nx * elem % 128 == 0; }
+__host__ __device__ inline bool rows_on_lines(int nx, size_t elem) { return (size_t)nx * elem % 128 == 0; }
 
 // Loads and stores of NV consecutive nodes of one population row.  `base`
 // is a wave-uniform byte pointer, `off` the lane's byte offset (the node's

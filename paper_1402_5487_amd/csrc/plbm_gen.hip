@@ -248,10 +248,7 @@ __global__ __launch_bounds__(sweep_threads<M>(), (sweep_per_cu<M, 2>())) void
 k_pair_gen(const typename M::T *__restrict__ src, typename M::T *__restrict__ dst, GenParams p, SweepGrid g)
 {
     extern __shared__ __align__(16) unsigned char sweep_lds[];
-    const int b = xcd_tile(blockIdx.x, gridDim.x);
-    const int c = b / g.strips, ya = c * g.h;
-    sweep<M, 2, NTS>(src, dst, p, (b - c * g.strips) * g.w, g.w, ya, min(ya + g.h, p.ny),
-                reinterpret_cast<typename M::T *>(sweep_lds));
+    sweep<M, 2, NTS>(src, dst, p, g, xcd_tile(blockIdx.x, gridDim.x), reinterpret_cast<typename M::T *>(sweep_lds));
 }
 
 // Initial state: f_eq of node (x, y) in FP64, written to (x - v_i, y - v_j).
@@ -534,9 +531,8 @@ int gen_pairs(const GenParams &p, void *fa, void *fb, int n, hipStream_t st)
     if (!sweep_fits<M>(p.nx) || (long long)p.nx * p.ny < 1 << 18) return 0;
     for (int i = 0; i < M::Q1; ++i)
         if (p.sx[i] != M::V[i]) return 0;
-    constexpr long long wmax = sweep_wmax<M, D>();
-    if (2ll * p.nx < (p.nx + wmax - 1) / wmax * wmax) return 0;
     const SweepGrid g = sweep_grid<M, D>(p.nx, p.ny);
+    if (2ll * p.nx * g.per < (long long)g.strips * sweep_threads<M>()) return 0;
     const int launches = fused_launches<D>(n);
     // D2Q49 in FP64, whose narrow strips write few whole lines either way:
     // 215 us a step non-temporal at 1501 x 1100, 222 not
@@ -544,7 +540,7 @@ int gen_pairs(const GenParams &p, void *fa, void *fb, int n, hipStream_t st)
     auto *kernel = nts ? k_pair_gen<M, true> : k_pair_gen<M, false>;
     for (int k = 0; k < launches; ++k) {
         (void)hipGetLastError();
-        hipLaunchKernelGGL(kernel, dim3(g.strips * g.chunks), dim3(sweep_threads<M>()),
+        hipLaunchKernelGGL(kernel, dim3(g.wgs), dim3(sweep_threads<M>()),
                            (sweep_lds_bytes<M, D>()), st, (const T *)((k & 1) ? fb : fa), (T *)((k & 1) ? fa : fb), p,
                            g);
         const int rc = gen_launch_status();

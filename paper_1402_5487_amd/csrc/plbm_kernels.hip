@@ -40,7 +40,6 @@
 #include <cstring>
 
 #include <mutex>
-#include <type_traits>
 
 #include "plbm_device.h"
 #include "plbm_internal.h"
@@ -93,50 +92,15 @@ __global__ __launch_bounds__(TX, PLBM_MIN_WAVES) void k_step2d_fields(const type
         step_tile<S, NV, false, NTS, true>(src, dst, p, tile, acc, fo);
 }
 
-// Two steps in one launch (plbm_sweep.h) of the set {0, +-1, +-3} in the
-// paper's order.
-template <class S>
-struct Thermal25 {
-    using T = typename S::T;
-    using C = typename S::C;
-    using P = KParams;
-    static constexpr int Q1 = Q;
-    static constexpr int V[Q] = {0, 1, -1, 3, -3};
-    static constexpr bool KEYED = S::keyed;
-    static constexpr int SPAN = 256, WGS = 4;
-    // 16-bit storage spends vector work, not bandwidth, on rows computed twice
-    static constexpr int ROUNDS_H = sizeof(T) == 2 ? 32 : 16;
-    static __device__ __forceinline__ C dec(T h, int k, const P &p) { return S::dec(h, k, p); }
-    static __device__ __forceinline__ T enc(C f, int k, const P &p, uint32_t key)
-    {
-        const T h = S::enc(f, k, p, key);
-        if constexpr (std::is_same_v<S, StF16>) {
-            // one value at a time: the compiler turns pairs into an FP32 FMA
-            // and a packed conversion, which rounds twice where the single
-            // step's v_fma_mixlo_f16 rounds once
-            _Float16 one = __builtin_bit_cast(_Float16, h);
-            asm("" : "+v"(one));
-            return __builtin_bit_cast(T, one);
-        } else {
-            return h;
-        }
-    }
-    static __device__ __forceinline__ uint32_t key(uint32_t node) { return S::key(node); }
-    static __device__ __forceinline__ void collide(C (&f)[NQ], const P &p) { collide2d<S>(f, p); }
-    static __device__ __forceinline__ void collide(C (&f)[NQ], const P &p, C (&mom)[4]) { collide2d<S>(f, p, mom); }
-};
-constexpr int PAIR = 2;
-
+// Two steps in one launch (plbm_sweep.h).
 template <class S, bool NTS, bool FIELDS>
 __global__ __launch_bounds__(sweep_threads<Thermal25<S>>(), (sweep_per_cu<Thermal25<S>, PAIR>())) void
 k_step2d_pair(const typename S::T *__restrict__ src, typename S::T *__restrict__ dst, KParams p, SweepGrid g,
               FieldsOut fo)
 {
     extern __shared__ __align__(16) unsigned char sweep_lds[];
-    const int b = xcd_tile(blockIdx.x, gridDim.x);
-    const int c = b / g.strips, ya = c * g.h;
-    sweep<Thermal25<S>, PAIR, NTS, FIELDS>(src, dst, p, (b - c * g.strips) * g.w, g.w, ya, min(ya + g.h, p.ny),
-                                      reinterpret_cast<typename S::T *>(sweep_lds), fo);
+    sweep<Thermal25<S>, PAIR, NTS, FIELDS>(src, dst, p, g, xcd_tile(blockIdx.x, gridDim.x),
+                                           reinterpret_cast<typename S::T *>(sweep_lds), fo);
 }
 
 // ---------------------------------------------------------------------------
@@ -469,30 +433,28 @@ int launch_pair(const KParams &p, const void *src, void *dst, hipStream_t st, Fi
     const SweepGrid g = sweep_grid<Thermal25<S>, PAIR>(p.nx, p.ny);
     clear_launch_error();
     auto *kernel = rows_on_lines(p.nx, sizeof(T)) ? k_step2d_pair<S, true, FIELDS> : k_step2d_pair<S, false, FIELDS>;
-    hipLaunchKernelGGL(kernel, dim3(g.strips * g.chunks), dim3(sweep_threads<Thermal25<S>>()),
+    hipLaunchKernelGGL(kernel, dim3(g.wgs), dim3(sweep_threads<Thermal25<S>>()),
                        (sweep_lds_bytes<Thermal25<S>, PAIR>()), st, (const T *)src, (T *)dst, p, g, fo);
     return launch_status();
 }
 
 // Which lattices take fused pairs.  Measured per step against single steps
-// (us, single -> pair): FP64 256^2 6.3 -> 8.6, 384^2 15.5 -> 10.9, 4096^2
-// 1050 -> 607; FP32 256^2 4.9 -> 6.3, 384^2 7.6 -> 7.0, 4096^2 519 -> 312: from
-// 2^17 nodes on.  The 16-bit forms are bound by vector work, of which short
-// chunks add up to as much again: FP16 1024^2 21.4 -> 23.9, 1501 x 1100
-// 40.7 -> 30.2, 4096^2 276 -> 202: from 1.5 M nodes on.  Rows that leave half
-// the lanes of their strips idle (a quarter: 16-bit) stay with single steps.
+// (us, single -> pair): FP64 256^2 6.8 -> 8.0, 320^2 11.9 -> 11.0, 4096^2
+// 1050 -> 607; FP32 320^2 6.1 -> 7.2, 384^2 7.2 -> 7.4, 448^2 9.7 -> 8.1, 4096^2
+// 519 -> 312.  The 16-bit forms are bound by vector work, of which short
+// chunks add up to as much again: FP16 1024^2 21.4 -> 24, 1501 x 1100
+// 40.4 -> 29.5, 4096^2 278 -> 203.  Rows that leave half the lanes of their
+// strips idle (a quarter: 16-bit) stay with single steps.
 template <class S>
 bool use_pairs(const KParams &p, const plbm_desc *d)
 {
     constexpr bool narrow = sizeof(typename S::T) == 2;
     using M = Thermal25<S>;
-    if (d->dim != 2 || !sweep_fits<M>(p.nx)) return false;
-    for (int i = 0; i < Q; ++i)
-        if (p.sx[i] != M::V[i]) return false;
-    if ((long long)p.nx * p.ny < (narrow ? 1500000 : 1 << 17)) return false;
-    constexpr long long wmax = sweep_wmax<M, PAIR>();
-    const long long lanes = (p.nx + wmax - 1) / wmax * wmax;
-    return narrow ? 4ll * p.nx >= 3 * lanes : 2ll * p.nx >= lanes;
+    if (d->dim != 2 || !sweep_fits<M>(p.nx) || !paper_set(p)) return false;
+    if ((long long)p.nx * p.ny < (narrow ? 1500000 : sizeof(typename S::T) == 8 ? 100000 : 150000)) return false;
+    const SweepGrid g = sweep_grid<M, PAIR>(p.nx, p.ny);
+    const long long used = (long long)p.nx * g.per, lanes = (long long)g.strips * sweep_threads<M>();
+    return narrow ? 4 * used >= 3 * lanes : 2 * used >= lanes;
 }
 
 // 2D steps of which the first also writes the fields of the state it reads.

@@ -207,10 +207,7 @@ __global__ __launch_bounds__(sweep_threads<M>(), (sweep_per_cu<M, D>())) void
 k_sweep_q9(const typename M::T *__restrict__ src, typename M::T *__restrict__ dst, Q9Params p, SweepGrid g)
 {
     extern __shared__ __align__(16) unsigned char sweep_lds[];
-    const int b = xcd_tile(blockIdx.x, gridDim.x);
-    const int c = b / g.strips, ya = c * g.h;
-    sweep<M, D, NTS>(src, dst, p, (b - c * g.strips) * g.w, g.w, ya, min(ya + g.h, p.ny),
-                reinterpret_cast<typename M::T *>(sweep_lds));
+    sweep<M, D, NTS>(src, dst, p, g, xcd_tile(blockIdx.x, gridDim.x), reinterpret_cast<typename M::T *>(sweep_lds));
 }
 
 // Initial state: node x evaluates f_eq(rho, u; theta0) in FP64 and writes
@@ -456,7 +453,7 @@ int launch_sweep_q9(const Q9Params &p, const typename M::T *src, typename M::T *
     const SweepGrid g = sweep_grid<M, D>(p.nx, p.ny);
     (void)hipGetLastError();
     auto *kernel = rows_on_lines(p.nx, sizeof(typename M::T)) ? k_sweep_q9<M, D, true> : k_sweep_q9<M, D, false>;
-    hipLaunchKernelGGL(kernel, dim3(g.strips * g.chunks), dim3(sweep_threads<M>()),
+    hipLaunchKernelGGL(kernel, dim3(g.wgs), dim3(sweep_threads<M>()),
                        (sweep_lds_bytes<M, D>()), st, src, dst, p, g);
     return q9_launch_status();
 }

@@ -21,6 +21,8 @@
 // the HBM rate; here once, plus the halo (R (D - 1) columns and rows on each
 // side are computed twice by neighbours).
 #pragma once
+#include <type_traits>
+
 #include "plbm_device.h"
 
 namespace {
@@ -84,19 +86,29 @@ constexpr int sweep_per_cu()
 template <int D>
 inline int fused_launches(int n) { return D & 1 ? n / D : n / D & ~1; }
 
-// Strips of w columns, chunks of h rows; workgroup b takes strip b % strips
-// of chunk b / strips.
+// Strips of w columns and chunks of h rows.  Workgroup b of a lattice takes
+// strip b % strips of `per` chunks side by side, from chunk b / strips * per on
+// (T / per threads each).  span: the columns held, the strip's and its halo; a
+// strip that is the whole row closes on itself and has none.
 struct SweepGrid {
-    int strips, chunks, w, h;
+    int strips, chunks, w, h, span, per, wgs;
+    __host__ void rows(int ny, int height)
+    {
+        h = height;
+        chunks = (ny + h - 1) / h;
+        wgs = strips * ((chunks + per - 1) / per);
+    }
 };
 
 // The partition of an nx x ny lattice.  Strips begin on cache lines (128 B;
 // 64 B for the 16-bit forms, whose 128 B would cost a quarter of the lanes):
 // stores that end inside a line left the D2Q25 pair at 4096^2 at 489 us a step
-// in FP32 against 373.  Chunks: one round of resident workgroups while that
-// leaves them at most 24 rows, else M::ROUNDS_H rows: long chunks spread the
-// accesses over so much memory that the D2Q25 FP32 pair at 4096^2 took 373 us
-// a step with 157 rows, 318 with 64 and 313 with 16.
+// in FP32 against 373.  Chunks: as many rounds of
+// resident workgroups as leave them about M::ROUNDS_H rows.  Long chunks
+// spread the accesses over so much memory that the D2Q25 FP32 pair at 4096^2
+// took 373 us a step with 157 rows, 318 with 64 and 313 with 16; a last round
+// of a few workgroups costs as much as a full one (D2Q9 FP32 2048^2, 1.1
+// rounds: 22.6 us a step, one: 17).
 template <class M>
 constexpr int sweep_align() { return sizeof(typename M::T) == 2 ? 32 : 128 / (int)sizeof(typename M::T); }
 template <class M, int D>
@@ -110,13 +122,24 @@ inline SweepGrid sweep_grid(int nx, int ny)
     constexpr int align = sweep_align<M>(), wmax = sweep_wmax<M, D>();
     constexpr int slots = SWEEP_CUS * sweep_per_cu<M, D>();
     SweepGrid g;
-    g.strips = (nx + wmax - 1) / wmax;
-    g.w = ((nx + g.strips - 1) / g.strips + align - 1) / align * align;
-    g.strips = (nx + g.w - 1) / g.w;
-    const int round = std::max(1, slots / g.strips);
-    g.h = (ny + round - 1) / round;
-    if (g.h > 24) g.h = std::min(ny, M::ROUNDS_H);
-    g.chunks = (ny + g.h - 1) / g.h;
+    g.per = 1;
+    if (nx <= M::SPAN) {
+        g.strips = 1;
+        g.w = g.span = nx;
+        for (int per = 4; per > 1 && g.per == 1; per /= 2)
+            if (nx <= sweep_threads<M>() / per && nx * per <= M::SPAN) g.per = per;
+    } else {
+        g.strips = (nx + wmax - 1) / wmax;
+        g.w = ((nx + g.strips - 1) / g.strips + align - 1) / align * align;
+        g.strips = (nx + g.w - 1) / g.w;
+        g.span = g.w + 2 * Lines<M>::R * (D - 1);
+    }
+    // rounds of resident workgroups, each filled alike
+    auto chunk_rows = [&](int rounds) {
+        const int chunks = std::max(1, rounds * slots * g.per / g.strips);
+        return (ny + chunks - 1) / chunks;
+    };
+    g.rows(ny, chunk_rows(std::max(1, chunk_rows(1) / M::ROUNDS_H)));
     return g;
 }
 
@@ -171,7 +194,7 @@ inline bool sweep_fits(int nx)
 // step also writes the fields of the owned nodes.
 template <class M, int D, bool NTS, bool FIELDS = false>
 __device__ __forceinline__ void sweep(const typename M::T *__restrict__ src, typename M::T *__restrict__ dst,
-                                      const typename M::P &p, int xs, int w, int ya, int yb,
+                                      const typename M::P &p, const SweepGrid &g, int b,
                                       typename M::T *__restrict__ lds, const FieldsOut &fo = FieldsOut{})
 {
     using T = typename M::T;
@@ -180,15 +203,20 @@ __device__ __forceinline__ void sweep(const typename M::T *__restrict__ src, typ
     constexpr int Q1 = M::Q1, NP = Q1 * Q1, I0 = L::I0;
     constexpr int halo = L::R * (D - 1);
     const int nx = p.nx, ny = p.ny;
-    const int t = threadIdx.x;
+    const int c = b / g.strips, xs = (b - c * g.strips) * g.w;
+    // this thread's chunk, uniform over its wave, and its place in the strip;
+    // a chunk past the last writes nothing
+    const int side = __builtin_amdgcn_readfirstlane((int)threadIdx.x * g.per / sweep_threads<M>());
+    const int t = (int)threadIdx.x - side * (sweep_threads<M>() / g.per);
+    const int ya = (c * g.per + side) * g.h, yb = min(ya + g.h, ny);
     const long long rowelems = (long long)NP * nx;
     const unsigned colbytes = (unsigned)nx * (unsigned)sizeof(T);
-    // threads 0 .. w - 1 hold the strip's own columns, the next `halo` those
-    // on its right and as many more those on its left; threads past them
-    // repeat the last (no new bytes)
-    const int span = w + 2 * halo;
-    const int tc = min(t, span - 1);
-    const int x = wrap_mod(xs + (tc < w + halo ? tc : tc - span), nx);
+    // threads 0 .. w - 1 hold the strip's own columns, the next ones the halo
+    // on its right and as many more that on its left; threads past them repeat
+    // the last (no new bytes)
+    const int w = g.w, span = g.span, edge = (span - w) / 2;
+    const int tc = min(t, span - 1), col0 = side * span;
+    const int x = wrap_mod(xs + (tc < w + edge ? tc : tc - span), nx);
     const bool own = t < w && xs + t < nx;
     const unsigned vo = own ? (unsigned)x * (unsigned)sizeof(T) : SWEEP_DROP;
     // where column x - v_i stands in memory and among the strip's (the strip
@@ -204,7 +232,7 @@ __device__ __forceinline__ void sweep(const typename M::T *__restrict__ src, typ
         c = tc - M::V[i];
         c += (c < 0) ? span : 0;
         c -= (c >= span) ? span : 0;
-        col[i] = L::column(i) * M::SPAN + c;
+        col[i] = L::column(i) * M::SPAN + col0 + c;
         asm volatile("" : "+v"(lo[i]), "+v"(col[i]));
     }
     T raw[NP], h[NP], reg[D - 1][L::REGS];
@@ -227,7 +255,7 @@ __device__ __forceinline__ void sweep(const typename M::T *__restrict__ src, typ
             }
         }
     };
-    const int iters = yb - ya + 2 * halo;
+    const int iters = g.h + 2 * halo;      // the same for all chunks: they share the barriers
     int slot[Q1];                       // of each line: the row being written, then the oldest
 #pragma unroll
     for (int j = 0; j < Q1; ++j) slot[j] = 0;
@@ -238,7 +266,7 @@ __device__ __forceinline__ void sweep(const typename M::T *__restrict__ src, typ
         return M::KEYED ? M::key((uint32_t)row_of(it, s) * (uint32_t)nx + (uint32_t)x) : 0u;
     };
     auto put_lines = [&](int s) {
-        T *ring = lds + s * (L::ROWS * L::COLS * M::SPAN) + tc;
+        T *ring = lds + s * (L::ROWS * L::COLS * M::SPAN) + col0 + tc;
 #pragma unroll
         for (int j = 0; j < Q1; ++j)
 #pragma unroll
@@ -284,7 +312,7 @@ __device__ __forceinline__ void sweep(const typename M::T *__restrict__ src, typ
         if constexpr (FIELDS) {
             C mom[4];
             M::collide(f, p, mom);
-            if (own && it >= halo && it < iters - halo) {
+            if (own && it >= halo && it < yb - ya + halo) {
                 const long long n = (long long)yr * nx + x;
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
@@ -310,7 +338,7 @@ __device__ __forceinline__ void sweep(const typename M::T *__restrict__ src, typ
         }
         lds_barrier();
     };
-    int yr = row_of(0, 0);
+    int yr = row_of(0, 0);              // ya may lie past ny in a chunk that does not exist
     load_row(yr);
 #pragma unroll 1
     for (int it = 0; it < 2 * halo; ++it) {
@@ -338,13 +366,55 @@ __device__ __forceinline__ void sweep(const typename M::T *__restrict__ src, typ
         stage(D - 1, f);
         const int yo = ya + it - 2 * halo;
         const uint32_t ko = M::KEYED ? M::key((uint32_t)yo * (uint32_t)nx + (uint32_t)x) : 0u;
-        const RowStore<NTS> out(dst + yo * rowelems, colbytes * NP);
+        // a row past the chunk's: a block of no bytes, which drops every store
+        const bool in = yo < yb;
+        const RowStore<NTS> out(dst + (in ? yo : 0) * rowelems, in ? colbytes * NP : 0);
 #pragma unroll
         for (int k = 0; k < NP; ++k) out.put(M::enc(f[k], k, p, ko), vo, (unsigned)k * colbytes);
         if constexpr (D == 2) lds_barrier();
         next_slot();
         yr = yn;
     }
+}
+
+// The thermal model of plbm_device.h with the set {0, +-1, +-3} in the paper's
+// order (paper_set: whether p's is that one); it takes pairs of steps.
+template <class S>
+struct Thermal25 {
+    using T = typename S::T;
+    using C = typename S::C;
+    using P = KParams;
+    static constexpr int Q1 = Q;
+    static constexpr int V[Q] = {0, 1, -1, 3, -3};
+    static constexpr bool KEYED = S::keyed;
+    static constexpr int SPAN = 256, WGS = 4;
+    // 16-bit storage spends vector work, not bandwidth, on rows computed twice
+    static constexpr int ROUNDS_H = sizeof(T) == 2 ? 32 : 16;
+    static __device__ __forceinline__ C dec(T h, int k, const P &p) { return S::dec(h, k, p); }
+    static __device__ __forceinline__ T enc(C f, int k, const P &p, uint32_t key)
+    {
+        const T h = S::enc(f, k, p, key);
+        if constexpr (std::is_same_v<S, StF16>) {
+            // one value at a time: the compiler turns pairs into an FP32 FMA
+            // and a packed conversion, which rounds twice where the single
+            // step's v_fma_mixlo_f16 rounds once
+            _Float16 one = __builtin_bit_cast(_Float16, h);
+            asm("" : "+v"(one));
+            return __builtin_bit_cast(T, one);
+        } else {
+            return h;
+        }
+    }
+    static __device__ __forceinline__ uint32_t key(uint32_t node) { return S::key(node); }
+    static __device__ __forceinline__ void collide(C (&f)[NQ], const P &p) { collide2d<S>(f, p); }
+    static __device__ __forceinline__ void collide(C (&f)[NQ], const P &p, C (&mom)[4]) { collide2d<S>(f, p, mom); }
+};
+constexpr int PAIR = 2;
+inline bool paper_set(const KParams &p)
+{
+    for (int i = 0; i < Q; ++i)
+        if (p.sx[i] != Thermal25<StF32>::V[i]) return false;
+    return true;
 }
 
 } // namespace

@@ -6,6 +6,7 @@ import pytest
 import torch
 
 from paper_1402_5487_amd import inputs
+from paper_1402_5487_amd.batch import Batch
 from paper_1402_5487_amd.lattice import Lattice
 
 pytestmark = pytest.mark.gpu
@@ -21,11 +22,12 @@ def _pair(make, fields, split, whole):
     return a, b
 
 
-# strips of 224 (FP32) and 240 (FP64) columns: just below, at and past their
-# multiples, ragged rows, rows that leave the last strip a single column,
-# more rows than a chunk and fewer than its halo
-@pytest.mark.parametrize("nx,ny", [(224, 601), (225, 590), (241, 600), (448, 293), (449, 300),
-                                   (1501, 97), (16385, 8), (4096, 37)])
+# one strip of up to 256 columns that closes on itself, with four, two or one
+# chunk side by side; strips of 224 (FP32) and 240 (FP64) columns beyond: at
+# and past their multiples, ragged rows, a last strip of a single column, more
+# rows than a chunk and fewer than its halo
+@pytest.mark.parametrize("nx,ny", [(63, 2400), (64, 2401), (65, 2311), (128, 1200), (256, 601), (257, 600),
+                                   (448, 353), (449, 340), (1501, 107), (16385, 10), (4096, 37)])
 @pytest.mark.parametrize("storage", ["f64", "f32"])
 def test_fused_steps_equal_single_steps(nx, ny, storage):
     fields = inputs.random_fields(nx, ny, seed=nx + ny)
@@ -33,7 +35,7 @@ def test_fused_steps_equal_single_steps(nx, ny, storage):
     assert torch.equal(a.f, b.f) and a.cur == b.cur
 
 
-@pytest.mark.parametrize("nx,ny", [(1501, 1100), (1345, 1121), (224, 6700)])
+@pytest.mark.parametrize("nx,ny", [(1501, 1100), (1345, 1121), (224, 6700), (128, 11730)])
 @pytest.mark.parametrize("storage,rounding", [("f16dev", "nearest"), ("bf16dev", "nearest"),
                                               ("f16dev", "stochastic"), ("bf16dev", "stochastic")])
 def test_fused_16_bit_steps_equal_single_steps(nx, ny, storage, rounding):
@@ -47,7 +49,7 @@ def test_fused_16_bit_steps_equal_single_steps(nx, ny, storage, rounding):
 def test_fused_steps_with_fields_and_sums(storage):
     """The first of the fused steps writes the fields of the state it reads;
     a step that takes sums comes after fused ones."""
-    nx, ny = 450, 400
+    nx, ny = 450, 402
     fields = inputs.random_fields(nx, ny, seed=5)
     a, b = (Lattice(2, nx, ny, omega=1.7, storage=storage).init(*fields) for _ in range(2))
     got, want = a.step_fields(7), b.step_fields(1)
@@ -124,3 +126,26 @@ def test_fused_tube_steps_equal_single_steps(nx, model, storage):
     for _ in range(4):
         b.step(1)
     assert s == b.step(1, sums=True) and torch.equal(a.f, b.f)
+
+
+# batches past 2^18 nodes: up to 48 sizes decode arithmetically, more go
+# through a list; rows of one, two and four chunks side by side, several
+# strips, ragged rows; graph replays, pairs and a last single step
+@pytest.mark.parametrize("sizes", [[(64, 64)] * 20 + [(100, 90)] * 12 + [(256, 250)] * 2 + [(300, 200), (513, 60), (31, 300)],
+                                   [(64 + i, 90 + i) for i in range(50)]])
+def test_fused_batch_steps_equal_single_lattices(sizes):
+    specs = [(nx, ny, 1.5 + 0.3 * i / len(sizes)) for i, (nx, ny) in enumerate(sizes)]
+    b = Batch(specs)
+    fields = [inputs.random_fields(nx, ny, seed=i) for i, (nx, ny, _) in enumerate(specs)]
+    for i, f in enumerate(fields):
+        b.init(i, *f)
+    for n in (3, 17, 2, 9):
+        b.step(n)
+    for i, (nx, ny, om) in enumerate(specs):
+        if i % 5 and i < len(specs) - 3:
+            continue
+        lat = Lattice(2, nx, ny, omega=om, storage="f32").init(*fields[i])
+        for _ in range(31):
+            lat.step(1)
+        assert torch.equal(b.buffer(i), lat.f), (nx, ny)
+    b.close()
