@@ -310,8 +310,9 @@ int plbm_dev_scales(plbm_desc *d, const double *rho, const double *ux,
  * Batching form: many independent D2Q25 lattices advanced together.
  * Each lattice is the model of plbm_step (same velocity set and table) with
  * its own size and relaxation constant, FP32 storage, periodic boundaries.
- * One kernel launch per step walks a work list of tiles of every lattice;
- * plbm_batch_step replays a captured hipGraph of several such launches.
+ * One kernel launch per step (or per two steps, for larger batches) walks a
+ * work list of every lattice; plbm_batch_step replays a captured hipGraph of
+ * several such launches.
  * ------------------------------------------------------------------------ */
 typedef struct plbm_batch plbm_batch;          /* opaque, owned by the library */
 
@@ -327,7 +328,7 @@ typedef struct plbm_batch_info {
     int32_t tiles;              /* work-list entries */
     int32_t grid_mode;          /* 0: one workgroup per tile; k: k per CU */
     int32_t lds_bytes;          /* LDS reserved per workgroup (occupancy cap) */
-    int32_t graph_steps;        /* launches per captured graph (0: no graph) */
+    int32_t graph_steps;        /* steps per captured graph (0: no graph) */
     int32_t parity;             /* which of the two buffers holds the state */
     int64_t nodes;              /* total lattice nodes */
     int64_t pool_bytes;         /* device memory of all population buffers */
@@ -368,7 +369,7 @@ int plbm_batch_init(plbm_batch *b, int i, const double *rho, const double *ux,
  */
 int plbm_batch_autotune(plbm_batch *b, const char *cache_path, void *stream);
 
-/* Launches recorded per graph (even, 0..64; 0 disables graphs; default 8). */
+/* Steps recorded per graph (even, 0..64; 0 disables graphs; default 8). */
 int plbm_batch_set_graph_steps(plbm_batch *b, int steps);
 
 /*

@@ -12,6 +12,9 @@
 //    and a persistent grid of a few blocks per CU are the same kernel.
 //  * The per-node work is the single-lattice row stepper with the lattice's
 //    own size and relaxation constant.
+//  * Batches of 2^18 nodes and more take two steps per launch (plbm_sweep.h),
+//    each lattice cut into the strips and chunks a lattice of its own would be
+//    cut into; the tiles remain for odd steps and small batches.
 //  * plbm_batch_step replays a captured hipGraph of `graph_steps` consecutive
 //    steps (alternating buffers), so the host issues one graph launch per
 //    graph_steps steps.  No memset is recorded in the graph.
@@ -35,6 +38,7 @@
 
 #include "plbm_device.h"
 #include "plbm_internal.h"
+#include "plbm_sweep.h"
 
 struct plbm_batch;
 
@@ -141,6 +145,80 @@ __global__ __launch_bounds__(TX) void k_step_groups(float *__restrict__ pool, co
     }
 }
 
+// A batch takes pairs from this many nodes on.  Measured per step (us, single
+// -> pair): 10 lattices of 64..128 (96 k nodes) 6.8 -> 8.7, 10 of 64..256
+// (330 k) 15.8 -> 12.2, 100 of 64 (410 k) 19.0 -> 14.1, 40 of 64..512 141 ->
+// 96, 256 of 64..512 899 -> 534.
+constexpr long long PAIR_NODES = 1 << 18;
+
+// Fused pairs (plbm_sweep.h): the same two forms of work list, with the
+// workgroups of each lattice's SweepGrid in place of tiles.
+using Pair32 = Thermal25<StF32>;
+
+struct BSweep {
+    float *buf[2];
+    int nx, ny;
+    float omega;
+    int b;                              // workgroup of its lattice
+    SweepGrid grid;
+};
+
+struct BSweepGroup {
+    long long base, stride, half;       // as BGroup
+    int first_lat;
+    int nx, ny;
+    SweepGrid grid;
+};
+
+struct BSweepGroups {
+    int count, nsweeps;
+    int first[MAX_GROUPS];              // first sweep of each group; INT_MAX past count
+    BSweepGroup g[MAX_GROUPS];
+};
+
+__device__ __forceinline__ void batch_sweep(const BSweep &t, const KParams &proto, int parity, float *lds)
+{
+    KParams q = proto;
+    q.nx = t.nx;
+    q.ny = t.ny;
+    q.r32.omega = t.omega;
+    float *const b0 = t.buf[0], *const b1 = t.buf[1];     // see batch_tile
+    const float *src = parity ? b1 : b0;
+    float *dst = parity ? b0 : b1;
+    if (rows_on_lines(t.nx, sizeof(float))) sweep<Pair32, PAIR, true>(src, dst, q, t.grid, t.b, lds);
+    else sweep<Pair32, PAIR, false>(src, dst, q, t.grid, t.b, lds);
+}
+
+__global__ __launch_bounds__(sweep_threads<Pair32>(), (sweep_per_cu<Pair32, PAIR>())) void
+k_pair_groups(float *__restrict__ pool, const float *__restrict__ omegas, BSweepGroups G, KParams proto, int parity)
+{
+    extern __shared__ __align__(16) unsigned char sweep_lds[];
+    const int t = xcd_tile(blockIdx.x, gridDim.x);
+    int gi = 0;
+#pragma unroll
+    for (int k = 1; k < MAX_GROUPS; ++k) gi += (t >= G.first[k]) ? 1 : 0;
+    const BSweepGroup &gr = G.g[gi];
+    const int local = t - G.first[gi];
+    const int lat = local / gr.grid.wgs;
+    BSweep s;
+    s.buf[0] = pool + gr.base + (long long)lat * gr.stride;
+    s.buf[1] = s.buf[0] + gr.half;
+    s.nx = gr.nx;
+    s.ny = gr.ny;
+    s.omega = omegas[gr.first_lat + lat];
+    s.b = local - lat * gr.grid.wgs;
+    s.grid = gr.grid;
+    batch_sweep(s, proto, parity, reinterpret_cast<float *>(sweep_lds));
+}
+
+__global__ __launch_bounds__(sweep_threads<Pair32>(), (sweep_per_cu<Pair32, PAIR>())) void
+k_pair_list(const BSweep *__restrict__ sweeps, KParams proto, int parity)
+{
+    extern __shared__ __align__(16) unsigned char sweep_lds[];
+    const BSweep s = sweeps[xcd_tile(blockIdx.x, gridDim.x)];
+    batch_sweep(s, proto, parity, reinterpret_cast<float *>(sweep_lds));
+}
+
 __global__ void k_fill(float *p, size_t n, float v)
 {
     const size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
@@ -179,6 +257,10 @@ struct plbm_batch {
     std::vector<long long> group_base;          // pool offset of each group
     float *d_omega = nullptr;        // omega per lattice, in group order
     BGroups groups;
+    bool pairs = false;              // steps are taken two at a time where they can be
+    BSweepGroups sweep_groups;
+    BSweep *d_sweeps = nullptr;      // when not grouped
+    int nsweeps = 0;
     float *pool = nullptr;
     size_t pool_elems = 0;
     int parity = 0;                  // buffer holding the current state
@@ -298,6 +380,96 @@ int build_tiles(plbm_batch *b)
         b->exec = nullptr;
     }
     return PLBM_OK;
+}
+
+// Rows a chunk of the batch's pairs takes: 16 (see sweep_grid) while that
+// makes a round of workgroups, fewer for smaller batches.
+int sweep_rows(const plbm_batch *b)
+{
+    constexpr int slots = SWEEP_CUS * sweep_per_cu<Pair32, PAIR>();
+    for (int h = 16; h > 4; h /= 2) {
+        long long n = 0;
+        for (const auto &s : b->specs) {
+            SweepGrid g = sweep_grid<Pair32, PAIR>(s.nx, s.ny);
+            g.rows(s.ny, std::min(h, s.ny));
+            n += g.wgs;
+        }
+        if (n >= slots) return h;
+    }
+    return 4;
+}
+
+int build_sweeps(plbm_batch *b)
+{
+    long long nodes = 0;
+    bool fit = paper_set(b->kp);
+    for (const auto &s : b->specs) {
+        nodes += (long long)s.nx * s.ny;
+        fit = fit && sweep_fits<Pair32>(s.nx);
+    }
+    b->pairs = fit && nodes >= PAIR_NODES;
+    if (!b->pairs) return PLBM_OK;
+    const int rows = sweep_rows(b);
+    auto grid_for_lattice = [&](const plbm_lattice_spec &s) {
+        SweepGrid g = sweep_grid<Pair32, PAIR>(s.nx, s.ny);
+        g.rows(s.ny, std::min(rows, s.ny));
+        return g;
+    };
+    long long total = 0;
+    for (const auto &s : b->specs) {
+        total += grid_for_lattice(s).wgs;
+    }
+    if (total > MAX_GRID) {
+        b->pairs = false;
+        return PLBM_OK;
+    }
+    b->nsweeps = (int)total;
+    if (b->grouped) {
+        BSweepGroups &G = b->sweep_groups;
+        std::memset(&G, 0, sizeof(G));
+        int at = 0, lat0 = 0;
+        for (size_t gi = 0; gi < b->group_lats.size(); ++gi) {
+            const plbm_lattice_spec &sp = b->specs[b->group_lats[gi][0]];
+            BSweepGroup &g = G.g[gi];
+            g.grid = grid_for_lattice(sp);
+            g.base = b->group_base[gi];
+            g.half = (long long)padded_elems(sp);
+            g.stride = 2 * g.half;
+            g.first_lat = lat0;
+            g.nx = sp.nx;
+            g.ny = sp.ny;
+            G.first[gi] = at;
+            at += g.grid.wgs * (int)b->group_lats[gi].size();
+            lat0 += (int)b->group_lats[gi].size();
+        }
+        G.count = (int)b->group_lats.size();
+        G.nsweeps = at;
+        for (int k = G.count; k < MAX_GROUPS; ++k) G.first[k] = 0x7fffffff;
+        return PLBM_OK;
+    }
+    std::vector<BSweep> list;
+    list.reserve(total);
+    for (size_t i = 0; i < b->specs.size(); ++i) {
+        const SweepGrid g = grid_for_lattice(b->specs[i]);
+        const BLat &L = b->lats[i];
+        for (int k = 0; k < g.wgs; ++k)
+            list.push_back(BSweep{{L.buf[0], L.buf[1]}, L.nx, L.ny, L.omega, k, g});
+    }
+    if (hipMalloc((void **)&b->d_sweeps, list.size() * sizeof(BSweep)) != hipSuccess) return PLBM_EHIP;
+    return hipck(hipMemcpy(b->d_sweeps, list.data(), list.size() * sizeof(BSweep), hipMemcpyHostToDevice));
+}
+
+// two steps of the whole batch
+int launch_pair(plbm_batch *b, int parity, hipStream_t st)
+{
+    (void)hipGetLastError();
+    if (b->grouped)
+        hipLaunchKernelGGL(k_pair_groups, dim3(b->nsweeps), dim3(sweep_threads<Pair32>()),
+                           (sweep_lds_bytes<Pair32, PAIR>()), st, b->pool, b->d_omega, b->sweep_groups, b->kp, parity);
+    else
+        hipLaunchKernelGGL(k_pair_list, dim3(b->nsweeps), dim3(sweep_threads<Pair32>()),
+                           (sweep_lds_bytes<Pair32, PAIR>()), st, b->d_sweeps, b->kp, parity);
+    return hipck(hipGetLastError());
 }
 
 int grid_of(const plbm_batch *b, int ntiles)
@@ -516,6 +688,7 @@ extern "C" int plbm_batch_create(const plbm_desc *proto, const plbm_lattice_spec
         return PLBM_EHIP;
     }
     rc = build_tiles(b);
+    if (rc == PLBM_OK) rc = build_sweeps(b);
     if (rc != PLBM_OK) {
         plbm_batch_destroy(b);
         return rc;
@@ -531,6 +704,7 @@ extern "C" int plbm_batch_destroy(plbm_batch *b)
     if (b->exec) (void)hipGraphExecDestroy(b->exec);
     if (b->capture) (void)hipStreamDestroy(b->capture);
     if (b->d_tiles) (void)hipFree(b->d_tiles);
+    if (b->d_sweeps) (void)hipFree(b->d_sweeps);
     if (b->d_omega) (void)hipFree(b->d_omega);
     if (b->pool) (void)hipFree(b->pool);
     delete b;
@@ -589,11 +763,14 @@ extern "C" int plbm_batch_step(plbm_batch *b, int nsteps, void *stream)
     int left = nsteps;
     if (b->graph_steps >= 2 && left >= b->graph_steps) {
         if (!b->exec) {
-            // record graph_steps launches (even: the state returns to the same buffer)
+            // record graph_steps steps in an even number of launches: the
+            // state returns to the same buffer
             hipGraph_t g = nullptr;
             rc = hipck(hipStreamBeginCapture(b->capture, hipStreamCaptureModeThreadLocal));
             if (rc != PLBM_OK) return rc;
-            for (int s = 0; s < b->graph_steps && rc == PLBM_OK; ++s)
+            const int pairs = b->pairs ? fused_launches<PAIR>(b->graph_steps) : 0;
+            for (int k = 0; k < pairs && rc == PLBM_OK; ++k) rc = launch_pair(b, k & 1, b->capture);
+            for (int s = PAIR * pairs; s < b->graph_steps && rc == PLBM_OK; ++s)
                 rc = launch_step(b, s & 1, b->capture);
             const int rc_end = hipck(hipStreamEndCapture(b->capture, &g));
             if (rc == PLBM_OK) rc = rc_end;
@@ -613,6 +790,11 @@ extern "C" int plbm_batch_step(plbm_batch *b, int nsteps, void *stream)
             if (rc != PLBM_OK) return rc;
             left -= b->graph_steps;
         }
+    }
+    for (; b->pairs && left >= PAIR; left -= PAIR) {
+        rc = launch_pair(b, b->parity, st);
+        if (rc != PLBM_OK) return rc;
+        b->parity ^= 1;
     }
     for (; left > 0; --left) {
         rc = launch_step(b, b->parity, st);
