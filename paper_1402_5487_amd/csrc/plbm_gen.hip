@@ -13,8 +13,8 @@
 // (y q + k) nx + x with q = q1d^2 and k = i + q1d j.  Same streaming design
 // as the specialised steps: one 256-node row segment per workgroup,
 // XCD-contiguous tiles, a scalar row base per y velocity and a lane offset
-// per x velocity (x wrap folded in), non-temporal stores; larger D2Q16 {+-1,
-// +-3} and D2Q49 lattices take two steps a launch.  FP64 storage
+// per x velocity (x wrap folded in), non-temporal stores; D2Q16 {+-1, +-3} and
+// D2Q49 lattices take two or three steps a launch.  FP64 storage
 // computes in FP64, FP32 in FP32.
 #include <hip/hip_runtime.h>
 
@@ -26,6 +26,7 @@
 #include "plbm_device.h"
 #include "plbm_internal.h"
 #include "plbm_sweep.h"
+#include "plbm_tile.h"
 #include "plbm_tube.h"
 
 namespace {
@@ -516,21 +517,41 @@ void gen_launch(const GenParams &p, const T *src, T *dst, double *part, hipStrea
         hipLaunchKernelGGL((k_step_gen1d_sums<Q1, T>), dim3(grid_g(p)), dim3(TX), 0, st, src, dst, p, part);
 }
 
-// Fused pairs fa -> fb -> fa .. of n steps; returns how many steps they took,
-// or a (negative) status.  Which lattices take them: from 2^18 nodes on, with
-// at least half the lanes of their strips in use.  Measured per step (us,
-// single -> pair): D2Q16 FP32 256^2 4.8 -> 5.2, 512^2 8.7 -> 7.5, 2048^2
-// 90 -> 58, FP64 2048^2 173 -> 108; D2Q49 FP32 256^2 6.0 -> 11.0, 512^2
-// 22.4 -> 21.2, 2048^2 270 -> 198, FP64 1501 x 1100 289 -> 215, 2048^2
-// 554 -> 490.  Three steps a launch leave D2Q16 one workgroup per CU: 70.
+// Tiles of fused steps (plbm_tile.h) for lattices up to `most` nodes, fused pairs
+// (plbm_sweep.h) beyond, with at least half the lanes of their strips in use;
+// returns how many of the n steps they took, or a (negative) status.  Measured
+// (us a step, single / pairs / tiles): D2Q16 FP32 64^2 3.4 / - / 1.8, 256^2 3.9 / - /
+// 2.4, 512^2 8.0 / 7.6 / 4.9, 1024^2 25.8 / 18.5 / 17.8, 2048^2 90 / 58 / -, FP64
+// 1024^2 49 / 29.7 / 28.8; D2Q49 FP32 128^2 5.0 / - / 3.4, 512^2 21.8 / 20.0 / 16.7,
+// 768^2 44 / 32 / 35, 2048^2 270 / 198 / -, FP64 256^2 12.5 / - / 9.8, 512^2 42 / 39 /
+// 34, 768^2 87 / 67 / 96, 2048^2 554 / 490 / -.  Three steps a strip leave D2Q16 one
+// workgroup per CU: 70 at 2048^2.
 template <class M>
-int gen_pairs(const GenParams &p, void *fa, void *fb, int n, hipStream_t st)
+int gen_fused(const GenParams &p, void *fa, void *fb, int n, hipStream_t st)
 {
     using T = typename M::T;
     constexpr int D = 2;
-    if (!sweep_fits<M>(p.nx) || (long long)p.nx * p.ny < 1 << 18) return 0;
+    constexpr long long most = M::Q1 == 4 ? TILE_NODES : 1 << 18;
     for (int i = 0; i < M::Q1; ++i)
         if (p.sx[i] != M::V[i]) return 0;
+    if ((long long)p.nx * p.ny <= most) {
+        constexpr bool wide = M::Q1 == 7 && sizeof(T) == 8;     // 16 x 16 nodes do not fit the LDS
+        int left = n;
+        TileRun<M> run(p, fa, fb, st);
+        (void)hipGetLastError();
+        if (run.template one_round<8, 8>()) {
+            run.template take<8, 8, 3>(left);
+        } else if constexpr (wide) {
+            run.template take<16, 8, 2>(left);
+        } else if (run.template one_round<16, 16>()) {
+            run.template take<16, 16, 3>(left);
+        } else {
+            run.template take<16, 16, 2>(left);
+        }
+        const int rc = gen_launch_status();
+        return rc == PLBM_OK ? n - left : rc;
+    }
+    if (!sweep_fits<M>(p.nx)) return 0;
     const SweepGrid g = sweep_grid<M, D>(p.nx, p.ny);
     if (2ll * p.nx * g.per < (long long)g.strips * sweep_threads<M>()) return 0;
     const int launches = fused_launches<D>(n);
@@ -540,9 +561,8 @@ int gen_pairs(const GenParams &p, void *fa, void *fb, int n, hipStream_t st)
     auto *kernel = nts ? k_pair_gen<M, true> : k_pair_gen<M, false>;
     for (int k = 0; k < launches; ++k) {
         (void)hipGetLastError();
-        hipLaunchKernelGGL(kernel, dim3(g.wgs), dim3(sweep_threads<M>()),
-                           (sweep_lds_bytes<M, D>()), st, (const T *)((k & 1) ? fb : fa), (T *)((k & 1) ? fa : fb), p,
-                           g);
+        hipLaunchKernelGGL(kernel, dim3(g.wgs), dim3(sweep_threads<M>()), (sweep_lds_bytes<M, D>()), st,
+                           (const T *)((k & 1) ? fb : fa), (T *)((k & 1) ? fa : fb), p, g);
         const int rc = gen_launch_status();
         if (rc != PLBM_OK) return rc;
     }
@@ -550,7 +570,7 @@ int gen_pairs(const GenParams &p, void *fa, void *fb, int n, hipStream_t st)
 }
 
 // How many of n steps were taken several per launch, or a (negative) status:
-// all in 1D, fused pairs in 2D of the sets that have them (in this order of
+// all in 1D, in 2D those of the sets that have fused steps (in this order of
 // their velocities).
 template <int Q1, typename T>
 int fused_steps(const GenParams &p, void *fa, void *fb, int n, hipStream_t st)
@@ -563,10 +583,10 @@ int fused_steps(const GenParams &p, void *fa, void *fb, int n, hipStream_t st)
         const int rc = gen_launch_status();
         return rc == PLBM_OK ? n : rc;
     }
-    if constexpr (Q1 == 4) return gen_pairs<GenSet<T, 256, 1, -1, 3, -3>>(p, fa, fb, n, st);
+    if constexpr (Q1 == 4) return gen_fused<GenSet<T, 256, 1, -1, 3, -3>>(p, fa, fb, n, st);
     // 28 rows of six columns: what the LDS of one workgroup holds
     if constexpr (Q1 == 7)
-        return gen_pairs<GenSet<T, sizeof(T) == 8 ? 112 : 232, 0, 1, -1, 2, -2, 3, -3>>(p, fa, fb, n, st);
+        return gen_fused<GenSet<T, sizeof(T) == 8 ? 112 : 232, 0, 1, -1, 2, -2, 3, -3>>(p, fa, fb, n, st);
     return 0;
 }
 

@@ -44,6 +44,7 @@
 #include "plbm_device.h"
 #include "plbm_internal.h"
 #include "plbm_sweep.h"
+#include "plbm_tile.h"
 #include "plbm_tube.h"
 
 // Scratch of plbm_step_noalloc: the per-workgroup FP64 partial sums of its
@@ -438,55 +439,52 @@ int launch_pair(const KParams &p, const void *src, void *dst, hipStream_t st, Fi
     return launch_status();
 }
 
-// Which lattices take fused pairs.  Measured per step against single steps
-// (us, single -> pair): FP64 256^2 6.8 -> 8.0, 320^2 11.9 -> 11.0, 4096^2
-// 1050 -> 607; FP32 320^2 6.1 -> 7.2, 384^2 7.2 -> 7.4, 448^2 9.7 -> 8.1, 4096^2
-// 519 -> 312.  The 16-bit forms are bound by vector work, of which short
-// chunks add up to as much again: FP16 1024^2 21.4 -> 24, 1501 x 1100
-// 40.4 -> 29.5, 4096^2 278 -> 203.  Rows that leave half the lanes of their
-// strips idle (a quarter: 16-bit) stay with single steps.
+// Which lattices take tiles of fused steps (plbm_tile.h) and which shape: the
+// smallest of 8 x 8, 16 x 16 and 20 x 20 nodes (16-bit, FP32) that gives each CU at
+// most one tile, three steps each; past those two steps on a larger tile,
+// whose margin is less of it, up to the size from which strips are faster.
+// Measured (us a step, single / pairs / tiles): FP64 384^2 15.5 / 11.2 / 8.2,
+// 768^2 44 / 30 / 26, 1024^2 73 / 47 / 60; FP32 384^2 7.2 / 7.3 / 5.1, 768^2 23.8 /
+// 15.5 / 13.9, 1024^2 37.7 / 25.6 / 24.4; FP16 384^2 5.5 / - / 4.2, 768^2 14.2 / - /
+// 12.1, 1024^2 21.9 / 24 / 22.0.
+template <class S>
+bool use_tiles(const KParams &p)
+{
+    return paper_set(p) && (long long)p.nx * p.ny <= (sizeof(typename S::T) == 4 ? TILE_NODES : 700000);
+}
+
+template <class S>
+void tile_steps(const KParams &p, void *fa, void *fb, int &n, hipStream_t st)
+{
+    using M = Thermal25<S>;
+    constexpr size_t elem = sizeof(typename S::T);
+    TileRun<M> run(p, fa, fb, st);
+    if (run.template one_round<8, 8>()) return run.template take<8, 8, 3>(n);
+    if (run.template one_round<16, 16>()) return run.template take<16, 16, 3>(n);
+    if constexpr (elem < 8)
+        if (run.template one_round<20, 20>()) return run.template take<20, 20, 3>(n);
+    if constexpr (elem == 8) run.template take<24, 16, 2>(n);
+    else if constexpr (elem == 4) run.template take<16, 16, 2>(n);
+    else run.template take<24, 24, 2>(n);
+    run.template take<16, 16, 3>(n);
+}
+
+// Which larger lattices take fused pairs of steps (plbm_sweep.h).  Measured per
+// step (us, single -> pair): FP64 4096^2 1050 -> 607, FP32 519 -> 312.  The 16-bit
+// forms are bound by vector work, of which short chunks add up to as much
+// again: FP16 1024^2 21.9 -> 24, 1501 x 1100 40.4 -> 29.5, 4096^2 278 -> 203.  Rows
+// that leave half the lanes of their strips idle (a quarter: 16-bit) stay with
+// single steps.
 template <class S>
 bool use_pairs(const KParams &p, const plbm_desc *d)
 {
     constexpr bool narrow = sizeof(typename S::T) == 2;
     using M = Thermal25<S>;
     if (d->dim != 2 || !sweep_fits<M>(p.nx) || !paper_set(p)) return false;
-    if ((long long)p.nx * p.ny < (narrow ? 1500000 : sizeof(typename S::T) == 8 ? 100000 : 150000)) return false;
+    if (narrow && (long long)p.nx * p.ny < 1500000) return false;
     const SweepGrid g = sweep_grid<M, PAIR>(p.nx, p.ny);
     const long long used = (long long)p.nx * g.per, lanes = (long long)g.strips * sweep_threads<M>();
     return narrow ? 4 * used >= 3 * lanes : 2 * used >= lanes;
-}
-
-// 2D steps of which the first also writes the fields of the state it reads.
-template <class S>
-int run_steps_fields(const KParams &p, const plbm_desc *d, void *fa, void *fb, int nsteps, FieldsOut fo,
-                     hipStream_t st)
-{
-    using T = typename S::T;
-    int s0 = 1;
-    const int pairs = use_pairs<S>(p, d) ? fused_launches<PAIR>(nsteps) : 0;
-    if (pairs > 0) {
-        int rc = launch_pair<S, true>(p, fa, fb, st, fo);
-        for (int k = 1; k < pairs && rc == PLBM_OK; ++k)
-            rc = launch_pair<S, false>(p, (k & 1) ? fb : fa, (k & 1) ? fa : fb, st);
-        if (rc != PLBM_OK) return rc;
-        s0 = 2 * pairs;
-    } else {
-        clear_launch_error();
-        const int nblocks = grid_for(p.ntiles);
-        const size_t lds = sizeof(T) == 2 ? (d->rounding == PLBM_ROUND_STOCHASTIC ? PLBM_LDS_CAP_16SR
-                                                                                 : PLBM_LDS_CAP_16)
-                                          : PLBM_LDS_CAP_WIDE;
-        const bool nts = rows_on_lines(p.nx, sizeof(T));
-        auto *kernel = p.nv == 2 ? (nts ? k_step2d_fields<S, 2, true> : k_step2d_fields<S, 2, false>)
-                                 : (nts ? k_step2d_fields<S, 1, true> : k_step2d_fields<S, 1, false>);
-        hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(TX), lds, st, (const T *)fa, (T *)fb, p, fo);
-    }
-    int rc = launch_status();
-    int nb = 0;
-    for (int s = s0; s < nsteps && rc == PLBM_OK; ++s)
-        rc = launch_step<S, false>(p, d, (s & 1) ? fb : fa, (s & 1) ? fa : fb, nullptr, st, nb);
-    return rc;
 }
 
 // `scratch`: NULL, or a device buffer of (NOALLOC_BLOCKS + 1) * 4 doubles
@@ -498,8 +496,15 @@ int run_steps(const KParams &p, const plbm_desc *d, void *fa, void *fb, int nste
 {
     int nb = 0;
     int s0 = 0;
-    if (use_pairs<S>(p, d)) {
-        const int pairs = fused_launches<PAIR>(nsteps - (sums ? 1 : 0));    // a step that takes sums is a single one
+    if (d->dim == 2 && use_tiles<S>(p)) {
+        int left = nsteps - (sums ? 1 : 0);                     // a step that takes sums is a single one
+        clear_launch_error();
+        tile_steps<S>(p, fa, fb, left, st);
+        const int rc = launch_status();
+        if (rc != PLBM_OK) return rc;
+        s0 = nsteps - (sums ? 1 : 0) - left;
+    } else if (use_pairs<S>(p, d)) {
+        const int pairs = fused_launches<PAIR>(nsteps - (sums ? 1 : 0));
         for (int k = 0; k < pairs; ++k) {
             const int rc = launch_pair<S, false>(p, (k & 1) ? fb : fa, (k & 1) ? fa : fb, st);
             if (rc != PLBM_OK) return rc;
@@ -538,6 +543,32 @@ int run_steps(const KParams &p, const plbm_desc *d, void *fa, void *fb, int nste
         if (rc != PLBM_OK) return rc;
     }
     return PLBM_OK;
+}
+
+// 2D steps of which the first also writes the fields of the state it reads: a
+// fused pair where those are taken, else a step of its own.
+template <class S>
+int run_steps_fields(const KParams &p, const plbm_desc *d, void *fa, void *fb, int nsteps, FieldsOut fo,
+                     hipStream_t st)
+{
+    using T = typename S::T;
+    const int pairs = !use_tiles<S>(p) && use_pairs<S>(p, d) ? fused_launches<PAIR>(nsteps) : 0;
+    if (pairs > 0) {
+        int rc = launch_pair<S, true>(p, fa, fb, st, fo);
+        // the pair that follows leaves the state in fa again
+        if (rc == PLBM_OK) rc = launch_pair<S, false>(p, fb, fa, st);
+        return rc == PLBM_OK && nsteps > 2 * PAIR ? run_steps<S>(p, d, fa, fb, nsteps - 2 * PAIR, nullptr, st, nullptr)
+                                                  : rc;
+    }
+    clear_launch_error();
+    const size_t lds = sizeof(T) == 2 ? (d->rounding == PLBM_ROUND_STOCHASTIC ? PLBM_LDS_CAP_16SR : PLBM_LDS_CAP_16)
+                                      : PLBM_LDS_CAP_WIDE;
+    const bool nts = rows_on_lines(p.nx, sizeof(T));
+    auto *kernel = p.nv == 2 ? (nts ? k_step2d_fields<S, 2, true> : k_step2d_fields<S, 2, false>)
+                             : (nts ? k_step2d_fields<S, 1, true> : k_step2d_fields<S, 1, false>);
+    hipLaunchKernelGGL(kernel, dim3(grid_for(p.ntiles)), dim3(TX), lds, st, (const T *)fa, (T *)fb, p, fo);
+    const int rc = launch_status();
+    return rc == PLBM_OK && nsteps > 1 ? run_steps<S>(p, d, fb, fa, nsteps - 1, nullptr, st, nullptr) : rc;
 }
 
 template <class S>

@@ -14,8 +14,8 @@
 // workgroup with XCD-contiguous tile numbering, a scalar row base per y
 // velocity plus a 32-bit lane offset per x velocity (the periodic wrap in x
 // folded into the offsets), non-temporal stores (and loads for 4- and
-// 8-byte populations).  The set {0, +-1} takes up to five steps a launch
-// (plbm_sweep.h).  FP64 storage computes in FP64, FP32 in FP32.
+// 8-byte populations).  The set {0, +-1} takes up to nine steps a launch
+// (plbm_tile.h, plbm_sweep.h).  FP64 storage computes in FP64, FP32 in FP32.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -26,6 +26,7 @@
 #include "plbm_device.h"
 #include "plbm_internal.h"
 #include "plbm_sweep.h"
+#include "plbm_tile.h"
 #include "plbm_tube.h"
 
 namespace {
@@ -465,8 +466,24 @@ int launch_sweep_q9(const Q9Params &p, const typename M::T *src, typename M::T *
 template <typename T>
 constexpr int Q9_DEPTH = sizeof(T) == 8 ? 4 : 5;
 
-// Every lattice but the narrowest gains: FP32 64^2 4.6 -> 2.7 us a step, 512^2
-// 5.0 -> 4.4, 1024^2 16.3 -> 6.3, 100 x 4000 7.6 -> 5.7.
+// Up to 2^20 nodes tiles (plbm_tile.h) are faster yet: nine steps on 8 x 8 nodes
+// or seven on 16 x 16 while that is at most one tile per CU, else five on
+// 24 x 24.  Measured (us a step, single / strips / tiles): FP32 64^2 4.3 / 2.6 /
+// 0.9, 256^2 4.4 / 2.8 / 1.2, 512^2 5.0 / 4.2 / 2.3, 1024^2 16.2 / 7.1 / 7.1,
+// 1501 x 1100 28 / 9.1 / 10.3; FP64 256^2 4.4 / 2.9 / 1.4, 768^2 16.8 / 7.8 / 5.7,
+// 1024^2 29 / 11.5 / 10.5, 1501 x 1100 44 / 14.5 / 16.0.
+inline bool use_tiles(const Q9Params &p) { return p.sx[1] == 1 && (long long)p.nx * p.ny <= TILE_NODES; }
+
+template <typename T>
+void tile_steps_q9(const Q9Params &p, void *fa, void *fb, int &n, hipStream_t st)
+{
+    TileRun<Iso9<T>> run(p, fa, fb, st);
+    if (run.template one_round<8, 8>()) run.template take<8, 8, 9>(n);
+    else if (run.template one_round<16, 16>()) run.template take<16, 16, 7>(n);
+    else run.template take<24, 24, 5>(n);
+    run.template take<16, 16, 3>(n);
+}
+
 template <typename T>
 bool use_sweeps(const Q9Params &p)
 {
@@ -478,7 +495,14 @@ int q9_run(const Q9Params &p, void *fa, void *fb, int nsteps, double *sums, hipS
 {
     const int nblocks = p.dim == 2 ? grid_for(p.ntiles) : p.tiles_x;
     int s0 = 0, launches = 0;
-    if (p.dim == 2 && use_sweeps<T>(p)) {
+    if (p.dim == 2 && use_tiles(p)) {
+        int left = nsteps - (sums ? 1 : 0);
+        (void)hipGetLastError();
+        tile_steps_q9<T>(p, fa, fb, left, st);
+        const int rc = q9_launch_status();
+        if (rc != PLBM_OK) return rc;
+        s0 = nsteps - (sums ? 1 : 0) - left;
+    } else if (p.dim == 2 && use_sweeps<T>(p)) {
         // D steps a launch, then three, and the rest (and a step that takes
         // sums) one by one
         using M = Iso9<T>;

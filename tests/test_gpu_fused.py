@@ -22,12 +22,35 @@ def _pair(make, fields, split, whole):
     return a, b
 
 
+# tiles: the largest lattices of 8 x 8, 16 x 16 and 20 x 20 nodes a tile, one more
+# row or column than that, ragged edges, fewer nodes than a tile and than its
+# margin, long thin ones; every remainder of the steps
+@pytest.mark.parametrize("nx,ny", [(3, 3), (5, 700), (64, 64), (128, 128), (129, 127), (256, 256), (300, 37),
+                                   (257, 250), (320, 320), (401, 257), (701, 3)])
+@pytest.mark.parametrize("storage,rounding", [("f64", "nearest"), ("f32", "nearest"), ("f16dev", "nearest"),
+                                              ("bf16dev", "nearest"), ("f16dev", "stochastic"),
+                                              ("bf16dev", "stochastic")])
+def test_fused_small_steps_equal_single_steps(nx, ny, storage, rounding):
+    fields = inputs.random_fields(nx, ny, seed=nx + ny)
+    a, b = _pair(lambda: Lattice(2, nx, ny, omega=1.7, storage=storage, rounding=rounding, theta0=0.35),
+                 fields, 28, (2, 3, 5, 8, 10))
+    assert torch.equal(a.f, b.f) and a.cur == b.cur
+    got, want = a.step_fields(6), b.step_fields(1)
+    for _ in range(5):
+        b.step(1)
+    assert torch.equal(a.f, b.f) and all(torch.equal(g, w) for g, w in zip(got, want))
+    s = a.step(8, sums=True)
+    for _ in range(7):
+        b.step(1)
+    assert s == b.step(1, sums=True) and torch.equal(a.f, b.f)
+
+
 # one strip of up to 256 columns that closes on itself, with four, two or one
 # chunk side by side; strips of 224 (FP32) and 240 (FP64) columns beyond: at
 # and past their multiples, ragged rows, a last strip of a single column, more
 # rows than a chunk and fewer than its halo
-@pytest.mark.parametrize("nx,ny", [(63, 2400), (64, 2401), (65, 2311), (128, 1200), (256, 601), (257, 600),
-                                   (448, 353), (449, 340), (1501, 107), (16385, 10), (4096, 37)])
+@pytest.mark.parametrize("nx,ny", [(63, 16700), (64, 16401), (65, 16200), (128, 8201), (256, 4101), (257, 4100),
+                                   (448, 2353), (449, 2340), (1501, 707), (16385, 65), (104850, 11)])
 @pytest.mark.parametrize("storage", ["f64", "f32"])
 def test_fused_steps_equal_single_steps(nx, ny, storage):
     fields = inputs.random_fields(nx, ny, seed=nx + ny)
@@ -49,7 +72,7 @@ def test_fused_16_bit_steps_equal_single_steps(nx, ny, storage, rounding):
 def test_fused_steps_with_fields_and_sums(storage):
     """The first of the fused steps writes the fields of the state it reads;
     a step that takes sums comes after fused ones."""
-    nx, ny = 450, 402
+    nx, ny = 1050, 1002
     fields = inputs.random_fields(nx, ny, seed=5)
     a, b = (Lattice(2, nx, ny, omega=1.7, storage=storage).init(*fields) for _ in range(2))
     got, want = a.step_fields(7), b.step_fields(1)
@@ -65,7 +88,7 @@ def test_fused_steps_with_fields_and_sums(storage):
 
 def test_fused_steps_in_a_graph():
     """Captured once, replayed between eager work: every replay as eager."""
-    nx, ny = 700, 300
+    nx, ny = 700, 1502
     fields = inputs.random_fields(nx, ny, seed=2)
     a, b = (Lattice(2, nx, ny, omega=1.7, storage="f32").init(*fields) for _ in range(2))
     s = torch.cuda.Stream()
@@ -82,9 +105,11 @@ def test_fused_steps_in_a_graph():
         assert torch.equal(a.f, b.f)
 
 
-# D2Q9: four (FP64) or five (FP32) steps a launch on strips of 240 and 224
-# columns, then three, then one; every remainder, fewer rows than the halo
-@pytest.mark.parametrize("nx,ny", [(16, 3), (17, 4), (31, 9), (224, 25), (225, 24), (241, 33), (700, 50)])
+# D2Q9: tiles of nine, seven and five steps, then three, then one; beyond them
+# strips of four (FP64) or five (FP32); every remainder, fewer rows than the halo
+@pytest.mark.parametrize("nx,ny", [(3, 3), (16, 5), (17, 4), (31, 9), (128, 128), (129, 128), (256, 255), (257, 256),
+                                   (700, 50), (1025, 3), (16, 65600), (17, 62000), (224, 4701), (225, 4700),
+                                   (241, 4400), (1501, 700), (262144, 5)])
 @pytest.mark.parametrize("storage", ["f64", "f32"])
 def test_fused_d2q9_steps_equal_single_steps(nx, ny, storage):
     fields = inputs.random_fields(nx, ny, seed=nx + ny, theta=(0.25, 0.25))
@@ -97,7 +122,7 @@ def test_fused_d2q9_steps_equal_single_steps(nx, ny, storage):
     assert s == b.step(1, sums=True) and torch.equal(a.f, b.f)
 
 
-@pytest.mark.parametrize("nx,ny", [(513, 512), (1121, 235), (8192, 33)])
+@pytest.mark.parametrize("nx,ny", [(3, 4), (64, 60), (128, 128), (129, 130), (256, 256), (300, 270), (1025, 1030)])
 @pytest.mark.parametrize("storage", ["f64", "f32"])
 @pytest.mark.parametrize("v,theta", [((1, -1, 3, -3), 4.0 / 3.0), ((0, 1, -1, 2, -2, 3, -3), 1.0)])
 def test_fused_general_steps_equal_single_steps(nx, ny, storage, v, theta):
