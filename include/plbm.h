@@ -254,10 +254,10 @@ int plbm_step_fields(const plbm_desc *d, void *f_a, void *f_b, int nsteps, doubl
  * lattice with sums may have at most 8192 * 256 = 2,097,152 nodes
  * (PLBM_EINVAL beyond, before any launch); without sums no scratch is used
  * and plbm_step's limits apply.
- * Every call on one GPU shares that GPU's scratch and it keeps the last
- * call's contents: calls that ask for sums and overlap on one GPU (other
- * streams or threads) race and must be serialised by the caller.  Calls
- * without sums do not touch it.
+ * One call on a GPU holds its scratch at a time: a call that asks for sums
+ * waits for one that overlaps with it on that GPU (other streams or threads).
+ * plbm_step and plbm_moments take their partial sums there too while it is
+ * free, and allocate otherwise.  Calls without sums do not touch it.
  */
 int plbm_step_noalloc(const plbm_desc *d, void *f_a, void *f_b, int nsteps,
                       double *sums, void *stream);

@@ -491,30 +491,16 @@ int gen_params(const plbm_desc *d, GenParams &p)
 
 inline int grid_g(const GenParams &p) { return std::min(p.ntiles, MAX_GRID_G); }
 
-int gen_finish_sums(double *dev, int nblocks, double *host, hipStream_t st)
-{
-    double *out = dev + (size_t)nblocks * 4;
-    (void)hipGetLastError();
-    hipLaunchKernelGGL(k_reduce_partials<4>, dim3(1), dim3(RED_THREADS), 0, st, dev, nblocks, out);
-    int rc = gen_launch_status();
-    if (rc == PLBM_OK) rc = gen_hip(hipMemcpyAsync(host, out, 4 * sizeof(double), hipMemcpyDeviceToHost, st));
-    if (rc == PLBM_OK) rc = gen_hip(hipStreamSynchronize(st));
-    if (rc != PLBM_OK) return rc;
-    for (int m = 0; m < 4; ++m)
-        if (!std::isfinite(host[m])) return PLBM_ENONFINITE;
-    return PLBM_OK;
-}
-
 template <int Q1, typename T, bool SUMS>
-void gen_launch(const GenParams &p, const T *src, T *dst, double *part, hipStream_t st)
+void gen_launch(const GenParams &p, const T *src, T *dst, double *part, hipStream_t st, int grid)
 {
     if (p.dim == 2) {
         const bool nts = rows_on_lines(p.nx, sizeof(T)), z0 = p.sx[0] == 0;
         auto *kernel = z0 ? (nts ? k_step_gen2d<Q1, T, SUMS, true, true> : k_step_gen2d<Q1, T, SUMS, true, false>)
                           : (nts ? k_step_gen2d<Q1, T, SUMS, false, true> : k_step_gen2d<Q1, T, SUMS, false, false>);
-        hipLaunchKernelGGL(kernel, dim3(grid_g(p)), dim3(TX), (gen_lds_cap<Q1, T>()), st, src, dst, p, part);
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(TX), (gen_lds_cap<Q1, T>()), st, src, dst, p, part);
     } else if constexpr (SUMS)
-        hipLaunchKernelGGL((k_step_gen1d_sums<Q1, T>), dim3(grid_g(p)), dim3(TX), 0, st, src, dst, p, part);
+        hipLaunchKernelGGL((k_step_gen1d_sums<Q1, T>), dim3(grid), dim3(TX), 0, st, src, dst, p, part);
 }
 
 // Tiles of fused steps (plbm_tile.h) for lattices up to `most` nodes, fused pairs
@@ -593,7 +579,6 @@ int fused_steps(const GenParams &p, void *fa, void *fb, int n, hipStream_t st)
 template <int Q1, typename T>
 int gen_run(const GenParams &p, void *fa, void *fb, int nsteps, double *sums, hipStream_t st)
 {
-    const int grid = grid_g(p);
     const int s0 = fused_steps<Q1, T>(p, fa, fb, nsteps - (sums ? 1 : 0), st);
     if (s0 < 0) return s0;
     for (int s = s0; s < nsteps; ++s) {
@@ -601,16 +586,15 @@ int gen_run(const GenParams &p, void *fa, void *fb, int nsteps, double *sums, hi
         T *dst = static_cast<T *>((s & 1) ? fa : fb);
         (void)hipGetLastError();
         if (s == nsteps - 1 && sums) {
-            double *part = nullptr;
-            int rc = gen_hip(hipMallocAsync((void **)&part, ((size_t)grid + 1) * 4 * sizeof(double), st));
+            int blocks = grid_g(p);
+            plbm::SumsArea area;
+            int rc = plbm::sums_begin(area, 4, blocks, true, st);
             if (rc != PLBM_OK) return rc;
-            gen_launch<Q1, T, true>(p, src, dst, part, st);
+            gen_launch<Q1, T, true>(p, src, dst, area.part, st, blocks);
             rc = gen_launch_status();
-            if (rc == PLBM_OK) rc = gen_finish_sums(part, grid, sums, st);
-            (void)hipFreeAsync(part, st);
-            return rc;
+            return plbm::sums_end(area, 4, blocks, rc, sums, st);
         }
-        gen_launch<Q1, T, false>(p, src, dst, nullptr, st);
+        gen_launch<Q1, T, false>(p, src, dst, nullptr, st, grid_g(p));
         const int rc = gen_launch_status();
         if (rc != PLBM_OK) return rc;
     }
@@ -634,23 +618,21 @@ template <int Q1, typename T>
 int gen_moments_t(const GenParams &p, const void *f, double *rho, double *ux, double *uy, double *th,
                   double *sums, hipStream_t st)
 {
-    const int grid = p.dim == 2 ? grid_g(p) : p.tiles_x;
-    double *part = nullptr;
-    int rc = PLBM_OK;
+    int grid = p.dim == 2 ? grid_g(p) : p.tiles_x;
+    plbm::SumsArea area;
     if (sums) {
-        rc = gen_hip(hipMallocAsync((void **)&part, ((size_t)grid + 1) * 4 * sizeof(double), st));
+        const int rc = plbm::sums_begin(area, 4, grid, p.dim == 2, st);
         if (rc != PLBM_OK) return rc;
     }
     (void)hipGetLastError();
     if (p.dim == 2)
         hipLaunchKernelGGL((k_moments_gen2d<Q1, T>), dim3(grid), dim3(TX), 0, st, (const T *)f, p, rho, ux, uy, th,
-                           part);
+                           area.part);
     else
-        hipLaunchKernelGGL((k_moments_gen1d<Q1, T>), dim3(grid), dim3(TX), 0, st, (const T *)f, p, rho, ux, th, part);
-    rc = gen_launch_status();
-    if (rc == PLBM_OK && sums) rc = gen_finish_sums(part, grid, sums, st);
-    if (part) (void)hipFreeAsync(part, st);
-    return rc;
+        hipLaunchKernelGGL((k_moments_gen1d<Q1, T>), dim3(grid), dim3(TX), 0, st, (const T *)f, p, rho, ux, th,
+                           area.part);
+    const int rc = gen_launch_status();
+    return sums ? plbm::sums_end(area, 4, grid, rc, sums, st) : rc;
 }
 
 #define PLBM_GEN_DISPATCH(p, storage, FN, ...)                                            \

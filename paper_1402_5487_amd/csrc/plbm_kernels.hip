@@ -47,9 +47,9 @@
 #include "plbm_tile.h"
 #include "plbm_tube.h"
 
-// Scratch of plbm_step_noalloc: the per-workgroup FP64 partial sums of its
-// sums launch (at most NOALLOC_BLOCKS workgroups, four doubles each) and the
-// four reduced sums behind them.  Each GPU the library runs on holds its own
+// Scratch of the calls that ask for sums: the per-workgroup FP64 partial sums
+// of the launch (at most NOALLOC_BLOCKS workgroups, four doubles each) and the
+// four reduced sums behind them; one call at a time holds it (see sums_begin).  Each GPU the library runs on holds its own
 // copy until the process ends.  Every workgroup of a sums launch writes its
 // own four partials before the reduction reads them, so nothing in it has to
 // start at zero.  Host code must not use this name as a device address: it
@@ -380,20 +380,42 @@ int hip_ok(hipError_t e)
 inline void clear_launch_error() { (void)hipGetLastError(); }
 inline int launch_status() { return hip_ok(hipGetLastError()); }
 
-// Finish a partial-sum reduction: second pass, copy the 4 doubles to the host,
-// synchronise, check finiteness.
-int finish_sums(double *dev, int nblocks, double *host, hipStream_t st)
+// Each device's scratch array: who holds it, and its device address, looked up
+// once (with that device current) and kept.
+constexpr int MAX_DEVICES = 64;
+struct Scratch {
+    std::mutex mu;
+    double *dev = nullptr;
+};
+Scratch g_scratch[MAX_DEVICES];
+
+// The address of the current device's scratch, whose lock the caller holds.
+int scratch_address(Scratch &s)
 {
-    double *out = dev + (size_t)nblocks * 4;
-    clear_launch_error();
-    hipLaunchKernelGGL(k_reduce_partials<4>, dim3(1), dim3(RED_THREADS), 0, st, dev, nblocks, out);
-    int rc = launch_status();
-    if (rc == PLBM_OK)
-        rc = hip_ok(hipMemcpyAsync(host, out, 4 * sizeof(double), hipMemcpyDeviceToHost, st));
-    if (rc == PLBM_OK) rc = hip_ok(hipStreamSynchronize(st));
+    if (s.dev) return PLBM_OK;
+    void *ptr = nullptr;
+    const int rc = hip_ok(hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)));
     if (rc != PLBM_OK) return rc;
-    for (int m = 0; m < 4; ++m)
-        if (!std::isfinite(host[m])) return PLBM_ENONFINITE;
+    if (!ptr) return PLBM_EHIP;
+    s.dev = static_cast<double *>(ptr);
+    return PLBM_OK;
+}
+
+// Takes the scratch of the current device, waiting for whoever holds it.
+int scratch_wait(plbm::SumsArea &a)
+{
+    int dev = -1;
+    int rc = hip_ok(hipGetDevice(&dev));
+    if (rc != PLBM_OK) return rc;
+    if (dev < 0 || dev >= MAX_DEVICES) return PLBM_EUNSUPPORTED;
+    g_scratch[dev].mu.lock();
+    rc = scratch_address(g_scratch[dev]);
+    if (rc != PLBM_OK) {
+        g_scratch[dev].mu.unlock();
+        return rc;
+    }
+    a.part = g_scratch[dev].dev;
+    a.device = dev;
     return PLBM_OK;
 }
 
@@ -487,12 +509,10 @@ bool use_pairs(const KParams &p, const plbm_desc *d)
     return narrow ? 4 * used >= 3 * lanes : 2 * used >= lanes;
 }
 
-// `scratch`: NULL, or a device buffer of (NOALLOC_BLOCKS + 1) * 4 doubles
-// that receives the partial sums instead of a stream-ordered allocation (the
-// sums launch then runs at most NOALLOC_BLOCKS workgroups).
+// noalloc: sums wait for the library's scratch rather than allocate.
 template <class S>
 int run_steps(const KParams &p, const plbm_desc *d, void *fa, void *fb, int nsteps, double *sums,
-              hipStream_t st, double *scratch)
+              hipStream_t st, bool noalloc)
 {
     int nb = 0;
     int s0 = 0;
@@ -524,20 +544,14 @@ int run_steps(const KParams &p, const plbm_desc *d, void *fa, void *fb, int nste
         const void *src = (s & 1) ? fb : fa;
         void *dst = (s & 1) ? fa : fb;
         const bool last = (s == nsteps - 1);
-        if (last && sums && scratch) {
-            const int rc = launch_step<S, true>(p, d, src, dst, scratch, st, nb, NOALLOC_BLOCKS);
-            return rc == PLBM_OK ? finish_sums(scratch, nb, sums, st) : rc;
-        }
         if (last && sums) {
-            const int nblocks = d->dim == 2 ? grid_for(p.ntiles) : (p.nx + TX - 1) / TX;
-            double *part = nullptr;
-            int rc = hip_ok(
-                hipMallocAsync((void **)&part, ((size_t)nblocks + 1) * 4 * sizeof(double), st));
+            int blocks = d->dim == 2 ? grid_for(p.ntiles) : (p.nx + TX - 1) / TX;
+            plbm::SumsArea area;
+            if (noalloc) blocks = std::min(blocks, NOALLOC_BLOCKS);
+            int rc = noalloc ? scratch_wait(area) : plbm::sums_begin(area, 4, blocks, d->dim == 2, st);
             if (rc != PLBM_OK) return rc;
-            rc = launch_step<S, true>(p, d, src, dst, part, st, nb);
-            if (rc == PLBM_OK) rc = finish_sums(part, nb, sums, st);
-            (void)hipFreeAsync(part, st);
-            return rc;
+            rc = launch_step<S, true>(p, d, src, dst, area.part, st, nb, blocks);
+            return plbm::sums_end(area, 4, blocks, rc, sums, st);
         }
         int rc = launch_step<S, false>(p, d, src, dst, nullptr, st, nb);
         if (rc != PLBM_OK) return rc;
@@ -557,7 +571,7 @@ int run_steps_fields(const KParams &p, const plbm_desc *d, void *fa, void *fb, i
         int rc = launch_pair<S, true>(p, fa, fb, st, fo);
         // the pair that follows leaves the state in fa again
         if (rc == PLBM_OK) rc = launch_pair<S, false>(p, fb, fa, st);
-        return rc == PLBM_OK && nsteps > 2 * PAIR ? run_steps<S>(p, d, fa, fb, nsteps - 2 * PAIR, nullptr, st, nullptr)
+        return rc == PLBM_OK && nsteps > 2 * PAIR ? run_steps<S>(p, d, fa, fb, nsteps - 2 * PAIR, nullptr, st, false)
                                                   : rc;
     }
     clear_launch_error();
@@ -568,7 +582,7 @@ int run_steps_fields(const KParams &p, const plbm_desc *d, void *fa, void *fb, i
                              : (nts ? k_step2d_fields<S, 1, true> : k_step2d_fields<S, 1, false>);
     hipLaunchKernelGGL(kernel, dim3(grid_for(p.ntiles)), dim3(TX), lds, st, (const T *)fa, (T *)fb, p, fo);
     const int rc = launch_status();
-    return rc == PLBM_OK && nsteps > 1 ? run_steps<S>(p, d, fb, fa, nsteps - 1, nullptr, st, nullptr) : rc;
+    return rc == PLBM_OK && nsteps > 1 ? run_steps<S>(p, d, fb, fa, nsteps - 1, nullptr, st, false) : rc;
 }
 
 template <class S>
@@ -624,9 +638,9 @@ int init_dispatch(const KParams &p, const plbm_desc *d, const double *rho, const
 }
 
 int step_dispatch(const KParams &p, const plbm_desc *d, void *fa, void *fb, int n, double *sums,
-                  hipStream_t st, double *scratch = nullptr)
+                  hipStream_t st, bool noalloc = false)
 {
-    PLBM_DISPATCH(d, run_steps, p, d, fa, fb, n, sums, st, scratch);
+    PLBM_DISPATCH(d, run_steps, p, d, fa, fb, n, sums, st, noalloc);
 }
 
 int step_fields_dispatch(const KParams &p, const plbm_desc *d, void *fa, void *fb, int n, FieldsOut fo,
@@ -661,6 +675,50 @@ namespace plbm {
 void note_hip_error(const char *what, int code)
 {
     std::snprintf(g_last_error, sizeof(g_last_error), "%s (%d)", what, code);
+}
+
+int sums_begin(SumsArea &a, int nv, int &blocks, bool walks, void *stream)
+{
+    hipStream_t st = as_stream(stream);
+    constexpr int held = (NOALLOC_BLOCKS + 1) * 4;
+    const int most = held / nv - 1;
+    if (walks) blocks = std::min(blocks, most);       // wherever the partials are: the sums do not depend on it
+    int dev = -1, of = -1;
+    if (blocks <= most && hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < MAX_DEVICES &&
+        (!st || (hipStreamGetDevice(st, &of) == hipSuccess && of == dev)) && g_scratch[dev].mu.try_lock()) {
+        if (scratch_address(g_scratch[dev]) == PLBM_OK) {
+            a.part = g_scratch[dev].dev;
+            a.device = dev;
+            return PLBM_OK;
+        }
+        g_scratch[dev].mu.unlock();
+    }
+    a.device = -1;
+    return hip_ok(hipMallocAsync((void **)&a.part, ((size_t)blocks + 1) * nv * sizeof(double), st));
+}
+
+int sums_end(SumsArea &a, int nv, int blocks, int rc, double *host, void *stream)
+{
+    hipStream_t st = as_stream(stream);
+    double *out = a.part + (size_t)blocks * nv;
+    if (rc == PLBM_OK) {
+        clear_launch_error();
+        if (nv == 4)
+            hipLaunchKernelGGL(k_reduce_partials<4>, dim3(1), dim3(RED_THREADS), 0, st, a.part, blocks, out);
+        else
+            hipLaunchKernelGGL(k_reduce_partials<5>, dim3(1), dim3(RED_THREADS), 0, st, a.part, blocks, out);
+        rc = launch_status();
+    }
+    if (rc == PLBM_OK) rc = hip_ok(hipMemcpyAsync(host, out, nv * sizeof(double), hipMemcpyDeviceToHost, st));
+    const int done = hip_ok(hipStreamSynchronize(st));
+    if (rc == PLBM_OK) rc = done;
+    if (a.device >= 0) g_scratch[a.device].mu.unlock();
+    else (void)hipFreeAsync(a.part, st);
+    a = SumsArea{};
+    if (rc != PLBM_OK) return rc;
+    for (int m = 0; m < nv; ++m)
+        if (!std::isfinite(host[m])) return PLBM_ENONFINITE;
+    return PLBM_OK;
 }
 } // namespace plbm
 
@@ -707,32 +765,6 @@ extern "C" int plbm_step_fields(const plbm_desc *d, void *f_a, void *f_b, int ns
     return step_fields_dispatch(p, d, f_a, f_b, nsteps, fo, as_stream(stream));
 }
 
-namespace {
-// Device address of the current device's scratch array, looked up once per
-// device (with that device current) and kept.
-constexpr int NOALLOC_MAX_DEVICES = 64;
-std::mutex g_scratch_mu;
-double *g_scratch_dev[NOALLOC_MAX_DEVICES] = {};
-
-int scratch_for_current_device(double **out)
-{
-    int dev = -1;
-    int rc = hip_ok(hipGetDevice(&dev));
-    if (rc != PLBM_OK) return rc;
-    if (dev < 0 || dev >= NOALLOC_MAX_DEVICES) return PLBM_EUNSUPPORTED;
-    std::lock_guard<std::mutex> lock(g_scratch_mu);
-    if (!g_scratch_dev[dev]) {
-        void *ptr = nullptr;
-        rc = hip_ok(hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)));
-        if (rc != PLBM_OK) return rc;
-        if (!ptr) return PLBM_EHIP;
-        g_scratch_dev[dev] = static_cast<double *>(ptr);
-    }
-    *out = g_scratch_dev[dev];
-    return PLBM_OK;
-}
-} // namespace
-
 extern "C" int plbm_step_noalloc(const plbm_desc *d, void *f_a, void *f_b, int nsteps,
                                  double *sums, void *stream)
 {
@@ -747,15 +779,14 @@ extern "C" int plbm_step_noalloc(const plbm_desc *d, void *f_a, void *f_b, int n
     if (sums && d->dim == 1 && (p.nx + TX - 1) / TX > NOALLOC_BLOCKS) return PLBM_EINVAL;
     if (!sums) return nsteps ? step_dispatch(p, d, f_a, f_b, nsteps, nullptr, as_stream(stream))
                              : PLBM_OK;
-    double *scr = nullptr;
-    rc = scratch_for_current_device(&scr);
-    if (rc != PLBM_OK) return rc;
     hipStream_t st = as_stream(stream);
-    if (nsteps > 0) return step_dispatch(p, d, f_a, f_b, nsteps, sums, st, scr);
+    if (nsteps > 0) return step_dispatch(p, d, f_a, f_b, nsteps, sums, st, true);
+    plbm::SumsArea area;
+    rc = scratch_wait(area);
+    if (rc != PLBM_OK) return rc;
     int nb = 0;
-    rc = moments_dispatch(p, d, f_a, nullptr, nullptr, nullptr, nullptr, scr, st, nb,
-                          NOALLOC_BLOCKS);
-    return rc == PLBM_OK ? finish_sums(scr, nb, sums, st) : rc;
+    rc = moments_dispatch(p, d, f_a, nullptr, nullptr, nullptr, nullptr, area.part, st, nb, NOALLOC_BLOCKS);
+    return plbm::sums_end(area, 4, nb, rc, sums, st);
 }
 
 extern "C" int plbm_moments(const plbm_desc *d, const void *f, double *rho, double *ux,
@@ -772,15 +803,12 @@ extern "C" int plbm_moments(const plbm_desc *d, const void *f, double *rho, doub
     hipStream_t st = as_stream(stream);
     int nb = 0;
     if (!sums) return moments_dispatch(p, d, f, rho, ux, uy, theta, nullptr, st, nb);
-    const int nblocks = d->dim == 2 ? grid_for((long long)((p.nx + TX - 1) / TX) * p.ny)
-                                    : (p.nx + TX - 1) / TX;
-    double *part = nullptr;
-    rc = hip_ok(hipMallocAsync((void **)&part, ((size_t)nblocks + 1) * 4 * sizeof(double), st));
+    int blocks = d->dim == 2 ? grid_for((long long)((p.nx + TX - 1) / TX) * p.ny) : (p.nx + TX - 1) / TX;
+    plbm::SumsArea area;
+    rc = plbm::sums_begin(area, 4, blocks, d->dim == 2, st);
     if (rc != PLBM_OK) return rc;
-    rc = moments_dispatch(p, d, f, rho, ux, uy, theta, part, st, nb);
-    if (rc == PLBM_OK) rc = finish_sums(part, nb, sums, st);
-    (void)hipFreeAsync(part, st);
-    return rc;
+    rc = moments_dispatch(p, d, f, rho, ux, uy, theta, area.part, st, nb, blocks);
+    return plbm::sums_end(area, 4, blocks, rc, sums, st);
 }
 
 extern "C" int plbm_dev_scales(plbm_desc *d, const double *rho, const double *ux,

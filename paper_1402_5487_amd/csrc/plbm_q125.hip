@@ -338,20 +338,6 @@ inline int grid_of(const P3 &p) { return std::min(p.ntiles, MAX_GRID3); }
 template <typename T>
 constexpr size_t lds_cap() { return sizeof(T) == 8 ? PLBM_Q125_LDS_F64 : PLBM_Q125_LDS_F32; }
 
-int q125_finish_sums(double *dev, int nblocks, double *host, hipStream_t st)
-{
-    double *out = dev + (size_t)nblocks * 5;
-    (void)hipGetLastError();
-    hipLaunchKernelGGL(k_reduce_partials<5>, dim3(1), dim3(RED_THREADS), 0, st, dev, nblocks, out);
-    int rc = q125_launch_status();
-    if (rc == PLBM_OK) rc = q125_hip(hipMemcpyAsync(host, out, 5 * sizeof(double), hipMemcpyDeviceToHost, st));
-    if (rc == PLBM_OK) rc = q125_hip(hipStreamSynchronize(st));
-    if (rc != PLBM_OK) return rc;
-    for (int m = 0; m < 5; ++m)
-        if (!std::isfinite(host[m])) return PLBM_ENONFINITE;
-    return PLBM_OK;
-}
-
 template <typename T>
 int q125_run(const P3 &p, void *fa, void *fb, int nsteps, double *sums, hipStream_t st)
 {
@@ -362,14 +348,14 @@ int q125_run(const P3 &p, void *fa, void *fb, int nsteps, double *sums, hipStrea
         T *dst = static_cast<T *>((s & 1) ? fa : fb);
         (void)hipGetLastError();
         if (s == nsteps - 1 && sums) {
-            double *part = nullptr;
-            int rc = q125_hip(hipMallocAsync((void **)&part, ((size_t)grid + 1) * 5 * sizeof(double), st));
+            int blocks = grid;
+            plbm::SumsArea area;
+            int rc = plbm::sums_begin(area, 5, blocks, true, st);
             if (rc != PLBM_OK) return rc;
-            hipLaunchKernelGGL((nts ? k_step3d<T, true, true> : k_step3d<T, true, false>), dim3(grid), dim3(TX), lds_cap<T>(), st, src, dst, p, part);
+            hipLaunchKernelGGL((nts ? k_step3d<T, true, true> : k_step3d<T, true, false>), dim3(blocks), dim3(TX),
+                               lds_cap<T>(), st, src, dst, p, area.part);
             rc = q125_launch_status();
-            if (rc == PLBM_OK) rc = q125_finish_sums(part, grid, sums, st);
-            (void)hipFreeAsync(part, st);
-            return rc;
+            return plbm::sums_end(area, 5, blocks, rc, sums, st);
         }
         hipLaunchKernelGGL((nts ? k_step3d<T, false, true> : k_step3d<T, false, false>), dim3(grid), dim3(TX), lds_cap<T>(), st, src, dst, p, nullptr);
         const int rc = q125_launch_status();
@@ -423,12 +409,13 @@ extern "C" int plbm_moments3(const plbm_desc *d, const void *f, double *rho, dou
     if (rc != PLBM_OK) return rc;
     if (!f) return PLBM_EINVAL;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    const int grid = grid_of(p);
-    double *part = nullptr;
+    int grid = grid_of(p);
+    plbm::SumsArea area;
     if (sums) {
-        rc = q125_hip(hipMallocAsync((void **)&part, ((size_t)grid + 1) * 5 * sizeof(double), st));
+        rc = plbm::sums_begin(area, 5, grid, true, st);
         if (rc != PLBM_OK) return rc;
     }
+    double *part = area.part;
     (void)hipGetLastError();
     if (d->storage == PLBM_F64)
         hipLaunchKernelGGL(k_moments3d<double>, dim3(grid), dim3(TX), 0, st, (const double *)f, p, rho, ux, uy, uz,
@@ -437,7 +424,5 @@ extern "C" int plbm_moments3(const plbm_desc *d, const void *f, double *rho, dou
         hipLaunchKernelGGL(k_moments3d<float>, dim3(grid), dim3(TX), 0, st, (const float *)f, p, rho, ux, uy, uz,
                            theta, part);
     rc = q125_launch_status();
-    if (rc == PLBM_OK && sums) rc = q125_finish_sums(part, grid, sums, st);
-    if (part) (void)hipFreeAsync(part, st);
-    return rc;
+    return sums ? plbm::sums_end(area, 5, grid, rc, sums, st) : rc;
 }

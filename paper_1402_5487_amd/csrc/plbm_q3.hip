@@ -422,29 +422,15 @@ int q9_params(const plbm_desc *d, Q9Params &p)
     return PLBM_OK;
 }
 
-int q9_finish_sums(double *dev, int nblocks, double *host, hipStream_t st)
-{
-    double *out = dev + (size_t)nblocks * 4;
-    (void)hipGetLastError();
-    hipLaunchKernelGGL(k_reduce_partials<4>, dim3(1), dim3(RED_THREADS), 0, st, dev, nblocks, out);
-    int rc = q9_launch_status();
-    if (rc == PLBM_OK) rc = q9_hip(hipMemcpyAsync(host, out, 4 * sizeof(double), hipMemcpyDeviceToHost, st));
-    if (rc == PLBM_OK) rc = q9_hip(hipStreamSynchronize(st));
-    if (rc != PLBM_OK) return rc;
-    for (int m = 0; m < 4; ++m)
-        if (!std::isfinite(host[m])) return PLBM_ENONFINITE;
-    return PLBM_OK;
-}
-
 template <typename T, typename C, bool SUMS>
-void q3_launch(const Q9Params &p, const T *src, T *dst, double *part, hipStream_t st)
+void q3_launch(const Q9Params &p, const T *src, T *dst, double *part, hipStream_t st, int blocks)
 {
     if (p.dim == 2) {
         const size_t lds = sizeof(T) == 8 ? PLBM_Q9_LDS_F64 : PLBM_Q9_LDS_F32;
         auto *kernel = rows_on_lines(p.nx, sizeof(T)) ? k_step_q9<T, C, SUMS, true> : k_step_q9<T, C, SUMS, false>;
-        hipLaunchKernelGGL(kernel, dim3(grid_for(p.ntiles)), dim3(TX), lds, st, src, dst, p, part);
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(TX), lds, st, src, dst, p, part);
     } else if constexpr (SUMS) {
-        hipLaunchKernelGGL((k_step_q3_1d_sums<T, C>), dim3(p.tiles_x), dim3(TX), 0, st, src, dst, p, part);
+        hipLaunchKernelGGL((k_step_q3_1d_sums<T, C>), dim3(blocks), dim3(TX), 0, st, src, dst, p, part);
     }
 }
 
@@ -529,16 +515,15 @@ int q9_run(const Q9Params &p, void *fa, void *fb, int nsteps, double *sums, hipS
         T *dst = static_cast<T *>((s & 1) ? fa : fb);
         (void)hipGetLastError();
         if (s == nsteps - 1 && sums) {
-            double *part = nullptr;
-            int rc = q9_hip(hipMallocAsync((void **)&part, ((size_t)nblocks + 1) * 4 * sizeof(double), st));
+            int blocks = nblocks;
+            plbm::SumsArea area;
+            int rc = plbm::sums_begin(area, 4, blocks, p.dim == 2, st);
             if (rc != PLBM_OK) return rc;
-            q3_launch<T, C, true>(p, src, dst, part, st);
+            q3_launch<T, C, true>(p, src, dst, area.part, st, blocks);
             rc = q9_launch_status();
-            if (rc == PLBM_OK) rc = q9_finish_sums(part, nblocks, sums, st);
-            (void)hipFreeAsync(part, st);
-            return rc;
+            return plbm::sums_end(area, 4, blocks, rc, sums, st);
         }
-        q3_launch<T, C, false>(p, src, dst, nullptr, st);
+        q3_launch<T, C, false>(p, src, dst, nullptr, st, nblocks);
         const int rc = q9_launch_status();
         if (rc != PLBM_OK) return rc;
     }
@@ -593,13 +578,14 @@ int q3_moments(const plbm_desc *d, const void *f, double *rho, double *ux, doubl
     if (rc != PLBM_OK) return rc;
     if (!f) return PLBM_EINVAL;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    const dim3 g(p.dim == 2 ? grid_for(p.ntiles) : p.tiles_x);
-    const int nblocks = (int)g.x;
-    double *part = nullptr;
+    int blocks = p.dim == 2 ? grid_for(p.ntiles) : p.tiles_x;
+    plbm::SumsArea area;
     if (sums) {
-        rc = q9_hip(hipMallocAsync((void **)&part, ((size_t)nblocks + 1) * 4 * sizeof(double), st));
+        rc = plbm::sums_begin(area, 4, blocks, p.dim == 2, st);
         if (rc != PLBM_OK) return rc;
     }
+    const dim3 g(blocks);
+    double *part = area.part;
     (void)hipGetLastError();
     if (p.dim == 1) {
         if (d->storage == PLBM_F64)
@@ -614,9 +600,7 @@ int q3_moments(const plbm_desc *d, const void *f, double *rho, double *ux, doubl
         hipLaunchKernelGGL(k_moments_q9<float>, g, dim3(TX), 0, st, (const float *)f, p, rho, ux, uy, theta, part);
     }
     rc = q9_launch_status();
-    if (rc == PLBM_OK && sums) rc = q9_finish_sums(part, nblocks, sums, st);
-    if (part) (void)hipFreeAsync(part, st);
-    return rc;
+    return sums ? plbm::sums_end(area, 4, blocks, rc, sums, st) : rc;
 }
 
 } // namespace plbm

@@ -174,3 +174,26 @@ def test_fused_batch_steps_equal_single_lattices(sizes):
             lat.step(1)
         assert torch.equal(b.buffer(i), lat.f), (nx, ny)
     b.close()
+
+
+def test_sums_of_threads_and_streams_do_not_mix():
+    """Calls that ask for sums share one scratch while it is free: threads on
+    streams of their own get their own lattice's sums."""
+    import threading
+    n, steps = 4, 12
+    lats = [[Lattice(2, 200 + 60 * i, 90, omega=1.7, storage="f64").init(
+        *inputs.random_fields(200 + 60 * i, 90, seed=i)) for _ in range(2)] for i in range(n)]
+    want = [[b.step(1, sums=True) for _ in range(steps)] for _, b in lats]
+    torch.cuda.synchronize()
+    got = [None] * n
+
+    def work(i):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            got[i] = [lats[i][0].step(1, sums=True) for _ in range(steps)]
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(n)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert got == want
