@@ -382,21 +382,31 @@ int build_tiles(plbm_batch *b)
     return PLBM_OK;
 }
 
-// Rows a chunk of the batch's pairs takes: 16 (see sweep_grid) while that
-// makes a round of workgroups, fewer for smaller batches.
+// Rows a chunk of the batch's pairs takes: those for which the rounds of
+// resident workgroups, each as long as a chunk and its halo, are least (a last
+// round of a few workgroups costs as much as a full one: 100 lattices of
+// 64..128 took 27 us a step with 10 rows, 34 with 16; 40 of 64..512 took 94 with
+// 22, 98 with 16); past eight rounds 16 (see sweep_grid: 256 of 64..512 took
+// 534 us, 561 with 32).
 int sweep_rows(const plbm_batch *b)
 {
     constexpr int slots = SWEEP_CUS * sweep_per_cu<Pair32, PAIR>();
-    for (int h = 16; h > 4; h /= 2) {
+    std::map<std::pair<int, int>, int> sizes;
+    for (const auto &s : b->specs) ++sizes[{s.nx, s.ny}];
+    auto rounds = [&](int h) {
         long long n = 0;
-        for (const auto &s : b->specs) {
-            SweepGrid g = sweep_grid<Pair32, PAIR>(s.nx, s.ny);
-            g.rows(s.ny, std::min(h, s.ny));
-            n += g.wgs;
+        for (const auto &kv : sizes) {
+            SweepGrid g = sweep_grid<Pair32, PAIR>(kv.first.first, kv.first.second);
+            g.rows(kv.first.second, std::min(h, kv.first.second));
+            n += (long long)g.wgs * kv.second;
         }
-        if (n >= slots) return h;
-    }
-    return 4;
+        return (n + slots - 1) / slots;
+    };
+    int best = 16;
+    if (rounds(best) > 8) return best;
+    for (int h = 4; h <= 24; h += 2)
+        if (rounds(h) * (h + 2 * Lines<Pair32>::R) < rounds(best) * (best + 2 * Lines<Pair32>::R)) best = h;
+    return best;
 }
 
 int build_sweeps(plbm_batch *b)
