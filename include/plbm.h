@@ -310,7 +310,7 @@ int plbm_dev_scales(plbm_desc *d, const double *rho, const double *ux,
  * Batching form: many independent D2Q25 lattices advanced together.
  * Each lattice is the model of plbm_step (same velocity set and table) with
  * its own size and relaxation constant, FP32 storage, periodic boundaries.
- * One kernel launch per step (or per two steps, for larger batches) walks a
+ * One kernel launch per step (or per two or three of them) walks a
  * work list of every lattice; plbm_batch_step replays a captured hipGraph of
  * several such launches.
  * ------------------------------------------------------------------------ */
@@ -375,7 +375,8 @@ int plbm_batch_set_graph_steps(plbm_batch *b, int steps);
 /*
  * plbm_batch_step -- advance every lattice by nsteps applications of
  * Eq. srt (as plbm_step).  Whole groups of graph_steps steps replay the
- * captured graph (recorded on first use); the rest are direct launches.
+ * captured graph (recorded on first use); the rest, and the steps of small
+ * batches that take three of them per launch, are direct launches.
  * Asynchronous on `stream`.
  */
 int plbm_batch_step(plbm_batch *b, int nsteps, void *stream);

@@ -12,9 +12,9 @@
 //    and a persistent grid of a few blocks per CU are the same kernel.
 //  * The per-node work is the single-lattice row stepper with the lattice's
 //    own size and relaxation constant.
-//  * Batches of 2^18 nodes and more take two steps per launch (plbm_sweep.h),
-//    each lattice cut into the strips and chunks a lattice of its own would be
-//    cut into; the tiles remain for odd steps and small batches.
+//  * Two or three steps are taken per launch: on tiles in LDS (plbm_tile.h) up
+//    to 2^20 nodes, on strips (plbm_sweep.h) beyond, each lattice cut as one
+//    of its own would be; the single step's tiles remain for the steps left.
 //  * plbm_batch_step replays a captured hipGraph of `graph_steps` consecutive
 //    steps (alternating buffers), so the host issues one graph launch per
 //    graph_steps steps.  No memset is recorded in the graph.
@@ -39,6 +39,7 @@
 #include "plbm_device.h"
 #include "plbm_internal.h"
 #include "plbm_sweep.h"
+#include "plbm_tile.h"
 
 struct plbm_batch;
 
@@ -145,38 +146,35 @@ __global__ __launch_bounds__(TX) void k_step_groups(float *__restrict__ pool, co
     }
 }
 
-// A batch takes pairs from this many nodes on.  Measured per step (us, single
-// -> pair): 10 lattices of 64..128 (96 k nodes) 6.8 -> 8.7, 10 of 64..256
-// (330 k) 15.8 -> 12.2, 100 of 64 (410 k) 19.0 -> 14.1, 40 of 64..512 141 ->
-// 96, 256 of 64..512 899 -> 534.
-constexpr long long PAIR_NODES = 1 << 18;
+// Fused steps: the same two forms of work list, with the workgroups of each
+// lattice's SweepGrid (pairs, plbm_sweep.h) or its tiles (plbm_tile.h) in place of
+// the single step's tiles.
+using Model32 = Thermal25<StF32>;
 
-// Fused pairs (plbm_sweep.h): the same two forms of work list, with the
-// workgroups of each lattice's SweepGrid in place of tiles.
-using Pair32 = Thermal25<StF32>;
-
-struct BSweep {
+struct BFused {
     float *buf[2];
     int nx, ny;
     float omega;
     int b;                              // workgroup of its lattice
-    SweepGrid grid;
+    SweepGrid grid;                     // tiles: strips to a row of them, wgs in all
 };
 
-struct BSweepGroup {
+struct BFusedGroup {
     long long base, stride, half;       // as BGroup
     int first_lat;
     int nx, ny;
     SweepGrid grid;
 };
 
-struct BSweepGroups {
-    int count, nsweeps;
-    int first[MAX_GROUPS];              // first sweep of each group; INT_MAX past count
-    BSweepGroup g[MAX_GROUPS];
+struct BFusedGroups {
+    int count;
+    int first[MAX_GROUPS];              // first workgroup of each group; INT_MAX past count
+    BFusedGroup g[MAX_GROUPS];
 };
 
-__device__ __forceinline__ void batch_sweep(const BSweep &t, const KParams &proto, int parity, float *lds)
+// BX = 0: a pair of steps of a strip, else D steps of a tile.
+template <int BX, int D>
+__device__ __forceinline__ void batch_fused(const BFused &t, const KParams &proto, int parity, float *lds)
 {
     KParams q = proto;
     q.nx = t.nx;
@@ -185,22 +183,31 @@ __device__ __forceinline__ void batch_sweep(const BSweep &t, const KParams &prot
     float *const b0 = t.buf[0], *const b1 = t.buf[1];     // see batch_tile
     const float *src = parity ? b1 : b0;
     float *dst = parity ? b0 : b1;
-    if (rows_on_lines(t.nx, sizeof(float))) sweep<Pair32, PAIR, true>(src, dst, q, t.grid, t.b, lds);
-    else sweep<Pair32, PAIR, false>(src, dst, q, t.grid, t.b, lds);
+    if constexpr (BX > 0) tile_steps<Model32, BX, BX, D>(src, dst, q, t.b, t.grid.strips, lds);
+    else if (rows_on_lines(t.nx, sizeof(float))) sweep<Model32, D, true>(src, dst, q, t.grid, t.b, lds);
+    else sweep<Model32, D, false>(src, dst, q, t.grid, t.b, lds);
 }
 
-__global__ __launch_bounds__(sweep_threads<Pair32>(), (sweep_per_cu<Pair32, PAIR>())) void
-k_pair_groups(float *__restrict__ pool, const float *__restrict__ omegas, BSweepGroups G, KParams proto, int parity)
+template <int BX, int D>
+constexpr int fused_threads() { return BX > 0 ? TileShape<Model32, BX ? BX : 8, BX ? BX : 8, D>::THREADS : sweep_threads<Model32>(); }
+template <int BX, int D>
+constexpr size_t fused_lds() { return BX > 0 ? TileShape<Model32, BX ? BX : 8, BX ? BX : 8, D>::LDS : sweep_lds_bytes<Model32, 2>(); }
+template <int BX>
+constexpr int fused_waves() { return BX > 0 ? 1 : sweep_per_cu<Model32, 2>(); }
+
+template <int BX, int D>
+__global__ __launch_bounds__((fused_threads<BX, D>()), (fused_waves<BX>())) void
+k_fused_groups(float *__restrict__ pool, const float *__restrict__ omegas, BFusedGroups G, KParams proto, int parity)
 {
-    extern __shared__ __align__(16) unsigned char sweep_lds[];
+    extern __shared__ __align__(16) unsigned char fused_lds_[];
     const int t = xcd_tile(blockIdx.x, gridDim.x);
     int gi = 0;
 #pragma unroll
     for (int k = 1; k < MAX_GROUPS; ++k) gi += (t >= G.first[k]) ? 1 : 0;
-    const BSweepGroup &gr = G.g[gi];
+    const BFusedGroup &gr = G.g[gi];
     const int local = t - G.first[gi];
     const int lat = local / gr.grid.wgs;
-    BSweep s;
+    BFused s;
     s.buf[0] = pool + gr.base + (long long)lat * gr.stride;
     s.buf[1] = s.buf[0] + gr.half;
     s.nx = gr.nx;
@@ -208,16 +215,25 @@ k_pair_groups(float *__restrict__ pool, const float *__restrict__ omegas, BSweep
     s.omega = omegas[gr.first_lat + lat];
     s.b = local - lat * gr.grid.wgs;
     s.grid = gr.grid;
-    batch_sweep(s, proto, parity, reinterpret_cast<float *>(sweep_lds));
+    batch_fused<BX, D>(s, proto, parity, reinterpret_cast<float *>(fused_lds_));
 }
 
-__global__ __launch_bounds__(sweep_threads<Pair32>(), (sweep_per_cu<Pair32, PAIR>())) void
-k_pair_list(const BSweep *__restrict__ sweeps, KParams proto, int parity)
+template <int BX, int D>
+__global__ __launch_bounds__((fused_threads<BX, D>()), (fused_waves<BX>())) void
+k_fused_list(const BFused *__restrict__ list, KParams proto, int parity)
 {
-    extern __shared__ __align__(16) unsigned char sweep_lds[];
-    const BSweep s = sweeps[xcd_tile(blockIdx.x, gridDim.x)];
-    batch_sweep(s, proto, parity, reinterpret_cast<float *>(sweep_lds));
+    extern __shared__ __align__(16) unsigned char fused_lds_[];
+    const BFused s = list[xcd_tile(blockIdx.x, gridDim.x)];
+    batch_fused<BX, D>(s, proto, parity, reinterpret_cast<float *>(fused_lds_));
 }
+
+// How a batch takes several steps per launch: three on tiles of 8 x 8 or
+// 16 x 16 nodes while that is at most one tile per CU, two on 16 x 16 up to 2^20
+// nodes, pairs of strips beyond.  Measured (us a step, single / strips / chosen):
+// 4 lattices of 64 4.9 / - / 2.6, 20 of 64 6.2 / - / 5.0, 6 of 64..128 5.5 / - / 3.6,
+// 40 of 64..128 18.3 / 12.9 / 10.9, 10 of 64..256 16.1 / 11.7 / 9.9, 5 of 64..512
+// 27.8 / 18.9 / 17.4, 40 of 64..512 142 / 94 / 94, 256 of 64..512 899 / 534 / 534.
+enum class Fused { none, pairs, tiles8, tiles16, tiles16x2 };
 
 __global__ void k_fill(float *p, size_t n, float v)
 {
@@ -257,10 +273,11 @@ struct plbm_batch {
     std::vector<long long> group_base;          // pool offset of each group
     float *d_omega = nullptr;        // omega per lattice, in group order
     BGroups groups;
-    bool pairs = false;              // steps are taken two at a time where they can be
-    BSweepGroups sweep_groups;
-    BSweep *d_sweeps = nullptr;      // when not grouped
-    int nsweeps = 0;
+    Fused fused = Fused::none;
+    int depth = 1;                   // steps of a fused launch
+    int nfused = 0;                  // its workgroups
+    BFusedGroups fused_groups;
+    BFused *d_fused = nullptr;       // when not grouped
     float *pool = nullptr;
     size_t pool_elems = 0;
     int parity = 0;                  // buffer holding the current state
@@ -390,13 +407,13 @@ int build_tiles(plbm_batch *b)
 // 534 us, 561 with 32).
 int sweep_rows(const plbm_batch *b)
 {
-    constexpr int slots = SWEEP_CUS * sweep_per_cu<Pair32, PAIR>();
+    constexpr int slots = SWEEP_CUS * sweep_per_cu<Model32, 2>();
     std::map<std::pair<int, int>, int> sizes;
     for (const auto &s : b->specs) ++sizes[{s.nx, s.ny}];
     auto rounds = [&](int h) {
         long long n = 0;
         for (const auto &kv : sizes) {
-            SweepGrid g = sweep_grid<Pair32, PAIR>(kv.first.first, kv.first.second);
+            SweepGrid g = sweep_grid<Model32, 2>(kv.first.first, kv.first.second);
             g.rows(kv.first.second, std::min(h, kv.first.second));
             n += (long long)g.wgs * kv.second;
         }
@@ -405,42 +422,73 @@ int sweep_rows(const plbm_batch *b)
     int best = 16;
     if (rounds(best) > 8) return best;
     for (int h = 4; h <= 24; h += 2)
-        if (rounds(h) * (h + 2 * Lines<Pair32>::R) < rounds(best) * (best + 2 * Lines<Pair32>::R)) best = h;
+        if (rounds(h) * (h + 2 * Lines<Model32>::R) < rounds(best) * (best + 2 * Lines<Model32>::R)) best = h;
     return best;
 }
 
-int build_sweeps(plbm_batch *b)
+// Tiles of the batch, side x side nodes each.
+long long count_tiles(const plbm_batch *b, int side)
+{
+    long long n = 0;
+    for (const auto &s : b->specs)
+        n += (long long)((s.nx + side - 1) / side) * ((s.ny + side - 1) / side);
+    return n;
+}
+
+int build_fused(plbm_batch *b)
 {
     long long nodes = 0;
     bool fit = paper_set(b->kp);
     for (const auto &s : b->specs) {
         nodes += (long long)s.nx * s.ny;
-        fit = fit && sweep_fits<Pair32>(s.nx);
+        fit = fit && sweep_fits<Model32>(s.nx);
     }
-    b->pairs = fit && nodes >= PAIR_NODES;
-    if (!b->pairs) return PLBM_OK;
-    const int rows = sweep_rows(b);
+    b->fused = Fused::none;
+    b->depth = 1;
+    if (!fit) return PLBM_OK;
+    int side = 0;
+    if (count_tiles(b, 8) <= SWEEP_CUS) {
+        b->fused = Fused::tiles8;
+        b->depth = 3;
+        side = 8;
+    } else if (count_tiles(b, 16) <= SWEEP_CUS) {
+        b->fused = Fused::tiles16;
+        b->depth = 3;
+        side = 16;
+    } else if (nodes <= TILE_NODES) {
+        b->fused = Fused::tiles16x2;
+        b->depth = 2;
+        side = 16;
+    } else {
+        b->fused = Fused::pairs;
+        b->depth = 2;
+    }
+    const int rows = side ? 0 : sweep_rows(b);
     auto grid_for_lattice = [&](const plbm_lattice_spec &s) {
-        SweepGrid g = sweep_grid<Pair32, PAIR>(s.nx, s.ny);
-        g.rows(s.ny, std::min(rows, s.ny));
+        SweepGrid g = sweep_grid<Model32, 2>(s.nx, s.ny);
+        if (side) {
+            g.strips = (s.nx + side - 1) / side;
+            g.wgs = g.strips * ((s.ny + side - 1) / side);
+        } else {
+            g.rows(s.ny, std::min(rows, s.ny));
+        }
         return g;
     };
     long long total = 0;
-    for (const auto &s : b->specs) {
-        total += grid_for_lattice(s).wgs;
-    }
+    for (const auto &s : b->specs) total += grid_for_lattice(s).wgs;
     if (total > MAX_GRID) {
-        b->pairs = false;
+        b->fused = Fused::none;
+        b->depth = 1;
         return PLBM_OK;
     }
-    b->nsweeps = (int)total;
+    b->nfused = (int)total;
     if (b->grouped) {
-        BSweepGroups &G = b->sweep_groups;
+        BFusedGroups &G = b->fused_groups;
         std::memset(&G, 0, sizeof(G));
         int at = 0, lat0 = 0;
         for (size_t gi = 0; gi < b->group_lats.size(); ++gi) {
             const plbm_lattice_spec &sp = b->specs[b->group_lats[gi][0]];
-            BSweepGroup &g = G.g[gi];
+            BFusedGroup &g = G.g[gi];
             g.grid = grid_for_lattice(sp);
             g.base = b->group_base[gi];
             g.half = (long long)padded_elems(sp);
@@ -453,32 +501,43 @@ int build_sweeps(plbm_batch *b)
             lat0 += (int)b->group_lats[gi].size();
         }
         G.count = (int)b->group_lats.size();
-        G.nsweeps = at;
         for (int k = G.count; k < MAX_GROUPS; ++k) G.first[k] = 0x7fffffff;
         return PLBM_OK;
     }
-    std::vector<BSweep> list;
+    std::vector<BFused> list;
     list.reserve(total);
     for (size_t i = 0; i < b->specs.size(); ++i) {
         const SweepGrid g = grid_for_lattice(b->specs[i]);
         const BLat &L = b->lats[i];
         for (int k = 0; k < g.wgs; ++k)
-            list.push_back(BSweep{{L.buf[0], L.buf[1]}, L.nx, L.ny, L.omega, k, g});
+            list.push_back(BFused{{L.buf[0], L.buf[1]}, L.nx, L.ny, L.omega, k, g});
     }
-    if (hipMalloc((void **)&b->d_sweeps, list.size() * sizeof(BSweep)) != hipSuccess) return PLBM_EHIP;
-    return hipck(hipMemcpy(b->d_sweeps, list.data(), list.size() * sizeof(BSweep), hipMemcpyHostToDevice));
+    if (hipMalloc((void **)&b->d_fused, list.size() * sizeof(BFused)) != hipSuccess) return PLBM_EHIP;
+    return hipck(hipMemcpy(b->d_fused, list.data(), list.size() * sizeof(BFused), hipMemcpyHostToDevice));
 }
 
-// two steps of the whole batch
-int launch_pair(plbm_batch *b, int parity, hipStream_t st)
+template <int BX, int D>
+void launch_fused_as(plbm_batch *b, int parity, hipStream_t st)
+{
+    if (b->grouped)
+        hipLaunchKernelGGL((k_fused_groups<BX, D>), dim3(b->nfused), dim3(fused_threads<BX, D>()),
+                           (fused_lds<BX, D>()), st, b->pool, b->d_omega, b->fused_groups, b->kp, parity);
+    else
+        hipLaunchKernelGGL((k_fused_list<BX, D>), dim3(b->nfused), dim3(fused_threads<BX, D>()),
+                           (fused_lds<BX, D>()), st, b->d_fused, b->kp, parity);
+}
+
+// `depth` steps of the whole batch
+int launch_fused(plbm_batch *b, int parity, hipStream_t st)
 {
     (void)hipGetLastError();
-    if (b->grouped)
-        hipLaunchKernelGGL(k_pair_groups, dim3(b->nsweeps), dim3(sweep_threads<Pair32>()),
-                           (sweep_lds_bytes<Pair32, PAIR>()), st, b->pool, b->d_omega, b->sweep_groups, b->kp, parity);
-    else
-        hipLaunchKernelGGL(k_pair_list, dim3(b->nsweeps), dim3(sweep_threads<Pair32>()),
-                           (sweep_lds_bytes<Pair32, PAIR>()), st, b->d_sweeps, b->kp, parity);
+    switch (b->fused) {
+    case Fused::pairs: launch_fused_as<0, 2>(b, parity, st); break;
+    case Fused::tiles8: launch_fused_as<8, 3>(b, parity, st); break;
+    case Fused::tiles16: launch_fused_as<16, 3>(b, parity, st); break;
+    case Fused::tiles16x2: launch_fused_as<16, 2>(b, parity, st); break;
+    case Fused::none: return PLBM_EINVAL;
+    }
     return hipck(hipGetLastError());
 }
 
@@ -698,7 +757,7 @@ extern "C" int plbm_batch_create(const plbm_desc *proto, const plbm_lattice_spec
         return PLBM_EHIP;
     }
     rc = build_tiles(b);
-    if (rc == PLBM_OK) rc = build_sweeps(b);
+    if (rc == PLBM_OK) rc = build_fused(b);
     if (rc != PLBM_OK) {
         plbm_batch_destroy(b);
         return rc;
@@ -714,7 +773,7 @@ extern "C" int plbm_batch_destroy(plbm_batch *b)
     if (b->exec) (void)hipGraphExecDestroy(b->exec);
     if (b->capture) (void)hipStreamDestroy(b->capture);
     if (b->d_tiles) (void)hipFree(b->d_tiles);
-    if (b->d_sweeps) (void)hipFree(b->d_sweeps);
+    if (b->d_fused) (void)hipFree(b->d_fused);
     if (b->d_omega) (void)hipFree(b->d_omega);
     if (b->pool) (void)hipFree(b->pool);
     delete b;
@@ -771,16 +830,18 @@ extern "C" int plbm_batch_step(plbm_batch *b, int nsteps, void *stream)
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     int rc = PLBM_OK;
     int left = nsteps;
-    if (b->graph_steps >= 2 && left >= b->graph_steps) {
+    // three steps a launch take longer than the host to issue, and an even
+    // number of steps in a graph would end in single ones
+    if (b->depth != 3 && b->graph_steps >= 2 && left >= b->graph_steps) {
         if (!b->exec) {
             // record graph_steps steps in an even number of launches: the
             // state returns to the same buffer
             hipGraph_t g = nullptr;
             rc = hipck(hipStreamBeginCapture(b->capture, hipStreamCaptureModeThreadLocal));
             if (rc != PLBM_OK) return rc;
-            const int pairs = b->pairs ? fused_launches<PAIR>(b->graph_steps) : 0;
-            for (int k = 0; k < pairs && rc == PLBM_OK; ++k) rc = launch_pair(b, k & 1, b->capture);
-            for (int s = PAIR * pairs; s < b->graph_steps && rc == PLBM_OK; ++s)
+            const int fused = b->depth == 2 ? fused_launches<2>(b->graph_steps) : 0;
+            for (int k = 0; k < fused && rc == PLBM_OK; ++k) rc = launch_fused(b, k & 1, b->capture);
+            for (int s = b->depth * fused; s < b->graph_steps && rc == PLBM_OK; ++s)
                 rc = launch_step(b, s & 1, b->capture);
             const int rc_end = hipck(hipStreamEndCapture(b->capture, &g));
             if (rc == PLBM_OK) rc = rc_end;
@@ -801,8 +862,8 @@ extern "C" int plbm_batch_step(plbm_batch *b, int nsteps, void *stream)
             left -= b->graph_steps;
         }
     }
-    for (; b->pairs && left >= PAIR; left -= PAIR) {
-        rc = launch_pair(b, b->parity, st);
+    for (; b->depth > 1 && left >= b->depth; left -= b->depth) {
+        rc = launch_fused(b, b->parity, st);
         if (rc != PLBM_OK) return rc;
         b->parity ^= 1;
     }

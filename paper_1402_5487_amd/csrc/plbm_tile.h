@@ -28,18 +28,16 @@ struct TileShape {
     static_assert(THREADS <= 1024 && LDS <= SWEEP_LDS, "the region of a tile fits one workgroup");
 };
 
+// Tile b of the lattice, tiles_x to a row of them.
 template <class M, int BX, int BY, int D>
-__global__ __launch_bounds__((TileShape<M, BX, BY, D>::THREADS)) void
-k_tile(const typename M::T *__restrict__ src, typename M::T *__restrict__ dst, typename M::P p, int tiles_x)
+__device__ __forceinline__ void tile_steps(const typename M::T *__restrict__ src, typename M::T *__restrict__ dst,
+                                           const typename M::P &p, int b, int tiles_x,
+                                           typename M::T *__restrict__ lds)
 {
-    using T = typename M::T;
     using C = typename M::C;
     using S = TileShape<M, BX, BY, D>;
     constexpr int Q1 = M::Q1, NP = Q1 * Q1;
-    extern __shared__ __align__(16) unsigned char tile_lds[];
-    T *const lds = reinterpret_cast<T *>(tile_lds);
     const int nx = p.nx, ny = p.ny;
-    const int b = xcd_tile(blockIdx.x, gridDim.x);
     const int ty = b / tiles_x, tx = b - ty * tiles_x;
     // threads past the region repeat its last node and write nothing
     const int node = min((int)threadIdx.x, S::NODES - 1);
@@ -83,6 +81,15 @@ k_tile(const typename M::T *__restrict__ src, typename M::T *__restrict__ dst, t
         return;
 #pragma unroll
     for (int k = 0; k < NP; ++k) store_stream<false>(M::enc(f[k], k, p, key), &dst[(y * NP + k) * nx + x]);
+}
+
+template <class M, int BX, int BY, int D>
+__global__ __launch_bounds__((TileShape<M, BX, BY, D>::THREADS)) void
+k_tile(const typename M::T *__restrict__ src, typename M::T *__restrict__ dst, typename M::P p, int tiles_x)
+{
+    extern __shared__ __align__(16) unsigned char tile_lds[];
+    tile_steps<M, BX, BY, D>(src, dst, p, xcd_tile(blockIdx.x, gridDim.x), tiles_x,
+                             reinterpret_cast<typename M::T *>(tile_lds));
 }
 
 // Launches of fused steps fa -> fb -> fa ..; the state ends in the buffer where
