@@ -96,6 +96,59 @@ struct ClNorm {
     float mw2[4];                           // loss weights 1 / sigma_m^2
 };
 
+// The neighbours of node (x, y) a population reaches: k = i + 5 j moves by
+// (v_i, v_j), so five columns and five rows (uniform over the block, whose
+// rows' addresses are then scalar) serve all 25.  SIGN -1: the pull's sources
+// x - v, +1: the push's targets.  With a column, a row and a conversion of
+// its own for every population and array the node kernels below were bound
+// by that: for 8 frames of 256^2 k_cl_shift took 38 us, k_cl_rstep_shift 89 and
+// k_cl_rstep_step 84.
+struct Near {
+    int xs[Q], ys[Q];
+};
+template <int SIGN>
+__device__ __forceinline__ Near near_of(const ClNorm &nm, int x, int y, int nx, int ny)
+{
+    Near n;
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+        int xs = x + SIGN * nm.ivx[i], ys = y + SIGN * nm.ivx[i];
+        xs += (xs < 0) ? nx : 0;
+        xs -= (xs >= nx) ? nx : 0;
+        ys += (ys < 0) ? ny : 0;
+        ys -= (ys >= ny) ? ny : 0;
+        n.xs[i] = xs;
+        n.ys[i] = ys;
+    }
+    return n;
+}
+// The velocities of the axis as the type of the arithmetic.
+template <typename C>
+struct Axis {
+    C v[Q], v2[Q];
+    __device__ __forceinline__ explicit Axis(const ClNorm &nm)
+    {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            v[i] = (C)nm.ivx[i];
+            v2[i] = v[i] * v[i];
+        }
+    }
+};
+
+// The 25 channels of a node's NHWC x 32 row of floats: seven 16-byte loads.
+__device__ __forceinline__ void load_channels(const float *__restrict__ row, float (&d)[CREAL])
+{
+#pragma unroll
+    for (int q = 0; q < 7; ++q) {
+        const float4 t = reinterpret_cast<const float4 *>(row)[q];
+        const float e[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+            if (4 * q + m < CREAL) d[4 * q + m] = e[m];
+    }
+}
+
 __device__ __forceinline__ u16 bf16_bits(float f) { return __builtin_bit_cast(u16, (__bf16)f); }
 __device__ __forceinline__ float bf16_val(u16 h) { return __uint_as_float((uint32_t)h << 16); }
 
@@ -148,8 +201,8 @@ __global__ __launch_bounds__(256) void k_cl_input(PtrList post, int nx, int ny, 
         for (int c = 0; c < CH; ++c) {
             v[c] = 0.f;
             if (c < CREAL) {
-                v[c] = (float)(P[((size_t)y * CREAL + c) * nx + x] - (T)nm.in_mean[c]) * nm.in_inv[c];
-                if (noise) v[c] += amp * noise[(((size_t)f * CREAL + c) * ny + y) * nx + x];
+                v[c] = (float)((P + ((size_t)y * CREAL + c) * nx)[x] - (T)nm.in_mean[c]) * nm.in_inv[c];
+                if (noise) v[c] += amp * (noise + (((size_t)f * CREAL + c) * ny + y) * nx)[x];
             }
         }
 #pragma unroll
@@ -526,8 +579,7 @@ __global__ __launch_bounds__(256) void k_cl_corr(const float *__restrict__ y3, i
         const size_t plane = (size_t)nx * ny;
         const size_t node = ((size_t)f * ny + y) * nx + x;
         float d[CREAL];
-#pragma unroll
-        for (int k = 0; k < CREAL; ++k) d[k] = y3[node * CH + k];
+        load_channels(y3 + node * CH, d);
         project(d, nm);
 #pragma unroll
         for (int k = 0; k < CREAL; ++k) {
@@ -555,14 +607,12 @@ __global__ __launch_bounds__(256) void k_cl_mloss(const float *__restrict__ C, P
     float lsum = 0.f;
     if (x < nx) {
         const size_t plane = (size_t)nx * ny;
+        const Near n = near_of<-1>(nm, x, y, nx, ny);
         float m[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int k = 0; k < CREAL; ++k) {
-            int xs = x - nm.ivx[k], ys = y - nm.ivy[k];
-            xs += xs < 0 ? nx : (xs >= nx ? -nx : 0);
-            ys += ys < 0 ? ny : (ys >= ny ? -ny : 0);
             const float *ck = C + ((size_t)f * CREAL + k) * plane;
-            const float c = ck[(size_t)ys * nx + xs] - ck[(size_t)y * nx + x];
+            const float c = (ck + (size_t)n.ys[k / Q] * nx)[n.xs[k % Q]] - (ck + (size_t)y * nx)[x];
             const float vx = nm.vx[k], vy = nm.vy[k];
             m[0] += c;
             m[1] += vx * c;
@@ -603,13 +653,11 @@ __global__ __launch_bounds__(256) void k_cl_mgrad(const float *__restrict__ A, c
     if (x < nx) {
         const size_t plane = (size_t)nx * ny;
         const size_t node = ((size_t)f * ny + y) * nx + x;
+        const Near n = near_of<1>(nm, x, y, nx, ny);
         float t[CREAL];
 #pragma unroll
         for (int k = 0; k < CREAL; ++k) {
-            int xs = x + nm.ivx[k], ys = y + nm.ivy[k];
-            xs += xs < 0 ? nx : (xs >= nx ? -nx : 0);
-            ys += ys < 0 ? ny : (ys >= ny ? -ny : 0);
-            const float4 a = reinterpret_cast<const float4 *>(A)[(size_t)f * plane + (size_t)ys * nx + xs];
+            const float4 a = (reinterpret_cast<const float4 *>(A) + (size_t)f * plane + (size_t)n.ys[k / Q] * nx)[n.xs[k % Q]];
             const float vx = nm.vx[k], vy = nm.vy[k];
             t[k] = nm.out_scale[k] * (a.x + vx * a.y + vy * a.z + (vx * vx + vy * vy) * a.w);
         }
@@ -695,8 +743,7 @@ __global__ __launch_bounds__(256) void k_cl_corr_apply(const float *__restrict__
     const size_t plane = (size_t)nx * ny;
     const size_t node = ((size_t)f * ny + y) * nx + x;
     float d[CREAL];
-#pragma unroll
-    for (int k = 0; k < CREAL; ++k) d[k] = y3[node * CH + k];
+    load_channels(y3 + node * CH, d);
     project(d, nm);
     bool ok = true;
 #pragma unroll
@@ -704,7 +751,7 @@ __global__ __launch_bounds__(256) void k_cl_corr_apply(const float *__restrict__
     if (!ok && skipped) atomicAdd(skipped, 1u);
 #pragma unroll
     for (int k = 0; k < CREAL; ++k)
-        C[((size_t)f * CREAL + k) * plane + (size_t)y * nx + x] = ok ? nm.out_scale[k] * d[k] : 0.f;
+        (C + ((size_t)f * CREAL + k) * plane + (size_t)y * nx)[x] = ok ? nm.out_scale[k] * d[k] : 0.f;
 }
 
 template <typename T>
@@ -719,21 +766,20 @@ __global__ __launch_bounds__(256) void k_cl_shift(PtrList post, const float *__r
     if (x >= nx) return;
     const size_t plane = (size_t)nx * ny;
     T *P = static_cast<T *>(post.p[f]);
+    const Near n = near_of<-1>(nm, x, y, nx, ny);
+    const Axis<double> ax(nm);
     double fp[NQ];
     double g[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int k = 0; k < CREAL; ++k) {
-        int xs = x - nm.ivx[k], ys = y - nm.ivy[k];
-        xs += xs < 0 ? nx : (xs >= nx ? -nx : 0);
-        ys += ys < 0 ? ny : (ys >= ny ? -ny : 0);
-        fp[k] = (double)P[((size_t)ys * CREAL + k) * nx + xs];
+        const int i = k % Q, j = k / Q;
+        fp[k] = (double)(P + ((size_t)n.ys[j] * CREAL + k) * nx)[n.xs[i]];
         const float *ck = C + ((size_t)f * CREAL + k) * plane;
-        const double c = (double)ck[(size_t)ys * nx + xs] - (double)ck[(size_t)y * nx + x];
-        const double vx = nm.vx[k], vy = nm.vy[k];
+        const double c = (double)(ck + (size_t)n.ys[j] * nx)[n.xs[i]] - (double)(ck + (size_t)y * nx)[x];
         g[0] += c;
-        g[1] += vx * c;
-        g[2] += vy * c;
-        g[3] += (vx * vx + vy * vy) * c;
+        g[1] += ax.v[i] * c;
+        g[2] += ax.v[j] * c;
+        g[3] += (ax.v2[i] + ax.v2[j]) * c;
     }
     double rho, jx, jy, e;
     sums2d<Fp64Math>(fp, kp, rho, jx, jy, e);
@@ -754,11 +800,8 @@ __global__ __launch_bounds__(256) void k_cl_shift(PtrList post, const float *__r
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
             const int k = i + Q * j;
-            int xs = x - nm.ivx[k], ys = y - nm.ivy[k];
-            xs += xs < 0 ? nx : (xs >= nx ? -nx : 0);
-            ys += ys < 0 ? ny : (ys >= ny ? -ny : 0);
             const double dlt = r1 * a1[i] * b1[j] - rho * a0[i] * b0[j];
-            P[((size_t)ys * CREAL + k) * nx + xs] = (T)fp[k] + (T)dlt;
+            (P + ((size_t)n.ys[j] * CREAL + k) * nx)[n.xs[i]] = (T)fp[k] + (T)dlt;
         }
 }
 
@@ -853,10 +896,16 @@ __device__ __forceinline__ void step_moments(const T *__restrict__ P, int x, int
                                              const KParams &kp, double (&m)[4])
 {
     m[0] = m[1] = m[2] = m[3] = 0.0;
+    int xs[Q], ys[Q];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+        xs[i] = wrap(x - kp.sx[i], nx);
+        ys[i] = wrap(y - kp.sx[i], ny);
+    }
 #pragma unroll
     for (int k = 0; k < NQ; ++k) {
         const int vx = kp.sx[k % Q], vy = kp.sx[k / Q];
-        const double f = (double)P[((size_t)wrap(y - vy, ny) * NQ + k) * nx + wrap(x - vx, nx)];
+        const double f = (double)(P + ((size_t)ys[k / Q] * NQ + k) * nx)[xs[k % Q]];
         m[0] += f;
         m[1] += vx * f;
         m[2] += vy * f;
@@ -874,11 +923,17 @@ __device__ __forceinline__ void step_vjp_scatter(const double (&m)[4], const dou
     double a[4];
     feq_vjp(kp.r64, m, l, a);
     const double w = kp.r64.omega;
+    int xs[Q], ys[Q];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+        xs[i] = wrap(x - kp.sx[i], nx);
+        ys[i] = wrap(y - kp.sx[i], ny);
+    }
 #pragma unroll
     for (int k = 0; k < NQ; ++k) {
         const int vx = kp.sx[k % Q], vy = kp.sx[k / Q];
         const double phi_a = a[0] + vx * a[1] + vy * a[2] + (vx * vx + vy * vy) * a[3];
-        out[((size_t)wrap(y - vy, ny) * NQ + k) * nx + wrap(x - vx, nx)] = (1.0 - w) * l[k] + w * phi_a;
+        (out + ((size_t)ys[k / Q] * NQ + k) * nx)[xs[k % Q]] = (1.0 - w) * l[k] + w * phi_a;
     }
 }
 
@@ -896,9 +951,10 @@ __global__ __launch_bounds__(256) void k_step_vjp(const T *__restrict__ P, const
 }
 
 // Phi_k . a for a per-node moment cotangent a = (a_rho, a_jx, a_jy, a_E)
-__device__ __forceinline__ double phi_dot(double vx, double vy, const double *__restrict__ a)
+__device__ __forceinline__ double phi_dot(const Axis<double> &ax, int k, const double *__restrict__ a)
 {
-    return a[0] + vx * a[1] + vy * a[2] + (vx * vx + vy * vy) * a[3];
+    const int i = k % Q, j = k / Q;
+    return a[0] + ax.v[i] * a[1] + ax.v[j] * a[2] + (ax.v2[i] + ax.v2[j]) * a[3];
 }
 
 // Up to MAX_FRAMES sets of (rho, u_x, u_y, theta) planes.
@@ -912,15 +968,17 @@ template <typename T>
 __device__ __forceinline__ double rloss_node(const T *__restrict__ P, const TruthList &truth, int f, int x, int y,
                                              int nx, int ny, const ClNorm &nm, double scale, double (&a)[4])
 {
+    const Near n = near_of<-1>(nm, x, y, nx, ny);
+    const Axis<double> ax(nm);
     double m[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int k = 0; k < CREAL; ++k) {
-        const double v = (double)P[((size_t)wrap(y - nm.ivy[k], ny) * CREAL + k) * nx + wrap(x - nm.ivx[k], nx)];
-        const double vx = nm.ivx[k], vy = nm.ivy[k];
+        const int i = k % Q, j = k / Q;
+        const double v = (double)(P + ((size_t)n.ys[j] * CREAL + k) * nx)[n.xs[i]];
         m[0] += v;
-        m[1] += vx * v;
-        m[2] += vy * v;
-        m[3] += (vx * vx + vy * vy) * v;
+        m[1] += ax.v[i] * v;
+        m[2] += ax.v[j] * v;
+        m[3] += (ax.v2[i] + ax.v2[j]) * v;
     }
     const size_t at = (size_t)y * nx + x;
     const double r0 = truth.p[4 * f][at], u = truth.p[4 * f + 1][at], w = truth.p[4 * f + 2][at],
@@ -979,10 +1037,12 @@ __global__ __launch_bounds__(256) void k_cl_push4(const double *__restrict__ A, 
     if (x >= nx) return;
     double *L = static_cast<double *>(lam.p[f]);
     const double *Af = A + (size_t)f * ny * nx * 4;
+    const Near n = near_of<1>(nm, x, y, nx, ny);
+    const Axis<double> ax(nm);
 #pragma unroll
     for (int k = 0; k < CREAL; ++k) {
-        const double *a = Af + ((size_t)wrap(y + nm.ivy[k], ny) * nx + wrap(x + nm.ivx[k], nx)) * 4;
-        L[((size_t)y * CREAL + k) * nx + x] += phi_dot(nm.ivx[k], nm.ivy[k], a);
+        const double *a = Af + (size_t)n.ys[k / Q] * nx * 4 + n.xs[k % Q] * 4;
+        (L + ((size_t)y * CREAL + k) * nx)[x] += phi_dot(ax, k, a);
     }
 }
 
@@ -999,14 +1059,16 @@ __device__ __forceinline__ void shift_vjp_node(const T *__restrict__ P, const do
                                                double (&am)[4], size_t node)
 {
     const size_t plane = (size_t)nx * ny;
+    const Near n = near_of<-1>(nm, x, y, nx, ny);
+    const Axis<double> ax(nm);
     double m[4] = {0.0, 0.0, 0.0, 0.0}, g[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int k = 0; k < CREAL; ++k) {
-        const int xs = wrap(x - nm.ivx[k], nx), ys = wrap(y - nm.ivy[k], ny);
-        const double v = (double)P[((size_t)ys * CREAL + k) * nx + xs];
+        const int i = k % Q, j = k / Q;
+        const double v = (double)(P + ((size_t)n.ys[j] * CREAL + k) * nx)[n.xs[i]];
         const float *ck = C + ((size_t)f * CREAL + k) * plane;
-        const double c = (double)ck[(size_t)ys * nx + xs] - (double)ck[(size_t)y * nx + x];
-        const double vx = nm.ivx[k], vy = nm.ivy[k], v2 = vx * vx + vy * vy;
+        const double c = (double)(ck + (size_t)n.ys[j] * nx)[n.xs[i]] - (double)(ck + (size_t)y * nx)[x];
+        const double vx = ax.v[i], vy = ax.v[j], v2 = ax.v2[i] + ax.v2[j];
         m[0] += v;
         m[1] += vx * v;
         m[2] += vy * v;
@@ -1041,10 +1103,10 @@ __global__ __launch_bounds__(256) void k_cl_shift_vjp(PtrList post, PtrList lam,
     const int x = blockIdx.x * 256 + threadIdx.x;
     if (x >= nx) return;
     const double *L = static_cast<const double *>(lam.p[f]);
+    const Near n = near_of<-1>(nm, x, y, nx, ny);
     double l[NQ];
 #pragma unroll
-    for (int k = 0; k < CREAL; ++k)
-        l[k] = L[((size_t)wrap(y - nm.ivy[k], ny) * CREAL + k) * nx + wrap(x - nm.ivx[k], nx)];
+    for (int k = 0; k < CREAL; ++k) l[k] = (L + ((size_t)n.ys[k / Q] * CREAL + k) * nx)[n.xs[k % Q]];
     const size_t node = (size_t)f * ny * nx + (size_t)y * nx + x;
     double am[4];
     shift_vjp_node(static_cast<const T *>(post.p[f]), l, C, f, x, y, nx, ny, nm, kp, Ag, am, node);
@@ -1062,9 +1124,10 @@ __global__ __launch_bounds__(256) void k_cl_input_vjp(const float *__restrict__ 
     if (x >= nx) return;
     double *L = static_cast<double *>(lam.p[f]);
     const size_t node = ((size_t)f * ny + y) * nx + x;
+    float d[CREAL];
+    load_channels(dx + node * CH, d);
 #pragma unroll
-    for (int k = 0; k < CREAL; ++k)
-        L[((size_t)y * CREAL + k) * nx + x] += (double)nm.in_inv[k] * (double)dx[node * CH + k];
+    for (int k = 0; k < CREAL; ++k) (L + ((size_t)y * CREAL + k) * nx)[x] += (double)nm.in_inv[k] * (double)d[k];
 }
 
 // ---------------------------------------------------------------------------
@@ -1103,12 +1166,13 @@ __global__ __launch_bounds__(256) void k_cl_rstep_shift(PtrList after, TruthList
         lsum = rloss_node(static_cast<const T *>(after.p[f]), truth, f, x, y, nx, ny, nm, scale, a);
         __builtin_amdgcn_sched_barrier(0);
         const double *L = static_cast<const double *>(lam_in.p[f]);
+        const Near n = near_of<-1>(nm, x, y, nx, ny);
+        const Axis<double> ax(nm);
         double l[NQ];
 #pragma unroll
         for (int k = 0; k < CREAL; ++k) {
-            const double in = LIN ? L[((size_t)wrap(y - nm.ivy[k], ny) * CREAL + k) * nx + wrap(x - nm.ivx[k], nx)]
-                                  : 0.0;
-            l[k] = in + phi_dot(nm.ivx[k], nm.ivy[k], a);
+            const double in = LIN ? (L + ((size_t)n.ys[k / Q] * CREAL + k) * nx)[n.xs[k % Q]] : 0.0;
+            l[k] = in + phi_dot(ax, k, a);
         }
         __builtin_amdgcn_sched_barrier(0);
         const size_t node = (size_t)f * ny * nx + (size_t)y * nx + x;
@@ -1138,6 +1202,8 @@ __global__ __launch_bounds__(256) void k_cl_rstep_step(PtrList before, PtrList l
     __builtin_amdgcn_sched_barrier(0);
     // the node's 25 input-gradient channels: seven 16-byte loads of its 128-byte row
     const float4 *d4 = reinterpret_cast<const float4 *>(dx + (fbase + (size_t)y * nx + x) * CH);
+    const Near n = near_of<1>(nm, x, y, nx, ny);
+    const Axis<double> ax(nm);
     double l[NQ];
 #pragma unroll
     for (int q = 0; q < 7; ++q) {
@@ -1147,11 +1213,10 @@ __global__ __launch_bounds__(256) void k_cl_rstep_step(PtrList before, PtrList l
         for (int e = 0; e < 4; ++e) {
             const int k = 4 * q + e;
             if (k >= CREAL) break;
-            const size_t nb = fbase + (size_t)wrap(y + nm.ivy[k], ny) * nx + wrap(x + nm.ivx[k], nx);
-            const double4 av = reinterpret_cast<const double4 *>(A)[nb];
+            const double4 av = (reinterpret_cast<const double4 *>(A) + fbase + (size_t)n.ys[k / Q] * nx)[n.xs[k % Q]];
             const double a[4] = {av.x, av.y, av.z, av.w};
-            double v = LIN ? L[((size_t)y * CREAL + k) * nx + x] : 0.0;
-            v += phi_dot(nm.ivx[k], nm.ivy[k], a);
+            double v = LIN ? (L + ((size_t)y * CREAL + k) * nx)[x] : 0.0;
+            v += phi_dot(ax, k, a);
             l[k] = v + (double)nm.in_inv[k] * (double)d[e];
         }
         __builtin_amdgcn_sched_barrier(0);     // four neighbours' loads in flight at a time
