@@ -184,13 +184,27 @@ __device__ __forceinline__ void project(float (&v)[CREAL], const ClNorm &nm)
 // coprime with the 64 banks), and the block then stores the 256 x 64 bytes
 // as consecutive 16-byte chunks, one per lane.
 // ---------------------------------------------------------------------------
+// The blocks of the slice past the last frame cast the FP32 parameters to bf16
+// [t][o][i] (forward) and [t][i][o] (input gradient): 5 us as a launch of its own.
 template <typename T>
-__global__ __launch_bounds__(256) void k_cl_input(PtrList post, int nx, int ny, ClNorm nm,
+__global__ __launch_bounds__(256) void k_cl_input(PtrList post, int nx, int ny, int frames, ClNorm nm,
                                                   const float *__restrict__ noise, float amp,
-                                                  u16 *__restrict__ x0)
+                                                  u16 *__restrict__ x0, const float *__restrict__ params,
+                                                  u16 *__restrict__ wf, u16 *__restrict__ wt)
 {
     __shared__ uint32_t tile[256][17];
     const int f = blockIdx.z;
+    if (f == frames) {
+        for (int e = (blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x; e < 3 * LAYER_W;
+             e += gridDim.x * gridDim.y * 256) {
+            const int layer = e / LAYER_W, r = e % LAYER_W;
+            const int t = r / (CH * CH), o = (r / CH) % CH, i = r % CH;
+            const u16 h = bf16_bits(params[(size_t)layer * LAYER_P + r]);
+            wf[e] = h;
+            wt[(size_t)layer * LAYER_W + ((size_t)t * CH + i) * CH + o] = h;
+        }
+        return;
+    }
     const int y = blockIdx.y;
     const int xb = blockIdx.x * 256;
     const int x = xb + threadIdx.x;
@@ -415,9 +429,19 @@ __device__ __forceinline__ bf16x8 wg_operand(const u16 (*rows)[CH], int n0, int 
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-__global__ __launch_bounds__(256) void k_cl_wgrad(const u16 *__restrict__ a, const u16 *__restrict__ dz,
-                                                  int nx, int ny, float *__restrict__ part)
+// The three layers' inputs and output gradients: blockIdx.y is the layer.  One
+// launch for all three, after the input gradients, as each of the small ones
+// (512 blocks at 8 frames of 256^2, and the two passes that sum its partials)
+// ended in a tail of its own: 3 x (23 + 7 + 5) us against 55 + 14 + 5.
+struct WgLayers {
+    const u16 *a[3], *dz[3];
+};
+
+__global__ __launch_bounds__(256) void k_cl_wgrad(WgLayers L, int nx, int ny, float *__restrict__ parts)
 {
+    const u16 *__restrict__ a = L.a[blockIdx.y];
+    const u16 *__restrict__ dz = L.dz[blockIdx.y];
+
     __shared__ __attribute__((aligned(16))) u16 sdz[WG_SEG][CH];
     // a ring of three input rows: row yy sits in slot (yy - y0 + 1) % 3
     __shared__ __attribute__((aligned(16))) u16 sa[3][WG_AN][CH];
@@ -494,9 +518,10 @@ __global__ __launch_bounds__(256) void k_cl_wgrad(const u16 *__restrict__ a, con
         for (int k = 0; k < 8; ++k) bred[wv][l][k] = bsum[k];
     }
     __syncthreads();
-    // partials: [block][t][o][i] then [block][bias o]
-    const size_t nblk = (size_t)gridDim.x * gridDim.y * gridDim.z;
-    const size_t blk = ((size_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+    // partials of a layer: [block][t][o][i] then [block][bias o]
+    const size_t nblk = (size_t)gridDim.x * gridDim.z;
+    const size_t blk = (size_t)blockIdx.z * gridDim.x + blockIdx.x;
+    float *part = parts + blockIdx.y * nblk * LAYER_P;
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
         const int tap = wv + 4 * q;
@@ -521,7 +546,7 @@ __global__ __launch_bounds__(256) void k_cl_wgrad(const u16 *__restrict__ a, con
     }
 }
 
-// Sum the block partials in a fixed order into the flat gradient of one
+// Sum the block partials in a fixed order into the flat gradient of each
 // layer, in two passes: slice z of the first pass sums blocks z, z + WR_SLICES,
 // ... ; the second sums the slices in order.  Deterministic, and wide enough
 // to keep the memory system busy (the partials of 16 row bands x 8 frames are
@@ -533,21 +558,25 @@ __device__ __forceinline__ float part_at(const float *part, int nblk, int b, int
     return i < LAYER_W ? part[(size_t)b * LAYER_W + i] : part[(size_t)nblk * LAYER_W + (size_t)b * CH + (i - LAYER_W)];
 }
 
-__global__ __launch_bounds__(256) void k_cl_wgrad_slices(const float *__restrict__ part, int nblk,
-                                                         float *__restrict__ slices)
+__global__ __launch_bounds__(256) void k_cl_wgrad_slices(const float *__restrict__ parts, int nblk,
+                                                         float *__restrict__ sums)
 {
     const int i = blockIdx.x * 256 + threadIdx.x, z = blockIdx.y;
     if (i >= LAYER_P) return;
+    const float *part = parts + (size_t)blockIdx.z * nblk * LAYER_P;
+    float *slices = sums + (size_t)blockIdx.z * WR_SLICES * LAYER_P;
     float s = 0.f;
     for (int b = z; b < nblk; b += WR_SLICES) s += part_at(part, nblk, b, i);
     slices[(size_t)z * LAYER_P + i] = s;
 }
 
-__global__ __launch_bounds__(256) void k_cl_wgrad_reduce(const float *__restrict__ slices,
-                                                         float *__restrict__ grad, int accumulate)
+__global__ __launch_bounds__(256) void k_cl_wgrad_reduce(const float *__restrict__ sums,
+                                                         float *__restrict__ grads, int accumulate)
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= LAYER_P) return;
+    const float *slices = sums + (size_t)blockIdx.y * WR_SLICES * LAYER_P;
+    float *grad = grads + blockIdx.y * LAYER_P;
     float s = 0.f;
 #pragma unroll 8
     for (int z = 0; z < WR_SLICES; ++z) s += slices[(size_t)z * LAYER_P + i];
@@ -1225,19 +1254,6 @@ __global__ __launch_bounds__(256) void k_cl_rstep_step(PtrList before, PtrList l
     step_vjp_scatter(m, l, static_cast<double *>(lam_out.p[f]), x, y, nx, ny, kp);
 }
 
-// FP32 parameters -> bf16 [t][o][i] (forward) and [t][i][o] (input gradient)
-__global__ __launch_bounds__(256) void k_cl_cast(const float *__restrict__ params, u16 *__restrict__ wf,
-                                                 u16 *__restrict__ wt)
-{
-    const int e = blockIdx.x * 256 + threadIdx.x;
-    if (e >= 3 * LAYER_W) return;
-    const int layer = e / LAYER_W, r = e % LAYER_W;
-    const int t = r / (CH * CH), o = (r / CH) % CH, i = r % CH;
-    const u16 h = bf16_bits(params[(size_t)layer * LAYER_P + r]);
-    wf[e] = h;
-    wt[(size_t)layer * LAYER_W + ((size_t)t * CH + i) * CH + o] = h;
-}
-
 __global__ __launch_bounds__(256) void k_cl_adam(float *__restrict__ p, const float *__restrict__ g,
                                                  float *__restrict__ m, float *__restrict__ v, float lr,
                                                  float b1, float b2, float eps, float c1, float c2)
@@ -1306,7 +1322,6 @@ struct plbm_closure {
     KParams kp;                                // the coarse lattice's rule
     int nwblk = 0, nlblk = 0;
     int frames_in_fwd = 0;
-    const float *cast_from = nullptr;
 };
 
 namespace {
@@ -1353,14 +1368,6 @@ int make_list(PtrList &l, const P *host, int n)
     return PLBM_OK;
 }
 
-void reduce_wgrad(plbm_closure *c, int nwblk, float *grad, hipStream_t st, int accumulate = 0)
-{
-    hipLaunchKernelGGL(k_cl_wgrad_slices, dim3((LAYER_P + 255) / 256, WR_SLICES), dim3(256), 0, st, c->part,
-                       nwblk, c->slices);
-    hipLaunchKernelGGL(k_cl_wgrad_reduce, dim3((LAYER_P + 255) / 256), dim3(256), 0, st, c->slices, grad,
-                       accumulate);
-}
-
 // From dy3 (the gradient of the network output): the weight gradients of the
 // three layers (written, or added to `grads` when accumulate), dz2 and dz1,
 // and with input_grad the gradient of the network input into c->dx.
@@ -1371,30 +1378,23 @@ void layers_backward(plbm_closure *c, int frames, float *grads, int accumulate, 
     // the input-gradient pass (with its ReLU mask read) is fastest at half the rows
     const int brows = std::max(1, crows / PLBM_CONV_BROWS_DIV);
     const dim3 gb((c->nx / 32 + 3) / 4, (c->ny + brows - 1) / brows, frames);
-    const dim3 gw((c->nx / WG_SEG) * ((c->ny + WG_ROWS - 1) / WG_ROWS), 1, frames);
+    const dim3 gw((c->nx / WG_SEG) * ((c->ny + WG_ROWS - 1) / WG_ROWS), 3, frames);
     const int nwblk = (int)(gw.x * gw.z);
-    // layer 3: dW3 from a2 and dy3; dz2 = (W3^T dy3) * (a2 > 0)
-    hipLaunchKernelGGL(k_cl_wgrad, gw, dim3(256), 0, st, c->a2, c->dy3, c->nx, c->ny, c->part);
-    reduce_wgrad(c, nwblk, grads + 2 * LAYER_P, st, accumulate);
+    // dz2 = (W3^T dy3) * (a2 > 0), dz1 = (W2^T dz2) * (a1 > 0)
     hipLaunchKernelGGL(k_cl_conv<2>, gb, dim3(256), 0, st, c->dy3, c->wt + 2 * LAYER_W, nullptr, c->a2,
                        c->dz2, c->nx, c->ny, brows);
-    // layer 2
-    hipLaunchKernelGGL(k_cl_wgrad, gw, dim3(256), 0, st, c->a1, c->dz2, c->nx, c->ny, c->part);
-    reduce_wgrad(c, nwblk, grads + LAYER_P, st, accumulate);
     hipLaunchKernelGGL(k_cl_conv<2>, gb, dim3(256), 0, st, c->dz2, c->wt + LAYER_W, nullptr, c->a1, c->dz1,
                        c->nx, c->ny, brows);
-    // layer 1
-    hipLaunchKernelGGL(k_cl_wgrad, gw, dim3(256), 0, st, c->x0, c->dz1, c->nx, c->ny, c->part);
-    reduce_wgrad(c, nwblk, grads, st, accumulate);
     if (input_grad)
         hipLaunchKernelGGL(k_cl_conv<3>, gb, dim3(256), 0, st, c->dz1, c->wt, nullptr, nullptr, c->dx, c->nx,
                            c->ny, brows);
-}
-
-int cast_weights(plbm_closure *c, const float *params, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_cl_cast, dim3((3 * LAYER_W + 255) / 256), dim3(256), 0, st, params, c->wf, c->wt);
-    return ck(hipGetLastError());
+    // dW of layer l from its input and the gradient of its output
+    const WgLayers L = {{c->x0, c->a1, c->a2}, {c->dz1, c->dz2, c->dy3}};
+    hipLaunchKernelGGL(k_cl_wgrad, gw, dim3(256), 0, st, L, c->nx, c->ny, c->part);
+    hipLaunchKernelGGL(k_cl_wgrad_slices, dim3((LAYER_P + 255) / 256, WR_SLICES, 3), dim3(256), 0, st, c->part,
+                       nwblk, c->slices);
+    hipLaunchKernelGGL(k_cl_wgrad_reduce, dim3((LAYER_P + 255) / 256, 3), dim3(256), 0, st, c->slices, grads,
+                       accumulate);
 }
 
 } // namespace
@@ -1453,9 +1453,9 @@ extern "C" int plbm_closure_create(const plbm_desc *coarse, int frames, plbm_clo
               hipMalloc((void **)&c->dy3, nodes * CH * sizeof(u16)) == hipSuccess &&
               hipMalloc((void **)&c->dz2, nodes * CH * sizeof(u16)) == hipSuccess &&
               hipMalloc((void **)&c->dz1, nodes * CH * sizeof(u16)) == hipSuccess &&
-              hipMalloc((void **)&c->part, (size_t)c->nwblk * (LAYER_W + CH) * sizeof(float)) == hipSuccess &&
+              hipMalloc((void **)&c->part, (size_t)3 * c->nwblk * LAYER_P * sizeof(float)) == hipSuccess &&
               hipMalloc((void **)&c->lpart, (size_t)c->nlblk * sizeof(float)) == hipSuccess &&
-              hipMalloc((void **)&c->slices, (size_t)WR_SLICES * LAYER_P * sizeof(float)) == hipSuccess &&
+              hipMalloc((void **)&c->slices, (size_t)3 * WR_SLICES * LAYER_P * sizeof(float)) == hipSuccess &&
               hipMalloc((void **)&c->corr, nodes * CREAL * sizeof(float)) == hipSuccess &&
               hipMalloc((void **)&c->mres, nodes * 4 * sizeof(float)) == hipSuccess &&
               hipMalloc((void **)&c->adj4, nodes * 4 * sizeof(double)) == hipSuccess &&
@@ -1516,17 +1516,15 @@ extern "C" int plbm_closure_forward(plbm_closure *c, const float *params, const 
     int rc = make_list(pl, post, frames);
     if (rc != PLBM_OK) return rc;
     (void)hipGetLastError();
-    rc = cast_weights(c, params, st);
-    if (rc != PLBM_OK) return rc;
-    const dim3 gn((c->nx + 255) / 256, c->ny, frames);
+    const dim3 gn((c->nx + 255) / 256, c->ny, frames + 1);     // the last slice casts the parameters
     const int crows = conv_rows(c->nx, c->ny, frames);
     const dim3 gc((c->nx / 32 + 3) / 4, (c->ny + crows - 1) / crows, frames);
     if (c->f64)
-        hipLaunchKernelGGL(k_cl_input<double>, gn, dim3(256), 0, st, pl, c->nx, c->ny, c->nm, noise, noise_amp,
-                           c->x0);
+        hipLaunchKernelGGL(k_cl_input<double>, gn, dim3(256), 0, st, pl, c->nx, c->ny, frames, c->nm, noise,
+                           noise_amp, c->x0, params, c->wf, c->wt);
     else
-        hipLaunchKernelGGL(k_cl_input<float>, gn, dim3(256), 0, st, pl, c->nx, c->ny, c->nm, noise, noise_amp,
-                           c->x0);
+        hipLaunchKernelGGL(k_cl_input<float>, gn, dim3(256), 0, st, pl, c->nx, c->ny, frames, c->nm, noise,
+                           noise_amp, c->x0, params, c->wf, c->wt);
     // bias of layer l: params + l * LAYER_P + LAYER_W
     hipLaunchKernelGGL(k_cl_conv<0>, gc, dim3(256), 0, st, c->x0, c->wf, params + LAYER_W, nullptr, c->a1,
                        c->nx, c->ny, crows);
