@@ -37,6 +37,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "plbm_device.h"
@@ -63,9 +64,6 @@ constexpr int NPARAM = 3 * LAYER_P;
 #endif
 #ifndef PLBM_CONV_WAVES
 #define PLBM_CONV_WAVES 2          // waves per SIMD the convolution's registers must allow
-#endif
-#ifndef PLBM_CONV_BROWS_DIV
-#define PLBM_CONV_BROWS_DIV 2      // input-gradient blocks take rows / this
 #endif
 constexpr int WG_ROWS = PLBM_WG_ROWS;          // rows per weight-gradient block
 constexpr int WG_SEG = 64;                     // nodes per weight-gradient row segment
@@ -249,11 +247,11 @@ __global__ __launch_bounds__(256) void k_cl_input(PtrList post, int nx, int ny, 
 // A block covers 4 waves x 32 nodes of `rows` consecutive rows; each lane
 // keeps its 18 weight operands in registers across the rows (the weights
 // are the same for every node, and reloading them per row made the L1 read
-// traffic several times the activations').  The A operands of the three
-// input rows an output row reads (3 columns x 2 channel halves each) form a
-// ring in registers: the next output row reuses two of them and loads one
-// new input row, issued while the current row's MFMAs run (three times
-// fewer operand loads; the forward pass is 20 % faster).  conv_rows() picks
+// traffic several times the activations').  The A operands of the input rows
+// an output row reads (3 columns x 2 channel halves each) form a ring in
+// registers: the next output row reuses two of them, and one new input row
+// is loaded per output row (three times fewer operand loads; the forward
+// pass is 20 % faster), two output rows before it is needed.  conv_rows() picks
 // the row count that leaves about 256 blocks, at most 16 rows each
 // (measured best at 8 frames of 256^2; a single frame keeps one row per
 // block).
@@ -263,32 +261,45 @@ inline int conv_rows(int nx, int ny, int frames)
     return (int)std::max<long long>(1, std::min<long long>(PLBM_CONV_MAX_ROWS, blocks1 / PLBM_CONV_BLOCKS));
 }
 
+constexpr int RING = 4;                // input rows a convolution wave holds
+
 // A operands of one input row: columns x - 1, x, x + 1 (periodic) of the
 // lane's node, channel halves 0..15 and 16..31
 __device__ __forceinline__ void cl_load_row(const u16 *__restrict__ in, size_t fbase, int nx, int ny,
-                                            int ys, const int (&xs)[3], int kh, bf16x8 (&a)[3][2])
+                                            int ys, const unsigned (&xs)[3], bf16x8 (&a)[3][2])
 {
     ys += (ys < 0) ? ny : 0;
     ys -= (ys >= ny) ? ny : 0;
-    const u16 *row = in + (fbase + (size_t)ys * nx) * CH + 8 * kh;
+    const u16 *row = in + (fbase + (size_t)ys * nx) * CH;
 #pragma unroll
     for (int d = 0; d < 3; ++d)
 #pragma unroll
         for (int h = 0; h < 2; ++h)
-            a[d][h] = *reinterpret_cast<const bf16x8 *>(row + (size_t)xs[d] * CH + h * 16);
+            a[d][h] = *reinterpret_cast<const bf16x8 *>(row + xs[d] + h * 16);
 }
 
 // Output row y with input rows y - 1, y, y + 1 in ring slots P, P + 1, P + 2
-// (mod 3).  The taps reading row y - 1 go first; when `more`, input row
-// y + 2 is then loaded into slot P while the other six MFMA pairs run.
+// (mod RING).  The taps reading row y - 1 go first; input row y - 1 + RING is
+// then loaded into slot P, for output row y + RING - 2 (rows from yend + 1 on
+// feed no output: yend stands in).  Three rows in the ring, each loaded one
+// output row ahead and behind a test, left every row waiting for memory: 17.7
+// us for a layer of 8 frames of 256^2 against 15.7, where reading and writing
+// its 67 MB takes 10.7 at the rate of a copy.
 template <int MODE, int P>
-__device__ __forceinline__ void cl_conv_row(bf16x8 (&A)[3][3][2], const bf16x8 (&bw)[TAPS][2],
+__device__ __forceinline__ void cl_conv_row(bf16x8 (&A)[RING][3][2], const bf16x8 (&bw)[TAPS][2],
                                             const u16 *__restrict__ in, const u16 *__restrict__ act,
-                                            void *__restrict__ out, size_t fbase, int nx, int ny, int y,
-                                            int x0, const int (&xs)[3], int l, float bj, bool more)
+                                            void *__restrict__ out, size_t fbase, int nx, int ny, int y, int yend,
+                                            int x0, const unsigned (&xs)[3], int l, float bj)
 {
-    const int kh = l >> 5, j = l & 31;
+    // one base per row (the same for the wave), the lane's offset and constants
+    const size_t at = (fbase + (size_t)y * nx + x0) * CH;
+    const unsigned lane = 4 * (l >> 5) * CH + (l & 31);
     f32x16 acc = {};
+    u16 av[16];
+    if (MODE == 2) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) av[r] = (act + at)[lane + (8 * (r / 4) + (r & 3)) * CH];
+    }
 #pragma unroll
     for (int r = 0; r < 3; ++r) {                 // input row y - 1 + r, ring slot P + r
 #pragma unroll
@@ -298,25 +309,28 @@ __device__ __forceinline__ void cl_conv_row(bf16x8 (&A)[3][3][2], const bf16x8 (
             const int t = (MODE >= 2) ? (2 - r) * 3 + (2 - d) : r * 3 + d;
 #pragma unroll
             for (int h = 0; h < 2; ++h)
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[(P + r) % 3][d][h], bw[t][h], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[(P + r) % RING][d][h], bw[t][h], acc, 0, 0, 0);
         }
-        if (r == 0 && more) cl_load_row(in, fbase, nx, ny, y + 2, xs, kh, A[P]);
+        if (r == 0) {
+            cl_load_row(in, fbase, nx, ny, min(y - 1 + RING, yend), xs, A[P]);
+            __builtin_amdgcn_sched_barrier(0);    // here, not next to their use
+        }
     }
+    __builtin_amdgcn_sched_barrier(0);
     // D[i][j]: i = node 8*(r/4) + 4*(l/32) + r%4, j = channel l%32
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-        const int i = 8 * (r / 4) + 4 * (l >> 5) + (r & 3);
-        const size_t node = fbase + (size_t)y * nx + x0 + i;
-        float v = acc[r] + bj;
+        const unsigned i = lane + (8 * (r / 4) + (r & 3)) * CH;
+        const float v = acc[r] + bj;
         if (MODE == 0) {
-            reinterpret_cast<u16 *>(out)[node * CH + j] = bf16_bits(fmaxf(v, 0.f));
+            (reinterpret_cast<u16 *>(out) + at)[i] = bf16_bits(fmaxf(v, 0.f));
         } else if (MODE == 1 || MODE == 3) {
-            reinterpret_cast<float *>(out)[node * CH + j] = v;
+            (reinterpret_cast<float *>(out) + at)[i] = v;
         } else {
-            const float a = bf16_val(act[node * CH + j]);
-            reinterpret_cast<u16 *>(out)[node * CH + j] = bf16_bits(a > 0.f ? v : 0.f);
+            (reinterpret_cast<u16 *>(out) + at)[i] = bf16_bits(bf16_val(av[r]) > 0.f ? v : 0.f);
         }
     }
+    __builtin_amdgcn_sched_barrier(0);
 }
 
 template <int MODE>
@@ -326,7 +340,7 @@ __global__ __launch_bounds__(256, PLBM_CONV_WAVES) void k_cl_conv(const u16 *__r
                                                  int nx, int ny, int rows)
 {
     const int f = blockIdx.z;
-    const int wv = threadIdx.x >> 6, l = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
     const int x0 = (blockIdx.x * 4 + wv) * 32;       // first node of this wave
     const int ybeg = blockIdx.y * rows;
     if (x0 >= nx || ybeg >= ny) return;
@@ -341,26 +355,33 @@ __global__ __launch_bounds__(256, PLBM_CONV_WAVES) void k_cl_conv(const u16 *__r
         for (int h = 0; h < 2; ++h)
             bw[t][h] = *reinterpret_cast<const bf16x8 *>(wb + ((size_t)t * CH + (l & 31)) * CH + h * 16 + 8 * kh);
     const float bj = (MODE >= 2) ? 0.f : bias[l & 31];
-    int xs[3];
+    unsigned xs[3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
         int x = x0 + row_i + d - 1;
         x += (x < 0) ? nx : 0;
         x -= (x >= nx) ? nx : 0;
-        xs[d] = x;
+        xs[d] = (unsigned)x * CH + 8 * kh;
     }
-    bf16x8 A[3][3][2];
-    cl_load_row(in, fbase, nx, ny, ybeg - 1, xs, kh, A[0]);
-    cl_load_row(in, fbase, nx, ny, ybeg, xs, kh, A[1]);
-    cl_load_row(in, fbase, nx, ny, ybeg + 1, xs, kh, A[2]);
+    bf16x8 A[RING][3][2];
+#pragma unroll
+    for (int i = 0; i < RING; ++i) cl_load_row(in, fbase, nx, ny, min(ybeg - 1 + i, yend), xs, A[i]);
+    auto row = [&](auto slot, int y) {
+        cl_conv_row<MODE, decltype(slot)::value>(A, bw, in, act, out, fbase, nx, ny, y, yend, x0, xs, l, bj);
+    };
+    int y = ybeg;
+    // no branch between these rows: the compiler would move each row's loads
+    // behind it, next to their use
 #pragma unroll 1
-    for (int y = ybeg; y < yend; y += 3) {
-        cl_conv_row<MODE, 0>(A, bw, in, act, out, fbase, nx, ny, y, x0, xs, l, bj, y + 1 < yend);
-        if (y + 1 >= yend) break;
-        cl_conv_row<MODE, 1>(A, bw, in, act, out, fbase, nx, ny, y + 1, x0, xs, l, bj, y + 2 < yend);
-        if (y + 2 >= yend) break;
-        cl_conv_row<MODE, 2>(A, bw, in, act, out, fbase, nx, ny, y + 2, x0, xs, l, bj, y + 3 < yend);
+    for (; y + RING <= yend; y += RING) {
+        row(std::integral_constant<int, 0>{}, y);
+        row(std::integral_constant<int, 1>{}, y + 1);
+        row(std::integral_constant<int, 2>{}, y + 2);
+        row(std::integral_constant<int, 3>{}, y + 3);
     }
+    if (y < yend) row(std::integral_constant<int, 0>{}, y);
+    if (y + 1 < yend) row(std::integral_constant<int, 1>{}, y + 1);
+    if (y + 2 < yend) row(std::integral_constant<int, 2>{}, y + 2);
 }
 
 // ---------------------------------------------------------------------------
@@ -1380,19 +1401,17 @@ void layers_backward(plbm_closure *c, int frames, float *grads, int accumulate, 
                      bool input_grad = false)
 {
     const int crows = conv_rows(c->nx, c->ny, frames);
-    // the input-gradient pass (with its ReLU mask read) is fastest at half the rows
-    const int brows = std::max(1, crows / PLBM_CONV_BROWS_DIV);
-    const dim3 gb((c->nx / 32 + 3) / 4, (c->ny + brows - 1) / brows, frames);
+    const dim3 gc((c->nx / 32 + 3) / 4, (c->ny + crows - 1) / crows, frames);
     const dim3 gw((c->nx / WG_SEG) * ((c->ny + WG_ROWS - 1) / WG_ROWS), 3, frames);
     const int nwblk = (int)(gw.x * gw.z);
     // dz2 = (W3^T dy3) * (a2 > 0), dz1 = (W2^T dz2) * (a1 > 0)
-    hipLaunchKernelGGL(k_cl_conv<2>, gb, dim3(256), 0, st, c->dy3, c->wt + 2 * LAYER_W, nullptr, c->a2,
-                       c->dz2, c->nx, c->ny, brows);
-    hipLaunchKernelGGL(k_cl_conv<2>, gb, dim3(256), 0, st, c->dz2, c->wt + LAYER_W, nullptr, c->a1, c->dz1,
-                       c->nx, c->ny, brows);
+    hipLaunchKernelGGL(k_cl_conv<2>, gc, dim3(256), 0, st, c->dy3, c->wt + 2 * LAYER_W, nullptr, c->a2,
+                       c->dz2, c->nx, c->ny, crows);
+    hipLaunchKernelGGL(k_cl_conv<2>, gc, dim3(256), 0, st, c->dz2, c->wt + LAYER_W, nullptr, c->a1, c->dz1,
+                       c->nx, c->ny, crows);
     if (input_grad)
-        hipLaunchKernelGGL(k_cl_conv<3>, gb, dim3(256), 0, st, c->dz1, c->wt, nullptr, nullptr, c->dx, c->nx,
-                           c->ny, brows);
+        hipLaunchKernelGGL(k_cl_conv<3>, gc, dim3(256), 0, st, c->dz1, c->wt, nullptr, nullptr, c->dx, c->nx,
+                           c->ny, crows);
     // dW of layer l from its input and the gradient of its output
     const WgLayers L = {{c->x0, c->a1, c->a2}, {c->dz1, c->dz2, c->dy3}};
     hipLaunchKernelGGL(k_cl_wgrad, gw, dim3(256), 0, st, L, c->nx, c->ny, c->part);
