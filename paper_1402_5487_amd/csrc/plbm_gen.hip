@@ -237,7 +237,9 @@ struct GenSet {
     static constexpr int Q1 = sizeof...(Vs);
     static constexpr int V[Q1] = {Vs...};
     static constexpr bool KEYED = false;
-    static constexpr int SPAN = SPAN_, WGS = 4, ROUNDS_H = 16;
+    static constexpr int SPAN = SPAN_, WGS = 4;
+    template <int D>
+    static constexpr int rounds_h() { return 16; }
     static __device__ __forceinline__ C dec(T h, int, const P &) { return h; }
     static __device__ __forceinline__ T enc(C f, int, const P &, uint32_t) { return f; }
     static __device__ __forceinline__ uint32_t key(uint32_t node) { return node; }

@@ -93,15 +93,15 @@ __global__ __launch_bounds__(TX, PLBM_MIN_WAVES) void k_step2d_fields(const type
         step_tile<S, NV, false, NTS, true>(src, dst, p, tile, acc, fo);
 }
 
-// Two steps in one launch (plbm_sweep.h).
-template <class S, bool NTS, bool FIELDS>
-__global__ __launch_bounds__(sweep_threads<Thermal25<S>>(), (sweep_per_cu<Thermal25<S>, PAIR>())) void
-k_step2d_pair(const typename S::T *__restrict__ src, typename S::T *__restrict__ dst, KParams p, SweepGrid g,
+// Two or three steps in one launch (plbm_sweep.h).
+template <class S, int D, bool NTS, bool FIELDS>
+__global__ __launch_bounds__(sweep_threads<Thermal25<S>>(), (sweep_per_cu<Thermal25<S>, D>())) void
+k_step2d_sweep(const typename S::T *__restrict__ src, typename S::T *__restrict__ dst, KParams p, SweepGrid g,
               FieldsOut fo)
 {
     extern __shared__ __align__(16) unsigned char sweep_lds[];
-    sweep<Thermal25<S>, PAIR, NTS, FIELDS>(src, dst, p, g, xcd_tile(blockIdx.x, gridDim.x),
-                                           reinterpret_cast<typename S::T *>(sweep_lds), fo);
+    sweep<Thermal25<S>, D, NTS, FIELDS>(src, dst, p, g, xcd_tile(blockIdx.x, gridDim.x),
+                                        reinterpret_cast<typename S::T *>(sweep_lds), fo);
 }
 
 // ---------------------------------------------------------------------------
@@ -448,17 +448,58 @@ int launch_step(const KParams &p, const plbm_desc *d, const void *src, void *dst
     return launch_status();
 }
 
-// Two fused steps src -> dst.
-template <class S, bool FIELDS>
-int launch_pair(const KParams &p, const void *src, void *dst, hipStream_t st, FieldsOut fo = FieldsOut{})
+// D fused steps src -> dst.
+template <class S, int D, bool FIELDS>
+int launch_sweep(const KParams &p, const void *src, void *dst, hipStream_t st, FieldsOut fo = FieldsOut{})
 {
     using T = typename S::T;
-    const SweepGrid g = sweep_grid<Thermal25<S>, PAIR>(p.nx, p.ny);
+    using M = Thermal25<S>;
+    const SweepGrid g = sweep_grid<M, D>(p.nx, p.ny);
     clear_launch_error();
-    auto *kernel = rows_on_lines(p.nx, sizeof(T)) ? k_step2d_pair<S, true, FIELDS> : k_step2d_pair<S, false, FIELDS>;
-    hipLaunchKernelGGL(kernel, dim3(g.wgs), dim3(sweep_threads<Thermal25<S>>()),
-                       (sweep_lds_bytes<Thermal25<S>, PAIR>()), st, (const T *)src, (T *)dst, p, g, fo);
+    auto *kernel = rows_on_lines(p.nx, sizeof(T)) ? k_step2d_sweep<S, D, true, FIELDS>
+                                                  : k_step2d_sweep<S, D, false, FIELDS>;
+    hipLaunchKernelGGL(kernel, dim3(g.wgs), dim3(sweep_threads<M>()), (sweep_lds_bytes<M, D>()), st,
+                       (const T *)src, (T *)dst, p, g, fo);
     return launch_status();
+}
+
+template <class S>
+int run_steps(const KParams &p, const plbm_desc *d, void *fa, void *fb, int nsteps, double *sums, hipStream_t st,
+              bool noalloc);
+
+// Of n steps in launches of three, those that pairs take instead, an even number
+// of pairs (see fused_launches): a step or two left over cost more (FP32 4096^2:
+// three 675 us, a pair 624, one 600).
+inline int pairs_beside_threes(int n)
+{
+    const int pairs = n % 3 == 0 ? 0 : n % 3 == 1 ? 2 : 4;
+    return std::min(pairs, fused_launches<2>(n));
+}
+
+// Launches of D, fa -> fb -> ..
+template <class S, int D>
+int run_sweeps(const KParams &p, void *fa, void *fb, int launches, hipStream_t st)
+{
+    int rc = PLBM_OK;
+    for (int k = 0; k < launches && rc == PLBM_OK; ++k)
+        rc = launch_sweep<S, D, false>(p, (k & 1) ? fb : fa, (k & 1) ? fa : fb, st);
+    return rc;
+}
+
+// The first D of n steps, with the fields of the state they read; an even depth
+// takes a second launch for the state to be where so many single steps leave it.
+template <class S, int D>
+int run_sweeps_fields(const KParams &p, const plbm_desc *d, void *fa, void *fb, int n, FieldsOut fo, hipStream_t st)
+{
+    int rc = launch_sweep<S, D, true>(p, fa, fb, st, fo);
+    if (D % 2 == 0) {
+        if (rc == PLBM_OK) rc = launch_sweep<S, D, false>(p, fb, fa, st);
+        n -= D;
+    } else {
+        std::swap(fa, fb);
+    }
+    n -= D;
+    return rc == PLBM_OK && n > 0 ? run_steps<S>(p, d, fa, fb, n, nullptr, st, false) : rc;
 }
 
 // Which lattices take tiles of fused steps (plbm_tile.h) and which shape: the
@@ -491,22 +532,34 @@ void tile_steps(const KParams &p, void *fa, void *fb, int &n, hipStream_t st)
     run.template take<16, 16, 3>(n);
 }
 
-// Which larger lattices take fused pairs of steps (plbm_sweep.h).  Measured per
-// step (us, single -> pair): FP64 4096^2 1050 -> 607, FP32 519 -> 312.  The 16-bit
-// forms are bound by vector work, of which short chunks add up to as much
-// again: FP16 1024^2 21.9 -> 24, 1501 x 1100 40.4 -> 29.5, 4096^2 278 -> 203.  Rows
-// that leave half the lanes of their strips idle (a quarter: 16-bit) stay with
-// single steps.
+// How many steps a strip of a larger lattice takes (plbm_sweep.h); 1: single
+// steps.  Measured (us a step, single / two / three): FP64 4096^2 1050 / 622 / -, FP32
+// 519 / 324 / 225, FP32 1501 x 1100 65 / 43 / 33.  The 16-bit forms are bound by
+// vector work, of which short chunks add up to as much again: FP16 1024^2 21.9 /
+// 24, 1501 x 1100 40.4 / 29.5, 4096^2 278 / 212.  Rows that leave half the lanes
+// of their strips idle (a quarter: 16-bit) stay with single steps.
+// FP32 takes three if the strips use 3/4 of their lanes (257 x 4100 - / 26 / 32) and
+// its workgroups, one a CU, come to fewer rows: a row of three steps takes 2.06
+// us, a row of each of two workgroups of pairs 3.1 (70000 x 16, two rounds of 313:
+// 46 / 26 / 36).
 template <class S>
-bool use_pairs(const KParams &p, const plbm_desc *d)
+int sweep_depth(const KParams &p, const plbm_desc *d)
 {
     constexpr bool narrow = sizeof(typename S::T) == 2;
     using M = Thermal25<S>;
-    if (d->dim != 2 || !sweep_fits<M>(p.nx) || !paper_set(p)) return false;
-    if (narrow && (long long)p.nx * p.ny < 1500000) return false;
-    const SweepGrid g = sweep_grid<M, PAIR>(p.nx, p.ny);
+    if (d->dim != 2 || !sweep_fits<M>(p.nx) || !paper_set(p)) return 1;
+    if (narrow && (long long)p.nx * p.ny < 1500000) return 1;
+    const SweepGrid g = sweep_grid<M, 2>(p.nx, p.ny);
     const long long used = (long long)p.nx * g.per, lanes = (long long)g.strips * sweep_threads<M>();
-    return narrow ? 4 * used >= 3 * lanes : 2 * used >= lanes;
+    if (narrow ? 4 * used < 3 * lanes : 2 * used < lanes) return 1;
+    if constexpr (sizeof(typename S::T) == 4) {
+        const SweepGrid g3 = sweep_grid<M, 3>(p.nx, p.ny);
+        const long long lanes3 = (long long)g3.strips * sweep_threads<M>();
+        if (4 * (long long)p.nx * g3.per >= 3 * lanes3 &&
+            2.06 / 3 * sweep_rounds<M, 3>(g3) <= 3.1 / 2 * sweep_rounds<M, 2>(g))
+            return 3;
+    }
+    return 2;
 }
 
 // noalloc: sums wait for the library's scratch rather than allocate.
@@ -523,13 +576,20 @@ int run_steps(const KParams &p, const plbm_desc *d, void *fa, void *fb, int nste
         const int rc = launch_status();
         if (rc != PLBM_OK) return rc;
         s0 = nsteps - (sums ? 1 : 0) - left;
-    } else if (use_pairs<S>(p, d)) {
-        const int pairs = fused_launches<PAIR>(nsteps - (sums ? 1 : 0));
-        for (int k = 0; k < pairs; ++k) {
-            const int rc = launch_pair<S, false>(p, (k & 1) ? fb : fa, (k & 1) ? fa : fb, st);
-            if (rc != PLBM_OK) return rc;
+    } else if (const int depth = sweep_depth<S>(p, d); depth > 1) {
+        const int n = nsteps - (sums ? 1 : 0);
+        const int pairs = depth == 3 ? pairs_beside_threes(n) : fused_launches<2>(n);
+        if constexpr (sizeof(typename S::T) == 4) {
+            if (depth == 3) {
+                const int threes = (n - 2 * pairs) / 3;
+                const int rc = run_sweeps<S, 3>(p, fa, fb, threes, st);
+                if (rc != PLBM_OK) return rc;
+                s0 = 3 * threes;
+            }
         }
-        s0 = 2 * pairs;
+        const int rc = run_sweeps<S, 2>(p, (s0 & 1) ? fb : fa, (s0 & 1) ? fa : fb, pairs, st);
+        if (rc != PLBM_OK) return rc;
+        s0 += 2 * pairs;
     }
     if constexpr (sizeof(typename S::T) >= 4) {
         if (d->dim == 1) {
@@ -560,20 +620,17 @@ int run_steps(const KParams &p, const plbm_desc *d, void *fa, void *fb, int nste
 }
 
 // 2D steps of which the first also writes the fields of the state it reads: a
-// fused pair where those are taken, else a step of its own.
+// fused launch where those are taken, else a step of its own.
 template <class S>
 int run_steps_fields(const KParams &p, const plbm_desc *d, void *fa, void *fb, int nsteps, FieldsOut fo,
                      hipStream_t st)
 {
     using T = typename S::T;
-    const int pairs = !use_tiles<S>(p) && use_pairs<S>(p, d) ? fused_launches<PAIR>(nsteps) : 0;
-    if (pairs > 0) {
-        int rc = launch_pair<S, true>(p, fa, fb, st, fo);
-        // the pair that follows leaves the state in fa again
-        if (rc == PLBM_OK) rc = launch_pair<S, false>(p, fb, fa, st);
-        return rc == PLBM_OK && nsteps > 2 * PAIR ? run_steps<S>(p, d, fa, fb, nsteps - 2 * PAIR, nullptr, st, false)
-                                                  : rc;
-    }
+    const int depth = use_tiles<S>(p) ? 1 : sweep_depth<S>(p, d);
+    if constexpr (sizeof(T) == 4)
+        if (depth == 3 && nsteps - 2 * pairs_beside_threes(nsteps) >= 3)
+            return run_sweeps_fields<S, 3>(p, d, fa, fb, nsteps, fo, st);
+    if (depth > 1 && fused_launches<2>(nsteps) > 0) return run_sweeps_fields<S, 2>(p, d, fa, fb, nsteps, fo, st);
     clear_launch_error();
     const size_t lds = sizeof(T) == 2 ? (d->rounding == PLBM_ROUND_STOCHASTIC ? PLBM_LDS_CAP_16SR : PLBM_LDS_CAP_16)
                                       : PLBM_LDS_CAP_WIDE;

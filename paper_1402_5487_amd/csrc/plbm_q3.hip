@@ -196,7 +196,9 @@ struct Iso9 {
     static constexpr int Q1 = Q3;
     static constexpr int V[Q3] = {0, 1, -1};
     static constexpr bool KEYED = false;
-    static constexpr int SPAN = 256, WGS = 4, ROUNDS_H = 24;
+    static constexpr int SPAN = 256, WGS = 4;
+    template <int D>
+    static constexpr int rounds_h() { return 24; }
     static __device__ __forceinline__ C dec(T h, int, const P &) { return h; }
     static __device__ __forceinline__ T enc(C f, int, const P &, uint32_t) { return f; }
     static __device__ __forceinline__ uint32_t key(uint32_t node) { return node; }

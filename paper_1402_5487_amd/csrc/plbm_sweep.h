@@ -104,7 +104,7 @@ struct SweepGrid {
 // 64 B for the 16-bit forms, whose 128 B would cost a quarter of the lanes):
 // stores that end inside a line left the D2Q25 pair at 4096^2 at 489 us a step
 // in FP32 against 373.  Chunks: as many rounds of
-// resident workgroups as leave them about M::ROUNDS_H rows.  Long chunks
+// resident workgroups as leave them about M::rounds_h<D>() rows.  Long chunks
 // spread the accesses over so much memory that the D2Q25 FP32 pair at 4096^2
 // took 373 us a step with 157 rows, 318 with 64 and 313 with 16; a last round
 // of a few workgroups costs as much as a full one (D2Q9 FP32 2048^2, 1.1
@@ -139,8 +139,16 @@ inline SweepGrid sweep_grid(int nx, int ny)
         const int chunks = std::max(1, rounds * slots * g.per / g.strips);
         return (ny + chunks - 1) / chunks;
     };
-    g.rows(ny, chunk_rows(std::max(1, chunk_rows(1) / M::ROUNDS_H)));
+    g.rows(ny, chunk_rows(std::max(1, chunk_rows(1) / M::template rounds_h<D>())));
     return g;
+}
+
+// Rows that the rounds of resident workgroups compute one after another.
+template <class M, int D>
+inline long long sweep_rounds(const SweepGrid &g)
+{
+    constexpr int slots = SWEEP_CUS * sweep_per_cu<M, D>();
+    return (long long)((g.wgs + slots - 1) / slots) * (g.h + 2 * Lines<M>::R * (D - 1));
 }
 
 // Barrier for LDS traffic only: global loads and stores stay in flight.
@@ -378,7 +386,10 @@ __device__ __forceinline__ void sweep(const typename M::T *__restrict__ src, typ
 }
 
 // The thermal model of plbm_device.h with the set {0, +-1, +-3} in the paper's
-// order (paper_set: whether p's is that one); it takes pairs of steps.
+// order (paper_set: whether p's is that one).  It takes two steps a strip; FP32
+// also three, whose 160 KB of LDS leave one workgroup a CU.  FP64 has no room for
+// a third step; the 16-bit forms have and gain 6 % (FP16 4096^2 200 us a step against
+// 212), less than the single steps left over cost calls of 4 or 8 steps.
 template <class S>
 struct Thermal25 {
     using T = typename S::T;
@@ -388,8 +399,13 @@ struct Thermal25 {
     static constexpr int V[Q] = {0, 1, -1, 3, -3};
     static constexpr bool KEYED = S::keyed;
     static constexpr int SPAN = 256, WGS = 4;
-    // 16-bit storage spends vector work, not bandwidth, on rows computed twice
-    static constexpr int ROUNDS_H = sizeof(T) == 2 ? 32 : 16;
+    // Tall chunks, as each computes 3 rows per step but the first twice at
+    // either end (FP32 4096^2 in threes, us a step: 335 with 16 rows, 254 with
+    // 53, 225 with one round of 316; FP64 2048^2 175 with 16, 160 with 93).  Two
+    // FP32 workgroups fit a CU in pairs, and lose more to the spread of
+    // their accesses (see sweep_grid).
+    template <int D>
+    static constexpr int rounds_h() { return sizeof(T) == 2 ? 32 : sizeof(T) == 4 && D == 2 ? 16 : 160; }
     static __device__ __forceinline__ C dec(T h, int k, const P &p) { return S::dec(h, k, p); }
     static __device__ __forceinline__ T enc(C f, int k, const P &p, uint32_t key)
     {
@@ -409,7 +425,6 @@ struct Thermal25 {
     static __device__ __forceinline__ void collide(C (&f)[NQ], const P &p) { collide2d<S>(f, p); }
     static __device__ __forceinline__ void collide(C (&f)[NQ], const P &p, C (&mom)[4]) { collide2d<S>(f, p, mom); }
 };
-constexpr int PAIR = 2;
 inline bool paper_set(const KParams &p)
 {
     for (int i = 0; i < Q; ++i)

@@ -58,6 +58,25 @@ def test_fused_steps_equal_single_steps(nx, ny, storage):
     assert torch.equal(a.f, b.f) and a.cur == b.cur
 
 
+# FP32 in threes: strips of 224 columns at and past their multiples, closed ones
+# with one, two and four chunks side by side, ragged rows, one chunk that is the
+# whole height; every remainder of the steps, with fields and with sums
+@pytest.mark.parametrize("nx,ny", [(64, 17000), (63, 17001), (128, 8300), (224, 4700), (256, 4101), (448, 2353),
+                                   (673, 1600), (1501, 707), (1121, 940), (16385, 65), (57344, 19)])
+def test_three_fused_steps_equal_single_steps(nx, ny):
+    fields = inputs.random_fields(nx, ny, seed=nx + ny)
+    a, b = _pair(lambda: Lattice(2, nx, ny, omega=1.7, storage="f32"), fields, 30, (3, 6, 7, 14))
+    assert torch.equal(a.f, b.f) and a.cur == b.cur
+    got, want = a.step_fields(9), b.step_fields(1)
+    for _ in range(8):
+        b.step(1)
+    assert torch.equal(a.f, b.f) and all(torch.equal(g, w) for g, w in zip(got, want))
+    s = a.step(10, sums=True)
+    for _ in range(9):
+        b.step(1)
+    assert s == b.step(1, sums=True) and torch.equal(a.f, b.f)
+
+
 @pytest.mark.parametrize("nx,ny", [(1501, 1100), (1345, 1121), (224, 6700), (128, 11730)])
 @pytest.mark.parametrize("storage,rounding", [("f16dev", "nearest"), ("bf16dev", "nearest"),
                                               ("f16dev", "stochastic"), ("bf16dev", "stochastic")])
