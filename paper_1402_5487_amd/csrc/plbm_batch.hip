@@ -17,7 +17,8 @@
 //    of its own would be; the single step's tiles remain for the steps left.
 //  * plbm_batch_step replays a captured hipGraph of `graph_steps` consecutive
 //    steps (alternating buffers), so the host issues one graph launch per
-//    graph_steps steps.  No memset is recorded in the graph.
+//    graph_steps steps.  No memset is recorded in the graph.  Launches of three
+//    steps are issued one by one.
 //  * Lattices of one size form a shape group: back to back in the pool, one
 //    tile shape, so a tile index decodes arithmetically from a table passed
 //    as a kernel argument (up to 48 sizes; beyond that a work list in device
@@ -147,7 +148,7 @@ __global__ __launch_bounds__(TX) void k_step_groups(float *__restrict__ pool, co
 }
 
 // Fused steps: the same two forms of work list, with the workgroups of each
-// lattice's SweepGrid (pairs, plbm_sweep.h) or its tiles (plbm_tile.h) in place of
+// lattice's SweepGrid (strips, plbm_sweep.h) or its tiles (plbm_tile.h) in place of
 // the single step's tiles.
 using Model32 = Thermal25<StF32>;
 
@@ -172,7 +173,7 @@ struct BFusedGroups {
     BFusedGroup g[MAX_GROUPS];
 };
 
-// BX = 0: a pair of steps of a strip, else D steps of a tile.
+// D steps of a strip (BX = 0) or of a tile.
 template <int BX, int D>
 __device__ __forceinline__ void batch_fused(const BFused &t, const KParams &proto, int parity, float *lds)
 {
@@ -191,12 +192,12 @@ __device__ __forceinline__ void batch_fused(const BFused &t, const KParams &prot
 template <int BX, int D>
 constexpr int fused_threads() { return BX > 0 ? TileShape<Model32, BX ? BX : 8, BX ? BX : 8, D>::THREADS : sweep_threads<Model32>(); }
 template <int BX, int D>
-constexpr size_t fused_lds() { return BX > 0 ? TileShape<Model32, BX ? BX : 8, BX ? BX : 8, D>::LDS : sweep_lds_bytes<Model32, 2>(); }
-template <int BX>
-constexpr int fused_waves() { return BX > 0 ? 1 : sweep_per_cu<Model32, 2>(); }
+constexpr size_t fused_lds() { return BX > 0 ? TileShape<Model32, BX ? BX : 8, BX ? BX : 8, D>::LDS : sweep_lds_bytes<Model32, D>(); }
+template <int BX, int D>
+constexpr int fused_waves() { return BX > 0 ? 1 : sweep_per_cu<Model32, D>(); }
 
 template <int BX, int D>
-__global__ __launch_bounds__((fused_threads<BX, D>()), (fused_waves<BX>())) void
+__global__ __launch_bounds__((fused_threads<BX, D>()), (fused_waves<BX, D>())) void
 k_fused_groups(float *__restrict__ pool, const float *__restrict__ omegas, BFusedGroups G, KParams proto, int parity)
 {
     extern __shared__ __align__(16) unsigned char fused_lds_[];
@@ -219,7 +220,7 @@ k_fused_groups(float *__restrict__ pool, const float *__restrict__ omegas, BFuse
 }
 
 template <int BX, int D>
-__global__ __launch_bounds__((fused_threads<BX, D>()), (fused_waves<BX>())) void
+__global__ __launch_bounds__((fused_threads<BX, D>()), (fused_waves<BX, D>())) void
 k_fused_list(const BFused *__restrict__ list, KParams proto, int parity)
 {
     extern __shared__ __align__(16) unsigned char fused_lds_[];
@@ -229,11 +230,21 @@ k_fused_list(const BFused *__restrict__ list, KParams proto, int parity)
 
 // How a batch takes several steps per launch: three on tiles of 8 x 8 or
 // 16 x 16 nodes while that is at most one tile per CU, two on 16 x 16 up to 2^20
-// nodes, pairs of strips beyond.  Measured (us a step, single / strips / chosen):
-// 4 lattices of 64 4.9 / - / 2.6, 20 of 64 6.2 / - / 5.0, 6 of 64..128 5.5 / - / 3.6,
-// 40 of 64..128 18.3 / 12.9 / 10.9, 10 of 64..256 16.1 / 11.7 / 9.9, 5 of 64..512
-// 27.8 / 18.9 / 17.4, 40 of 64..512 142 / 94 / 94, 256 of 64..512 899 / 534 / 534.
-enum class Fused { none, pairs, tiles8, tiles16, tiles16x2 };
+// nodes, three on strips beyond, with a pair for two steps left over (pairs
+// alone where their workgroups come to fewer rows, see strip_rows).  Measured
+// (us a step, single / strips of two / chosen): 4 lattices of 64 4.9 / - / 2.6, 20 of 64
+// 6.2 / - / 5.0, 6 of 64..128 5.5 / - / 3.6, 40 of 64..128 18.3 / 12.9 / 10.9, 10 of
+// 64..256 16.1 / 11.7 / 9.9, 5 of 64..512 27.8 / 18.9 / 17.4, 40 of 64..512 142 / 94 /
+// 79, 256 of 64..512 899 / 534 / 464.
+enum class Fused { none, strips2, strips3, tiles8, tiles16, tiles16x2 };
+
+// One fused launch of the whole batch.
+struct FusedWork {
+    Fused form = Fused::none;
+    int wgs = 0;
+    BFusedGroups groups;
+    BFused *list = nullptr;          // when not grouped
+};
 
 __global__ void k_fill(float *p, size_t n, float v)
 {
@@ -273,11 +284,9 @@ struct plbm_batch {
     std::vector<long long> group_base;          // pool offset of each group
     float *d_omega = nullptr;        // omega per lattice, in group order
     BGroups groups;
-    Fused fused = Fused::none;
-    int depth = 1;                   // steps of a fused launch
-    int nfused = 0;                  // its workgroups
-    BFusedGroups fused_groups;
-    BFused *d_fused = nullptr;       // when not grouped
+    FusedWork fused;                 // `depth` steps a launch
+    int depth = 1;
+    FusedWork rest;                  // two steps that launches of three leave over
     float *pool = nullptr;
     size_t pool_elems = 0;
     int parity = 0;                  // buffer holding the current state
@@ -399,30 +408,35 @@ int build_tiles(plbm_batch *b)
     return PLBM_OK;
 }
 
-// Rows a chunk of the batch's pairs takes: those for which the rounds of
+// Rows a chunk of strips of D steps takes: those for which the rounds of
 // resident workgroups, each as long as a chunk and its halo, are least (a last
 // round of a few workgroups costs as much as a full one: 100 lattices of
-// 64..128 took 27 us a step with 10 rows, 34 with 16; 40 of 64..512 took 94 with
-// 22, 98 with 16); past eight rounds 16 (see sweep_grid: 256 of 64..512 took
-// 534 us, 561 with 32).
-int sweep_rows(const plbm_batch *b)
+// 64..128 took 27 us a step with 10 rows in pairs, 34 with 16; 40 of 64..512 took
+// 94 with 22, 98 with 16).  Pairs: past eight rounds 16 (see sweep_grid: 256 of
+// 64..512 took 534 us, 561 with 32).  cost: the rows of these rounds.
+template <int D>
+int strip_rows(const plbm_batch *b, long long &cost)
 {
-    constexpr int slots = SWEEP_CUS * sweep_per_cu<Model32, 2>();
+    constexpr int slots = SWEEP_CUS * sweep_per_cu<Model32, D>(), halo = 2 * Lines<Model32>::R * (D - 1);
     std::map<std::pair<int, int>, int> sizes;
     for (const auto &s : b->specs) ++sizes[{s.nx, s.ny}];
-    auto rounds = [&](int h) {
+    auto rows = [&](int h) {
         long long n = 0;
         for (const auto &kv : sizes) {
-            SweepGrid g = sweep_grid<Model32, 2>(kv.first.first, kv.first.second);
-            g.rows(kv.first.second, std::min(h, kv.first.second));
+            SweepGrid g = sweep_grid<Model32, D>(kv.first.first, kv.first.second);
+            g.even_rows(kv.first.second, h);
             n += (long long)g.wgs * kv.second;
         }
-        return (n + slots - 1) / slots;
+        return (n + slots - 1) / slots * (h + halo);
     };
     int best = 16;
-    if (rounds(best) > 8) return best;
-    for (int h = 4; h <= 24; h += 2)
-        if (rounds(h) * (h + 2 * Lines<Model32>::R) < rounds(best) * (best + 2 * Lines<Model32>::R)) best = h;
+    cost = rows(best);
+    if (D == 2 && cost > 8 * (best + halo)) return best;
+    for (int h = 4; h <= (D == 2 ? 24 : 200); h += 2)
+        if (const long long c = rows(h); c < cost) {
+            best = h;
+            cost = c;
+        }
     return best;
 }
 
@@ -435,61 +449,23 @@ long long count_tiles(const plbm_batch *b, int side)
     return n;
 }
 
-int build_fused(plbm_batch *b)
+// The work list of one fused launch from each lattice's grid.
+template <class Grid>
+int build_work(plbm_batch *b, FusedWork &w, Fused form, const Grid &grid)
 {
-    long long nodes = 0;
-    bool fit = paper_set(b->kp);
-    for (const auto &s : b->specs) {
-        nodes += (long long)s.nx * s.ny;
-        fit = fit && sweep_fits<Model32>(s.nx);
-    }
-    b->fused = Fused::none;
-    b->depth = 1;
-    if (!fit) return PLBM_OK;
-    int side = 0;
-    if (count_tiles(b, 8) <= SWEEP_CUS) {
-        b->fused = Fused::tiles8;
-        b->depth = 3;
-        side = 8;
-    } else if (count_tiles(b, 16) <= SWEEP_CUS) {
-        b->fused = Fused::tiles16;
-        b->depth = 3;
-        side = 16;
-    } else if (nodes <= TILE_NODES) {
-        b->fused = Fused::tiles16x2;
-        b->depth = 2;
-        side = 16;
-    } else {
-        b->fused = Fused::pairs;
-        b->depth = 2;
-    }
-    const int rows = side ? 0 : sweep_rows(b);
-    auto grid_for_lattice = [&](const plbm_lattice_spec &s) {
-        SweepGrid g = sweep_grid<Model32, 2>(s.nx, s.ny);
-        if (side) {
-            g.strips = (s.nx + side - 1) / side;
-            g.wgs = g.strips * ((s.ny + side - 1) / side);
-        } else {
-            g.rows(s.ny, std::min(rows, s.ny));
-        }
-        return g;
-    };
     long long total = 0;
-    for (const auto &s : b->specs) total += grid_for_lattice(s).wgs;
-    if (total > MAX_GRID) {
-        b->fused = Fused::none;
-        b->depth = 1;
-        return PLBM_OK;
-    }
-    b->nfused = (int)total;
+    for (const auto &s : b->specs) total += grid(s).wgs;
+    if (total > MAX_GRID) return PLBM_OK;
+    w.form = form;
+    w.wgs = (int)total;
     if (b->grouped) {
-        BFusedGroups &G = b->fused_groups;
+        BFusedGroups &G = w.groups;
         std::memset(&G, 0, sizeof(G));
         int at = 0, lat0 = 0;
         for (size_t gi = 0; gi < b->group_lats.size(); ++gi) {
             const plbm_lattice_spec &sp = b->specs[b->group_lats[gi][0]];
             BFusedGroup &g = G.g[gi];
-            g.grid = grid_for_lattice(sp);
+            g.grid = grid(sp);
             g.base = b->group_base[gi];
             g.half = (long long)padded_elems(sp);
             g.stride = 2 * g.half;
@@ -507,35 +483,89 @@ int build_fused(plbm_batch *b)
     std::vector<BFused> list;
     list.reserve(total);
     for (size_t i = 0; i < b->specs.size(); ++i) {
-        const SweepGrid g = grid_for_lattice(b->specs[i]);
+        const SweepGrid g = grid(b->specs[i]);
         const BLat &L = b->lats[i];
         for (int k = 0; k < g.wgs; ++k)
             list.push_back(BFused{{L.buf[0], L.buf[1]}, L.nx, L.ny, L.omega, k, g});
     }
-    if (hipMalloc((void **)&b->d_fused, list.size() * sizeof(BFused)) != hipSuccess) return PLBM_EHIP;
-    return hipck(hipMemcpy(b->d_fused, list.data(), list.size() * sizeof(BFused), hipMemcpyHostToDevice));
+    if (hipMalloc((void **)&w.list, list.size() * sizeof(BFused)) != hipSuccess) return PLBM_EHIP;
+    return hipck(hipMemcpy(w.list, list.data(), list.size() * sizeof(BFused), hipMemcpyHostToDevice));
+}
+
+template <int D>
+int build_strips(plbm_batch *b, FusedWork &w, int rows)
+{
+    return build_work(b, w, D == 2 ? Fused::strips2 : Fused::strips3, [&](const plbm_lattice_spec &s) {
+        SweepGrid g = sweep_grid<Model32, D>(s.nx, s.ny);
+        g.even_rows(s.ny, rows);
+        return g;
+    });
+}
+
+int build_tiles(plbm_batch *b, Fused form, int side)
+{
+    return build_work(b, b->fused, form, [&](const plbm_lattice_spec &s) {
+        SweepGrid g = sweep_grid<Model32, 2>(s.nx, s.ny);
+        g.strips = (s.nx + side - 1) / side;
+        g.wgs = g.strips * ((s.ny + side - 1) / side);
+        return g;
+    });
+}
+
+int build_fused(plbm_batch *b)
+{
+    long long nodes = 0;
+    bool fit = paper_set(b->kp);
+    for (const auto &s : b->specs) {
+        nodes += (long long)s.nx * s.ny;
+        fit = fit && sweep_fits<Model32>(s.nx);
+    }
+    b->depth = 1;
+    if (!fit) return PLBM_OK;
+    int rc = PLBM_OK, depth = 3;
+    if (count_tiles(b, 8) <= SWEEP_CUS) {
+        rc = build_tiles(b, Fused::tiles8, 8);
+    } else if (count_tiles(b, 16) <= SWEEP_CUS) {
+        rc = build_tiles(b, Fused::tiles16, 16);
+    } else if (nodes <= TILE_NODES) {
+        rc = build_tiles(b, Fused::tiles16x2, 16);
+        depth = 2;
+    } else {
+        long long cost2, cost3;
+        const int rows2 = strip_rows<2>(b, cost2), rows3 = strip_rows<3>(b, cost3);
+        // microseconds of a row and step, as for single lattices
+        depth = 2.06 / 3 * cost3 <= 3.1 / 2 * cost2 ? 3 : 2;
+        if (depth == 3) {
+            rc = build_strips<3>(b, b->fused, rows3);
+            if (rc == PLBM_OK) rc = build_strips<2>(b, b->rest, rows2);
+        } else {
+            rc = build_strips<2>(b, b->fused, rows2);
+        }
+    }
+    if (b->fused.form != Fused::none) b->depth = depth;
+    return rc;
 }
 
 template <int BX, int D>
-void launch_fused_as(plbm_batch *b, int parity, hipStream_t st)
+void launch_fused_as(const plbm_batch *b, const FusedWork &w, int parity, hipStream_t st)
 {
     if (b->grouped)
-        hipLaunchKernelGGL((k_fused_groups<BX, D>), dim3(b->nfused), dim3(fused_threads<BX, D>()),
-                           (fused_lds<BX, D>()), st, b->pool, b->d_omega, b->fused_groups, b->kp, parity);
+        hipLaunchKernelGGL((k_fused_groups<BX, D>), dim3(w.wgs), dim3(fused_threads<BX, D>()),
+                           (fused_lds<BX, D>()), st, b->pool, b->d_omega, w.groups, b->kp, parity);
     else
-        hipLaunchKernelGGL((k_fused_list<BX, D>), dim3(b->nfused), dim3(fused_threads<BX, D>()),
-                           (fused_lds<BX, D>()), st, b->d_fused, b->kp, parity);
+        hipLaunchKernelGGL((k_fused_list<BX, D>), dim3(w.wgs), dim3(fused_threads<BX, D>()),
+                           (fused_lds<BX, D>()), st, w.list, b->kp, parity);
 }
 
-// `depth` steps of the whole batch
-int launch_fused(plbm_batch *b, int parity, hipStream_t st)
+int launch_fused(const plbm_batch *b, const FusedWork &w, int parity, hipStream_t st)
 {
     (void)hipGetLastError();
-    switch (b->fused) {
-    case Fused::pairs: launch_fused_as<0, 2>(b, parity, st); break;
-    case Fused::tiles8: launch_fused_as<8, 3>(b, parity, st); break;
-    case Fused::tiles16: launch_fused_as<16, 3>(b, parity, st); break;
-    case Fused::tiles16x2: launch_fused_as<16, 2>(b, parity, st); break;
+    switch (w.form) {
+    case Fused::strips2: launch_fused_as<0, 2>(b, w, parity, st); break;
+    case Fused::strips3: launch_fused_as<0, 3>(b, w, parity, st); break;
+    case Fused::tiles8: launch_fused_as<8, 3>(b, w, parity, st); break;
+    case Fused::tiles16: launch_fused_as<16, 3>(b, w, parity, st); break;
+    case Fused::tiles16x2: launch_fused_as<16, 2>(b, w, parity, st); break;
     case Fused::none: return PLBM_EINVAL;
     }
     return hipck(hipGetLastError());
@@ -773,7 +803,8 @@ extern "C" int plbm_batch_destroy(plbm_batch *b)
     if (b->exec) (void)hipGraphExecDestroy(b->exec);
     if (b->capture) (void)hipStreamDestroy(b->capture);
     if (b->d_tiles) (void)hipFree(b->d_tiles);
-    if (b->d_fused) (void)hipFree(b->d_fused);
+    if (b->fused.list) (void)hipFree(b->fused.list);
+    if (b->rest.list) (void)hipFree(b->rest.list);
     if (b->d_omega) (void)hipFree(b->d_omega);
     if (b->pool) (void)hipFree(b->pool);
     delete b;
@@ -840,7 +871,7 @@ extern "C" int plbm_batch_step(plbm_batch *b, int nsteps, void *stream)
             rc = hipck(hipStreamBeginCapture(b->capture, hipStreamCaptureModeThreadLocal));
             if (rc != PLBM_OK) return rc;
             const int fused = b->depth == 2 ? fused_launches<2>(b->graph_steps) : 0;
-            for (int k = 0; k < fused && rc == PLBM_OK; ++k) rc = launch_fused(b, k & 1, b->capture);
+            for (int k = 0; k < fused && rc == PLBM_OK; ++k) rc = launch_fused(b, b->fused, k & 1, b->capture);
             for (int s = b->depth * fused; s < b->graph_steps && rc == PLBM_OK; ++s)
                 rc = launch_step(b, s & 1, b->capture);
             const int rc_end = hipck(hipStreamEndCapture(b->capture, &g));
@@ -862,10 +893,15 @@ extern "C" int plbm_batch_step(plbm_batch *b, int nsteps, void *stream)
             left -= b->graph_steps;
         }
     }
-    for (; b->depth > 1 && left >= b->depth; left -= b->depth) {
-        rc = launch_fused(b, b->parity, st);
+    // threes, and pairs for the two or four steps at their end (40 lattices of
+    // 64..512: four steps 368 us in pairs, 390 as three and one)
+    const bool pairs = b->rest.form != Fused::none;
+    while (b->depth > 1 && left >= (pairs ? 2 : b->depth)) {
+        const bool pair = pairs && (left == 2 || left == 4);
+        rc = launch_fused(b, pair ? b->rest : b->fused, b->parity, st);
         if (rc != PLBM_OK) return rc;
         b->parity ^= 1;
+        left -= pair ? 2 : b->depth;
     }
     for (; left > 0; --left) {
         rc = launch_step(b, b->parity, st);

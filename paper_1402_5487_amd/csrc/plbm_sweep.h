@@ -98,6 +98,12 @@ struct SweepGrid {
         chunks = (ny + h - 1) / h;
         wgs = strips * ((chunks + per - 1) / per);
     }
+    // chunks of one height, `height` at most
+    __host__ void even_rows(int ny, int height)
+    {
+        const int n = (ny + height - 1) / height;
+        rows(ny, (ny + n - 1) / n);
+    }
 };
 
 // The partition of an nx x ny lattice.  Strips begin on cache lines (128 B;

@@ -201,6 +201,28 @@ def test_fused_batch_steps_equal_single_lattices(sizes):
     b.close()
 
 
+# strips of three, up to 48 sizes and more: closed strips with one, two and four
+# chunks side by side, several strips, ragged rows; pairs for two and four steps left
+@pytest.mark.parametrize("sizes", [[(256, 250)] * 9 + [(448, 300)] * 4 + [(64, 700)] * 9 + [(31, 300), (700, 333)],
+                                   [(200 + i, 250 + 3 * i) for i in range(50)]])
+def test_three_fused_batch_steps_equal_single_lattices(sizes):
+    specs = [(nx, ny, 1.5 + 0.3 * i / len(sizes)) for i, (nx, ny) in enumerate(sizes)]
+    b = Batch(specs)
+    fields = [inputs.random_fields(nx, ny, seed=i) for i, (nx, ny, _) in enumerate(specs)]
+    for i, f in enumerate(fields):
+        b.init(i, *f)
+    for n in (3, 4, 7, 8, 1, 2):
+        b.step(n)
+    for i, (nx, ny, om) in enumerate(specs):
+        if i % 7 and i < len(specs) - 2:
+            continue
+        lat = Lattice(2, nx, ny, omega=om, storage="f32").init(*fields[i])
+        for _ in range(25):
+            lat.step(1)
+        assert torch.equal(b.buffer(i), lat.f), (nx, ny)
+    b.close()
+
+
 def test_sums_of_threads_and_streams_do_not_mix():
     """Calls that ask for sums share one scratch while it is free: threads on
     streams of their own get their own lattice's sums."""
