@@ -238,8 +238,10 @@ struct GenSet {
     static constexpr int V[Q1] = {Vs...};
     static constexpr bool KEYED = false;
     static constexpr int SPAN = SPAN_, WGS = 4;
+    // tall chunks (us a step with 16 / 100 rows at 2048^2: D2Q16 FP32 60 / 55, FP64 114 /
+    // 99; D2Q49 FP32 200 / 175, FP64 491 / 426)
     template <int D>
-    static constexpr int rounds_h() { return 16; }
+    static constexpr int rounds_h() { return 100; }
     static __device__ __forceinline__ C dec(T h, int, const P &) { return h; }
     static __device__ __forceinline__ T enc(C f, int, const P &, uint32_t) { return f; }
     static __device__ __forceinline__ uint32_t key(uint32_t node) { return node; }
@@ -509,11 +511,11 @@ void gen_launch(const GenParams &p, const T *src, T *dst, double *part, hipStrea
 // (plbm_sweep.h) beyond, with at least half the lanes of their strips in use;
 // returns how many of the n steps they took, or a (negative) status.  Measured
 // (us a step, single / pairs / tiles): D2Q16 FP32 64^2 3.4 / - / 1.8, 256^2 3.9 / - /
-// 2.4, 512^2 8.0 / 7.6 / 4.9, 1024^2 25.8 / 18.5 / 17.8, 2048^2 90 / 58 / -, FP64
+// 2.4, 512^2 8.0 / 7.6 / 4.9, 1024^2 25.8 / 18.5 / 17.8, 2048^2 90 / 55 / -, FP64
 // 1024^2 49 / 29.7 / 28.8; D2Q49 FP32 128^2 5.0 / - / 3.4, 512^2 21.8 / 20.0 / 16.7,
-// 768^2 44 / 32 / 35, 2048^2 270 / 198 / -, FP64 256^2 12.5 / - / 9.8, 512^2 42 / 39 /
-// 34, 768^2 87 / 67 / 96, 2048^2 554 / 490 / -.  Three steps a strip leave D2Q16 one
-// workgroup per CU: 70 at 2048^2.
+// 768^2 44 / 32 / 35, 2048^2 270 / 177 / -, FP64 256^2 12.5 / - / 9.8, 512^2 42 / 39 /
+// 34, 768^2 87 / 67 / 96, 2048^2 554 / 426 / -.  Three steps a strip leave D2Q16 one
+// workgroup per CU: 56 at 2048^2.
 template <class M>
 int gen_fused(const GenParams &p, void *fa, void *fb, int n, hipStream_t st)
 {
@@ -544,7 +546,7 @@ int gen_fused(const GenParams &p, void *fa, void *fb, int n, hipStream_t st)
     if (2ll * p.nx * g.per < (long long)g.strips * sweep_threads<M>()) return 0;
     const int launches = fused_launches<D>(n);
     // D2Q49 in FP64, whose narrow strips write few whole lines either way:
-    // 215 us a step non-temporal at 1501 x 1100, 222 not
+    // 296 us a step non-temporal at 3001 x 1000, 302 not
     const bool nts = rows_on_lines(p.nx, sizeof(T)) || (M::Q1 == 7 && sizeof(T) == 8);
     auto *kernel = nts ? k_pair_gen<M, true> : k_pair_gen<M, false>;
     for (int k = 0; k < launches; ++k) {
