@@ -238,6 +238,9 @@ struct GenSet {
     static constexpr int V[Q1] = {Vs...};
     static constexpr bool KEYED = false;
     static constexpr int SPAN = SPAN_, WGS = 4;
+    // D2Q49 in FP64 holds 112 columns: 104 of them in half lines, 96 in whole ones
+    template <int D>
+    static constexpr int line() { return Q1 == 7 && sizeof(T) == 8 ? 64 : 128; }
     // tall chunks (us a step with 16 / 100 rows at 2048^2: D2Q16 FP32 60 / 55, FP64 114 /
     // 99; D2Q49 FP32 200 / 175, FP64 491 / 426)
     template <int D>
@@ -514,7 +517,7 @@ void gen_launch(const GenParams &p, const T *src, T *dst, double *part, hipStrea
 // 2.4, 512^2 8.0 / 7.6 / 4.9, 1024^2 25.8 / 18.5 / 17.8, 2048^2 90 / 55 / -, FP64
 // 1024^2 49 / 29.7 / 28.8; D2Q49 FP32 128^2 5.0 / - / 3.4, 512^2 21.8 / 20.0 / 16.7,
 // 768^2 44 / 32 / 35, 2048^2 270 / 177 / -, FP64 256^2 12.5 / - / 9.8, 512^2 42 / 39 /
-// 34, 768^2 87 / 67 / 96, 2048^2 554 / 426 / -.  Three steps a strip leave D2Q16 one
+// 34, 768^2 87 / 67 / 96, 2048^2 554 / 399 / -.  Three steps a strip leave D2Q16 one
 // workgroup per CU: 56 at 2048^2.
 template <class M>
 int gen_fused(const GenParams &p, void *fa, void *fb, int n, hipStream_t st)

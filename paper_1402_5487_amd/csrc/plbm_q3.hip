@@ -198,6 +198,8 @@ struct Iso9 {
     static constexpr bool KEYED = false;
     static constexpr int SPAN = 256, WGS = 4;
     template <int D>
+    static constexpr int line() { return 128; }
+    template <int D>
     static constexpr int rounds_h() { return 24; }
     static __device__ __forceinline__ C dec(T h, int, const P &) { return h; }
     static __device__ __forceinline__ T enc(C f, int, const P &, uint32_t) { return f; }

@@ -106,26 +106,25 @@ struct SweepGrid {
     }
 };
 
-// The partition of an nx x ny lattice.  Strips begin on cache lines (128 B;
-// 64 B for the 16-bit forms, whose 128 B would cost a quarter of the lanes):
-// stores that end inside a line left the D2Q25 pair at 4096^2 at 489 us a step
-// in FP32 against 373.  Chunks: as many rounds of
+// The partition of an nx x ny lattice.  Strips begin on cache lines, whole or
+// half (M::line<D>() bytes): stores that end inside a line left the D2Q25 pair at
+// 4096^2 at 489 us a step in FP32 against 373.  Chunks: as many rounds of
 // resident workgroups as leave them about M::rounds_h<D>() rows.  Long chunks
 // spread the accesses over so much memory that the D2Q25 FP32 pair at 4096^2
 // took 373 us a step with 157 rows, 318 with 64 and 313 with 16; a last round
 // of a few workgroups costs as much as a full one (D2Q9 FP32 2048^2, 1.1
 // rounds: 22.6 us a step, one: 17).
-template <class M>
-constexpr int sweep_align() { return sizeof(typename M::T) == 2 ? 32 : 128 / (int)sizeof(typename M::T); }
+template <class M, int D>
+constexpr int sweep_align() { return M::template line<D>() / (int)sizeof(typename M::T); }
 template <class M, int D>
 constexpr int sweep_wmax()
 {
-    return (M::SPAN - 2 * Lines<M>::R * (D - 1)) / sweep_align<M>() * sweep_align<M>();
+    return (M::SPAN - 2 * Lines<M>::R * (D - 1)) / sweep_align<M, D>() * sweep_align<M, D>();
 }
 template <class M, int D>
 inline SweepGrid sweep_grid(int nx, int ny)
 {
-    constexpr int align = sweep_align<M>(), wmax = sweep_wmax<M, D>();
+    constexpr int align = sweep_align<M, D>(), wmax = sweep_wmax<M, D>();
     constexpr int slots = SWEEP_CUS * sweep_per_cu<M, D>();
     SweepGrid g;
     g.per = 1;
@@ -405,6 +404,11 @@ struct Thermal25 {
     static constexpr int V[Q] = {0, 1, -1, 3, -3};
     static constexpr bool KEYED = S::keyed;
     static constexpr int SPAN = 256, WGS = 4;
+    // Half lines where 128 B would cost a quarter of the lanes (16-bit) or a
+    // twelfth (FP32 threes: 2500^2 106 us a step with 224 columns, 102 with 240;
+    // 2048 x 4096 139, 126), and one workgroup of each CU writes.
+    template <int D>
+    static constexpr int line() { return sizeof(T) == 2 || (sizeof(T) == 4 && D == 3) ? 64 : 128; }
     // Tall chunks, as each computes 3 rows per step but the first twice at
     // either end (FP32 4096^2 in threes, us a step: 335 with 16 rows, 254 with
     // 53, 225 with one round of 316; FP64 2048^2 175 with 16, 160 with 93).  Two

@@ -151,6 +151,17 @@ def test_fused_general_steps_equal_single_steps(nx, ny, storage, v, theta):
     assert torch.equal(a.f, b.f) and a.cur == b.cur
 
 
+# strips on half lines, of 240 (FP32 in threes) and 104 columns (D2Q49 in FP64): at
+# and past their multiples and whole ragged rows
+@pytest.mark.parametrize("nx,ny", [(104, 2600), (208, 1300), (209, 1301), (480, 2200), (481, 2190), (720, 1460)])
+@pytest.mark.parametrize("storage,v,theta", [("f32", (0, 1, -1, 3, -3), 0.4), ("f64", (0, 1, -1, 2, -2, 3, -3), 1.0)])
+def test_fused_steps_on_half_lines_equal_single_steps(nx, ny, storage, v, theta):
+    fields = inputs.random_fields(nx, ny, seed=nx + ny, theta=(theta, theta), u=0.03)
+    a, b = _pair(lambda: Lattice(2, nx, ny, omega=1.6, storage=storage, velocities=v, theta0=theta), fields, 13,
+                 (9, 4))
+    assert torch.equal(a.f, b.f) and a.cur == b.cur
+
+
 # 1D: one workgroup up to 1024 nodes (in place for an even number of steps);
 # tiles with halos beyond, the tile that leaves one node, fewer nodes than the
 # halo in the last tile; one step, few, many; the ghosts belong to the buffer
