@@ -78,8 +78,16 @@ __device__ __forceinline__ int wrap(int s, int n)
 struct Segment {
     int row, x;
 };
+// WHOLE: rows of a multiple of four segments, whose four waves are the tile's;
+// the row is the workgroup's (256^3 FP64 5820 us a step, 5900 by waves; 200 x 100 x
+// 150 1165, 1195; FP32 only with non-temporal stores: 250 x 128 x 100 636, 624).
+template <bool WHOLE = false>
 __device__ __forceinline__ Segment segment(const P3 &p, int tile)
 {
+    if constexpr (WHOLE) {
+        const int row = tile / (p.segs_x / 4);
+        return {row, (tile - row * (p.segs_x / 4)) * TX + (int)threadIdx.x};
+    }
     const int seg = __builtin_amdgcn_readfirstlane(tile * (TX / 64) + (int)(threadIdx.x >> 6));
     const int row = seg / p.segs_x;
     return {seg < p.nsegs ? row : -1, (seg - row * p.segs_x) * 64 + (int)(threadIdx.x & 63)};
@@ -187,7 +195,7 @@ __device__ __forceinline__ void collide125(C (&f)[N125], const SymRule<C> &R)
 // One step over the row segments (z ny + y) segs_x + sx.  Optional
 // FP64 block sums of what is stored: (sum f, sum f v_x, sum f v_y,
 // sum f |v|^2, sum f v_z).
-template <typename T, bool SUMS, bool NTS>
+template <typename T, bool SUMS, bool NTS, bool WHOLE>
 __global__ __launch_bounds__(TX) void k_step3d(const T *__restrict__ src, T *__restrict__ dst, P3 p,
                                                double *__restrict__ partials)
 {
@@ -198,8 +206,8 @@ __global__ __launch_bounds__(TX) void k_step3d(const T *__restrict__ src, T *__r
     const int slot = xcd_tile(blockIdx.x, gridDim.x);
 #pragma unroll 1
     for (int tile = slot; tile < p.ntiles; tile += gridDim.x) {
-        const Segment g = segment(p, tile);
-        if (g.row < 0) continue;
+        const Segment g = segment<WHOLE>(p, tile);
+        if (!WHOLE && g.row < 0) continue;
         const int row = g.row, z = row / p.ny, y = row - z * p.ny, xb = g.x;
         C f[N125];
         gather125<T, C>(src, p, xb, y, z, f);
@@ -338,11 +346,22 @@ inline int grid_of(const P3 &p) { return std::min(p.ntiles, MAX_GRID3); }
 template <typename T>
 constexpr size_t lds_cap() { return sizeof(T) == 8 ? PLBM_Q125_LDS_F64 : PLBM_Q125_LDS_F32; }
 
+// Non-temporal stores where the rows begin on half lines (us a step, not / non-
+// temporal: 200 x 100 x 150 FP64 1306 / 1194, 104 x 100 x 150 685 / 634, FP32
+// 112 x 150 x 150 493 / 473; off them 250 x 200 x 200 FP64 3816 / 4270, FP32
+// 200 x 150 x 150 885 / 974).
+template <typename T, bool SUMS>
+auto step3_kernel(const P3 &p)
+{
+    const bool nts = (long long)p.nx * (long long)sizeof(T) % 64 == 0;
+    if (p.segs_x % 4 == 0 && (nts || sizeof(T) == 8)) return nts ? k_step3d<T, SUMS, true, true> : k_step3d<T, SUMS, false, true>;
+    return nts ? k_step3d<T, SUMS, true, false> : k_step3d<T, SUMS, false, false>;
+}
+
 template <typename T>
 int q125_run(const P3 &p, void *fa, void *fb, int nsteps, double *sums, hipStream_t st)
 {
     const int grid = grid_of(p);
-    const bool nts = rows_on_lines(p.nx, sizeof(T));
     for (int s = 0; s < nsteps; ++s) {
         const T *src = static_cast<const T *>((s & 1) ? fb : fa);
         T *dst = static_cast<T *>((s & 1) ? fa : fb);
@@ -352,12 +371,12 @@ int q125_run(const P3 &p, void *fa, void *fb, int nsteps, double *sums, hipStrea
             plbm::SumsArea area;
             int rc = plbm::sums_begin(area, 5, blocks, true, st);
             if (rc != PLBM_OK) return rc;
-            hipLaunchKernelGGL((nts ? k_step3d<T, true, true> : k_step3d<T, true, false>), dim3(blocks), dim3(TX),
-                               lds_cap<T>(), st, src, dst, p, area.part);
+            hipLaunchKernelGGL((step3_kernel<T, true>(p)), dim3(blocks), dim3(TX), lds_cap<T>(), st, src, dst, p,
+                               area.part);
             rc = q125_launch_status();
             return plbm::sums_end(area, 5, blocks, rc, sums, st);
         }
-        hipLaunchKernelGGL((nts ? k_step3d<T, false, true> : k_step3d<T, false, false>), dim3(grid), dim3(TX), lds_cap<T>(), st, src, dst, p, nullptr);
+        hipLaunchKernelGGL((step3_kernel<T, false>(p)), dim3(grid), dim3(TX), lds_cap<T>(), st, src, dst, p, nullptr);
         const int rc = q125_launch_status();
         if (rc != PLBM_OK) return rc;
     }

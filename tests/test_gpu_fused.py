@@ -7,7 +7,7 @@ import torch
 
 from paper_1402_5487_amd import inputs
 from paper_1402_5487_amd.batch import Batch
-from paper_1402_5487_amd.lattice import Lattice
+from paper_1402_5487_amd.lattice import Lattice, Lattice3
 
 pytestmark = pytest.mark.gpu
 
@@ -232,6 +232,24 @@ def test_three_fused_batch_steps_equal_single_lattices(sizes):
             lat.step(1)
         assert torch.equal(b.buffer(i), lat.f), (nx, ny)
     b.close()
+
+
+# D3Q125: a row of two copies of a periodic row keeps both copies, whether the rows
+# are taken by waves or whole, and however they are stored (ragged, on half lines)
+@pytest.mark.parametrize("nx", [100, 102, 104, 120, 125, 128, 129, 250])
+@pytest.mark.parametrize("storage", ["f64", "f32"])
+def test_box_rows_side_by_side_equal_one(nx, storage):
+    ny, nz = 4, 5
+    g = torch.Generator().manual_seed(nx)
+    fields = [c + a * torch.rand(nz, ny, nx, generator=g, dtype=torch.float64)
+              for c, a in ((1.0, 0.02), (0.0, 0.02), (0.0, 0.02), (0.0, 0.02), (0.4, 0.01))]
+    a, b = (Lattice3(n, ny, nz, omega=1.2, storage=storage) for n in (nx, 2 * nx))
+    a.init(*fields)
+    b.init(*(f.repeat(1, 1, 2) for f in fields))
+    a.step(3)
+    b.step(3)
+    one, two = (lat.f.view(nz, ny, 125, lat.nx) for lat in (a, b))
+    assert torch.equal(two, one.repeat(1, 1, 1, 2))
 
 
 def test_sums_of_threads_and_streams_do_not_mix():
