@@ -494,20 +494,22 @@ __device__ __forceinline__ int xcd_tile(int b, int nblocks)
 // ---------------------------------------------------------------------------
 // 2D fused step
 // ---------------------------------------------------------------------------
-// Stores are non-temporal (NTS) where the rows begin on cache lines, and
-// ordinary where they do not: neighbouring waves then write parts of one
-// line, which meet in L2 only if the first part is kept there.  Measured, non-
-// temporal against ordinary: aligned rows, D2Q25 FP32 4096^2 313 against 336 us
-// a step (fused pairs), 256 x 128^2 D3Q125 729 against 797; ragged rows, D2Q25
-// FP32 3001 x 2000 190 against 145, D2Q16 FP32 1501 x 1100 29.8 against 21.7,
-// D3Q125 FP32 255 x 80^2 409 against 330.
+// Stores are non-temporal (NTS) where the rows begin on cache lines or half
+// lines (64 B, what memory moves), and ordinary where they do not: neighbouring
+// waves then write parts of one half line, which meet in L2 only if the first
+// part is kept there.  Measured, non-temporal against ordinary, us a step: whole
+// lines, D2Q25 FP32 4096^2 313 against 336 (fused pairs), 256 x 128^2 D3Q125 729
+// against 797; half lines, D2Q9 FP64 3000 x 2000 151 against 163, D2Q49 FP64
+// 1000^2 150 against 161, D3Q125 FP64 200 x 100 x 150 1194 against 1306; ragged
+// rows, D2Q25 FP32 3001 x 2000 190 against 145, D2Q16 FP32 1501 x 1100 29.8
+// against 21.7, D3Q125 FP32 255 x 80^2 409 against 330.
 template <bool NTS = true, class T>
 __device__ __forceinline__ void store_stream(T v, T *p)
 {
     if constexpr (NTS) __builtin_nontemporal_store(v, p);
     else *p = v;
 }
-__host__ __device__ inline bool rows_on_lines(int nx, size_t elem) { return (size_t)nx * elem % 128 == 0; }
+__host__ __device__ inline bool rows_on_lines(int nx, size_t elem) { return (size_t)nx * elem % 64 == 0; }
 
 // Loads and stores of NV consecutive nodes of one population row.  `base`
 // is a wave-uniform byte pointer, `off` the lane's byte offset (the node's

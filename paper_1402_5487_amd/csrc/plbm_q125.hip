@@ -346,14 +346,10 @@ inline int grid_of(const P3 &p) { return std::min(p.ntiles, MAX_GRID3); }
 template <typename T>
 constexpr size_t lds_cap() { return sizeof(T) == 8 ? PLBM_Q125_LDS_F64 : PLBM_Q125_LDS_F32; }
 
-// Non-temporal stores where the rows begin on half lines (us a step, not / non-
-// temporal: 200 x 100 x 150 FP64 1306 / 1194, 104 x 100 x 150 685 / 634, FP32
-// 112 x 150 x 150 493 / 473; off them 250 x 200 x 200 FP64 3816 / 4270, FP32
-// 200 x 150 x 150 885 / 974).
 template <typename T, bool SUMS>
 auto step3_kernel(const P3 &p)
 {
-    const bool nts = (long long)p.nx * (long long)sizeof(T) % 64 == 0;
+    const bool nts = rows_on_lines(p.nx, sizeof(T));
     if (p.segs_x % 4 == 0 && (nts || sizeof(T) == 8)) return nts ? k_step3d<T, SUMS, true, true> : k_step3d<T, SUMS, false, true>;
     return nts ? k_step3d<T, SUMS, true, false> : k_step3d<T, SUMS, false, false>;
 }
