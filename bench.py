@@ -8,12 +8,14 @@ grows ~6% per step and FP16 storage goes non-finite within ~200 steps).
 Throughput does not depend on the values; the stable variant keeps every
 timed step finite.
 
-One step = one fused collide-and-stream launch over all nodes (plbm_step).
-The headline is the FP16-deviation storage form (FP32 arithmetic, 100 B per
-node per step); the plain FP64 step (400 B), FP32 storage (200 B) and
-BF16-deviation storage are timed beside it.  Each form's error is stated
-against the FP64 form after --accuracy-steps steps from the same initial
-state (the FP64 form matches the CPU oracle to 1e-12 in the test suite).
+One step = one collide-and-stream update of all nodes (plbm_step, which takes
+two or three of them per launch).  The headline is the FP16-deviation storage
+form (FP32 arithmetic, 100 B per node for a step by itself); the plain FP64
+step (400 B), FP32 storage (200 B) and BF16-deviation storage are timed beside
+it.  GB/s and fractions count the bytes of single steps, of which a launch of
+several moves a half or a third: they may pass the memory's rate.  Each form's
+error is stated against the FP64 form after --accuracy-steps steps from the same
+initial state (the FP64 form matches the CPU oracle to 1e-12 in the test suite).
 
 Prints ONE JSON line (N = 1).
 """
@@ -32,7 +34,7 @@ METRIC = ("MLUPS and % of HBM roofline, D2Q25 thermal KH 4096², "
           "vs plain FP64 step at stated err")
 HBM_PEAK_GBS = 8000.0
 KERNEL_SRC = [os.path.join(ROOT, "paper_1402_5487_amd", "csrc", n)
-              for n in ("plbm_kernels.hip", "plbm_device.h")]
+              for n in ("plbm_kernels.hip", "plbm_device.h", "plbm_sweep.h", "plbm_tile.h")]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "step2d_kh4096_traffic.json")
 COMPUTE_DTYPE = {"f64": "f64", "f32": "f32", "f16dev": "f32", "bf16dev": "f32",
                  "f16dev_sr": "f32", "bf16dev_sr": "f32"}

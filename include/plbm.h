@@ -375,7 +375,7 @@ int plbm_batch_set_graph_steps(plbm_batch *b, int steps);
 /*
  * plbm_batch_step -- advance every lattice by nsteps applications of
  * Eq. srt (as plbm_step).  Whole groups of graph_steps steps replay the
- * captured graph (recorded on first use); the rest, and the steps of small
+ * captured graph (recorded on first use); the rest, and the steps of
  * batches that take three of them per launch, are direct launches.
  * Asynchronous on `stream`.
  */

@@ -23,9 +23,9 @@
 //    lane keeps five 32-bit offsets (one per x velocity), so each of the 50
 //    accesses is a scalar base plus a vector offset.  Only the waves whose
 //    windows cross the periodic seam in x take a per-node wrapped path.
-//  * Calls of four steps and more on larger lattices take them two at a time
-//    (plbm_sweep.h): the populations between the two steps stay in LDS and
-//    registers, so a pair reads and writes them once.
+//  * Calls of several steps take two or three per launch, larger lattices on
+//    strips (plbm_sweep.h), smaller ones on tiles (plbm_tile.h): the populations
+//    between the steps stay in LDS and registers and are read and written once.
 //  * Arithmetic per node: column/row sums give rho, j and sum f|v|^2; the
 //    Maxwell moments follow mu_(n+1) = u mu_n + n theta mu_(n-1); the 1D rule
 //    r = C mu uses the reduced table of a symmetric velocity set; f_eq =
