@@ -106,6 +106,14 @@ struct SweepGrid {
     }
 };
 
+// Which of the g.per chunks side by side a thread works on.  The kernel asks
+// once per wave, so sweep_grid puts no more of them side by side than the
+// workgroup has waves.
+__host__ __device__ inline int sweep_side(const SweepGrid &g, int thread, int threads)
+{
+    return thread * g.per / threads;
+}
+
 // The partition of an nx x ny lattice.  Strips begin on cache lines, whole or
 // half (M::line<D>() bytes): stores that end inside a line left the D2Q25 pair at
 // 4096^2 at 489 us a step in FP32 against 373.  Chunks: as many rounds of
@@ -129,9 +137,13 @@ inline SweepGrid sweep_grid(int nx, int ny)
     SweepGrid g;
     g.per = 1;
     if (nx <= M::SPAN) {
+        // chunks side by side, each of whole waves: two waves (D2Q49 in FP64) take
+        // two at most
+        constexpr int waves = sweep_threads<M>() / 64;
+        static_assert(waves == 1 || waves == 2 || waves == 4, "the chunks side by side share the waves evenly");
         g.strips = 1;
         g.w = g.span = nx;
-        for (int per = 4; per > 1 && g.per == 1; per /= 2)
+        for (int per = waves; per > 1 && g.per == 1; per /= 2)
             if (nx <= sweep_threads<M>() / per && nx * per <= M::SPAN) g.per = per;
     } else {
         g.strips = (nx + wmax - 1) / wmax;
@@ -219,7 +231,7 @@ __device__ __forceinline__ void sweep(const typename M::T *__restrict__ src, typ
     const int c = b / g.strips, xs = (b - c * g.strips) * g.w;
     // this thread's chunk, uniform over its wave, and its place in the strip;
     // a chunk past the last writes nothing
-    const int side = __builtin_amdgcn_readfirstlane((int)threadIdx.x * g.per / sweep_threads<M>());
+    const int side = __builtin_amdgcn_readfirstlane(sweep_side(g, (int)threadIdx.x, sweep_threads<M>()));
     const int t = (int)threadIdx.x - side * (sweep_threads<M>() / g.per);
     const int ya = (c * g.per + side) * g.h, yb = min(ya + g.h, ny);
     const long long rowelems = (long long)NP * nx;

@@ -1,0 +1,29 @@
+"""Fused steps on rows that close on themselves, one to four chunks side by
+side in a workgroup, against the same steps one by one.  Both round the same
+operations in the same order: equal bit for bit, the tolerance is zero."""
+import pytest
+import torch
+
+from paper_1402_5487_amd import inputs
+from paper_1402_5487_amd.lattice import Lattice
+
+pytestmark = pytest.mark.gpu
+
+
+# D2Q49: a lane holds one of 112 (FP64) or 232 (FP32) columns of two or four
+# waves; D2Q16 one of 256.  At, below and past what lets chunks share them.
+@pytest.mark.parametrize("v,theta,least,widths", [
+    ((0, 1, -1, 2, -2, 3, -3), 1.0, 1 << 18, (16, 24, 28, 29, 32, 33, 56, 57, 58, 59, 112, 116)),
+    ((1, -1, 3, -3), 4.0 / 3.0, 1 << 20, (32, 64, 65, 128))])
+@pytest.mark.parametrize("storage", ["f64", "f32"])
+def test_chunks_side_by_side_equal_single_steps(v, theta, least, widths, storage):
+    for nx in widths:
+        ny = least // nx + 5
+        fields = inputs.random_fields(nx, ny, seed=nx, theta=(theta, theta), u=0.03)
+        a, b = (Lattice(2, nx, ny, omega=1.6, storage=storage, velocities=v, theta0=theta).init(*fields)
+                for _ in range(2))
+        for n in (5, 4, 2):
+            a.step(n)
+        for _ in range(11):
+            b.step(1)
+        assert torch.equal(a.f, b.f) and a.cur == b.cur, (nx, ny)
