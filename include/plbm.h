@@ -190,12 +190,14 @@ int plbm_init3(const plbm_desc *d, const double *rho, const double *ux,
  *   f_i(x + v_i, t + 1) = (1 - omega) f_i(x, t) + omega f_eq_i(x, t),
  * each one a fused pull: gather f_k(x) = src_k(x - v_k), take rho, u, theta,
  * the Maxwell moments mu_0..mu_(q1d-1) per axis, the rule r = C mu per axis,
- * f_eq = rho r^x r^y, relax, and write dst at x.  Steps of one call may share
- * a launch; the populations are bitwise those of one launch per step.
+ * f_eq = rho r^x r^y, relax, and write dst at x.  Steps of one call but its
+ * last may share a launch; the populations are bitwise those of one launch
+ * per step.
  *   f_a, f_b : device pointers, two distinct buffers of plbm_buffer_elems(d)
- *              elements.  The result is in f_a when nsteps is even and in
- *              f_b when it is odd; the other buffer is scratch (after one
- *              step it still holds the state before).  nsteps >= 0.
+ *              elements.  Step s reads f_a and writes f_b when s is even,
+ *              the reverse when odd: the result is in f_a when nsteps is
+ *              even and in f_b when it is odd, and the other buffer holds the
+ *              state one step before.  nsteps >= 0.
  *   sums     : NULL, or a host pointer to 4 doubles (5 when dim = 3)
  *              receiving, after the last step, the FP64 sums over all nodes
  *              of the post-collision populations it wrote: sum f, sum f v_x,
@@ -218,6 +220,14 @@ int plbm_step(const plbm_desc *d, void *f_a, void *f_b, int nsteps,
               double *sums, void *stream);
 
 /*
+ * plbm_advance -- plbm_step for callers that read only the result: the same
+ * arguments, results and errors, but for nsteps > 1 the other buffer is
+ * scratch, so the last step may share a launch too.
+ */
+int plbm_advance(const plbm_desc *d, void *f_a, void *f_b, int nsteps,
+                 double *sums, void *stream);
+
+/*
  * plbm_step_fields -- plbm_step (without sums) whose first step also writes
  * the fields (rho, u_x, u_y, theta) of the state it reads, i.e. of the
  * state at the start of the call (Sec. 2: rho = sum f, rho u = sum f v,
@@ -235,6 +245,10 @@ int plbm_step(const plbm_desc *d, void *f_a, void *f_b, int nsteps,
  */
 int plbm_step_fields(const plbm_desc *d, void *f_a, void *f_b, int nsteps, double *rho,
                      double *ux, double *uy, double *theta, void *stream);
+
+/* plbm_advance_fields -- plbm_step_fields with plbm_advance's other buffer. */
+int plbm_advance_fields(const plbm_desc *d, void *f_a, void *f_b, int nsteps, double *rho,
+                        double *ux, double *uy, double *theta, void *stream);
 
 /*
  * plbm_step_noalloc -- plbm_step without any device allocation, for callers

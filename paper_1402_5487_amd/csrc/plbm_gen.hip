@@ -562,31 +562,32 @@ int gen_fused(const GenParams &p, void *fa, void *fb, int n, hipStream_t st)
     return launches * D;
 }
 
-// How many of n steps were taken several per launch, or a (negative) status:
-// all in 1D, in 2D those of the sets that have fused steps (in this order of
-// their velocities).
+// How many of n steps were taken, `fusable` of them several per launch, or a
+// (negative) status: all in 1D, in 2D those of the sets that have fused steps (in
+// this order of their velocities).
 template <int Q1, typename T>
-int fused_steps(const GenParams &p, void *fa, void *fb, int n, hipStream_t st)
+int fused_steps(const GenParams &p, void *fa, void *fb, int n, int fusable, hipStream_t st)
 {
     if (p.dim == 1) {
         int reach = 0;
         for (int i = 0; i < Q1; ++i) reach = std::max(reach, std::abs(p.sx[i]));
         (void)hipGetLastError();
-        run_tube<GenTube<Q1, T>>(p, fa, fb, n, reach, st);
+        run_tube<GenTube<Q1, T>>(p, fa, fb, n, fusable, reach, st);
         const int rc = gen_launch_status();
         return rc == PLBM_OK ? n : rc;
     }
-    if constexpr (Q1 == 4) return gen_fused<GenSet<T, 256, 1, -1, 3, -3>>(p, fa, fb, n, st);
+    if constexpr (Q1 == 4) return gen_fused<GenSet<T, 256, 1, -1, 3, -3>>(p, fa, fb, fusable, st);
     // 28 rows of six columns: what the LDS of one workgroup holds
     if constexpr (Q1 == 7)
-        return gen_fused<GenSet<T, sizeof(T) == 8 ? 112 : 232, 0, 1, -1, 2, -2, 3, -3>>(p, fa, fb, n, st);
+        return gen_fused<GenSet<T, sizeof(T) == 8 ? 112 : 232, 0, 1, -1, 2, -2, 3, -3>>(p, fa, fb, fusable, st);
     return 0;
 }
 
 template <int Q1, typename T>
-int gen_run(const GenParams &p, void *fa, void *fb, int nsteps, double *sums, hipStream_t st)
+int gen_run(const GenParams &p, void *fa, void *fb, int nsteps, const plbm::StepCall &call, hipStream_t st)
 {
-    const int s0 = fused_steps<Q1, T>(p, fa, fb, nsteps - (sums ? 1 : 0), st);
+    double *const sums = call.sums;
+    const int s0 = fused_steps<Q1, T>(p, fa, fb, nsteps - (sums ? 1 : 0), call.fusable(nsteps), st);
     if (s0 < 0) return s0;
     for (int s = s0; s < nsteps; ++s) {
         const T *src = static_cast<const T *>((s & 1) ? fb : fa);
@@ -679,15 +680,16 @@ int gen_init(const plbm_desc *d, const double *rho, const double *ux, const doub
     PLBM_GEN_DISPATCH(p, d->storage, gen_init_t, p, rho, ux, uy, theta, f, st);
 }
 
-int gen_step(const plbm_desc *d, void *fa, void *fb, int nsteps, double *sums, void *stream)
+int gen_step(const plbm_desc *d, void *fa, void *fb, int nsteps, const StepCall &call, void *stream)
 {
     GenParams p;
     const int rc = gen_params(d, p);
     if (rc != PLBM_OK) return rc;
     if (!fa || !fb || fa == fb || nsteps < 0) return PLBM_EINVAL;
-    if (nsteps == 0) return sums ? gen_moments(d, fa, nullptr, nullptr, nullptr, nullptr, sums, stream) : PLBM_OK;
+    if (nsteps == 0)
+        return call.sums ? gen_moments(d, fa, nullptr, nullptr, nullptr, nullptr, call.sums, stream) : PLBM_OK;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    PLBM_GEN_DISPATCH(p, d->storage, gen_run, p, fa, fb, nsteps, sums, st);
+    PLBM_GEN_DISPATCH(p, d->storage, gen_run, p, fa, fb, nsteps, call, st);
 }
 
 int gen_moments(const plbm_desc *d, const void *f, double *rho, double *ux, double *uy, double *theta,

@@ -27,12 +27,22 @@ int sums_begin(SumsArea &a, int nv, int &blocks, bool walks, void *stream);
 // checks the nv sums.
 int sums_end(SumsArea &a, int nv, int blocks, int rc, double *host, void *stream);
 
+// What a call of several steps asks for besides the state.
+struct StepCall {
+    double *sums = nullptr;   // host: the sums after the last step
+    bool keep = false;        // the other buffer ends with the state one step before
+    bool noalloc = false;     // sums wait for the library's scratch rather than allocate
+    // Of n steps, those that may share launches: not a last one that takes sums
+    // or reads the state that is kept.
+    int fusable(int n) const { return sums || keep ? n - 1 : n; }
+};
+
 // The isothermal three-velocity family (q1d = 3: D1Q3 and its tensor product
 // D2Q9), plbm_q3.hip; the public plbm_init / plbm_step / plbm_moments forward
 // to these.
 int q3_init(const plbm_desc *d, const double *rho, const double *ux, const double *uy, void *f,
             void *stream);
-int q3_step(const plbm_desc *d, void *f_a, void *f_b, int nsteps, double *sums, void *stream);
+int q3_step(const plbm_desc *d, void *f_a, void *f_b, int nsteps, const StepCall &call, void *stream);
 int q3_moments(const plbm_desc *d, const void *f, double *rho, double *ux, double *uy,
                double *theta, double *sums, void *stream);
 
@@ -42,7 +52,7 @@ int q3_moments(const plbm_desc *d, const void *f, double *rho, double *ux, doubl
 bool gen_handles(const plbm_desc *d);
 int gen_init(const plbm_desc *d, const double *rho, const double *ux, const double *uy,
              const double *theta, void *f, void *stream);
-int gen_step(const plbm_desc *d, void *f_a, void *f_b, int nsteps, double *sums, void *stream);
+int gen_step(const plbm_desc *d, void *f_a, void *f_b, int nsteps, const StepCall &call, void *stream);
 int gen_moments(const plbm_desc *d, const void *f, double *rho, double *ux, double *uy,
                 double *theta, double *sums, void *stream);
 

@@ -464,8 +464,8 @@ int launch_sweep(const KParams &p, const void *src, void *dst, hipStream_t st, F
 }
 
 template <class S>
-int run_steps(const KParams &p, const plbm_desc *d, void *fa, void *fb, int nsteps, double *sums, hipStream_t st,
-              bool noalloc);
+int run_steps(const KParams &p, const plbm_desc *d, void *fa, void *fb, int nsteps, const plbm::StepCall &call,
+              hipStream_t st);
 
 // Of n steps in launches of three, those that pairs take instead, an even number
 // of pairs (see fused_launches): a step or two left over cost more (FP32 4096^2:
@@ -489,7 +489,8 @@ int run_sweeps(const KParams &p, void *fa, void *fb, int launches, hipStream_t s
 // The first D of n steps, with the fields of the state they read; an even depth
 // takes a second launch for the state to be where so many single steps leave it.
 template <class S, int D>
-int run_sweeps_fields(const KParams &p, const plbm_desc *d, void *fa, void *fb, int n, FieldsOut fo, hipStream_t st)
+int run_sweeps_fields(const KParams &p, const plbm_desc *d, void *fa, void *fb, int n, FieldsOut fo,
+                      const plbm::StepCall &call, hipStream_t st)
 {
     int rc = launch_sweep<S, D, true>(p, fa, fb, st, fo);
     if (D % 2 == 0) {
@@ -499,7 +500,7 @@ int run_sweeps_fields(const KParams &p, const plbm_desc *d, void *fa, void *fb, 
         std::swap(fa, fb);
     }
     n -= D;
-    return rc == PLBM_OK && n > 0 ? run_steps<S>(p, d, fa, fb, n, nullptr, st, false) : rc;
+    return rc == PLBM_OK && n > 0 ? run_steps<S>(p, d, fa, fb, n, call, st) : rc;
 }
 
 // Which lattices take tiles of fused steps (plbm_tile.h) and which shape: the
@@ -562,22 +563,23 @@ int sweep_depth(const KParams &p, const plbm_desc *d)
     return 2;
 }
 
-// noalloc: sums wait for the library's scratch rather than allocate.
 template <class S>
-int run_steps(const KParams &p, const plbm_desc *d, void *fa, void *fb, int nsteps, double *sums,
-              hipStream_t st, bool noalloc)
+int run_steps(const KParams &p, const plbm_desc *d, void *fa, void *fb, int nsteps, const plbm::StepCall &call,
+              hipStream_t st)
 {
+    double *const sums = call.sums;
+    const int fusable = call.fusable(nsteps);
     int nb = 0;
     int s0 = 0;
     if (d->dim == 2 && use_tiles<S>(p)) {
-        int left = nsteps - (sums ? 1 : 0);                     // a step that takes sums is a single one
+        int left = fusable;
         clear_launch_error();
         tile_steps<S>(p, fa, fb, left, st);
         const int rc = launch_status();
         if (rc != PLBM_OK) return rc;
-        s0 = nsteps - (sums ? 1 : 0) - left;
+        s0 = fusable - left;
     } else if (const int depth = sweep_depth<S>(p, d); depth > 1) {
-        const int n = nsteps - (sums ? 1 : 0);
+        const int n = fusable;
         const int pairs = depth == 3 ? pairs_beside_threes(n) : fused_launches<2>(n);
         if constexpr (sizeof(typename S::T) == 4) {
             if (depth == 3) {
@@ -595,7 +597,7 @@ int run_steps(const KParams &p, const plbm_desc *d, void *fa, void *fb, int nste
         if (d->dim == 1) {
             s0 = nsteps - (sums ? 1 : 0);      // a step that takes sums is a single one
             clear_launch_error();
-            run_tube<Thermal5<S>>(p, fa, fb, s0, std::max(std::abs(p.sx[1]), std::abs(p.sx[3])), st);
+            run_tube<Thermal5<S>>(p, fa, fb, s0, fusable, std::max(std::abs(p.sx[1]), std::abs(p.sx[3])), st);
             const int rc = launch_status();
             if (rc != PLBM_OK) return rc;
         }
@@ -607,8 +609,8 @@ int run_steps(const KParams &p, const plbm_desc *d, void *fa, void *fb, int nste
         if (last && sums) {
             int blocks = d->dim == 2 ? grid_for(p.ntiles) : (p.nx + TX - 1) / TX;
             plbm::SumsArea area;
-            if (noalloc) blocks = std::min(blocks, NOALLOC_BLOCKS);
-            int rc = noalloc ? scratch_wait(area) : plbm::sums_begin(area, 4, blocks, d->dim == 2, st);
+            if (call.noalloc) blocks = std::min(blocks, NOALLOC_BLOCKS);
+            int rc = call.noalloc ? scratch_wait(area) : plbm::sums_begin(area, 4, blocks, d->dim == 2, st);
             if (rc != PLBM_OK) return rc;
             rc = launch_step<S, true>(p, d, src, dst, area.part, st, nb, blocks);
             return plbm::sums_end(area, 4, blocks, rc, sums, st);
@@ -623,14 +625,16 @@ int run_steps(const KParams &p, const plbm_desc *d, void *fa, void *fb, int nste
 // fused launch where those are taken, else a step of its own.
 template <class S>
 int run_steps_fields(const KParams &p, const plbm_desc *d, void *fa, void *fb, int nsteps, FieldsOut fo,
-                     hipStream_t st)
+                     const plbm::StepCall &call, hipStream_t st)
 {
     using T = typename S::T;
+    const int fusable = call.fusable(nsteps);
     const int depth = use_tiles<S>(p) ? 1 : sweep_depth<S>(p, d);
     if constexpr (sizeof(T) == 4)
-        if (depth == 3 && nsteps - 2 * pairs_beside_threes(nsteps) >= 3)
-            return run_sweeps_fields<S, 3>(p, d, fa, fb, nsteps, fo, st);
-    if (depth > 1 && fused_launches<2>(nsteps) > 0) return run_sweeps_fields<S, 2>(p, d, fa, fb, nsteps, fo, st);
+        if (depth == 3 && fusable - 2 * pairs_beside_threes(fusable) >= 3)
+            return run_sweeps_fields<S, 3>(p, d, fa, fb, nsteps, fo, call, st);
+    if (depth > 1 && fused_launches<2>(fusable) > 0)
+        return run_sweeps_fields<S, 2>(p, d, fa, fb, nsteps, fo, call, st);
     clear_launch_error();
     const size_t lds = sizeof(T) == 2 ? (d->rounding == PLBM_ROUND_STOCHASTIC ? PLBM_LDS_CAP_16SR : PLBM_LDS_CAP_16)
                                       : PLBM_LDS_CAP_WIDE;
@@ -639,7 +643,7 @@ int run_steps_fields(const KParams &p, const plbm_desc *d, void *fa, void *fb, i
                              : (nts ? k_step2d_fields<S, 1, true> : k_step2d_fields<S, 1, false>);
     hipLaunchKernelGGL(kernel, dim3(grid_for(p.ntiles)), dim3(TX), lds, st, (const T *)fa, (T *)fb, p, fo);
     const int rc = launch_status();
-    return rc == PLBM_OK && nsteps > 1 ? run_steps<S>(p, d, fb, fa, nsteps - 1, nullptr, st, false) : rc;
+    return rc == PLBM_OK && nsteps > 1 ? run_steps<S>(p, d, fb, fa, nsteps - 1, call, st) : rc;
 }
 
 template <class S>
@@ -694,16 +698,16 @@ int init_dispatch(const KParams &p, const plbm_desc *d, const double *rho, const
     PLBM_DISPATCH(d, launch_init, p, d, rho, ux, uy, th, f, st);
 }
 
-int step_dispatch(const KParams &p, const plbm_desc *d, void *fa, void *fb, int n, double *sums,
-                  hipStream_t st, bool noalloc = false)
+int step_dispatch(const KParams &p, const plbm_desc *d, void *fa, void *fb, int n, const plbm::StepCall &call,
+                  hipStream_t st)
 {
-    PLBM_DISPATCH(d, run_steps, p, d, fa, fb, n, sums, st, noalloc);
+    PLBM_DISPATCH(d, run_steps, p, d, fa, fb, n, call, st);
 }
 
 int step_fields_dispatch(const KParams &p, const plbm_desc *d, void *fa, void *fb, int n, FieldsOut fo,
-                         hipStream_t st)
+                         const plbm::StepCall &call, hipStream_t st)
 {
-    PLBM_DISPATCH(d, run_steps_fields, p, d, fa, fb, n, fo, st);
+    PLBM_DISPATCH(d, run_steps_fields, p, d, fa, fb, n, fo, call, st);
 }
 
 int moments_dispatch(const KParams &p, const plbm_desc *d, const void *f, double *rho, double *ux,
@@ -792,25 +796,26 @@ extern "C" int plbm_init(const plbm_desc *d, const double *rho, const double *ux
     return init_dispatch(p, d, rho, ux, uy, theta, f, as_stream(stream));
 }
 
-extern "C" int plbm_step(const plbm_desc *d, void *f_a, void *f_b, int nsteps, double *sums,
-                         void *stream)
+namespace {
+int step_entry(const plbm_desc *d, void *f_a, void *f_b, int nsteps, const plbm::StepCall &call, void *stream)
 {
-    if (d && d->dim == 3) return plbm::q125_step(d, f_a, f_b, nsteps, sums, stream);
-    if (plbm::gen_handles(d)) return plbm::gen_step(d, f_a, f_b, nsteps, sums, stream);
-    if (d && d->q1d == 3) return plbm::q3_step(d, f_a, f_b, nsteps, sums, stream);
+    // a step of its own leaves the state before where it read it
+    if (d && d->dim == 3) return plbm::q125_step(d, f_a, f_b, nsteps, call.sums, stream);
+    if (plbm::gen_handles(d)) return plbm::gen_step(d, f_a, f_b, nsteps, call, stream);
+    if (d && d->q1d == 3) return plbm::q3_step(d, f_a, f_b, nsteps, call, stream);
     KParams p;
     int rc = make_params(d, p);
     if (rc != PLBM_OK) return rc;
     if (!f_a || !f_b || f_a == f_b || nsteps < 0) return PLBM_EINVAL;
     if (nsteps == 0) {
-        if (sums) return plbm_moments(d, f_a, nullptr, nullptr, nullptr, nullptr, sums, stream);
+        if (call.sums) return plbm_moments(d, f_a, nullptr, nullptr, nullptr, nullptr, call.sums, stream);
         return PLBM_OK;
     }
-    return step_dispatch(p, d, f_a, f_b, nsteps, sums, as_stream(stream));
+    return step_dispatch(p, d, f_a, f_b, nsteps, call, as_stream(stream));
 }
 
-extern "C" int plbm_step_fields(const plbm_desc *d, void *f_a, void *f_b, int nsteps, double *rho, double *ux,
-                                double *uy, double *theta, void *stream)
+int step_fields_entry(const plbm_desc *d, void *f_a, void *f_b, int nsteps, FieldsOut fo,
+                      const plbm::StepCall &call, void *stream)
 {
     if (!d) return PLBM_EINVAL;
     if (d->dim != 2 || plbm::gen_handles(d) || d->q1d != Q) return PLBM_EUNSUPPORTED;
@@ -818,8 +823,38 @@ extern "C" int plbm_step_fields(const plbm_desc *d, void *f_a, void *f_b, int ns
     int rc = make_params(d, p);
     if (rc != PLBM_OK) return rc;
     if (!f_a || !f_b || f_a == f_b || nsteps < 1) return PLBM_EINVAL;
-    FieldsOut fo = {{rho, ux, uy, theta}};
-    return step_fields_dispatch(p, d, f_a, f_b, nsteps, fo, as_stream(stream));
+    return step_fields_dispatch(p, d, f_a, f_b, nsteps, fo, call, as_stream(stream));
+}
+} // namespace
+
+extern "C" int plbm_step(const plbm_desc *d, void *f_a, void *f_b, int nsteps, double *sums,
+                         void *stream)
+{
+    plbm::StepCall call;
+    call.sums = sums;
+    call.keep = true;
+    return step_entry(d, f_a, f_b, nsteps, call, stream);
+}
+
+extern "C" int plbm_advance(const plbm_desc *d, void *f_a, void *f_b, int nsteps, double *sums, void *stream)
+{
+    plbm::StepCall call;
+    call.sums = sums;
+    return step_entry(d, f_a, f_b, nsteps, call, stream);
+}
+
+extern "C" int plbm_step_fields(const plbm_desc *d, void *f_a, void *f_b, int nsteps, double *rho, double *ux,
+                                double *uy, double *theta, void *stream)
+{
+    plbm::StepCall call;
+    call.keep = true;
+    return step_fields_entry(d, f_a, f_b, nsteps, FieldsOut{{rho, ux, uy, theta}}, call, stream);
+}
+
+extern "C" int plbm_advance_fields(const plbm_desc *d, void *f_a, void *f_b, int nsteps, double *rho, double *ux,
+                                   double *uy, double *theta, void *stream)
+{
+    return step_fields_entry(d, f_a, f_b, nsteps, FieldsOut{{rho, ux, uy, theta}}, plbm::StepCall{}, stream);
 }
 
 extern "C" int plbm_step_noalloc(const plbm_desc *d, void *f_a, void *f_b, int nsteps,
@@ -834,10 +869,13 @@ extern "C" int plbm_step_noalloc(const plbm_desc *d, void *f_a, void *f_b, int n
     // the 1D kernels run one workgroup per 256 nodes: at most NOALLOC_BLOCKS
     // of them fit the scratch when sums are asked for
     if (sums && d->dim == 1 && (p.nx + TX - 1) / TX > NOALLOC_BLOCKS) return PLBM_EINVAL;
-    if (!sums) return nsteps ? step_dispatch(p, d, f_a, f_b, nsteps, nullptr, as_stream(stream))
-                             : PLBM_OK;
     hipStream_t st = as_stream(stream);
-    if (nsteps > 0) return step_dispatch(p, d, f_a, f_b, nsteps, sums, st, true);
+    plbm::StepCall call;
+    call.sums = sums;
+    call.keep = true;
+    call.noalloc = true;
+    if (nsteps > 0) return step_dispatch(p, d, f_a, f_b, nsteps, call, st);
+    if (!sums) return PLBM_OK;
     plbm::SumsArea area;
     rc = scratch_wait(area);
     if (rc != PLBM_OK) return rc;

@@ -481,22 +481,23 @@ bool use_sweeps(const Q9Params &p)
 }
 
 template <typename T, typename C>
-int q9_run(const Q9Params &p, void *fa, void *fb, int nsteps, double *sums, hipStream_t st)
+int q9_run(const Q9Params &p, void *fa, void *fb, int nsteps, const plbm::StepCall &call, hipStream_t st)
 {
+    double *const sums = call.sums;
+    const int fusable = call.fusable(nsteps);
     const int nblocks = p.dim == 2 ? grid_for(p.ntiles) : p.tiles_x;
     int s0 = 0, launches = 0;
     if (p.dim == 2 && use_tiles(p)) {
-        int left = nsteps - (sums ? 1 : 0);
+        int left = fusable;
         (void)hipGetLastError();
         tile_steps_q9<T>(p, fa, fb, left, st);
         const int rc = q9_launch_status();
         if (rc != PLBM_OK) return rc;
-        s0 = nsteps - (sums ? 1 : 0) - left;
+        s0 = fusable - left;
     } else if (p.dim == 2 && use_sweeps<T>(p)) {
-        // D steps a launch, then three, and the rest (and a step that takes
-        // sums) one by one
+        // D steps a launch, then three, and the rest one by one
         using M = Iso9<T>;
-        const int n = nsteps - (sums ? 1 : 0);
+        const int n = fusable;
         const int deep = fused_launches<Q9_DEPTH<T>>(n), three = (n - deep * Q9_DEPTH<T>) / 3;
         for (; launches < deep + three; ++launches) {
             const T *src = static_cast<const T *>((launches & 1) ? fb : fa);
@@ -510,7 +511,7 @@ int q9_run(const Q9Params &p, void *fa, void *fb, int nsteps, double *sums, hipS
     if (p.dim == 1) {
         s0 = nsteps - (sums ? 1 : 0);
         (void)hipGetLastError();
-        run_tube<Iso3<T>>(p, fa, fb, s0, p.sx[1], st);
+        run_tube<Iso3<T>>(p, fa, fb, s0, fusable, p.sx[1], st);
         const int rc = q9_launch_status();
         if (rc != PLBM_OK) return rc;
     }
@@ -562,16 +563,17 @@ int q3_init(const plbm_desc *d, const double *rho, const double *ux, const doubl
     return q9_launch_status();
 }
 
-int q3_step(const plbm_desc *d, void *fa, void *fb, int nsteps, double *sums, void *stream)
+int q3_step(const plbm_desc *d, void *fa, void *fb, int nsteps, const StepCall &call, void *stream)
 {
     Q9Params p;
     const int rc = q9_params(d, p);
     if (rc != PLBM_OK) return rc;
     if (!fa || !fb || fa == fb || nsteps < 0) return PLBM_EINVAL;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    if (nsteps == 0) return sums ? q3_moments(d, fa, nullptr, nullptr, nullptr, nullptr, sums, stream) : PLBM_OK;
-    if (d->storage == PLBM_F64) return q9_run<double, double>(p, fa, fb, nsteps, sums, st);
-    return q9_run<float, float>(p, fa, fb, nsteps, sums, st);
+    if (nsteps == 0)
+        return call.sums ? q3_moments(d, fa, nullptr, nullptr, nullptr, nullptr, call.sums, stream) : PLBM_OK;
+    if (d->storage == PLBM_F64) return q9_run<double, double>(p, fa, fb, nsteps, call, st);
+    return q9_run<float, float>(p, fa, fb, nsteps, call, st);
 }
 
 int q3_moments(const plbm_desc *d, const void *f, double *rho, double *ux, double *uy, double *theta,

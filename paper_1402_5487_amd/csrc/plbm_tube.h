@@ -127,11 +127,17 @@ __global__ __launch_bounds__(TUBE_T) void k_tube(const typename M::T *src, typen
     tube<M>(src, dst, p, x0, min(x0 + tile, p.nx), reach, steps, reinterpret_cast<typename M::T *>(tube_lds));
 }
 
-// n steps; the result is in fa when n is even and in fb when it is odd.
+// n steps, of which the first `fusable` may share launches and a last one beyond
+// them is a launch of its own; the result is in fa when n is even and in fb when
+// it is odd.
 template <class M>
-void run_tube(const typename M::P &p, void *fa, void *fb, int n, int reach, hipStream_t st)
+void run_tube(const typename M::P &p, void *fa, void *fb, int n, int fusable, int reach, hipStream_t st)
 {
     using T = typename M::T;
+    if (n > fusable) {
+        run_tube<M>(p, fa, fb, fusable, fusable, reach, st);
+        return run_tube<M>(p, (fusable & 1) ? fb : fa, (fusable & 1) ? fa : fb, 1, 1, reach, st);
+    }
     if (n < 1) return;
     const TubePlan t = tube_plan<M>(p.nx, n, reach);
     for (int k = 0; k < t.launches; ++k) {

@@ -28,6 +28,8 @@ class Lattice:
     storage: "f64", "f32", "f16dev" or "bf16dev" (16-bit deviations from the
     rest state rho0 w_k with per-plane power-of-two scales; D2Q25 only).
     rounding: "nearest" or "stochastic" (16-bit deviations only).
+
+    `f` is the state; the other of the two `bufs` is scratch between calls.
     """
 
     def __init__(self, dim, nx, ny=1, omega=1.0, storage="f64", device="cuda:0",
@@ -88,7 +90,7 @@ class Lattice:
 
     def step(self, nsteps=1, sums=False):
         fa, fb = self.bufs[self.cur], self.bufs[1 - self.cur]
-        out = _plbm.step(self.desc, fa, fb, nsteps, sums, self.stream)
+        out = _plbm.advance(self.desc, fa, fb, nsteps, sums, self.stream)
         if nsteps % 2 == 1:
             self.cur = 1 - self.cur
         self.t += nsteps
@@ -102,7 +104,7 @@ class Lattice:
             out = tuple(torch.empty((self.ny, self.nx), dtype=torch.float64, device=self.device)
                         for _ in range(4))
         fa, fb = self.bufs[self.cur], self.bufs[1 - self.cur]
-        _plbm.step_fields(self.desc, fa, fb, nsteps, *out, self.stream)
+        _plbm.advance_fields(self.desc, fa, fb, nsteps, *out, self.stream)
         if nsteps % 2 == 1:
             self.cur = 1 - self.cur
         self.t += nsteps

@@ -34,8 +34,8 @@ class Recorder:
         lib.rec_bytes.restype = ctypes.c_longlong
         lib.rec_allow_mallocs.argtypes = [ctypes.c_longlong]
         P, vp, D = ctypes.POINTER(_plbm.PlbmDesc), ctypes.c_void_p, ctypes.POINTER(ctypes.c_double)
-        lib.plbm_step.argtypes = [P, vp, vp, ctypes.c_int, D, vp]
-        lib.plbm_step_noalloc.argtypes = [P, vp, vp, ctypes.c_int, D, vp]
+        for f in (lib.plbm_step, lib.plbm_advance, lib.plbm_step_noalloc):
+            f.argtypes = [P, vp, vp, ctypes.c_int, D, vp]
         lib.plbm_step_fields.argtypes = [P, vp, vp, ctypes.c_int, vp, vp, vp, vp, vp]
         _plbm._setup_batch(lib)
 

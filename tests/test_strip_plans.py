@@ -48,3 +48,37 @@ def test_strips_write_every_node_once(recorder, model, storage, nx):  # noqa: F8
                 own = _owners(recorder, launch, nx, ny)
                 assert own.min() == 1 and own.max() == 1, (ny, launch.extra, launch.block)
                 seen += 1
+
+
+# what a step of its own launches
+SINGLE = {"k_step2d", "k_step2d_fields", "k_step_q9", "k_step_gen2d", "k_step1d_sums", "k_step_q3_1d_sums",
+          "k_step_gen1d_sums", "k_step3d"}
+SIZES = {1: [(7, 1), (1000, 1), (1025, 1), (70000, 1)],
+         2: [(8, 9), (64, 64), (129, 127), (300, 400), (28, 10000), (900, 1300), (1501, 1100)]}
+
+
+@pytest.mark.parametrize("model,storage,entry", [
+    (m, st, e) for m, st in FORMS + [("d1q5", "f64"), ("d1q3", "f32"), ("d1q7", "f64")]
+    for e in ("plbm_step", "plbm_advance", "plbm_step_noalloc") if e != "plbm_step_noalloc" or m in ("d2q25", "d1q5")])
+def test_launches_hand_the_state_on_and_end_where_steps_do(recorder, model, storage, entry):  # noqa: F811
+    """Each launch reads what the one before wrote (a 1D lattice in place too),
+    the last writes the buffer that the number of steps says, and of the calls
+    that keep the state before it is a single step."""
+    dim = int(model[1])
+    tube = {"d1q5": lambda nx, ny, st: _plbm.desc_default(1, nx, 1, 1.2, st),
+            "d1q3": lambda nx, ny, st: _plbm.desc_q3(1, nx, 1, 1.2, st, zeta=4.0),
+            "d1q7": lambda nx, ny, st: _plbm.desc_general(1, nx, 1, 1.2, st, V49, 1.0)}
+    for nx, ny in SIZES[dim]:
+        d = (MODELS.get(model) or tube[model])(nx, ny, storage)
+        for n in list(range(1, 14)) + [40, 41]:
+            for sums in (False, True):
+                at = 0x1000
+                ls = [x for x in recorder.step(d, n, entry, sums) if x.kernel != "k_reduce_partials"]
+                for x in ls:
+                    assert x.src == at and x.block <= 1024 and x.lds <= 160 * 1024, (nx, ny, n, x.name)
+                    at = x.dst
+                assert at == (0x1000 if n % 2 == 0 else 0x2000), (nx, ny, n)
+                if entry != "plbm_advance":
+                    last = ls[-1]
+                    assert last.src != last.dst
+                    assert last.kernel in SINGLE or (last.kernel == "k_tube" and last.extra[2] == 1), (nx, ny, n, last.name)
