@@ -596,7 +596,7 @@ int gen_run(const GenParams &p, void *fa, void *fb, int nsteps, const plbm::Step
         if (s == nsteps - 1 && sums) {
             int blocks = grid_g(p);
             plbm::SumsArea area;
-            int rc = plbm::sums_begin(area, 4, blocks, true, st);
+            int rc = plbm::sums_begin(area, 4, blocks, st);
             if (rc != PLBM_OK) return rc;
             gen_launch<Q1, T, true>(p, src, dst, area.part, st, blocks);
             rc = gen_launch_status();
@@ -629,7 +629,7 @@ int gen_moments_t(const GenParams &p, const void *f, double *rho, double *ux, do
     int grid = p.dim == 2 ? grid_g(p) : p.tiles_x;
     plbm::SumsArea area;
     if (sums) {
-        const int rc = plbm::sums_begin(area, 4, grid, p.dim == 2, st);
+        const int rc = plbm::sums_begin(area, 4, grid, st);
         if (rc != PLBM_OK) return rc;
     }
     (void)hipGetLastError();

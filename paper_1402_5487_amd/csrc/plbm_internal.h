@@ -12,17 +12,15 @@ void note_hip_error(const char *what, int code);
 
 // Device memory for the partial sums of one call that asks for sums (`blocks`
 // workgroups, nv doubles each, and nv results).  It is the library's static
-// scratch while that is free and the stream belongs to the current device
-// (allocating and freeing took 18 us of a 50 us call), else a stream-ordered
-// allocation.  walks: the kernel may run fewer workgroups than `blocks`, which
-// is then lowered to what the scratch holds partials of.  Every sums_begin that returned
-// PLBM_OK is followed by sums_end, which synchronises the stream before it
-// gives the memory back.
+// scratch while that is free, holds so many and the stream belongs to the
+// current device (allocating and freeing took 18 us of a 50 us call), else a
+// stream-ordered allocation.  Every sums_begin that returned PLBM_OK is followed
+// by sums_end, which synchronises the stream before it gives the memory back.
 struct SumsArea {
     double *part = nullptr;
     int device = -1;          // whose scratch is held (-1: allocated)
 };
-int sums_begin(SumsArea &a, int nv, int &blocks, bool walks, void *stream);
+int sums_begin(SumsArea &a, int nv, int blocks, void *stream);
 // rc: the status of the launches so far; reduces the partials, fetches and
 // checks the nv sums.
 int sums_end(SumsArea &a, int nv, int blocks, int rc, double *host, void *stream);

@@ -610,7 +610,7 @@ int run_steps(const KParams &p, const plbm_desc *d, void *fa, void *fb, int nste
             int blocks = d->dim == 2 ? grid_for(p.ntiles) : (p.nx + TX - 1) / TX;
             plbm::SumsArea area;
             if (call.noalloc) blocks = std::min(blocks, NOALLOC_BLOCKS);
-            int rc = call.noalloc ? scratch_wait(area) : plbm::sums_begin(area, 4, blocks, d->dim == 2, st);
+            int rc = call.noalloc ? scratch_wait(area) : plbm::sums_begin(area, 4, blocks, st);
             if (rc != PLBM_OK) return rc;
             rc = launch_step<S, true>(p, d, src, dst, area.part, st, nb, blocks);
             return plbm::sums_end(area, 4, blocks, rc, sums, st);
@@ -738,12 +738,11 @@ void note_hip_error(const char *what, int code)
     std::snprintf(g_last_error, sizeof(g_last_error), "%s (%d)", what, code);
 }
 
-int sums_begin(SumsArea &a, int nv, int &blocks, bool walks, void *stream)
+int sums_begin(SumsArea &a, int nv, int blocks, void *stream)
 {
     hipStream_t st = as_stream(stream);
     constexpr int held = (NOALLOC_BLOCKS + 1) * 4;
     const int most = held / nv - 1;
-    if (walks) blocks = std::min(blocks, most);       // wherever the partials are: the sums do not depend on it
     int dev = -1, of = -1;
     if (blocks <= most && hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < MAX_DEVICES &&
         (!st || (hipStreamGetDevice(st, &of) == hipSuccess && of == dev)) && g_scratch[dev].mu.try_lock()) {
@@ -900,7 +899,7 @@ extern "C" int plbm_moments(const plbm_desc *d, const void *f, double *rho, doub
     if (!sums) return moments_dispatch(p, d, f, rho, ux, uy, theta, nullptr, st, nb);
     int blocks = d->dim == 2 ? grid_for((long long)((p.nx + TX - 1) / TX) * p.ny) : (p.nx + TX - 1) / TX;
     plbm::SumsArea area;
-    rc = plbm::sums_begin(area, 4, blocks, d->dim == 2, st);
+    rc = plbm::sums_begin(area, 4, blocks, st);
     if (rc != PLBM_OK) return rc;
     rc = moments_dispatch(p, d, f, rho, ux, uy, theta, area.part, st, nb, blocks);
     return plbm::sums_end(area, 4, blocks, rc, sums, st);

@@ -365,7 +365,7 @@ int q125_run(const P3 &p, void *fa, void *fb, int nsteps, double *sums, hipStrea
         if (s == nsteps - 1 && sums) {
             int blocks = grid;
             plbm::SumsArea area;
-            int rc = plbm::sums_begin(area, 5, blocks, true, st);
+            int rc = plbm::sums_begin(area, 5, blocks, st);
             if (rc != PLBM_OK) return rc;
             hipLaunchKernelGGL((step3_kernel<T, true>(p)), dim3(blocks), dim3(TX), lds_cap<T>(), st, src, dst, p,
                                area.part);
@@ -427,7 +427,7 @@ extern "C" int plbm_moments3(const plbm_desc *d, const void *f, double *rho, dou
     int grid = grid_of(p);
     plbm::SumsArea area;
     if (sums) {
-        rc = plbm::sums_begin(area, 5, grid, true, st);
+        rc = plbm::sums_begin(area, 5, grid, st);
         if (rc != PLBM_OK) return rc;
     }
     double *part = area.part;

@@ -522,7 +522,7 @@ int q9_run(const Q9Params &p, void *fa, void *fb, int nsteps, const plbm::StepCa
         if (s == nsteps - 1 && sums) {
             int blocks = nblocks;
             plbm::SumsArea area;
-            int rc = plbm::sums_begin(area, 4, blocks, p.dim == 2, st);
+            int rc = plbm::sums_begin(area, 4, blocks, st);
             if (rc != PLBM_OK) return rc;
             q3_launch<T, C, true>(p, src, dst, area.part, st, blocks);
             rc = q9_launch_status();
@@ -587,7 +587,7 @@ int q3_moments(const plbm_desc *d, const void *f, double *rho, double *ux, doubl
     int blocks = p.dim == 2 ? grid_for(p.ntiles) : p.tiles_x;
     plbm::SumsArea area;
     if (sums) {
-        rc = plbm::sums_begin(area, 4, blocks, p.dim == 2, st);
+        rc = plbm::sums_begin(area, 4, blocks, st);
         if (rc != PLBM_OK) return rc;
     }
     const dim3 g(blocks);

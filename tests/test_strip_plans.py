@@ -82,3 +82,13 @@ def test_launches_hand_the_state_on_and_end_where_steps_do(recorder, model, stor
                     last = ls[-1]
                     assert last.src != last.dst
                     assert last.kernel in SINGLE or (last.kernel == "k_tube" and last.extra[2] == 1), (nx, ny, n, last.name)
+
+
+@pytest.mark.parametrize("nx,ny", [(4096, 4096), (257, 4200), (64, 64)])
+@pytest.mark.parametrize("model,storage", [f for f in FORMS if f[1] != "f16dev"])
+def test_sums_take_a_workgroup_per_row_tile(recorder, model, storage, nx, ny):  # noqa: F811
+    """However many partials that makes: a lane that walked several tiles would
+    add them up uncompensated."""
+    last = [x for x in recorder.step(MODELS[model](nx, ny, storage), 2, sums=True) if x.kernel in SINGLE][-1]
+    assert last.grid == -(-nx // 256) * ny
+    assert recorder.lib.rec_bytes() == 0
