@@ -268,10 +268,12 @@ int plbm_advance_fields(const plbm_desc *d, void *f_a, void *f_b, int nsteps, do
  * lattice with sums may have at most 8192 * 256 = 2,097,152 nodes
  * (PLBM_EINVAL beyond, before any launch); without sums no scratch is used
  * and plbm_step's limits apply.
- * One call on a GPU holds its scratch at a time: a call that asks for sums
- * waits for one that overlaps with it on that GPU (other streams or threads).
- * plbm_step and plbm_moments take their partial sums there too while it is
- * free, and allocate otherwise.  Calls without sums do not touch it.
+ * One call on a GPU holds that scratch at a time: a call that asks for sums
+ * waits for another plbm_step_noalloc with sums that overlaps with it on that
+ * GPU (other streams or threads).  It waits for no other call: plbm_step and
+ * plbm_moments keep their partial sums in a second such array while that is
+ * free, and in an allocation otherwise.  Calls without sums do not touch
+ * either.
  */
 int plbm_step_noalloc(const plbm_desc *d, void *f_a, void *f_b, int nsteps,
                       double *sums, void *stream);

@@ -1,6 +1,8 @@
 // Internal declarations shared by the host and device translation units of
 // libplbm (not part of the public ABI).
 #pragma once
+#include <mutex>
+
 #include "plbm.h"
 
 namespace plbm {
@@ -18,7 +20,7 @@ void note_hip_error(const char *what, int code);
 // by sums_end, which synchronises the stream before it gives the memory back.
 struct SumsArea {
     double *part = nullptr;
-    int device = -1;          // whose scratch is held (-1: allocated)
+    std::mutex *held = nullptr;   // of the scratch in use (null: allocated)
 };
 int sums_begin(SumsArea &a, int nv, int blocks, void *stream);
 // rc: the status of the launches so far; reduces the partials, fetches and

@@ -47,15 +47,17 @@
 #include "plbm_tile.h"
 #include "plbm_tube.h"
 
-// Scratch of the calls that ask for sums: the per-workgroup FP64 partial sums
-// of the launch (at most NOALLOC_BLOCKS workgroups, four doubles each) and the
-// four reduced sums behind them; one call at a time holds it (see sums_begin).  Each GPU the library runs on holds its own
-// copy until the process ends.  Every workgroup of a sums launch writes its
-// own four partials before the reduction reads them, so nothing in it has to
-// start at zero.  Host code must not use this name as a device address: it
+// Scratch of the calls that ask for sums, one array for plbm_step_noalloc and one
+// for the others: the per-workgroup FP64 partial sums of the launch (at most
+// NOALLOC_BLOCKS workgroups, four doubles each) and the four reduced sums behind
+// them; one call at a time holds an array (see sums_begin).  Each GPU the library
+// runs on holds its own copies until the process ends.  Every workgroup of a
+// sums launch writes its own four partials before the reduction reads them, so
+// nothing in it has to start at zero.  Host code must not use this name as a device address: it
 // takes the address hipGetSymbolAddress returns for the current device.
 constexpr int NOALLOC_BLOCKS = 8192;
-static __device__ __align__(256) double scratch[(NOALLOC_BLOCKS + 1) * 4];
+constexpr int SCRATCH_ELEMS = (NOALLOC_BLOCKS + 1) * 4;
+static __device__ __align__(256) double scratch[2 * SCRATCH_ELEMS];
 
 namespace {
 
@@ -380,42 +382,47 @@ int hip_ok(hipError_t e)
 inline void clear_launch_error() { (void)hipGetLastError(); }
 inline int launch_status() { return hip_ok(hipGetLastError()); }
 
-// Each device's scratch array: who holds it, and its device address, looked up
-// once (with that device current) and kept.
+// Each device's scratch arrays: who holds one, and its device address, looked up
+// once (with that device current) and kept.  plbm_step_noalloc's own comes first:
+// a call that may not allocate waits for others of its kind only, never for the
+// end of a plbm_step on another stream.
 constexpr int MAX_DEVICES = 64;
 struct Scratch {
     std::mutex mu;
     double *dev = nullptr;
 };
-Scratch g_scratch[MAX_DEVICES];
+Scratch g_scratch[2][MAX_DEVICES];
 
-// The address of the current device's scratch, whose lock the caller holds.
-int scratch_address(Scratch &s)
+// The address of the current device's scratch of a kind, whose lock the caller
+// holds.
+int scratch_address(Scratch &s, int kind)
 {
     if (s.dev) return PLBM_OK;
     void *ptr = nullptr;
     const int rc = hip_ok(hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)));
     if (rc != PLBM_OK) return rc;
     if (!ptr) return PLBM_EHIP;
-    s.dev = static_cast<double *>(ptr);
+    s.dev = static_cast<double *>(ptr) + kind * SCRATCH_ELEMS;
     return PLBM_OK;
 }
 
-// Takes the scratch of the current device, waiting for whoever holds it.
+// Takes plbm_step_noalloc's scratch of the current device, waiting for whoever
+// holds it.
 int scratch_wait(plbm::SumsArea &a)
 {
     int dev = -1;
     int rc = hip_ok(hipGetDevice(&dev));
     if (rc != PLBM_OK) return rc;
     if (dev < 0 || dev >= MAX_DEVICES) return PLBM_EUNSUPPORTED;
-    g_scratch[dev].mu.lock();
-    rc = scratch_address(g_scratch[dev]);
+    Scratch &s = g_scratch[0][dev];
+    s.mu.lock();
+    rc = scratch_address(s, 0);
     if (rc != PLBM_OK) {
-        g_scratch[dev].mu.unlock();
+        s.mu.unlock();
         return rc;
     }
-    a.part = g_scratch[dev].dev;
-    a.device = dev;
+    a.part = s.dev;
+    a.held = &s.mu;
     return PLBM_OK;
 }
 
@@ -741,19 +748,18 @@ void note_hip_error(const char *what, int code)
 int sums_begin(SumsArea &a, int nv, int blocks, void *stream)
 {
     hipStream_t st = as_stream(stream);
-    constexpr int held = (NOALLOC_BLOCKS + 1) * 4;
-    const int most = held / nv - 1;
+    const int most = SCRATCH_ELEMS / nv - 1;
     int dev = -1, of = -1;
     if (blocks <= most && hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < MAX_DEVICES &&
-        (!st || (hipStreamGetDevice(st, &of) == hipSuccess && of == dev)) && g_scratch[dev].mu.try_lock()) {
-        if (scratch_address(g_scratch[dev]) == PLBM_OK) {
-            a.part = g_scratch[dev].dev;
-            a.device = dev;
+        (!st || (hipStreamGetDevice(st, &of) == hipSuccess && of == dev)) && g_scratch[1][dev].mu.try_lock()) {
+        Scratch &s = g_scratch[1][dev];
+        if (scratch_address(s, 1) == PLBM_OK) {
+            a.part = s.dev;
+            a.held = &s.mu;
             return PLBM_OK;
         }
-        g_scratch[dev].mu.unlock();
+        s.mu.unlock();
     }
-    a.device = -1;
     return hip_ok(hipMallocAsync((void **)&a.part, ((size_t)blocks + 1) * nv * sizeof(double), st));
 }
 
@@ -772,7 +778,7 @@ int sums_end(SumsArea &a, int nv, int blocks, int rc, double *host, void *stream
     if (rc == PLBM_OK) rc = hip_ok(hipMemcpyAsync(host, out, nv * sizeof(double), hipMemcpyDeviceToHost, st));
     const int done = hip_ok(hipStreamSynchronize(st));
     if (rc == PLBM_OK) rc = done;
-    if (a.device >= 0) g_scratch[a.device].mu.unlock();
+    if (a.held) a.held->unlock();
     else (void)hipFreeAsync(a.part, st);
     a = SumsArea{};
     if (rc != PLBM_OK) return rc;

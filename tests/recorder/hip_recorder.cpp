@@ -4,10 +4,12 @@
 // which buffer each launch reads and writes.  Device memory is host memory.
 #include <hip/hip_runtime.h>
 
+#include <condition_variable>
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -30,6 +32,10 @@ std::map<const void *, std::string> &kernels()
 }
 std::vector<Launch> launches;
 long long bytes_held = 0, mallocs_left = -1;
+std::mutex mu;                     // of what follows and of the launches
+std::condition_variable changed;
+hipStream_t busy = nullptr;        // a stream whose synchronisation waits
+bool waiting = false;              // somebody does
 struct {
     dim3 grid, block;
     size_t lds;
@@ -90,6 +96,7 @@ hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, si
         for (int k = 0; k < 3; ++k) l.extra[k] = *(int *)args[3 + k];
     else if (is("k_step2d_sweep") || is("k_sweep_q9") || is("k_pair_gen"))
         std::memcpy(l.extra, args[3], sizeof(SweepGrid));
+    std::lock_guard<std::mutex> lock(mu);
     launches.push_back(l);
     return hipSuccess;
 }
@@ -129,14 +136,24 @@ hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int)
 }
 hipError_t hipGetSymbolAddress(void **p, const void *)
 {
-    static double scratch[(8192 + 1) * 4];
+    static double scratch[2 * (8192 + 1) * 4];
     *p = scratch;
     return hipSuccess;
 }
 const char *hipGetErrorString(hipError_t) { return "recorded"; }
 hipError_t hipGetLastError() { return hipSuccess; }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t st)
+{
+    std::unique_lock<std::mutex> lock(mu);
+    if (busy && st == busy) {
+        waiting = true;
+        changed.notify_all();
+        changed.wait(lock, [] { return !busy; });
+        waiting = false;
+    }
+    return hipSuccess;
+}
 hipError_t hipStreamGetDevice(hipStream_t, hipDevice_t *d)
 {
     *d = 0;
@@ -181,6 +198,19 @@ void rec_launch(int i, unsigned *grid, unsigned *block, size_t *lds, void **src,
     *src = l.src;
     *dst = l.dst;
     std::memcpy(extra, l.extra, sizeof(l.extra));
+}
+// Work on the stream st does not end until rec_busy(0); rec_await returns once a
+// call waits for it.
+void rec_busy(void *st)
+{
+    std::lock_guard<std::mutex> lock(mu);
+    busy = static_cast<hipStream_t>(st);
+    changed.notify_all();
+}
+void rec_await()
+{
+    std::unique_lock<std::mutex> lock(mu);
+    changed.wait(lock, [] { return waiting; });
 }
 // Device memory in use, and how many more allocations succeed (-1: all).
 long long rec_bytes() { return bytes_held; }
