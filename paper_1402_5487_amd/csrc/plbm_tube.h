@@ -9,7 +9,7 @@
 // populations between the steps are exchanged through LDS (two buffers, one
 // barrier a step).  Its nodes are the tile's plus reach * (steps - 1) on each
 // side, computed again by the neighbours; a tile that holds the whole lattice
-// has no such halo and takes any number of steps.  The ghost nodes beyond an
+// has no such halo and takes up to TUBE_STEPS steps.  The ghost nodes beyond an
 // end hold the end node's own post-collision populations, so past the first
 // step (whose ghosts are in memory) their pull is a clamped index.
 //
@@ -22,12 +22,16 @@
 namespace {
 
 constexpr int TUBE_T = 1024;          // most nodes (threads) of a workgroup
+// Most steps of a launch: 0.5 to 3 ms, so that a call of any length is made of
+// short kernels, at 4 us for each of them.
+constexpr int TUBE_STEPS = 4096;
+static_assert(TUBE_STEPS % 2 == 0, "launches in place take an even number of steps");
 
 struct TubePlan {
     int launches;                     // each takes n / launches steps, the first n % launches one more
     int tile;                         // nodes a workgroup writes
     int threads;
-    bool whole;                       // one workgroup holds the lattice: one launch, in place if need be
+    bool whole;                       // one workgroup holds the lattice: TUBE_STEPS steps a launch, in place
 };
 
 template <class M>
@@ -50,16 +54,16 @@ inline TubePlan tube_plan(int nx, int n, int reach)
     auto cost = [&](const TubePlan &t, int resident) {
         return 4.0 * t.launches + n * (base + per * t.threads * resident);
     };
-    TubePlan best = {1, nx, (nx + 63) / 64 * 64, true};
+    TubePlan best = {(n - 1) / TUBE_STEPS + 1, nx, (nx + 63) / 64 * 64, true};
     double least = nx <= TUBE_T ? cost(best, 1) : HUGE_VAL;
     for (int threads = 256; threads <= TUBE_T; threads += 256)
         for (int steps : {1, 8, 12, 16, 20, 24, 32, 40, 48, 64}) {
-            TubePlan t = {(n + steps - 1) / steps, 0, threads, false};
+            TubePlan t = {(n - 1) / steps + 1, 0, threads, false};
             // as many launches, modulo two, as there are steps: the state
             // ends in the buffer where single steps leave it
             if ((t.launches ^ n) & 1) ++t.launches;
             if (t.launches > n) continue;
-            t.tile = threads - 2 * reach * ((n + t.launches - 1) / t.launches - 1);
+            t.tile = threads - 2 * reach * ((n - 1) / t.launches);
             if (t.tile < 32) continue;
             const int tiles = (nx - 1) / t.tile + 1;
             const double c = cost(t, (tiles - 1) / SWEEP_CUS + 1);
@@ -141,9 +145,15 @@ void run_tube(const typename M::P &p, void *fa, void *fb, int n, int fusable, in
     if (n < 1) return;
     const TubePlan t = tube_plan<M>(p.nx, n, reach);
     for (int k = 0; k < t.launches; ++k) {
-        const int steps = n / t.launches + (k < n % t.launches ? 1 : 0);
+        int steps = n / t.launches + (k < n % t.launches ? 1 : 0);
         T *src = static_cast<T *>((k & 1) ? fb : fa);
-        T *dst = static_cast<T *>(t.whole ? ((n & 1) ? fb : fa) : ((k & 1) ? fa : fb));
+        T *dst = static_cast<T *>((k & 1) ? fa : fb);
+        if (t.whole) {                // the last takes what is left, an odd number into fb
+            const bool last = k == t.launches - 1;
+            steps = last ? n - k * TUBE_STEPS : TUBE_STEPS;
+            src = static_cast<T *>(fa);
+            dst = static_cast<T *>(last && (n & 1) ? fb : fa);
+        }
         hipLaunchKernelGGL(k_tube<M>, dim3((p.nx - 1) / t.tile + 1), dim3(t.threads),
                            tube_lds_bytes<M>(t.threads), st, src, dst, p, t.tile, reach, steps);
     }

@@ -27,3 +27,17 @@ def test_chunks_side_by_side_equal_single_steps(v, theta, least, widths, storage
         for _ in range(11):
             b.step(1)
         assert torch.equal(a.f, b.f) and a.cur == b.cur, (nx, ny)
+
+
+@pytest.mark.parametrize("nx,storage", [(64, "f64"), (200, "f32"), (1000, "f64")])
+def test_a_long_call_of_a_tube_equals_short_ones(nx, storage):
+    """More steps than one launch takes (4096), in place and into the other
+    buffer: 8193 and then 8192 of them against calls of 127."""
+    rho, ux, _, th = inputs.shock_tube(nx, rho_r=0.7)
+    a, b = (Lattice(1, nx, omega=1.1, storage=storage).init(rho, ux, None, th) for _ in range(2))
+    for n in (8193, 8192):
+        a.step(n)
+    for _ in range((8193 + 8192) // 127):
+        b.step(127)
+    b.step((8193 + 8192) % 127)
+    assert torch.equal(a.f, b.f) and a.cur == b.cur

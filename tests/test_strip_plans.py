@@ -92,3 +92,24 @@ def test_sums_take_a_workgroup_per_row_tile(recorder, model, storage, nx, ny):  
     last = [x for x in recorder.step(MODELS[model](nx, ny, storage), 2, sums=True) if x.kernel in SINGLE][-1]
     assert last.grid == -(-nx // 256) * ny
     assert recorder.lib.rec_bytes() == 0
+
+
+TUBES = {"d1q5": lambda nx, st: _plbm.desc_default(1, nx, 1, 1.2, st),
+         "d1q3": lambda nx, st: _plbm.desc_q3(1, nx, 1, 1.2, st, zeta=4.0),
+         "d1q7": lambda nx, st: _plbm.desc_general(1, nx, 1, 1.2, st, V49, 1.0)}
+
+
+@pytest.mark.parametrize("model,storage", [("d1q5", "f64"), ("d1q3", "f32"), ("d1q7", "f64")])
+@pytest.mark.parametrize("nx", [1, 64, 1000, 1024, 1025, 20000])
+@pytest.mark.parametrize("n", [1, 4095, 4096, 4097, 4098, 8192, 8193, 100001, 2 ** 31 - 1])
+def test_long_calls_of_a_tube_are_short_launches(recorder, model, storage, nx, n):  # noqa: F811
+    """No launch takes more than 4096 steps, together they take all of them, and
+    the halo of a tile (three nodes a step) stays a small number."""
+    if n > 10 ** 6 and (nx, model) != (64, "d1q5"):
+        n = 10 ** 5 + 7                                # up to tens of millions of launches otherwise
+    at, taken = 0x1000, 0
+    for x in recorder.step(TUBES[model](nx, storage), n, "plbm_advance"):
+        assert x.kernel == "k_tube" and x.src == at and 1 <= x.extra[2] <= 4096
+        assert x.src != x.dst or x.extra[2] % 2 == 0
+        at, taken = x.dst, taken + x.extra[2]
+    assert taken == n and at == (0x1000 if n % 2 == 0 else 0x2000)
