@@ -449,16 +449,17 @@ long long count_tiles(const plbm_batch *b, int side)
     return n;
 }
 
-// The work list of one fused launch from each lattice's grid.
+// The work list of one fused launch from each lattice's grid.  Without memory for
+// it (the pool may have taken all there is) the batch steps one by one.
 template <class Grid>
 int build_work(plbm_batch *b, FusedWork &w, Fused form, const Grid &grid)
 {
     long long total = 0;
     for (const auto &s : b->specs) total += grid(s).wgs;
     if (total > MAX_GRID) return PLBM_OK;
-    w.form = form;
     w.wgs = (int)total;
     if (b->grouped) {
+        w.form = form;
         BFusedGroups &G = w.groups;
         std::memset(&G, 0, sizeof(G));
         int at = 0, lat0 = 0;
@@ -488,7 +489,12 @@ int build_work(plbm_batch *b, FusedWork &w, Fused form, const Grid &grid)
         for (int k = 0; k < g.wgs; ++k)
             list.push_back(BFused{{L.buf[0], L.buf[1]}, L.nx, L.ny, L.omega, k, g});
     }
-    if (hipMalloc((void **)&w.list, list.size() * sizeof(BFused)) != hipSuccess) return PLBM_EHIP;
+    if (hipMalloc((void **)&w.list, list.size() * sizeof(BFused)) != hipSuccess) {
+        (void)hipGetLastError();
+        w.list = nullptr;
+        return PLBM_OK;
+    }
+    w.form = form;
     return hipck(hipMemcpy(w.list, list.data(), list.size() * sizeof(BFused), hipMemcpyHostToDevice));
 }
 
