@@ -238,6 +238,13 @@ struct GenSet {
     static constexpr int V[Q1] = {Vs...};
     static constexpr bool KEYED = false;
     static constexpr int SPAN = SPAN_, WGS = 4;
+    // see LaunchTime: D2Q16 and D2Q49; tiles of two steps on 16 x 16 nodes (D2Q49 in
+    // FP64 16 x 8), strips of two
+    static constexpr int FORM = (Q1 == 7 ? 2 : 0) + (sizeof(T) == 8 ? 0 : 1);
+    static constexpr LaunchTime SINGLES[4] = {{3.5, 0, 38.2}, {3.3, 0, 23.1}, {5.8, 0, 144}, {4.2, 0, 60.5}};
+    static constexpr LaunchTime TILES[4] = {{4.4, 1.3, 28.4}, {4.1, 1.0, 10.2}, {2.1, 4.4, 114}, {4.5, 4.1, 56.4}};
+    static constexpr LaunchTime PAIRS[4] = {{2.4, 1.2, 21}, {4.0, 0.8, 15.1}, {1.8, 2.8, 68}, {1.2, 2.1, 30.6}};
+    static constexpr LaunchTime SINGLE = SINGLES[FORM], TILE = TILES[FORM], PAIR = PAIRS[FORM];
     // D2Q49 in FP64 holds 112 columns: 104 of them in half lines, 96 in whole ones
     template <int D>
     static constexpr int line() { return Q1 == 7 && sizeof(T) == 8 ? 64 : 128; }
@@ -535,18 +542,19 @@ int gen_fused(const GenParams &p, void *fa, void *fb, int n, hipStream_t st)
         if (run.template one_round<8, 8>()) {
             run.template take<8, 8, 3>(left);
         } else if constexpr (wide) {
-            run.template take<16, 8, 2>(left);
+            if (run.template pay<16, 8, 2>(M::TILE)) run.template take<16, 8, 2>(left);
         } else if (run.template one_round<16, 16>()) {
             run.template take<16, 16, 3>(left);
-        } else {
+        } else if (run.template pay<16, 16, 2>(M::TILE)) {
             run.template take<16, 16, 2>(left);
         }
         const int rc = gen_launch_status();
-        return rc == PLBM_OK ? n - left : rc;
+        if (rc != PLBM_OK || left < n) return rc == PLBM_OK ? n - left : rc;
     }
     if (!sweep_fits<M>(p.nx)) return 0;
     const SweepGrid g = sweep_grid<M, D>(p.nx, p.ny);
     if (2ll * p.nx * g.per < (long long)g.strips * sweep_threads<M>()) return 0;
+    if (!strips_pay<M, D>(g, M::PAIR, p.nx, p.ny)) return 0;
     const int launches = fused_launches<D>(n);
     // D2Q49 in FP64, whose narrow strips write few whole lines either way:
     // 296 us a step non-temporal at 3001 x 1000, 302 not

@@ -534,10 +534,9 @@ void tile_steps(const KParams &p, void *fa, void *fb, int &n, hipStream_t st)
     if (run.template one_round<16, 16>()) return run.template take<16, 16, 3>(n);
     if constexpr (elem < 8)
         if (run.template one_round<20, 20>()) return run.template take<20, 20, 3>(n);
-    if constexpr (elem == 8) run.template take<24, 16, 2>(n);
-    else if constexpr (elem == 4) run.template take<16, 16, 2>(n);
-    else run.template take<24, 24, 2>(n);
-    run.template take<16, 16, 3>(n);
+    constexpr int BX = elem == 4 ? 16 : 24, BY = elem == 2 ? 24 : 16;
+    if (run.template pay<BX, BY, 2>(M::TILE2)) run.template take<BX, BY, 2>(n);
+    if (run.template pay<16, 16, 3>(M::TILE3)) run.template take<16, 16, 3>(n);
 }
 
 // How many steps a strip of a larger lattice takes (plbm_sweep.h); 1: single
@@ -549,7 +548,7 @@ void tile_steps(const KParams &p, void *fa, void *fb, int &n, hipStream_t st)
 // FP32 takes three if the strips use 3/4 of their lanes (257 x 4100 - / 26 / 32) and
 // its workgroups, one a CU, come to fewer rows: a row of three steps takes 2.06
 // us, a row of each of two workgroups of pairs 3.1 (70000 x 16, two rounds of 313:
-// 46 / 26 / 36).
+// 46 / 26 / 36).  And either has to be faster than single steps (see LaunchTime).
 template <class S>
 int sweep_depth(const KParams &p, const plbm_desc *d)
 {
@@ -564,10 +563,11 @@ int sweep_depth(const KParams &p, const plbm_desc *d)
         const SweepGrid g3 = sweep_grid<M, 3>(p.nx, p.ny);
         const long long lanes3 = (long long)g3.strips * sweep_threads<M>();
         if (4 * (long long)p.nx * g3.per >= 3 * lanes3 &&
-            2.06 / 3 * sweep_rounds<M, 3>(g3) <= 3.1 / 2 * sweep_rounds<M, 2>(g))
+            2.06 / 3 * sweep_rounds<M, 3>(g3) <= 3.1 / 2 * sweep_rounds<M, 2>(g) &&
+            strips_pay<M, 3>(g3, M::TRIPLE, p.nx, p.ny))
             return 3;
     }
-    return 2;
+    return narrow || strips_pay<M, 2>(g, M::PAIR, p.nx, p.ny) ? 2 : 1;
 }
 
 template <class S>
@@ -585,7 +585,8 @@ int run_steps(const KParams &p, const plbm_desc *d, void *fa, void *fb, int nste
         const int rc = launch_status();
         if (rc != PLBM_OK) return rc;
         s0 = fusable - left;
-    } else if (const int depth = sweep_depth<S>(p, d); depth > 1) {
+    }
+    if (const int depth = s0 == 0 ? sweep_depth<S>(p, d) : 1; depth > 1) {
         const int n = fusable;
         const int pairs = depth == 3 ? pairs_beside_threes(n) : fused_launches<2>(n);
         if constexpr (sizeof(typename S::T) == 4) {

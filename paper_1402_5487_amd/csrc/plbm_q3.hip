@@ -197,6 +197,12 @@ struct Iso9 {
     static constexpr int V[Q3] = {0, 1, -1};
     static constexpr bool KEYED = false;
     static constexpr int SPAN = 256, WGS = 4;
+    // see LaunchTime: tiles of five steps on 24 x 24 nodes and three on 16 x 16, strips
+    static constexpr bool WIDE = sizeof(T) == 8;
+    static constexpr LaunchTime SINGLE = WIDE ? LaunchTime{2.8, 0, 24.4} : LaunchTime{2.9, 0, 11.5};
+    static constexpr LaunchTime TILE5 = WIDE ? LaunchTime{5.7, 3.6, 8.8} : LaunchTime{4.4, 2.6, 4.3};
+    static constexpr LaunchTime TILE3 = WIDE ? LaunchTime{4.4, 1.0, 9.9} : LaunchTime{4.0, 0.8, 3.5};
+    static constexpr LaunchTime STRIP = WIDE ? LaunchTime{7.5, 0.65, 24.1} : LaunchTime{11.7, 0.31, 13.5};
     template <int D>
     static constexpr int line() { return 128; }
     template <int D>
@@ -467,17 +473,21 @@ inline bool use_tiles(const Q9Params &p) { return p.sx[1] == 1 && (long long)p.n
 template <typename T>
 void tile_steps_q9(const Q9Params &p, void *fa, void *fb, int &n, hipStream_t st)
 {
-    TileRun<Iso9<T>> run(p, fa, fb, st);
+    using M = Iso9<T>;
+    TileRun<M> run(p, fa, fb, st);
+    const bool one = run.template one_round<16, 16>();
     if (run.template one_round<8, 8>()) run.template take<8, 8, 9>(n);
-    else if (run.template one_round<16, 16>()) run.template take<16, 16, 7>(n);
-    else run.template take<24, 24, 5>(n);
-    run.template take<16, 16, 3>(n);
+    else if (one) run.template take<16, 16, 7>(n);
+    else if (run.template pay<24, 24, 5>(M::TILE5)) run.template take<24, 24, 5>(n);
+    if (one || run.template pay<16, 16, 3>(M::TILE3)) run.template take<16, 16, 3>(n);
 }
 
 template <typename T>
 bool use_sweeps(const Q9Params &p)
 {
-    return p.sx[1] == 1 && p.nx >= 16 && sweep_fits<Iso9<T>>(p.nx);
+    using M = Iso9<T>;
+    if (p.sx[1] != 1 || p.nx < 16 || !sweep_fits<M>(p.nx)) return false;
+    return strips_pay<M, Q9_DEPTH<T>>(sweep_grid<M, Q9_DEPTH<T>>(p.nx, p.ny), M::STRIP, p.nx, p.ny);
 }
 
 template <typename T, typename C>
@@ -494,7 +504,8 @@ int q9_run(const Q9Params &p, void *fa, void *fb, int nsteps, const plbm::StepCa
         const int rc = q9_launch_status();
         if (rc != PLBM_OK) return rc;
         s0 = fusable - left;
-    } else if (p.dim == 2 && use_sweeps<T>(p)) {
+    }
+    if (p.dim == 2 && s0 == 0 && use_sweeps<T>(p)) {
         // D steps a launch, then three, and the rest one by one
         using M = Iso9<T>;
         const int n = fusable;

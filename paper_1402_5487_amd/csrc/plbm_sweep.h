@@ -30,6 +30,26 @@ namespace {
 constexpr int SWEEP_CUS = 256;            // compute units of an MI355X
 constexpr size_t SWEEP_LDS = 160 * 1024;  // LDS of one of them
 
+// What a launch takes on an MI355X, in microseconds: `base`, `unit` for what its
+// workgroups do one after another (rounds of tiles, rows of strips), and
+// `mnode` for a million nodes read and written.  A launch of several steps is
+// taken where it is faster than the single steps it stands for: on lattices of
+// a few rows a tile or a strip computes several times its own nodes.  Fitted to
+// lattices of 3 to 48 rows and 3000 to 300000 nodes a row, to 10 % (16-bit strips,
+// taken on large lattices only, have no such rule).  What the rule changed, us a
+// step before and after: D2Q25 FP16 100000 x 3 32.7 and 8.9, FP64 37.2 and 20.9; D2Q9
+// FP32 300000 x 3 27.2 and 7.6; D2Q49 FP32 10000 x 3 9.1 and 5.8.
+struct LaunchTime {
+    double base, unit, mnode;
+    double us(double units, double nodes) const { return base + unit * units + 1e-6 * mnode * nodes; }
+};
+// A single step, which takes rows by segments of TX lanes.
+template <class M>
+inline double single_us(int nx, int ny)
+{
+    return M::SINGLE.us(0, (double)((nx + TX - 1) / TX * TX) * ny);
+}
+
 // The delay lines of a velocity set.
 template <class M>
 struct Lines {
@@ -402,6 +422,16 @@ __device__ __forceinline__ void sweep(const typename M::T *__restrict__ src, typ
     }
 }
 
+// Whether the strips of D steps are faster than single steps (see LaunchTime).
+template <class M, int D>
+inline bool strips_pay(const SweepGrid &g, const LaunchTime &t, int nx, int ny)
+{
+    // few rounds end together, many one after another
+    const double rounds = (double)g.wgs / (SWEEP_CUS * sweep_per_cu<M, D>());
+    const double rows = (rounds > 4 ? rounds : std::ceil(rounds)) * (g.h + 2 * Lines<M>::R * (D - 1));
+    return t.us(rows, (double)nx * ny) < D * single_us<M>(nx, ny);
+}
+
 // The thermal model of plbm_device.h with the set {0, +-1, +-3} in the paper's
 // order (paper_set: whether p's is that one).  It takes two steps a strip; FP32
 // also three, whose 160 KB of LDS leave one workgroup a CU.  FP64 has no room for
@@ -416,6 +446,15 @@ struct Thermal25 {
     static constexpr int V[Q] = {0, 1, -1, 3, -3};
     static constexpr bool KEYED = S::keyed;
     static constexpr int SPAN = 256, WGS = 4;
+    // see LaunchTime: tiles of two steps (FP64 24 x 16 nodes, FP32 16 x 16, 16-bit
+    // 24 x 24) and of three (16 x 16), strips of two and of three
+    static constexpr int FORM = sizeof(T) == 8 ? 0 : sizeof(T) == 4 ? 1 : KEYED ? 3 : 2;
+    static constexpr LaunchTime SINGLES[4] = {{3.5, 0, 72.7}, {3.1, 0, 36.2}, {3.1, 0, 19.7}, {3.8, 0, 20.1}};
+    static constexpr LaunchTime TILES2[4] = {{2.4, 4.0, 57.5}, {5.2, 1.0, 22.6}, {4.0, 3.3, 7.7}, {4.2, 3.7, 8.2}};
+    static constexpr LaunchTime TILES3[4] = {{2.5, 6.2, 63}, {3.9, 3.4, 20.6}, {3.8, 4.7, 17.8}, {3.2, 5.3, 18}};
+    static constexpr LaunchTime SINGLE = SINGLES[FORM], TILE2 = TILES2[FORM], TILE3 = TILES3[FORM];
+    static constexpr LaunchTime PAIR = sizeof(T) == 8 ? LaunchTime{2.5, 2.1, 42.9} : LaunchTime{2.8, 1.4, 26.4};
+    static constexpr LaunchTime TRIPLE = {4.7, 1.5, 10.4};
     // Half lines where 128 B would cost a quarter of the lanes (16-bit) or a
     // twelfth (FP32 threes: 2500^2 106 us a step with 224 columns, 102 with 240;
     // 2048 x 4096 139, 126), and one workgroup of each CU writes.

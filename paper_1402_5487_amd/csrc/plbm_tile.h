@@ -106,6 +106,13 @@ public:
     {
         return (long long)((p_.nx + BX - 1) / BX) * ((p_.ny + BY - 1) / BY) <= SWEEP_CUS;
     }
+    // whether they are faster than single steps (see LaunchTime)
+    template <int BX, int BY, int D>
+    bool pay(const LaunchTime &t) const
+    {
+        const double tiles = (double)((p_.nx + BX - 1) / BX) * ((p_.ny + BY - 1) / BY);
+        return t.us(std::ceil(tiles / SWEEP_CUS), (double)p_.nx * p_.ny) < D * single_us<M>(p_.nx, p_.ny);
+    }
     // as many of n steps as launches of D take; n becomes what is left
     template <int BX, int BY, int D>
     void take(int &n)

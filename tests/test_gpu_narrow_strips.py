@@ -41,3 +41,19 @@ def test_a_long_call_of_a_tube_equals_short_ones(nx, storage):
         b.step(127)
     b.step((8193 + 8192) % 127)
     assert torch.equal(a.f, b.f) and a.cur == b.cur
+
+
+# flat lattices: tiles, strips and single steps as they pay
+@pytest.mark.parametrize("nx,ny", [(3000, 20), (10000, 3), (10000, 24), (30000, 4), (100000, 3), (300000, 3)])
+@pytest.mark.parametrize("kw,theta,storage", [({}, 0.4, "f64"), ({}, 0.4, "f32"), ({}, 0.35, "f16dev"),
+                                              (dict(zeta=4.0), 0.25, "f32"), (dict(zeta=4.0), 0.25, "f64"),
+                                              (dict(velocities=(1, -1, 3, -3), theta0=4.0 / 3.0), 4.0 / 3.0, "f32"),
+                                              (dict(velocities=(0, 1, -1, 2, -2, 3, -3), theta0=1.0), 1.0, "f64")])
+def test_flat_lattices_equal_single_steps(nx, ny, kw, theta, storage):
+    fields = inputs.random_fields(nx, ny, seed=nx + ny, theta=(theta, theta), u=0.03)
+    a, b = (Lattice(2, nx, ny, omega=1.6, storage=storage, **kw).init(*fields) for _ in range(2))
+    for n in (3, 4, 12):
+        a.step(n)
+    for _ in range(19):
+        b.step(1)
+    assert torch.equal(a.f, b.f) and a.cur == b.cur

@@ -113,3 +113,33 @@ def test_long_calls_of_a_tube_are_short_launches(recorder, model, storage, nx, n
         assert x.src != x.dst or x.extra[2] % 2 == 0
         at, taken = x.dst, taken + x.extra[2]
     assert taken == n and at == (0x1000 if n % 2 == 0 else 0x2000)
+
+
+# (model, storage, nx, ny, steps): measured at up to five times the single steps
+# on tiles or strips
+FLAT = [("d2q25", "f16dev", 100000, 3, 20), ("d2q25", "f16dev", 10000, 24, 3), ("d2q25", "f64", 10000, 3, 20),
+        ("d2q25", "f32", 30000, 3, 4), ("d2q16", "f32", 30000, 3, 20),
+        ("d2q49", "f32", 10000, 3, 20), ("d2q49", "f64", 300000, 3, 20), ("d2q49", "f64", 100000, 3, 4)]
+# no tiles there: strips are faster than single steps
+FLAT_STRIPS = [("d2q25", "f64", 100000, 4, 4), ("d2q25", "f32", 300000, 3, 20), ("d2q9", "f64", 300000, 3, 20),
+               ("d2q9", "f32", 300000, 3, 20), ("d2q16", "f32", 100000, 3, 20), ("d2q16", "f64", 300000, 3, 20)]
+# and these stay
+TILED = [("d2q25", "f64", 256, 256, 6), ("d2q25", "f16dev", 700, 900, 4), ("d2q25", "f32", 1000, 1000, 4),
+         ("d2q25", "f64", 3, 30000, 4), ("d2q25", "f32", 3000, 3, 6), ("d2q9", "f32", 1000, 1000, 10),
+         ("d2q16", "f64", 1000, 900, 4), ("d2q49", "f32", 500, 500, 4), ("d2q49", "f64", 500, 500, 4)]
+
+
+@pytest.mark.parametrize("model,storage,nx,ny,n", FLAT)
+def test_flat_lattices_take_single_steps(recorder, model, storage, nx, ny, n):  # noqa: F811
+    assert {x.kernel for x in recorder.step(MODELS[model](nx, ny, storage), n, "plbm_advance")} <= SINGLE
+
+
+@pytest.mark.parametrize("model,storage,nx,ny,n", FLAT_STRIPS)
+def test_long_flat_lattices_take_strips(recorder, model, storage, nx, ny, n):  # noqa: F811
+    assert {x.kernel for x in recorder.step(MODELS[model](nx, ny, storage), n, "plbm_advance")} & STRIPS
+    assert "k_tile" not in {x.kernel for x in recorder.step(MODELS[model](nx, ny, storage), n, "plbm_advance")}
+
+
+@pytest.mark.parametrize("model,storage,nx,ny,n", TILED)
+def test_other_lattices_keep_their_tiles(recorder, model, storage, nx, ny, n):  # noqa: F811
+    assert {x.kernel for x in recorder.step(MODELS[model](nx, ny, storage), n, "plbm_advance")} == {"k_tile"}
