@@ -44,7 +44,7 @@ def test_a_long_call_of_a_tube_equals_short_ones(nx, storage):
 
 
 # flat lattices: tiles, strips and single steps as they pay
-@pytest.mark.parametrize("nx,ny", [(3000, 20), (10000, 3), (10000, 24), (30000, 4), (100000, 3), (300000, 3)])
+@pytest.mark.parametrize("nx,ny", [(3000, 20), (10000, 3), (10000, 24), (30000, 4), (100000, 3), (300000, 3), (30000, 48)])
 @pytest.mark.parametrize("kw,theta,storage", [({}, 0.4, "f64"), ({}, 0.4, "f32"), ({}, 0.35, "f16dev"),
                                               (dict(zeta=4.0), 0.25, "f32"), (dict(zeta=4.0), 0.25, "f64"),
                                               (dict(velocities=(1, -1, 3, -3), theta0=4.0 / 3.0), 4.0 / 3.0, "f32"),

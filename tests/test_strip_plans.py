@@ -143,3 +143,15 @@ def test_long_flat_lattices_take_strips(recorder, model, storage, nx, ny, n):  #
 @pytest.mark.parametrize("model,storage,nx,ny,n", TILED)
 def test_other_lattices_keep_their_tiles(recorder, model, storage, nx, ny, n):  # noqa: F811
     assert {x.kernel for x in recorder.step(MODELS[model](nx, ny, storage), n, "plbm_advance")} == {"k_tile"}
+
+
+@pytest.mark.parametrize("nx,ny", [(27000, 64), (30000, 48), (55000, 40)])
+def test_strips_fill_their_rounds(recorder, nx, ny):  # noqa: F811
+    """D2Q49 FP64 has more strips than the 256 workgroups that run at once: the
+    rounds take fewer rows one after another than whole strips would (halo: three
+    rows at either end)."""
+    x = recorder.step(MODELS["d2q49"](nx, ny, "f64"), 4, "plbm_advance")[0]
+    strips, chunks, _, h, _, per, wgs = x.extra
+    assert x.kernel == "k_pair_gen" and strips > 256 and per == 1
+    assert -(-wgs // 256) * (h + 6) < -(-strips // 256) * (ny + 6)
+    assert (_owners(recorder, x, nx, ny) == 1).all()
