@@ -510,6 +510,17 @@ __device__ __forceinline__ void store_stream(T v, T *p)
     else *p = v;
 }
 __host__ __device__ inline bool rows_on_lines(int nx, size_t elem) { return (size_t)nx * elem % 64 == 0; }
+// Single steps of 2D lattices also store non-temporally where the two buffers just
+// fit the 32 MB of L2 and the rows are few: an XCD's rows are then read by its
+// neighbours, from memory or from lines still dirty in the first one's L2.  Measured,
+// non-temporal against ordinary, us a step: D2Q25 FP16 30000 x 6 6.8 against 7.6, 10000 x
+// 20 7.5 / 7.8, FP64 3001 x 16 6.8 / 7.3, D2Q16 FP32 30001 x 6 7.7 / 9.4; twice the size
+// 11.6 / 10.1 (FP16 30000 x 13), more rows 7.6 / 6.9 (D2Q16 FP32 5000 x 40).
+inline bool single_step_nt(int nx, int ny, int pops, size_t elem)
+{
+    const double bytes = (double)nx * ny * pops * (double)elem;
+    return rows_on_lines(nx, elem) || (ny <= 36 && bytes >= 8e6 && bytes < 16e6);
+}
 
 // Loads and stores of NV consecutive nodes of one population row.  `base`
 // is a wave-uniform byte pointer, `off` the lane's byte offset (the node's

@@ -509,7 +509,7 @@ template <int Q1, typename T, bool SUMS>
 void gen_launch(const GenParams &p, const T *src, T *dst, double *part, hipStream_t st, int grid)
 {
     if (p.dim == 2) {
-        const bool nts = rows_on_lines(p.nx, sizeof(T)), z0 = p.sx[0] == 0;
+        const bool nts = single_step_nt(p.nx, p.ny, Q1 * Q1, sizeof(T)), z0 = p.sx[0] == 0;
         auto *kernel = z0 ? (nts ? k_step_gen2d<Q1, T, SUMS, true, true> : k_step_gen2d<Q1, T, SUMS, true, false>)
                           : (nts ? k_step_gen2d<Q1, T, SUMS, false, true> : k_step_gen2d<Q1, T, SUMS, false, false>);
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(TX), (gen_lds_cap<Q1, T>()), st, src, dst, p, part);

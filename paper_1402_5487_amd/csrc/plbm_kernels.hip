@@ -444,7 +444,7 @@ int launch_step(const KParams &p, const plbm_desc *d, const void *src, void *dst
         const size_t lds = sizeof(T) == 2 ? (d->rounding == PLBM_ROUND_STOCHASTIC ? PLBM_LDS_CAP_16SR
                                                                                  : PLBM_LDS_CAP_16)
                                           : PLBM_LDS_CAP_WIDE;
-        const bool nts = rows_on_lines(p.nx, sizeof(T));
+        const bool nts = single_step_nt(p.nx, p.ny, NQ, sizeof(T));
         auto *kernel = p.nv == 2 ? (nts ? k_step2d<S, 2, SUMS, true> : k_step2d<S, 2, SUMS, false>)
                                  : (nts ? k_step2d<S, 1, SUMS, true> : k_step2d<S, 1, SUMS, false>);
         hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(TX), lds, st, (const T *)src, (T *)dst, p, partials);
@@ -646,7 +646,7 @@ int run_steps_fields(const KParams &p, const plbm_desc *d, void *fa, void *fb, i
     clear_launch_error();
     const size_t lds = sizeof(T) == 2 ? (d->rounding == PLBM_ROUND_STOCHASTIC ? PLBM_LDS_CAP_16SR : PLBM_LDS_CAP_16)
                                       : PLBM_LDS_CAP_WIDE;
-    const bool nts = rows_on_lines(p.nx, sizeof(T));
+    const bool nts = single_step_nt(p.nx, p.ny, NQ, sizeof(T));
     auto *kernel = p.nv == 2 ? (nts ? k_step2d_fields<S, 2, true> : k_step2d_fields<S, 2, false>)
                              : (nts ? k_step2d_fields<S, 1, true> : k_step2d_fields<S, 1, false>);
     hipLaunchKernelGGL(kernel, dim3(grid_for(p.ntiles)), dim3(TX), lds, st, (const T *)fa, (T *)fb, p, fo);

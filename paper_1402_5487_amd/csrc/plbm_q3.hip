@@ -437,7 +437,8 @@ void q3_launch(const Q9Params &p, const T *src, T *dst, double *part, hipStream_
 {
     if (p.dim == 2) {
         const size_t lds = sizeof(T) == 8 ? PLBM_Q9_LDS_F64 : PLBM_Q9_LDS_F32;
-        auto *kernel = rows_on_lines(p.nx, sizeof(T)) ? k_step_q9<T, C, SUMS, true> : k_step_q9<T, C, SUMS, false>;
+        auto *kernel = single_step_nt(p.nx, p.ny, N9, sizeof(T)) ? k_step_q9<T, C, SUMS, true>
+                                                                 : k_step_q9<T, C, SUMS, false>;
         hipLaunchKernelGGL(kernel, dim3(blocks), dim3(TX), lds, st, src, dst, p, part);
     } else if constexpr (SUMS) {
         hipLaunchKernelGGL((k_step_q3_1d_sums<T, C>), dim3(blocks), dim3(TX), 0, st, src, dst, p, part);

@@ -1,6 +1,7 @@
 """How the fused steps cut a lattice (CPU): every node of it is written by
 exactly one lane of one launch, whatever the size and the model."""
 import ctypes
+import re
 
 import numpy as np
 import pytest
@@ -155,3 +156,16 @@ def test_strips_fill_their_rounds(recorder, nx, ny):  # noqa: F811
     assert x.kernel == "k_pair_gen" and strips > 256 and per == 1
     assert -(-wgs // 256) * (h + 6) < -(-strips // 256) * (ny + 6)
     assert (_owners(recorder, x, nx, ny) == 1).all()
+
+
+# (model, storage, nx, ny, whether single steps store non-temporally): rows on
+# half lines; ragged ones of which two buffers just fill L2; ragged ones
+@pytest.mark.parametrize("model,storage,nx,ny,nt", [
+    ("d2q25", "f16dev", 3008, 700, True), ("d2q25", "f16dev", 30000, 6, True), ("d2q25", "f64", 3001, 16, True),
+    ("d2q16", "f32", 30001, 6, True), ("d2q49", "f32", 1501, 33, True), ("d2q9", "f64", 30001, 6, True),
+    ("d2q25", "f16dev", 30000, 13, False), ("d2q25", "f32", 1501, 66, False), ("d2q9", "f64", 1501, 66, False),
+    ("d2q16", "f32", 3000, 66, False), ("d2q49", "f64", 1501, 33, False)])
+def test_stores_of_single_steps(recorder, model, storage, nx, ny, nt):  # noqa: F811
+    x, = recorder.step(MODELS[model](nx, ny, storage), 1)
+    last = re.search(r"Lb([01])EEEv", x.name)          # the last template argument
+    assert x.kernel in SINGLE and last.group(1) == str(int(nt)), x.name
