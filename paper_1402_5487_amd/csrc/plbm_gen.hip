@@ -362,9 +362,9 @@ struct GenTube {
     static __device__ __forceinline__ void collide(T (&f)[Q1], const P &p) { collide_gen1d<Q1, T>(f, p); }
 };
 
-// One step with the FP64 sums of what it stores.
-template <int Q1, typename T>
-__global__ __launch_bounds__(TX) void k_step_gen1d_sums(const T *__restrict__ src, T *__restrict__ dst, GenParams p,
+// One step, optionally with the FP64 sums of what it stores.
+template <int Q1, typename T, bool SUMS>
+__global__ __launch_bounds__(TX) void k_step_gen1d(const T *__restrict__ src, T *__restrict__ dst, GenParams p,
                                                    double *__restrict__ partials)
 {
     using C = T;
@@ -386,13 +386,15 @@ __global__ __launch_bounds__(TX) void k_step_gen1d_sums(const T *__restrict__ sr
                 for (int g = 0; g < PLBM_GHOST; ++g) dst[k * ps + g] = h;
             if (x == p.nx - 1)
                 for (int g = 0; g < PLBM_GHOST; ++g) dst[k * ps + p.nx + PLBM_GHOST + g] = h;
-            const double vk = p.v64[k];
-            acc[0] += (double)h;
-            acc[1] += (double)h * vk;
-            acc[3] += (double)h * vk * vk;
+            if constexpr (SUMS) {
+                const double vk = p.v64[k];
+                acc[0] += (double)h;
+                acc[1] += (double)h * vk;
+                acc[3] += (double)h * vk * vk;
+            }
         }
     }
-    block_sums_store<4>(acc, partials + (size_t)blockIdx.x * 4);
+    if constexpr (SUMS) block_sums_store<4>(acc, partials + (size_t)blockIdx.x * 4);
 }
 
 // Padded index q holds node q - 3; its population k is f_eq_k of node
@@ -513,8 +515,8 @@ void gen_launch(const GenParams &p, const T *src, T *dst, double *part, hipStrea
         auto *kernel = z0 ? (nts ? k_step_gen2d<Q1, T, SUMS, true, true> : k_step_gen2d<Q1, T, SUMS, true, false>)
                           : (nts ? k_step_gen2d<Q1, T, SUMS, false, true> : k_step_gen2d<Q1, T, SUMS, false, false>);
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(TX), (gen_lds_cap<Q1, T>()), st, src, dst, p, part);
-    } else if constexpr (SUMS)
-        hipLaunchKernelGGL((k_step_gen1d_sums<Q1, T>), dim3(grid), dim3(TX), 0, st, src, dst, p, part);
+    } else
+        hipLaunchKernelGGL((k_step_gen1d<Q1, T, SUMS>), dim3(grid), dim3(TX), 0, st, src, dst, p, part);
 }
 
 // Tiles of fused steps (plbm_tile.h) for lattices up to `most` nodes, fused pairs
@@ -570,24 +572,24 @@ int gen_fused(const GenParams &p, void *fa, void *fb, int n, hipStream_t st)
     return launches * D;
 }
 
-// How many of n steps were taken, `fusable` of them several per launch, or a
-// (negative) status: all in 1D, in 2D those of the sets that have fused steps (in
-// this order of their velocities).
+// How many of n steps were taken several per launch, or a (negative) status: in
+// 1D, and in 2D those of the sets that have fused steps (in this order of their
+// velocities).
 template <int Q1, typename T>
-int fused_steps(const GenParams &p, void *fa, void *fb, int n, int fusable, hipStream_t st)
+int fused_steps(const GenParams &p, void *fa, void *fb, int n, hipStream_t st)
 {
     if (p.dim == 1) {
         int reach = 0;
         for (int i = 0; i < Q1; ++i) reach = std::max(reach, std::abs(p.sx[i]));
         (void)hipGetLastError();
-        run_tube<GenTube<Q1, T>>(p, fa, fb, n, fusable, reach, st);
+        const int taken = run_tube<GenTube<Q1, T>>(p, fa, fb, n, reach, st);
         const int rc = gen_launch_status();
-        return rc == PLBM_OK ? n : rc;
+        return rc == PLBM_OK ? taken : rc;
     }
-    if constexpr (Q1 == 4) return gen_fused<GenSet<T, 256, 1, -1, 3, -3>>(p, fa, fb, fusable, st);
+    if constexpr (Q1 == 4) return gen_fused<GenSet<T, 256, 1, -1, 3, -3>>(p, fa, fb, n, st);
     // 28 rows of six columns: what the LDS of one workgroup holds
     if constexpr (Q1 == 7)
-        return gen_fused<GenSet<T, sizeof(T) == 8 ? 112 : 232, 0, 1, -1, 2, -2, 3, -3>>(p, fa, fb, fusable, st);
+        return gen_fused<GenSet<T, sizeof(T) == 8 ? 112 : 232, 0, 1, -1, 2, -2, 3, -3>>(p, fa, fb, n, st);
     return 0;
 }
 
@@ -595,7 +597,7 @@ template <int Q1, typename T>
 int gen_run(const GenParams &p, void *fa, void *fb, int nsteps, const plbm::StepCall &call, hipStream_t st)
 {
     double *const sums = call.sums;
-    const int s0 = fused_steps<Q1, T>(p, fa, fb, nsteps - (sums ? 1 : 0), call.fusable(nsteps), st);
+    const int s0 = fused_steps<Q1, T>(p, fa, fb, call.fusable(nsteps), st);
     if (s0 < 0) return s0;
     for (int s = s0; s < nsteps; ++s) {
         const T *src = static_cast<const T *>((s & 1) ? fb : fa);

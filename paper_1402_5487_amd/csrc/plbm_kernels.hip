@@ -227,9 +227,9 @@ __device__ __forceinline__ void collide1d(typename S::C (&f)[Q], const KParams &
     for (int i = 0; i < Q; ++i) f[i] = fma(keep, f[i], wr * r[i]);
 }
 
-// One step with the FP64 sums of what it stores (steps without: plbm_tube.h).
-template <class S>
-__global__ __launch_bounds__(TX) void k_step1d_sums(const typename S::T *__restrict__ src,
+// One step, optionally with the FP64 sums of what it stores (several: plbm_tube.h).
+template <class S, bool SUMS>
+__global__ __launch_bounds__(TX) void k_step1d(const typename S::T *__restrict__ src,
                                                typename S::T *__restrict__ dst, KParams p,
                                                double *__restrict__ partials)
 {
@@ -252,14 +252,16 @@ __global__ __launch_bounds__(TX) void k_step1d_sums(const typename S::T *__restr
             if (x == p.nx - 1)
                 for (int g = 0; g < PLBM_GHOST; ++g) dst[k * p.pstride + p.nx + PLBM_GHOST + g] = h;
         }
+        if constexpr (SUMS) {
 #pragma unroll
-        for (int k = 0; k < Q; ++k) {
-            const double g = (double)S::dec(S::enc(f[k], k, p, (uint32_t)x), k, p);
-            const double vk = (double)p.sx[k];
-            acc[0] += g; acc[1] += g * vk; acc[3] += g * vk * vk;
+            for (int k = 0; k < Q; ++k) {
+                const double g = (double)S::dec(S::enc(f[k], k, p, (uint32_t)x), k, p);
+                const double vk = (double)p.sx[k];
+                acc[0] += g; acc[1] += g * vk; acc[3] += g * vk * vk;
+            }
         }
     }
-    block_sums_store<4>(acc, partials + (size_t)blockIdx.x * 4);
+    if constexpr (SUMS) block_sums_store<4>(acc, partials + (size_t)blockIdx.x * 4);
 }
 
 // Many steps per launch (plbm_tube.h).
@@ -448,9 +450,9 @@ int launch_step(const KParams &p, const plbm_desc *d, const void *src, void *dst
         auto *kernel = p.nv == 2 ? (nts ? k_step2d<S, 2, SUMS, true> : k_step2d<S, 2, SUMS, false>)
                                  : (nts ? k_step2d<S, 1, SUMS, true> : k_step2d<S, 1, SUMS, false>);
         hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(TX), lds, st, (const T *)src, (T *)dst, p, partials);
-    } else if constexpr (SUMS && sizeof(T) >= 4) {
+    } else if constexpr (sizeof(T) >= 4) {
         nblocks = (p.nx + TX - 1) / TX;
-        hipLaunchKernelGGL(k_step1d_sums<S>, dim3(nblocks), dim3(TX), 0, st, (const T *)src, (T *)dst, p, partials);
+        hipLaunchKernelGGL((k_step1d<S, SUMS>), dim3(nblocks), dim3(TX), 0, st, (const T *)src, (T *)dst, p, partials);
     }
     return launch_status();
 }
@@ -603,9 +605,8 @@ int run_steps(const KParams &p, const plbm_desc *d, void *fa, void *fb, int nste
     }
     if constexpr (sizeof(typename S::T) >= 4) {
         if (d->dim == 1) {
-            s0 = nsteps - (sums ? 1 : 0);      // a step that takes sums is a single one
             clear_launch_error();
-            run_tube<Thermal5<S>>(p, fa, fb, s0, fusable, std::max(std::abs(p.sx[1]), std::abs(p.sx[3])), st);
+            s0 = run_tube<Thermal5<S>>(p, fa, fb, fusable, std::max(std::abs(p.sx[1]), std::abs(p.sx[3])), st);
             const int rc = launch_status();
             if (rc != PLBM_OK) return rc;
         }

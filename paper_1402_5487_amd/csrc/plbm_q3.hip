@@ -311,9 +311,9 @@ struct Iso3 {
     static __device__ __forceinline__ void collide(T (&f)[Q3], const P &p) { collide3<T>(f, rule_of<T>(p)); }
 };
 
-// One step with the FP64 sums of what it stores.
-template <typename T, typename C>
-__global__ __launch_bounds__(TX) void k_step_q3_1d_sums(const T *__restrict__ src, T *__restrict__ dst, Q9Params p,
+// One step, optionally with the FP64 sums of what it stores.
+template <typename T, typename C, bool SUMS>
+__global__ __launch_bounds__(TX) void k_step_q3_1d(const T *__restrict__ src, T *__restrict__ dst, Q9Params p,
                                                    double *__restrict__ partials)
 {
     const Rule3<C> &R = rule_of<C>(p);
@@ -333,13 +333,15 @@ __global__ __launch_bounds__(TX) void k_step_q3_1d_sums(const T *__restrict__ sr
                 for (int g = 0; g < PLBM_GHOST; ++g) dst[k * ps + g] = h;
             if (x == p.nx - 1)
                 for (int g = 0; g < PLBM_GHOST; ++g) dst[k * ps + p.nx + PLBM_GHOST + g] = h;
-            const double vk = (double)p.sx[k];
-            acc[0] += (double)h;
-            acc[1] += (double)h * vk;
-            acc[3] += (double)h * vk * vk;
+            if constexpr (SUMS) {
+                const double vk = (double)p.sx[k];
+                acc[0] += (double)h;
+                acc[1] += (double)h * vk;
+                acc[3] += (double)h * vk * vk;
+            }
         }
     }
-    block_sums_store<4>(acc, partials + (size_t)blockIdx.x * 4);
+    if constexpr (SUMS) block_sums_store<4>(acc, partials + (size_t)blockIdx.x * 4);
 }
 
 // Padded index q holds node y = q - 3; population k there is f_eq_k of node
@@ -440,8 +442,8 @@ void q3_launch(const Q9Params &p, const T *src, T *dst, double *part, hipStream_
         auto *kernel = single_step_nt(p.nx, p.ny, N9, sizeof(T)) ? k_step_q9<T, C, SUMS, true>
                                                                  : k_step_q9<T, C, SUMS, false>;
         hipLaunchKernelGGL(kernel, dim3(blocks), dim3(TX), lds, st, src, dst, p, part);
-    } else if constexpr (SUMS) {
-        hipLaunchKernelGGL((k_step_q3_1d_sums<T, C>), dim3(blocks), dim3(TX), 0, st, src, dst, p, part);
+    } else {
+        hipLaunchKernelGGL((k_step_q3_1d<T, C, SUMS>), dim3(blocks), dim3(TX), 0, st, src, dst, p, part);
     }
 }
 
@@ -521,9 +523,8 @@ int q9_run(const Q9Params &p, void *fa, void *fb, int nsteps, const plbm::StepCa
         s0 = deep * Q9_DEPTH<T> + three * 3;
     }
     if (p.dim == 1) {
-        s0 = nsteps - (sums ? 1 : 0);
         (void)hipGetLastError();
-        run_tube<Iso3<T>>(p, fa, fb, s0, fusable, p.sx[1], st);
+        s0 = run_tube<Iso3<T>>(p, fa, fb, fusable, p.sx[1], st);
         const int rc = q9_launch_status();
         if (rc != PLBM_OK) return rc;
     }

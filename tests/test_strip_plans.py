@@ -52,8 +52,8 @@ def test_strips_write_every_node_once(recorder, model, storage, nx):  # noqa: F8
 
 
 # what a step of its own launches
-SINGLE = {"k_step2d", "k_step2d_fields", "k_step_q9", "k_step_gen2d", "k_step1d_sums", "k_step_q3_1d_sums",
-          "k_step_gen1d_sums", "k_step3d"}
+SINGLE = {"k_step2d", "k_step2d_fields", "k_step_q9", "k_step_gen2d", "k_step1d", "k_step_q3_1d", "k_step_gen1d",
+          "k_step3d"}
 SIZES = {1: [(7, 1), (1000, 1), (1025, 1), (70000, 1)],
          2: [(8, 9), (64, 64), (129, 127), (300, 400), (28, 10000), (900, 1300), (1501, 1100)]}
 
@@ -82,7 +82,7 @@ def test_launches_hand_the_state_on_and_end_where_steps_do(recorder, model, stor
                 if entry != "plbm_advance":
                     last = ls[-1]
                     assert last.src != last.dst
-                    assert last.kernel in SINGLE or (last.kernel == "k_tube" and last.extra[2] == 1), (nx, ny, n, last.name)
+                    assert last.kernel in SINGLE, (nx, ny, n, last.name)
 
 
 @pytest.mark.parametrize("nx,ny", [(4096, 4096), (257, 4200), (64, 64)])
@@ -110,9 +110,10 @@ def test_long_calls_of_a_tube_are_short_launches(recorder, model, storage, nx, n
         n = 10 ** 5 + 7                                # up to tens of millions of launches otherwise
     at, taken = 0x1000, 0
     for x in recorder.step(TUBES[model](nx, storage), n, "plbm_advance"):
-        assert x.kernel == "k_tube" and x.src == at and 1 <= x.extra[2] <= 4096
-        assert x.src != x.dst or x.extra[2] % 2 == 0
-        at, taken = x.dst, taken + x.extra[2]
+        steps = x.extra[2] if x.kernel == "k_tube" else 1
+        assert x.kernel in ("k_tube", *SINGLE) and x.src == at and 1 <= steps <= 4096
+        assert x.src != x.dst or steps % 2 == 0
+        at, taken = x.dst, taken + steps
     assert taken == n and at == (0x1000 if n % 2 == 0 else 0x2000)
 
 
@@ -169,3 +170,12 @@ def test_stores_of_single_steps(recorder, model, storage, nx, ny, nt):  # noqa: 
     x, = recorder.step(MODELS[model](nx, ny, storage), 1)
     last = re.search(r"Lb([01])EEEv", x.name)          # the last template argument
     assert x.kernel in SINGLE and last.group(1) == str(int(nt)), x.name
+
+
+@pytest.mark.parametrize("model,storage", [("d1q5", "f64"), ("d1q3", "f32"), ("d1q7", "f64")])
+@pytest.mark.parametrize("nx,n,entry,kernels", [
+    (1000, 1, "plbm_advance", 1), (1000, 2, "plbm_step", 2), (3000, 2, "plbm_advance", 2), (40_000_000, 1, "plbm_step", 1),
+    (150_000, 1, "plbm_advance", 1)])
+def test_launches_of_one_step_of_a_tube_are_single_steps(recorder, model, storage, nx, n, entry, kernels):  # noqa: F811
+    ls = recorder.step(TUBES[model](nx, storage), n, entry)
+    assert [x.kernel in SINGLE for x in ls] == [True] * kernels
