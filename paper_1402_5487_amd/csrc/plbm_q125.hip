@@ -343,8 +343,13 @@ int q125_params(const plbm_desc *d, P3 &p)
 
 inline int grid_of(const P3 &p) { return std::min(p.ntiles, MAX_GRID3); }
 
-template <typename T>
-constexpr size_t lds_cap() { return sizeof(T) == 8 ? PLBM_Q125_LDS_F64 : PLBM_Q125_LDS_F32; }
+// FP32 reserves the LDS of a CU (one workgroup each), less what the block sums of
+// a step that takes them hold there.
+template <typename T, bool SUMS>
+constexpr size_t lds_cap()
+{
+    return sizeof(T) == 8 ? PLBM_Q125_LDS_F64 : PLBM_Q125_LDS_F32 - (SUMS ? 1024 : 0);
+}
 
 template <typename T, bool SUMS>
 auto step3_kernel(const P3 &p)
@@ -367,12 +372,13 @@ int q125_run(const P3 &p, void *fa, void *fb, int nsteps, double *sums, hipStrea
             plbm::SumsArea area;
             int rc = plbm::sums_begin(area, 5, blocks, st);
             if (rc != PLBM_OK) return rc;
-            hipLaunchKernelGGL((step3_kernel<T, true>(p)), dim3(blocks), dim3(TX), lds_cap<T>(), st, src, dst, p,
+            hipLaunchKernelGGL((step3_kernel<T, true>(p)), dim3(blocks), dim3(TX), (lds_cap<T, true>()), st, src, dst, p,
                                area.part);
             rc = q125_launch_status();
             return plbm::sums_end(area, 5, blocks, rc, sums, st);
         }
-        hipLaunchKernelGGL((step3_kernel<T, false>(p)), dim3(grid), dim3(TX), lds_cap<T>(), st, src, dst, p, nullptr);
+        hipLaunchKernelGGL((step3_kernel<T, false>(p)), dim3(grid), dim3(TX), (lds_cap<T, false>()), st, src, dst, p,
+                           nullptr);
         const int rc = q125_launch_status();
         if (rc != PLBM_OK) return rc;
     }

@@ -102,6 +102,21 @@ def test_sums_while_another_call_holds_the_scratch():
         t.join()
 
 
+@pytest.mark.parametrize("nx,ny,nz", [(30, 165, 163), (20, 9, 8), (256, 6, 5)])
+def test_sums_of_fp32_boxes(nx, ny, nz):
+    """A node's sums are taken in FP32: fewer than 130 additions and products, each
+    off by at most 2^-24."""
+    lat = Lattice3(nx, ny, nz, omega=1.4, storage="f32")
+    g = torch.Generator().manual_seed(nx)
+    lat.init(*(c + a * torch.rand(nz, ny, nx, generator=g, dtype=torch.float64)
+               for c, a in ((1.0, 0.02), (0.0, 0.02), (0.0, 0.02), (0.0, 0.02), (0.4, 0.01))))
+    v = (0, 1, -1, 3, -3)
+    got = np.array(lat.step(2, sums=True))
+    P = lat.f.double().view(nz * ny, 125, nx).transpose(0, 1).reshape(125, -1)
+    want, mag = _want(P, [(a, b, c) for c in v for b in v for a in v])
+    assert np.all(np.abs(got - want) <= 130 * 2.0 ** -24 * mag), (got, want)
+
+
 def test_noalloc_sums_of_more_tiles_than_the_scratch_holds():
     lat = Lattice(2, 257, 4200, omega=1.7).init(*inputs.random_fields(257, 4200, seed=3))
     a, b = lat.f.clone(), torch.empty_like(lat.f)

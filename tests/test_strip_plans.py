@@ -179,3 +179,13 @@ def test_stores_of_single_steps(recorder, model, storage, nx, ny, nt):  # noqa: 
 def test_launches_of_one_step_of_a_tube_are_single_steps(recorder, model, storage, nx, n, entry, kernels):  # noqa: F811
     ls = recorder.step(TUBES[model](nx, storage), n, entry)
     assert [x.kernel in SINGLE for x in ls] == [True] * kernels
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32"])
+@pytest.mark.parametrize("nx", [16, 256, 250])
+def test_a_box_with_sums_leaves_lds_for_them(recorder, nx, storage):  # noqa: F811
+    """The block sums hold five doubles a wave of a workgroup's four beside what
+    the launch reserves; a CU has 160 KB."""
+    d = _plbm.desc_3d(nx, 8, 8, 1.2, storage)
+    one, last = [x for x in recorder.step(d, 2, sums=True) if x.kernel == "k_step3d"]
+    assert one.lds <= 160 * 1024 and last.lds + 5 * 4 * 8 <= 160 * 1024
