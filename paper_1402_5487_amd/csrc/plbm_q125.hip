@@ -50,6 +50,7 @@ namespace {
 
 constexpr int N125 = Q * Q * Q;
 constexpr int MAX_GRID3 = 1 << 22;   // workgroups per launch; larger grids loop
+constexpr int CUS = 256;             // compute units of an MI355X
 
 struct P3 {
     int nx, ny, nz;
@@ -78,15 +79,18 @@ __device__ __forceinline__ int wrap(int s, int n)
 struct Segment {
     int row, x;
 };
-// WHOLE: rows of a multiple of four segments, whose four waves are the tile's;
-// the row is the workgroup's (256^3 FP64 5820 us a step, 5900 by waves; 200 x 100 x
-// 150 1165, 1195; FP32 only with non-temporal stores: 250 x 128 x 100 636, 624).
+// WHOLE: tiles of up to four segments of one row, which is the workgroup's: rows
+// of a multiple of four segments (256^3 FP64 5820 us a step, 5900 by waves; 200 x 100
+// x 150 1165, 1195; FP32 only with non-temporal stores: 250 x 128 x 100 636, 624), and
+// lattices of at most a tile per CU, whose rows four to a workgroup would leave
+// three quarters of the CUs idle (16^3 FP64 9.9 us a step, 15.3 by waves; 30^3, of
+// 900 tiles, 31.7 and 16.7).
 template <bool WHOLE = false>
 __device__ __forceinline__ Segment segment(const P3 &p, int tile)
 {
     if constexpr (WHOLE) {
-        const int row = tile / (p.segs_x / 4);
-        return {row, (tile - row * (p.segs_x / 4)) * TX + (int)threadIdx.x};
+        const int across = (p.segs_x + 3) / 4, row = tile / across;
+        return {row, (tile - row * across) * TX + (int)threadIdx.x};
     }
     const int seg = __builtin_amdgcn_readfirstlane(tile * (TX / 64) + (int)(threadIdx.x >> 6));
     const int row = seg / p.segs_x;
@@ -351,17 +355,29 @@ constexpr size_t lds_cap()
     return sizeof(T) == 8 ? PLBM_Q125_LDS_F64 : PLBM_Q125_LDS_F32 - (SUMS ? 1024 : 0);
 }
 
+// Whether the tiles of a step are whole rows (see segment); then as many of them.
+template <typename T>
+bool whole_rows(const P3 &p, int &tiles)
+{
+    const long long whole = (long long)((p.segs_x + 3) / 4) * p.ny * p.nz;
+    const bool fill = p.segs_x % 4 == 0 && (sizeof(T) == 8 || rows_on_lines(p.nx, sizeof(T)));
+    if (!fill && whole > CUS) return false;
+    tiles = (int)whole;
+    return true;
+}
+
 template <typename T, bool SUMS>
-auto step3_kernel(const P3 &p)
+auto step3_kernel(const P3 &p, bool whole)
 {
     const bool nts = rows_on_lines(p.nx, sizeof(T));
-    if (p.segs_x % 4 == 0 && (nts || sizeof(T) == 8)) return nts ? k_step3d<T, SUMS, true, true> : k_step3d<T, SUMS, false, true>;
+    if (whole) return nts ? k_step3d<T, SUMS, true, true> : k_step3d<T, SUMS, false, true>;
     return nts ? k_step3d<T, SUMS, true, false> : k_step3d<T, SUMS, false, false>;
 }
 
 template <typename T>
-int q125_run(const P3 &p, void *fa, void *fb, int nsteps, double *sums, hipStream_t st)
+int q125_run(P3 p, void *fa, void *fb, int nsteps, double *sums, hipStream_t st)
 {
+    const bool whole = whole_rows<T>(p, p.ntiles);
     const int grid = grid_of(p);
     for (int s = 0; s < nsteps; ++s) {
         const T *src = static_cast<const T *>((s & 1) ? fb : fa);
@@ -372,13 +388,13 @@ int q125_run(const P3 &p, void *fa, void *fb, int nsteps, double *sums, hipStrea
             plbm::SumsArea area;
             int rc = plbm::sums_begin(area, 5, blocks, st);
             if (rc != PLBM_OK) return rc;
-            hipLaunchKernelGGL((step3_kernel<T, true>(p)), dim3(blocks), dim3(TX), (lds_cap<T, true>()), st, src, dst, p,
-                               area.part);
+            hipLaunchKernelGGL((step3_kernel<T, true>(p, whole)), dim3(blocks), dim3(TX), (lds_cap<T, true>()), st, src,
+                               dst, p, area.part);
             rc = q125_launch_status();
             return plbm::sums_end(area, 5, blocks, rc, sums, st);
         }
-        hipLaunchKernelGGL((step3_kernel<T, false>(p)), dim3(grid), dim3(TX), (lds_cap<T, false>()), st, src, dst, p,
-                           nullptr);
+        hipLaunchKernelGGL((step3_kernel<T, false>(p, whole)), dim3(grid), dim3(TX), (lds_cap<T, false>()), st, src, dst,
+                           p, nullptr);
         const int rc = q125_launch_status();
         if (rc != PLBM_OK) return rc;
     }

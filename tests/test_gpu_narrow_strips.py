@@ -5,7 +5,7 @@ import pytest
 import torch
 
 from paper_1402_5487_amd import inputs
-from paper_1402_5487_amd.lattice import Lattice
+from paper_1402_5487_amd.lattice import Lattice, Lattice3
 
 pytestmark = pytest.mark.gpu
 
@@ -57,3 +57,19 @@ def test_flat_lattices_equal_single_steps(nx, ny, kw, theta, storage):
     for _ in range(19):
         b.step(1)
     assert torch.equal(a.f, b.f) and a.cur == b.cur
+
+
+# boxes of at most 256 rows take whole rows, larger ones four segments a
+# workgroup: a box and four copies of it, along z, keep the same state
+@pytest.mark.parametrize("nx,ny,nz", [(16, 16, 16), (3, 5, 7), (129, 8, 20), (300, 9, 14), (70, 11, 13)])
+@pytest.mark.parametrize("storage", ["f64", "f32"])
+def test_small_boxes_equal_their_doubles(nx, ny, nz, storage):
+    g = torch.Generator().manual_seed(nx)
+    fields = [c + a * torch.rand(nz, ny, nx, generator=g, dtype=torch.float64)
+              for c, a in ((1.0, 0.02), (0.0, 0.02), (0.0, 0.02), (0.0, 0.02), (0.4, 0.01))]
+    a, b = (Lattice3(nx, ny, n, omega=1.2, storage=storage) for n in (nz, 4 * nz))
+    a.init(*fields)
+    b.init(*(f.repeat(4, 1, 1) for f in fields))
+    sa, sb = a.step(3, sums=True), b.step(3, sums=True)
+    assert torch.equal(b.f.view(4, -1), a.f.view(1, -1).expand(4, -1))
+    assert all(abs(4 * x - y) <= 1e-12 * 4 * abs(sa[0]) for x, y in zip(sa, sb))

@@ -189,3 +189,13 @@ def test_a_box_with_sums_leaves_lds_for_them(recorder, nx, storage):  # noqa: F8
     d = _plbm.desc_3d(nx, 8, 8, 1.2, storage)
     one, last = [x for x in recorder.step(d, 2, sums=True) if x.kernel == "k_step3d"]
     assert one.lds <= 160 * 1024 and last.lds + 5 * 4 * 8 <= 160 * 1024
+
+
+@pytest.mark.parametrize("nx,ny,nz,grid", [
+    (16, 16, 16, 256), (3, 3, 3, 9), (128, 16, 16, 256), (300, 16, 8, 256),     # whole rows, at most one per CU
+    (16, 16, 17, 68), (30, 30, 30, 225), (129, 16, 17, 204),                    # four segments a workgroup
+    (256, 20, 20, 400)])                                                        # whole rows that fill it
+@pytest.mark.parametrize("storage", ["f64", "f32"])
+def test_workgroups_of_a_box(recorder, nx, ny, nz, grid, storage):  # noqa: F811
+    d = _plbm.desc_3d(nx, ny, nz, 1.2, storage)
+    assert [x.grid for x in recorder.step(d, 2)] == [grid] * 2
