@@ -85,7 +85,7 @@ struct Segment {
 // lattices of at most a tile per CU, whose rows four to a workgroup would leave
 // three quarters of the CUs idle (16^3 FP64 9.9 us a step, 15.3 by waves; 30^3, of
 // 900 tiles, 31.7 and 16.7).
-template <bool WHOLE = false>
+template <bool WHOLE>
 __device__ __forceinline__ Segment segment(const P3 &p, int tile)
 {
     if constexpr (WHOLE) {
@@ -240,7 +240,7 @@ __global__ __launch_bounds__(TX) void k_step3d(const T *__restrict__ src, T *__r
 // Initial state: node (x, y, z) evaluates f_eq(rho, u, theta) in FP64 and
 // writes population k to (x - v_i, y - v_j, z - v_l), so the first pull
 // returns exactly f_eq.
-template <typename T>
+template <typename T, bool WHOLE>
 __global__ __launch_bounds__(TX) void k_init3d(const double *__restrict__ rho, const double *__restrict__ ux,
                                                const double *__restrict__ uy, const double *__restrict__ uz,
                                                const double *__restrict__ th, T *__restrict__ dst, P3 p)
@@ -248,9 +248,9 @@ __global__ __launch_bounds__(TX) void k_init3d(const double *__restrict__ rho, c
     const long long rowelems = (long long)N125 * p.nx;
 #pragma unroll 1
     for (int tile = blockIdx.x; tile < p.ntiles; tile += gridDim.x) {
-        const Segment g = segment(p, tile);
+        const Segment g = segment<WHOLE>(p, tile);
         const int row = g.row, z = row / p.ny, y = row - z * p.ny, x = g.x;
-        if (row < 0 || x >= p.nx) continue;
+        if ((!WHOLE && row < 0) || x >= p.nx) continue;
         const long long n = (long long)row * p.nx + x;
         double rx[Q], ry[Q], rz[Q];
         rule_sym<double>(ux[n], th[n], p.r64, rx);
@@ -277,7 +277,7 @@ __global__ __launch_bounds__(TX) void k_init3d(const double *__restrict__ rho, c
 
 // Macroscopic fields of the pulled state (3 rho theta = sum f |v - u|^2) and
 // optional FP64 block sums in the order of the step's.
-template <typename T>
+template <typename T, bool WHOLE>
 __global__ __launch_bounds__(TX) void k_moments3d(const T *__restrict__ src, P3 p, double *__restrict__ rho,
                                                   double *__restrict__ ux, double *__restrict__ uy,
                                                   double *__restrict__ uz, double *__restrict__ th,
@@ -286,9 +286,9 @@ __global__ __launch_bounds__(TX) void k_moments3d(const T *__restrict__ src, P3 
     double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
 #pragma unroll 1
     for (int tile = blockIdx.x; tile < p.ntiles; tile += gridDim.x) {
-        const Segment g = segment(p, tile);
+        const Segment g = segment<WHOLE>(p, tile);
         const int row = g.row, z = row / p.ny, y = row - z * p.ny, x = g.x;
-        if (row < 0 || x >= p.nx) continue;
+        if ((!WHOLE && row < 0) || x >= p.nx) continue;
         double f[N125];
         gather125<T, double>(src, p, x, y, z, f);
         double r, jx, jy, jz, e;
@@ -429,12 +429,13 @@ extern "C" int plbm_init3(const plbm_desc *d, const double *rho, const double *u
     if (!rho || !ux || !uy || !uz || !theta || !f) return PLBM_EINVAL;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     (void)hipGetLastError();
-    if (d->storage == PLBM_F64)
-        hipLaunchKernelGGL(k_init3d<double>, dim3(grid_of(p)), dim3(TX), 0, st, rho, ux, uy, uz, theta,
-                           (double *)f, p);
-    else
-        hipLaunchKernelGGL(k_init3d<float>, dim3(grid_of(p)), dim3(TX), 0, st, rho, ux, uy, uz, theta,
-                           (float *)f, p);
+    if (d->storage == PLBM_F64) {
+        auto *kernel = whole_rows<double>(p, p.ntiles) ? k_init3d<double, true> : k_init3d<double, false>;
+        hipLaunchKernelGGL(kernel, dim3(grid_of(p)), dim3(TX), 0, st, rho, ux, uy, uz, theta, (double *)f, p);
+    } else {
+        auto *kernel = whole_rows<float>(p, p.ntiles) ? k_init3d<float, true> : k_init3d<float, false>;
+        hipLaunchKernelGGL(kernel, dim3(grid_of(p)), dim3(TX), 0, st, rho, ux, uy, uz, theta, (float *)f, p);
+    }
     return q125_launch_status();
 }
 
@@ -446,6 +447,8 @@ extern "C" int plbm_moments3(const plbm_desc *d, const void *f, double *rho, dou
     if (rc != PLBM_OK) return rc;
     if (!f) return PLBM_EINVAL;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+    const bool wide = d->storage == PLBM_F64;
+    const bool whole = wide ? whole_rows<double>(p, p.ntiles) : whole_rows<float>(p, p.ntiles);
     int grid = grid_of(p);
     plbm::SumsArea area;
     if (sums) {
@@ -454,12 +457,12 @@ extern "C" int plbm_moments3(const plbm_desc *d, const void *f, double *rho, dou
     }
     double *part = area.part;
     (void)hipGetLastError();
-    if (d->storage == PLBM_F64)
-        hipLaunchKernelGGL(k_moments3d<double>, dim3(grid), dim3(TX), 0, st, (const double *)f, p, rho, ux, uy, uz,
-                           theta, part);
+    if (wide)
+        hipLaunchKernelGGL((whole ? k_moments3d<double, true> : k_moments3d<double, false>), dim3(grid), dim3(TX), 0, st,
+                           (const double *)f, p, rho, ux, uy, uz, theta, part);
     else
-        hipLaunchKernelGGL(k_moments3d<float>, dim3(grid), dim3(TX), 0, st, (const float *)f, p, rho, ux, uy, uz,
-                           theta, part);
+        hipLaunchKernelGGL((whole ? k_moments3d<float, true> : k_moments3d<float, false>), dim3(grid), dim3(TX), 0, st,
+                           (const float *)f, p, rho, ux, uy, uz, theta, part);
     rc = q125_launch_status();
     return sums ? plbm::sums_end(area, 5, grid, rc, sums, st) : rc;
 }

@@ -199,3 +199,14 @@ def test_a_box_with_sums_leaves_lds_for_them(recorder, nx, storage):  # noqa: F8
 def test_workgroups_of_a_box(recorder, nx, ny, nz, grid, storage):  # noqa: F811
     d = _plbm.desc_3d(nx, ny, nz, 1.2, storage)
     assert [x.grid for x in recorder.step(d, 2)] == [grid] * 2
+
+
+@pytest.mark.parametrize("nx,ny,nz,grid", [(16, 16, 16, 256), (20, 20, 20, 100), (256, 20, 20, 400)])
+def test_workgroups_of_fields_of_a_box(recorder, nx, ny, nz, grid):  # noqa: F811
+    """Initial states and moments are cut as the step is."""
+    d = _plbm.desc_3d(nx, ny, nz, 1.2, "f64")
+    at = [ctypes.c_void_p(0x1000 * (i + 1)) for i in range(6)]
+    recorder.lib.rec_clear()
+    assert recorder.lib.plbm_init3(ctypes.byref(d), *at, None) == _plbm.PLBM_OK
+    assert recorder.lib.plbm_moments3(ctypes.byref(d), *at, None, None) == _plbm.PLBM_OK
+    assert [(x.kernel, x.grid) for x in recorder.launches()] == [("k_init3d", grid), ("k_moments3d", grid)]
