@@ -257,7 +257,7 @@ int plbm_advance_fields(const plbm_desc *d, void *f_a, void *f_b, int nsteps, do
  * errors as plbm_step, for the descriptors of the symmetric five-velocity
  * model (D1Q5 and D2Q25, every storage form); other descriptors return
  * PLBM_EUNSUPPORTED.  The populations it writes are bitwise those of
- * plbm_step; the sums agree to FP64 rounding (their partial sums are grouped
+ * plbm_step; the sums agree to FP64 rounding (their partial sums may be grouped
  * differently).
  * Scratch: the partial sums of a call that asks for sums live in a
  * library-owned array in device memory, (8192 + 1) * 4 doubles (256 KiB),

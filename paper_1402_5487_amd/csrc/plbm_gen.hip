@@ -198,7 +198,7 @@ __global__ __launch_bounds__(TX) void k_step_gen2d(const T *__restrict__ src, T 
 {
     using C = T;
     constexpr int NG = Q1 * Q1;
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    LaneSums<4> sums;
     const long long rowelems = (long long)NG * p.nx;
     const int slot = xcd_tile(blockIdx.x, gridDim.x);
 #pragma unroll 1
@@ -215,17 +215,15 @@ __global__ __launch_bounds__(TX) void k_step_gen2d(const T *__restrict__ src, T 
                 for (int k = 0; k < NG; ++k) g[k] = (C)(T)f[k];
                 C rho, jx, jy, e;
                 sums_gen2d<Q1, C>(g, p, rho, jx, jy, e);
-                acc[0] += rho;
-                acc[1] += jx;
-                acc[2] += jy;
-                acc[3] += e;
+                const double all[4] = {rho, jx, jy, e};
+                sums.add(all);
             }
             T *out = dst + (y * rowelems + xb);
 #pragma unroll
             for (int k = 0; k < NG; ++k) store_stream<NTS>((T)f[k], out + (long long)k * p.nx);
         }
     }
-    if constexpr (SUMS) block_sums_store<4>(acc, partials + (size_t)blockIdx.x * 4);
+    if constexpr (SUMS) sums.store(partials + (size_t)blockIdx.x * 4);
 }
 
 // Two steps per launch (plbm_sweep.h) of one velocity set.
@@ -303,7 +301,7 @@ __global__ __launch_bounds__(TX) void k_moments_gen2d(const T *__restrict__ src,
                                                       double *__restrict__ uy, double *__restrict__ th,
                                                       double *__restrict__ partials)
 {
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    LaneSums<4> sums;
 #pragma unroll 1
     for (int tile = blockIdx.x; tile < p.ntiles; tile += gridDim.x) {
         const int y = tile / p.tiles_x;
@@ -319,12 +317,10 @@ __global__ __launch_bounds__(TX) void k_moments_gen2d(const T *__restrict__ src,
         if (ux) ux[n] = u;
         if (uy) uy[n] = w;
         if (th) th[n] = 0.5 * (e / r - u * u - w * w);
-        acc[0] += r;
-        acc[1] += jx;
-        acc[2] += jy;
-        acc[3] += e;
+        const double all[4] = {r, jx, jy, e};
+        sums.add(all);
     }
-    if (partials) block_sums_store<4>(acc, partials + (size_t)blockIdx.x * 4);
+    if (partials) sums.store(partials + (size_t)blockIdx.x * 4);
 }
 
 // ---------------------------------------------------------------------------
@@ -369,7 +365,7 @@ __global__ __launch_bounds__(TX) void k_step_gen1d(const T *__restrict__ src, T 
 {
     using C = T;
     const long long ps = (long long)p.nx + 2 * PLBM_GHOST;
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    LaneSums<4> sums;
 #pragma unroll 1
     for (int tile = blockIdx.x; tile < p.ntiles; tile += gridDim.x) {
         const int x = tile * TX + threadIdx.x;
@@ -378,6 +374,7 @@ __global__ __launch_bounds__(TX) void k_step_gen1d(const T *__restrict__ src, T 
 #pragma unroll
         for (int k = 0; k < Q1; ++k) f[k] = (C)src[k * ps + x + PLBM_GHOST - p.sx[k]];
         collide_gen1d<Q1, C>(f, p);
+        double acc[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int k = 0; k < Q1; ++k) {
             const T h = (T)f[k];
@@ -393,8 +390,9 @@ __global__ __launch_bounds__(TX) void k_step_gen1d(const T *__restrict__ src, T 
                 acc[3] += (double)h * vk * vk;
             }
         }
+        if constexpr (SUMS) sums.add(acc);
     }
-    if constexpr (SUMS) block_sums_store<4>(acc, partials + (size_t)blockIdx.x * 4);
+    if constexpr (SUMS) sums.store(partials + (size_t)blockIdx.x * 4);
 }
 
 // Padded index q holds node q - 3; its population k is f_eq_k of node
@@ -606,7 +604,7 @@ int gen_run(const GenParams &p, void *fa, void *fb, int nsteps, const plbm::Step
         if (s == nsteps - 1 && sums) {
             int blocks = grid_g(p);
             plbm::SumsArea area;
-            int rc = plbm::sums_begin(area, 4, blocks, st);
+            int rc = plbm::sums_begin(area, 4, blocks, true, st);
             if (rc != PLBM_OK) return rc;
             gen_launch<Q1, T, true>(p, src, dst, area.part, st, blocks);
             rc = gen_launch_status();
@@ -639,7 +637,7 @@ int gen_moments_t(const GenParams &p, const void *f, double *rho, double *ux, do
     int grid = p.dim == 2 ? grid_g(p) : p.tiles_x;
     plbm::SumsArea area;
     if (sums) {
-        const int rc = plbm::sums_begin(area, 4, grid, st);
+        const int rc = plbm::sums_begin(area, 4, grid, p.dim == 2, st);
         if (rc != PLBM_OK) return rc;
     }
     (void)hipGetLastError();

@@ -14,15 +14,17 @@ void note_hip_error(const char *what, int code);
 
 // Device memory for the partial sums of one call that asks for sums (`blocks`
 // workgroups, nv doubles each, and nv results).  It is the library's static
-// scratch while that is free, holds so many and the stream belongs to the
-// current device (allocating and freeing took 18 us of a 50 us call), else a
-// stream-ordered allocation.  Every sums_begin that returned PLBM_OK is followed
-// by sums_end, which synchronises the stream before it gives the memory back.
+// scratch while that is free and the stream belongs to the current device
+// (allocating and freeing took 18 us of a 50 us call), else a stream-ordered
+// allocation.  walks: the workgroups walk the tiles (see LaneSums), and `blocks` is
+// lowered to what the scratch holds partials of, wherever they go in the end.
+// Every sums_begin that returned PLBM_OK is followed by sums_end, which
+// synchronises the stream before it gives the memory back.
 struct SumsArea {
     double *part = nullptr;
     std::mutex *held = nullptr;   // of the scratch in use (null: allocated)
 };
-int sums_begin(SumsArea &a, int nv, int blocks, void *stream);
+int sums_begin(SumsArea &a, int nv, int &blocks, bool walks, void *stream);
 // rc: the status of the launches so far; reduces the partials, fetches and
 // checks the nv sums.
 int sums_end(SumsArea &a, int nv, int blocks, int rc, double *host, void *stream);

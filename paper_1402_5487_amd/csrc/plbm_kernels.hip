@@ -73,12 +73,15 @@ __global__ __launch_bounds__(TX, PLBM_MIN_WAVES) void k_step2d(const typename S:
                                                                KParams p,
                                                                double *__restrict__ partials)
 {
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    LaneSums<4> sums;
     const int slot = xcd_tile(blockIdx.x, gridDim.x);
 #pragma unroll 1
-    for (int tile = slot; tile < p.ntiles; tile += gridDim.x)
+    for (int tile = slot; tile < p.ntiles; tile += gridDim.x) {
+        double acc[4] = {0.0, 0.0, 0.0, 0.0};
         step_tile<S, NV, SUMS, NTS>(src, dst, p, tile, acc);
-    if constexpr (SUMS) block_sums_store<4>(acc, partials + (size_t)blockIdx.x * 4);
+        if constexpr (SUMS) sums.add(acc);
+    }
+    if constexpr (SUMS) sums.store(partials + (size_t)blockIdx.x * 4);
 }
 
 // The same step, also writing the pre-collision fields of the state it reads
@@ -168,7 +171,7 @@ __global__ __launch_bounds__(TX) void k_moments2d(const typename S::T *__restric
                                                   double *__restrict__ uy, double *__restrict__ th,
                                                   double *__restrict__ partials)
 {
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    LaneSums<4> sums;
     const int segs = (p.nx + TX - 1) / TX;
     const long long total = (long long)segs * p.ny;
 #pragma unroll 1
@@ -200,9 +203,10 @@ __global__ __launch_bounds__(TX) void k_moments2d(const typename S::T *__restric
         if (ux) ux[n] = u;
         if (uy) uy[n] = w;
         if (th) th[n] = 0.5 * (e * inv - u * u - w * w);
-        acc[0] += r; acc[1] += jx; acc[2] += jy; acc[3] += e;
+        const double all[4] = {r, jx, jy, e};
+        sums.add(all);
     }
-    if (partials) block_sums_store<4>(acc, partials + (size_t)blockIdx.x * 4);
+    if (partials) sums.store(partials + (size_t)blockIdx.x * 4);
 }
 
 // ---------------------------------------------------------------------------
@@ -619,7 +623,7 @@ int run_steps(const KParams &p, const plbm_desc *d, void *fa, void *fb, int nste
             int blocks = d->dim == 2 ? grid_for(p.ntiles) : (p.nx + TX - 1) / TX;
             plbm::SumsArea area;
             if (call.noalloc) blocks = std::min(blocks, NOALLOC_BLOCKS);
-            int rc = call.noalloc ? scratch_wait(area) : plbm::sums_begin(area, 4, blocks, st);
+            int rc = call.noalloc ? scratch_wait(area) : plbm::sums_begin(area, 4, blocks, d->dim == 2, st);
             if (rc != PLBM_OK) return rc;
             rc = launch_step<S, true>(p, d, src, dst, area.part, st, nb, blocks);
             return plbm::sums_end(area, 4, blocks, rc, sums, st);
@@ -747,10 +751,11 @@ void note_hip_error(const char *what, int code)
     std::snprintf(g_last_error, sizeof(g_last_error), "%s (%d)", what, code);
 }
 
-int sums_begin(SumsArea &a, int nv, int blocks, void *stream)
+int sums_begin(SumsArea &a, int nv, int &blocks, bool walks, void *stream)
 {
     hipStream_t st = as_stream(stream);
     const int most = SCRATCH_ELEMS / nv - 1;
+    if (walks) blocks = std::min(blocks, most);
     int dev = -1, of = -1;
     if (blocks <= most && hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < MAX_DEVICES &&
         (!st || (hipStreamGetDevice(st, &of) == hipSuccess && of == dev)) && g_scratch[1][dev].mu.try_lock()) {
@@ -907,7 +912,7 @@ extern "C" int plbm_moments(const plbm_desc *d, const void *f, double *rho, doub
     if (!sums) return moments_dispatch(p, d, f, rho, ux, uy, theta, nullptr, st, nb);
     int blocks = d->dim == 2 ? grid_for((long long)((p.nx + TX - 1) / TX) * p.ny) : (p.nx + TX - 1) / TX;
     plbm::SumsArea area;
-    rc = plbm::sums_begin(area, 4, blocks, st);
+    rc = plbm::sums_begin(area, 4, blocks, d->dim == 2, st);
     if (rc != PLBM_OK) return rc;
     rc = moments_dispatch(p, d, f, rho, ux, uy, theta, area.part, st, nb, blocks);
     return plbm::sums_end(area, 4, blocks, rc, sums, st);

@@ -205,7 +205,7 @@ __global__ __launch_bounds__(TX) void k_step3d(const T *__restrict__ src, T *__r
 {
     using C = T;
     const SymRule<C> &R = rule_of<C>(p);
-    double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    LaneSums<5> sums;
     const long long rowelems = (long long)N125 * p.nx;
     const int slot = xcd_tile(blockIdx.x, gridDim.x);
 #pragma unroll 1
@@ -223,18 +223,15 @@ __global__ __launch_bounds__(TX) void k_step3d(const T *__restrict__ src, T *__r
                 for (int k = 0; k < N125; ++k) g[k] = (C)(T)f[k];
                 C rho, jx, jy, jz, e;
                 sums125<C>(g, R, rho, jx, jy, jz, e);
-                acc[0] += rho;
-                acc[1] += jx;
-                acc[2] += jy;
-                acc[3] += e;
-                acc[4] += jz;
+                const double all[5] = {rho, jx, jy, e, jz};
+                sums.add(all);
             }
             T *base = dst + ((long long)row * rowelems + xb);
 #pragma unroll
             for (int k = 0; k < N125; ++k) store_stream<NTS>((T)f[k], base + (long long)k * p.nx);
         }
     }
-    if constexpr (SUMS) block_sums_store<5>(acc, partials + (size_t)blockIdx.x * 5);
+    if constexpr (SUMS) sums.store(partials + (size_t)blockIdx.x * 5);
 }
 
 // Initial state: node (x, y, z) evaluates f_eq(rho, u, theta) in FP64 and
@@ -283,7 +280,7 @@ __global__ __launch_bounds__(TX) void k_moments3d(const T *__restrict__ src, P3 
                                                   double *__restrict__ uz, double *__restrict__ th,
                                                   double *__restrict__ partials)
 {
-    double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    LaneSums<5> sums;
 #pragma unroll 1
     for (int tile = blockIdx.x; tile < p.ntiles; tile += gridDim.x) {
         const Segment g = segment<WHOLE>(p, tile);
@@ -300,13 +297,10 @@ __global__ __launch_bounds__(TX) void k_moments3d(const T *__restrict__ src, P3 
         if (uy) uy[n] = v;
         if (uz) uz[n] = w;
         if (th) th[n] = (e / r - (u * u + v * v + w * w)) / 3.0;
-        acc[0] += r;
-        acc[1] += jx;
-        acc[2] += jy;
-        acc[3] += e;
-        acc[4] += jz;
+        const double all[5] = {r, jx, jy, e, jz};
+        sums.add(all);
     }
-    if (partials) block_sums_store<5>(acc, partials + (size_t)blockIdx.x * 5);
+    if (partials) sums.store(partials + (size_t)blockIdx.x * 5);
 }
 
 int q125_hip(hipError_t e)
@@ -386,7 +380,7 @@ int q125_run(P3 p, void *fa, void *fb, int nsteps, double *sums, hipStream_t st)
         if (s == nsteps - 1 && sums) {
             int blocks = grid;
             plbm::SumsArea area;
-            int rc = plbm::sums_begin(area, 5, blocks, st);
+            int rc = plbm::sums_begin(area, 5, blocks, true, st);
             if (rc != PLBM_OK) return rc;
             hipLaunchKernelGGL((step3_kernel<T, true>(p, whole)), dim3(blocks), dim3(TX), (lds_cap<T, true>()), st, src,
                                dst, p, area.part);
@@ -452,7 +446,7 @@ extern "C" int plbm_moments3(const plbm_desc *d, const void *f, double *rho, dou
     int grid = grid_of(p);
     plbm::SumsArea area;
     if (sums) {
-        rc = plbm::sums_begin(area, 5, grid, st);
+        rc = plbm::sums_begin(area, 5, grid, true, st);
         if (rc != PLBM_OK) return rc;
     }
     double *part = area.part;

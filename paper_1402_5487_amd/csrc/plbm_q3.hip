@@ -157,7 +157,7 @@ __global__ __launch_bounds__(TX) void k_step_q9(const T *__restrict__ src, T *__
                                                 double *__restrict__ partials)
 {
     const Rule3<C> &R = rule_of<C>(p);
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    LaneSums<4> sums;
     const long long rowelems = (long long)N9 * p.nx;
     const int slot = xcd_tile(blockIdx.x, gridDim.x);
 #pragma unroll 1
@@ -174,17 +174,15 @@ __global__ __launch_bounds__(TX) void k_step_q9(const T *__restrict__ src, T *__
                 for (int k = 0; k < N9; ++k) g[k] = (C)(T)f[k];
                 C rho, jx, jy, e;
                 sums9<C>(g, R, rho, jx, jy, e);
-                acc[0] += rho;
-                acc[1] += jx;
-                acc[2] += jy;
-                acc[3] += e;
+                const double all[4] = {rho, jx, jy, e};
+                sums.add(all);
             }
             T *out = dst + (y * rowelems + xb);
 #pragma unroll
             for (int k = 0; k < N9; ++k) store_stream<NTS>((T)f[k], out + (long long)k * p.nx);
         }
     }
-    if constexpr (SUMS) block_sums_store<4>(acc, partials + (size_t)blockIdx.x * 4);
+    if constexpr (SUMS) sums.store(partials + (size_t)blockIdx.x * 4);
 }
 
 // Several steps per launch (plbm_sweep.h) of the set {0, +1, -1}.
@@ -260,7 +258,7 @@ __global__ __launch_bounds__(TX) void k_moments_q9(const T *__restrict__ src, Q9
                                                    double *__restrict__ ux, double *__restrict__ uy,
                                                    double *__restrict__ th, double *__restrict__ partials)
 {
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    LaneSums<4> sums;
 #pragma unroll 1
     for (int tile = blockIdx.x; tile < p.ntiles; tile += gridDim.x) {
         const int y = tile / p.tiles_x;
@@ -276,12 +274,10 @@ __global__ __launch_bounds__(TX) void k_moments_q9(const T *__restrict__ src, Q9
         if (ux) ux[n] = u;
         if (uy) uy[n] = w;
         if (th) th[n] = 0.5 * (e / r - u * u - w * w);
-        acc[0] += r;
-        acc[1] += jx;
-        acc[2] += jy;
-        acc[3] += e;
+        const double all[4] = {r, jx, jy, e};
+        sums.add(all);
     }
-    if (partials) block_sums_store<4>(acc, partials + (size_t)blockIdx.x * 4);
+    if (partials) sums.store(partials + (size_t)blockIdx.x * 4);
 }
 
 // ---------------------------------------------------------------------------
@@ -535,7 +531,7 @@ int q9_run(const Q9Params &p, void *fa, void *fb, int nsteps, const plbm::StepCa
         if (s == nsteps - 1 && sums) {
             int blocks = nblocks;
             plbm::SumsArea area;
-            int rc = plbm::sums_begin(area, 4, blocks, st);
+            int rc = plbm::sums_begin(area, 4, blocks, p.dim == 2, st);
             if (rc != PLBM_OK) return rc;
             q3_launch<T, C, true>(p, src, dst, area.part, st, blocks);
             rc = q9_launch_status();
@@ -600,7 +596,7 @@ int q3_moments(const plbm_desc *d, const void *f, double *rho, double *ux, doubl
     int blocks = p.dim == 2 ? grid_for(p.ntiles) : p.tiles_x;
     plbm::SumsArea area;
     if (sums) {
-        rc = plbm::sums_begin(area, 4, blocks, st);
+        rc = plbm::sums_begin(area, 4, blocks, p.dim == 2, st);
         if (rc != PLBM_OK) return rc;
     }
     const dim3 g(blocks);

@@ -1,8 +1,9 @@
 """The FP64 sums of a step and of moments() against torch's FP64 sum of the
 stored populations with the weights 1, v_x, v_y, |v|^2 (and v_z), on lattices
 of more row tiles than the library's scratch holds partials of (8192 in 1D and
-2D, 6553 in 3D), where they go to an allocation, and of fewer.  FP64 storage
-(the FP32 forms add up the populations of one node in FP32).
+2D, 6553 in 3D), where workgroups walk several or, in 1D, the partials go to an
+allocation, and of fewer.  FP64 storage (the FP32 forms add up the populations
+of one node in FP32).
 
 Tolerance: a chain of n additions in FP64 is off by at most n u sum |w f|, u =
 2^-53.  A lane adds fewer than 64 populations per tile of at most two, a tree of
