@@ -231,7 +231,7 @@ k_fused_list(const BFused *__restrict__ list, KParams proto, int parity)
 // How a batch takes several steps per launch: three on tiles of 8 x 8 or
 // 16 x 16 nodes while that is at most one tile per CU, two on 16 x 16 up to 2^20
 // nodes, three on strips beyond, with a pair for two steps left over (pairs
-// alone where their workgroups come to fewer rows, see strip_rows).  Measured
+// alone where they are faster), as far as that beats single steps (see build_fused).  Measured
 // (us a step, single / strips of two / chosen): 4 lattices of 64 4.9 / - / 2.6, 20 of 64
 // 6.2 / - / 5.0, 6 of 64..128 5.5 / - / 3.6, 40 of 64..128 18.3 / 12.9 / 10.9, 10 of
 // 64..256 16.1 / 11.7 / 9.9, 5 of 64..512 27.8 / 18.9 / 17.4, 40 of 64..512 142 / 94 /
@@ -408,32 +408,37 @@ int build_tiles(plbm_batch *b)
     return PLBM_OK;
 }
 
-// Rows a chunk of strips of D steps takes: those for which the rounds of
-// resident workgroups, each as long as a chunk and its halo, are least (a last
-// round of a few workgroups costs as much as a full one: 100 lattices of
-// 64..128 took 27 us a step with 10 rows in pairs, 34 with 16; 40 of 64..512 took
-// 94 with 22, 98 with 16).  Pairs: past eight rounds 16 (see sweep_grid: 256 of
-// 64..512 took 534 us, 561 with 32).  cost: the rows of these rounds.
+// What the rounds of resident workgroups compute one after another when each
+// lattice's strips of D steps are cut into chunks of at most `height` rows.
 template <int D>
-int strip_rows(const plbm_batch *b, long long &cost)
+long long strip_rounds(const std::map<std::pair<int, int>, int> &sizes, int height)
 {
     constexpr int slots = SWEEP_CUS * sweep_per_cu<Model32, D>(), halo = 2 * Lines<Model32>::R * (D - 1);
-    std::map<std::pair<int, int>, int> sizes;
-    for (const auto &s : b->specs) ++sizes[{s.nx, s.ny}];
-    auto rows = [&](int h) {
-        long long n = 0;
-        for (const auto &kv : sizes) {
-            SweepGrid g = sweep_grid<Model32, D>(kv.first.first, kv.first.second);
-            g.even_rows(kv.first.second, h);
-            n += (long long)g.wgs * kv.second;
-        }
-        return (n + slots - 1) / slots * (h + halo);
-    };
+    long long n = 0;
+    int h = 0;
+    for (const auto &kv : sizes) {
+        SweepGrid g = sweep_grid<Model32, D>(kv.first.first, kv.first.second);
+        g.even_rows(kv.first.second, height);
+        n += (long long)g.wgs * kv.second;
+        h = std::max(h, g.h);
+    }
+    return (n + slots - 1) / slots * (h + halo);
+}
+
+// Rows a chunk of strips of D steps takes: those for which the rounds are least (a
+// last round of a few workgroups costs as much as a full one: 100 lattices of
+// 64..128 took 27 us a step with 10 rows in pairs, 34 with 16; 40 of 64..512 took
+// 94 with 22, 98 with 16).  Pairs: past eight rounds 16 (see sweep_grid: 256 of
+// 64..512 took 534 us, 561 with 32).  cost: strip_rounds.
+template <int D>
+int strip_rows(const std::map<std::pair<int, int>, int> &sizes, long long &cost)
+{
+    constexpr int halo = 2 * Lines<Model32>::R * (D - 1);
     int best = 16;
-    cost = rows(best);
+    cost = strip_rounds<D>(sizes, best);
     if (D == 2 && cost > 8 * (best + halo)) return best;
     for (int h = 4; h <= (D == 2 ? 24 : 200); h += 2)
-        if (const long long c = rows(h); c < cost) {
+        if (const long long c = strip_rounds<D>(sizes, h); c < cost) {
             best = h;
             cost = c;
         }
@@ -518,14 +523,26 @@ int build_tiles(plbm_batch *b, Fused form, int side)
     });
 }
 
+// What a launch of a batch takes (see LaunchTime): a single step, by segments of 64
+// lanes; a pair of steps on tiles of 16 x 16; two and three on strips.  Fitted to 4
+// to 300 lattices of 3 x 3000 to 10000 x 3 nodes.  The rule changed, us a step before
+// and after: 40 lattices of 3000 x 3 32 and 18, 300 of 1000 x 3 75 and 38, 300 of 3000 x 3
+// 139 and 90.
+constexpr LaunchTime BATCH_SINGLE = {4.0, 0, 38}, BATCH_TILE = {4.5, 1.8, 12}, BATCH_PAIR = {2, 1.4, 22},
+                     BATCH_TRIPLE = {9.9, 1.8, 3.6};
+
 int build_fused(plbm_batch *b)
 {
-    long long nodes = 0;
+    long long nodes = 0, lanes = 0;
+    std::map<std::pair<int, int>, int> sizes;
     bool fit = paper_set(b->kp);
     for (const auto &s : b->specs) {
         nodes += (long long)s.nx * s.ny;
+        lanes += (long long)((s.nx + 63) / 64 * 64) * s.ny;
+        ++sizes[{s.nx, s.ny}];
         fit = fit && sweep_fits<Model32>(s.nx);
     }
+    const double single = BATCH_SINGLE.us(0, (double)lanes);
     b->depth = 1;
     if (!fit) return PLBM_OK;
     int rc = PLBM_OK, depth = 3;
@@ -534,13 +551,19 @@ int build_fused(plbm_batch *b)
     } else if (count_tiles(b, 16) <= SWEEP_CUS) {
         rc = build_tiles(b, Fused::tiles16, 16);
     } else if (nodes <= TILE_NODES) {
+        const double rounds = std::ceil((double)count_tiles(b, 16) / SWEEP_CUS);
+        if (BATCH_TILE.us(rounds, (double)nodes) >= 2 * single) return PLBM_OK;
         rc = build_tiles(b, Fused::tiles16x2, 16);
         depth = 2;
     } else {
         long long cost2, cost3;
-        const int rows2 = strip_rows<2>(b, cost2), rows3 = strip_rows<3>(b, cost3);
-        // microseconds of a row and step, as for single lattices
-        depth = 2.06 / 3 * cost3 <= 3.1 / 2 * cost2 ? 3 : 2;
+        const int rows2 = strip_rows<2>(sizes, cost2), rows3 = strip_rows<3>(sizes, cost3);
+        const double two = BATCH_PAIR.us((double)cost2, (double)nodes) / 2;
+        const double three = BATCH_TRIPLE.us((double)cost3, (double)nodes) / 3;
+        if (std::min(two, three) >= single) return PLBM_OK;
+        // an odd number of pairs' steps leaves a single one, which rows of a few
+        // nodes make dear (300 lattices of 3 x 3000: 4254 us, three steps 1930)
+        depth = three <= two || single > 3 * two ? 3 : 2;
         if (depth == 3) {
             rc = build_strips<3>(b, b->fused, rows3);
             if (rc == PLBM_OK) rc = build_strips<2>(b, b->rest, rows2);

@@ -27,6 +27,30 @@ class Batch:
         self.rec.lib.plbm_batch_destroy(self.h)
 
 
+FUSED = {"k_fused_groups", "k_fused_list"}
+
+
+# lattices of a few rows, of which tiles and strips compute several times the
+# nodes: measured at up to twice the single steps
+@pytest.mark.parametrize("sizes", [[(3000, 3)] * 40, [(1000, 3)] * 300, [(100, 3)] * 300, [(10000, 4)] * 4,
+                                   [(600 + i, 3 + i % 3) for i in range(60)]])
+def test_flat_batches_take_single_steps(recorder, sizes):  # noqa: F811
+    b = Batch(recorder, sizes)
+    assert not set(b.step(6)) & FUSED
+    b.close()
+
+
+# (sizes, fused launches of six steps, launches of two)
+@pytest.mark.parametrize("sizes,six", [([(3000, 3)] * 300, 3), ([(10000, 4)] * 300, 3), ([(70, 70)] * 300, 3),
+                                       ([(64, 64)] * 3, 2), ([(96, 96)] * 7, 2), ([(300, 300)] * 4, 3),
+                                       ([(512, 512)] * 40, 2), ([(2000, 33)] * 300, 2), ([(3, 3000)] * 300, 2)])
+def test_other_batches_are_fused(recorder, sizes, six):  # noqa: F811
+    b = Batch(recorder, sizes)
+    assert b.rec.lib.plbm_batch_set_graph_steps(b.h, 0) == _plbm.PLBM_OK
+    assert [k in FUSED for k in b.step(6)] == [True] * six
+    b.close()
+
+
 @pytest.mark.parametrize("sizes", [[(200 + i, 250 + 3 * i) for i in range(50)], [(64 + i, 90 + i) for i in range(50)]])
 def test_a_batch_without_memory_for_fused_lists_steps_one_by_one(recorder, sizes):  # noqa: F811
     """The population pool and the work list of the single step fit, nothing
