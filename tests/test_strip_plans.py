@@ -120,7 +120,7 @@ def test_long_calls_of_a_tube_are_short_launches(recorder, model, storage, nx, n
 
 # (model, storage, nx, ny, steps): measured at up to five times the single steps
 # on tiles or strips
-FLAT = [("d2q25", "f16dev", 100000, 3, 20), ("d2q25", "f16dev", 10000, 24, 3), ("d2q25", "f64", 10000, 3, 20),
+FLAT = [("d2q25", "f16dev", 100000, 3, 20), ("d2q25", "f16dev", 10000, 24, 3), ("d2q25", "f16dev", 113, 3000, 3), ("d2q25", "f64", 10000, 3, 20),
         ("d2q25", "f32", 30000, 3, 4), ("d2q16", "f32", 30000, 3, 20),
         ("d2q49", "f32", 10000, 3, 20), ("d2q49", "f64", 300000, 3, 20), ("d2q49", "f64", 100000, 3, 4)]
 # no tiles there: strips are faster than single steps
