@@ -58,9 +58,10 @@ def test_fused_steps_equal_single_steps(nx, ny, storage):
     assert torch.equal(a.f, b.f) and a.cur == b.cur
 
 
-# FP32 in threes: strips of 224 columns at and past their multiples, closed ones
-# with one, two and four chunks side by side, ragged rows, one chunk that is the
-# whole height; every remainder of the steps, with fields and with sums
+# FP32 in threes (strips of up to 240 columns) and, where those do not fill the
+# lanes, in pairs: closed strips with one, two and four chunks side by side, ragged
+# rows, one chunk that is the whole height; every remainder of the steps, with
+# fields and with sums
 @pytest.mark.parametrize("nx,ny", [(64, 17000), (63, 17001), (128, 8300), (224, 4700), (256, 4101), (448, 2353),
                                    (673, 1600), (1501, 707), (1121, 940), (16385, 65), (57344, 19)])
 def test_three_fused_steps_equal_single_steps(nx, ny):
@@ -75,6 +76,16 @@ def test_three_fused_steps_equal_single_steps(nx, ny):
     for _ in range(9):
         b.step(1)
     assert s == b.step(1, sums=True) and torch.equal(a.f, b.f)
+
+
+# widths that FP32 threes take in whole strips of 240 columns, and one column more
+# (a closed strip of 241, five and six of 208)
+@pytest.mark.parametrize("nx,ny", [(240, 4700), (241, 4700), (480, 2353), (960, 1200), (961, 1300), (1200, 900),
+                                   (1201, 1000)])
+def test_three_fused_steps_of_whole_strips_equal_single_steps(nx, ny):
+    fields = inputs.random_fields(nx, ny, seed=nx + ny)
+    a, b = _pair(lambda: Lattice(2, nx, ny, omega=1.7, storage="f32"), fields, 14, (9, 3, 2))
+    assert torch.equal(a.f, b.f) and a.cur == b.cur
 
 
 @pytest.mark.parametrize("nx,ny", [(1501, 1100), (1345, 1121), (224, 6700), (128, 11730)])
@@ -151,8 +162,8 @@ def test_fused_general_steps_equal_single_steps(nx, ny, storage, v, theta):
     assert torch.equal(a.f, b.f) and a.cur == b.cur
 
 
-# strips on half lines, of 240 (FP32 in threes) and 104 columns (D2Q49 in FP64): at
-# and past their multiples and whole ragged rows
+# strips on half lines, of 240 (FP32, threes and pairs) and 104 columns (D2Q49 in
+# FP64): at and past their multiples and whole ragged rows
 @pytest.mark.parametrize("nx,ny", [(104, 2600), (208, 1300), (209, 1301), (480, 2200), (481, 2190), (720, 1460)])
 @pytest.mark.parametrize("storage,v,theta", [("f32", (0, 1, -1, 3, -3), 0.4), ("f64", (0, 1, -1, 2, -2, 3, -3), 1.0)])
 def test_fused_steps_on_half_lines_equal_single_steps(nx, ny, storage, v, theta):
@@ -162,9 +173,10 @@ def test_fused_steps_on_half_lines_equal_single_steps(nx, ny, storage, v, theta)
     assert torch.equal(a.f, b.f) and a.cur == b.cur
 
 
-# 1D: one workgroup up to 1024 nodes (in place for an even number of steps);
-# tiles with halos beyond, the tile that leaves one node, fewer nodes than the
-# halo in the last tile; one step, few, many; the ghosts belong to the buffer
+# 1D: short lattices in one workgroup (in place for an even number of steps); tiles
+# with halos for longer ones, and for many steps of 1000 nodes; the tile that
+# leaves one node, fewer nodes than the halo in the last tile; one step, few, many;
+# the ghosts belong to the buffer
 @pytest.mark.parametrize("nx", [1, 2, 5, 63, 65, 1000, 1024, 1025, 1143, 5001, 70000])
 @pytest.mark.parametrize("model,storage", [("d1q5", "f64"), ("d1q5", "f32"), ("d1q3", "f64"), ("d1q3", "f32"),
                                            ("d1q4", "f64"), ("d1q7", "f32"), ("d1q7", "f64")])
@@ -184,7 +196,7 @@ def test_fused_tube_steps_equal_single_steps(nx, model, storage):
 
 
 # batches by their size: three steps on tiles of 8 x 8 and 16 x 16, two on
-# 16 x 16, pairs of strips past 2^20 nodes (rows of one, two and four chunks side
+# 16 x 16, strips of three past 2^20 nodes (rows of one, two and four chunks side
 # by side, several strips, ragged rows); up to 48 sizes decode arithmetically,
 # more go through a list; graph replays, a last fused launch and single steps
 MIXED = [(64, 64)] * 20 + [(100, 90)] * 12 + [(256, 250)] * 2 + [(300, 200), (513, 60), (31, 300)]

@@ -148,6 +148,13 @@ def test_other_lattices_keep_their_tiles(recorder, model, storage, nx, ny, n):  
     assert {x.kernel for x in recorder.step(MODELS[model](nx, ny, storage), n, "plbm_advance")} == {"k_tile"}
 
 
+@pytest.mark.parametrize("nx,ny,w", [(240, 4700, 240), (241, 4700, 241), (480, 2353, 240), (960, 1200, 240),
+                                     (961, 1300, 208), (1200, 900, 240), (1201, 1000, 208)])
+def test_whole_strips_take_three_steps(recorder, nx, ny, w):  # noqa: F811
+    got = recorder.step(MODELS["d2q25"](nx, ny, "f32"), 9, "plbm_advance")
+    assert len(got) == 3 and {(x.kernel, x.extra[2]) for x in got} == {("k_step2d_sweep", w)}
+
+
 @pytest.mark.parametrize("nx,ny", [(27000, 64), (30000, 48), (55000, 40)])
 def test_strips_fill_their_rounds(recorder, nx, ny):  # noqa: F811
     """D2Q49 FP64 has more strips than the 256 workgroups that run at once: the
