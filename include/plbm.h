@@ -344,7 +344,8 @@ typedef struct plbm_batch_info {
     int32_t tiles;              /* work-list entries */
     int32_t grid_mode;          /* 0: one workgroup per tile; k: k per CU */
     int32_t lds_bytes;          /* LDS reserved per workgroup (occupancy cap) */
-    int32_t graph_steps;        /* steps per captured graph (0: no graph) */
+    int32_t graph_steps;        /* steps per graph as set (0: no graph); not used by
+                                   batches that take three steps per launch */
     int32_t parity;             /* which of the two buffers holds the state */
     int64_t nodes;              /* total lattice nodes */
     int64_t pool_bytes;         /* device memory of all population buffers */
@@ -378,7 +379,9 @@ int plbm_batch_init(plbm_batch *b, int i, const double *rho, const double *ux,
  * (max(nx, ny); width 64/128/256 nodes, 1/2/4/8 passes) from a few policies
  * (the narrowest width covering the class, 64-wide, 256-wide; one or two
  * passes), together with the grid mode and LDS occupancy cap, by timing
- * whole-batch launches.  cache_path (nullable) names a JSON file read first
+ * whole-batch launches of single steps.  Tiles, grid mode and LDS cap are those
+ * of the single-step launch; a batch that takes several steps per launch uses
+ * them for the steps left over only.  cache_path (nullable) names a JSON file read first
  * (when it holds every class and the grid for this architecture nothing is
  * timed) and rewritten with the choices.  Overwrites every population
  * buffer (call before plbm_batch_init).  Synchronises `stream`.
@@ -391,8 +394,9 @@ int plbm_batch_set_graph_steps(plbm_batch *b, int steps);
 /*
  * plbm_batch_step -- advance every lattice by nsteps applications of
  * Eq. srt (as plbm_step).  Whole groups of graph_steps steps replay the
- * captured graph (recorded on first use); the rest, and the steps of
- * batches that take three of them per launch, are direct launches.
+ * captured graph (recorded on first use, of launches of one or two steps; of
+ * one when graph_steps is 2); the rest, and all steps of a batch that takes three
+ * of them per launch, are direct launches.
  * Asynchronous on `stream`.
  */
 int plbm_batch_step(plbm_batch *b, int nsteps, void *stream);

@@ -15,7 +15,11 @@
 //
 // What bounds it: single steps of short lattices take 4.1 us each, 2 us of
 // them the kernel, whatever the length; here a step is one trip through LDS
-// and one collision.
+// and one collision.  1000 nodes in FP64, 500 steps: 14 launches of 35 or 36 steps
+// on 22 workgroups of 256 threads, 46 of whose nodes are their own; 11.6 us each,
+// 0.32 a step (write, barrier, read, collision: vector instructions in 0.38 of the
+// issue slots), 1984 -> 161 us a call.  200000 nodes in FP32, 100 steps: 4 launches
+// of 25, vector instructions in 0.83 of the slots, 387 -> 59.
 #pragma once
 #include "plbm_sweep.h"
 
