@@ -12,9 +12,10 @@ One step = one collide-and-stream update of all nodes (plbm_step, which takes
 two or three of them per launch).  The headline is the FP16-deviation storage
 form (FP32 arithmetic, 100 B per node for a step by itself); the plain FP64
 step (400 B), FP32 storage (200 B) and BF16-deviation storage are timed beside
-it.  GB/s and fractions count the bytes of single steps, of which a launch of
-several moves a half or a third: they may pass the memory's rate.  Each form's
-error is stated against the FP64 form after --accuracy-steps steps from the same
+it.  `roofline` divides the HBM bytes that the headline's launches move, from
+stored counter totals, by their time; each form's `single_step_gbs` and
+`single_step_frac` count the bytes of single steps, of which a launch of several
+moves a half or a third, and may pass the memory's rate.  Each form's error is stated against the FP64 form after --accuracy-steps steps from the same
 initial state (the FP64 form matches the CPU oracle to 1e-12 in the test suite).
 
 Prints ONE JSON line (N = 1).
@@ -50,16 +51,40 @@ def kernel_hash():
     return h.hexdigest()[:16]
 
 
-def stored_traffic(form, path=TRAFFIC_FILE):
-    """HBM bytes per launch of the step in `form` from the stored counter
-    totals, or None when they are missing or were taken on other sources."""
+def stored_counters(path):
+    """The stored counter totals, empty when they are missing or were taken on
+    other sources."""
     if not os.path.exists(path):
-        return None
+        return {}
     with open(path) as fh:
         tr = json.load(fh)
-    if tr.get("kernel_sha256_16") != kernel_hash() or form not in tr.get("forms", {}):
-        return None
-    return tr["forms"][form]["hbm_bytes_per_launch"]
+    return tr if tr.get("kernel_sha256_16") == kernel_hash() else {}
+
+
+def stored_traffic(form, path=TRAFFIC_FILE):
+    """HBM bytes per launch of a single step in `form`, or None."""
+    return stored_counters(path).get("forms", {}).get(form, {}).get("hbm_bytes_per_launch")
+
+
+def stored_fused(form, path=TRAFFIC_FILE):
+    """What the launch of several steps in `form` moves and does
+    ("hbm_bytes_per_launch", "steps_per_launch", "vector_slots"), or None."""
+    return stored_counters(path).get("fused", {}).get(form)
+
+
+def roofline(form, ms_per_step, n):
+    """HBM bytes moved by the launches of `form` (counter totals of 4096^2 nodes),
+    over their time; null where no counters of these sources and size exist."""
+    c = stored_fused(form) if n == 4096 else None
+    gbs = c["hbm_bytes_per_launch"] / c["steps_per_launch"] / (ms_per_step * 1e-3) / 1e9 if c else None
+    return {"bound": "hbm", "achieved": round(gbs, 1) if c else None, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+            "frac": round(gbs / HBM_PEAK_GBS, 4) if c else None,
+            "traffic": c["hbm_bytes_per_launch"] if c else None,
+            "steps_per_launch": c["steps_per_launch"] if c else None,
+            "vector_slots": c["vector_slots"] if c else None,
+            "single_step_traffic": stored_traffic(form) if n == 4096 else None,
+            "what": "achieved: counted HBM bytes of a launch of steps_per_launch steps (traffic) over its time; "
+                    "vector_slots: share of the busy compute units' issue slots that vector instructions fill"}
 
 
 def parse():
@@ -156,14 +181,15 @@ def timed_windows(step, steps, windows=WINDOWS):
 
 
 def summarize(times, nodes, bytes_step):
-    """Median window and the spread of all windows."""
+    """Median window and the spread of all windows.  bytes_step: every
+    population read and written once, as a step by itself does."""
     ms = statistics.median(times)
     gbs = bytes_step / (ms * 1e-3) / 1e9
-    return {"ms_per_step": ms, "mlups": nodes / (ms * 1e-3) / 1e6, "gbs": gbs,
-            "frac": gbs / HBM_PEAK_GBS, "bytes_per_node": bytes_step // nodes,
+    return {"ms_per_step": ms, "mlups": nodes / (ms * 1e-3) / 1e6, "single_step_gbs": gbs,
+            "single_step_frac": gbs / HBM_PEAK_GBS, "bytes_per_node": bytes_step // nodes,
             "windows": len(times), "window_ms": [min(times), max(times)],
-            "frac_range": [bytes_step / (max(times) * 1e-3) / 1e9 / HBM_PEAK_GBS,
-                           bytes_step / (min(times) * 1e-3) / 1e9 / HBM_PEAK_GBS]}
+            "single_step_frac_range": [bytes_step / (max(times) * 1e-3) / 1e9 / HBM_PEAK_GBS,
+                                       bytes_step / (min(times) * 1e-3) / 1e9 / HBM_PEAK_GBS]}
 
 
 PREWARM_MS = 100.0
@@ -288,7 +314,7 @@ def accuracy(forms, n, fields, steps, theta):
         job_ms = timed_windows(lat.step, steps, windows=1)[0] * steps
         job = {"steps": steps, "ms": job_ms,
                "mlups": n * n * steps / (job_ms * 1e-3) / 1e6,
-               "frac": lat.bytes_per_step * steps / (job_ms * 1e-3) / 1e9 / HBM_PEAK_GBS}
+               "single_step_frac": lat.bytes_per_step * steps / (job_ms * 1e-3) / 1e9 / HBM_PEAK_GBS}
         mom = [t for t in lat.moments()]
         del lat
         torch.cuda.empty_cache()
@@ -718,7 +744,6 @@ def main():
 
     head = "f16dev" if "f16dev" in results else forms[0]
     h = results[head]
-    traffic = stored_traffic(head)
     # the CPU leg: everything that runs the oracle (baseline timing, the
     # anchor of the FP64 reference, the forms against the oracle, and the
     # von Neumann predictions of the literal runs)
@@ -771,9 +796,7 @@ def main():
                              f"pre-warm (the same form on a separate lattice); each form's "
                              f"whole {args.accuracy_steps}-step run is timed too "
                              f"(forms.*.job_{args.accuracy_steps})"},
-        "roofline": {"bound": "hbm", "achieved": round(h["gbs"], 1),
-                     "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": round(h["frac"], 4), "traffic": traffic},
+        "roofline": roofline(head, h["ms_per_step"], n),
         "cpu_baseline": cpu,
         "forms": rnd(results),
         "fp64_ref": rnd({

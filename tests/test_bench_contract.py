@@ -82,6 +82,36 @@ def test_stored_counters_match_the_algorithmic_bytes():
         assert abs(v["hbm_over_algorithmic"] - 1) < 0.03, form
 
 
+def test_roofline_counts_the_bytes_of_the_launches(monkeypatch, tmp_path):
+    """achieved = a launch's counted bytes over its steps' time; null at other
+    sizes and without counters of these sources."""
+    p = tmp_path / "t.json"
+    p.write_text(json.dumps({"kernel_sha256_16": bench.kernel_hash(),
+                             "forms": {"f16dev": {"hbm_bytes_per_launch": 1600000000}},
+                             "fused": {"f16dev": {"hbm_bytes_per_launch": 1800000000, "steps_per_launch": 2,
+                                                  "vector_slots": 0.8}}}))
+    monkeypatch.setattr(bench.stored_fused, "__defaults__", (str(p),))
+    monkeypatch.setattr(bench.stored_traffic, "__defaults__", (str(p),))
+    r = bench.roofline("f16dev", 0.2, 4096)
+    assert r["achieved"] == 4500.0 and r["peak"] == 8000.0 and r["frac"] == 0.5625
+    assert r["traffic"] == 1800000000 and r["steps_per_launch"] == 2 and r["single_step_traffic"] == 1600000000
+    for form, n in (("f16dev", 1024), ("f32", 4096)):
+        r = bench.roofline(form, 0.2, n)
+        assert r["achieved"] is None and r["frac"] is None and r["traffic"] is None
+
+
+def test_stored_fused_counters():
+    """The committed totals of the fused launches: at least one read and one
+    write of the state, and less than that for each of their steps."""
+    with open(bench.TRAFFIC_FILE) as fh:
+        tr = json.load(fh)
+    assert set(tr["fused"]) == set(tr["forms"])
+    for form, v in tr["fused"].items():
+        one = tr["forms"][form]["algorithmic_bytes_per_launch"]
+        assert one <= v["hbm_bytes_per_launch"] < one * v["steps_per_launch"], form
+        assert v["steps_per_launch"] in (2, 3) and 0 < v["vector_slots"] <= 1.05, form
+
+
 def test_first_nonfinite_stops_at_the_reported_step():
     from paper_1402_5487_amd import _plbm
     calls = []
